@@ -72,7 +72,7 @@ typedef struct {
 
 /* Counters of the last decode call on a model (Analysis, "Jump Distribution"). */
 typedef struct {
-  int64_t iterations;       /* loop iterations that had at least one active utterance        */
+  int64_t iterations;       /* loop iterations that had at least one active utterance: the most windows of any utterance */
   int64_t windows;          /* (utterance, iteration) pairs = joiner calls on a window       */
   int64_t rows;             /* window rows evaluated = sum of n over windows                 */
   int64_t useful_rows;      /* rows at or before the first non-blank of their window         */
@@ -318,7 +318,7 @@ int wind_get_call_times(wind_model *m, double *total_ms, double *loop_ms);
 int wind_get_joint_launches(wind_model *m, int32_t *rows, float *us, int cap, int *n);
 
 /*
- * How the last decode call ran its loop (the loop of Algorithm 2, for one or two utterances, can run
+ * How the last decode call ran its loop (the loop of Algorithm 2, for small batches, can run
  * as one resident kernel; option "loop_kernel"): *workgroups receives the number of workgroups of
  * that kernel, 0 if the call replayed the graph of per-step kernels instead; *one_l2 receives 1 if
  * those workgroups all sat on one XCD and exchanged their values through its L2 (option
@@ -346,9 +346,14 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             costs fp32 re-evaluations, never correctness
  *   "pred_mfma_min_batch"  smallest B for which the prediction network runs on MFMA tiles
  *             (default 1; bf16 models only; below it one wave per hidden unit does fp32 FMA)
- *   "loop_kernel"  1 (default): decodes of one or two utterances with at most 32 window rows (bf16, one
- *             LSTM layer, weights that fit the chip's LDS) run the whole loop as one resident kernel
- *             whose workgroups meet at grid barriers; 0: always the graph of per-step kernels
+ *   "loop_kernel"  1 (default): small decodes run the whole loop as one resident kernel; 0: always the graph of
+ *             per-step kernels.  Two such kernels: groups of workgroups, one group per XCD with utterances of its
+ *             own (up to 256 utterances, windows of at most 16 rows; bf16, one LSTM layer, Hp = Hj a multiple of
+ *             128 and at most 640, at most 1024 labels; the options lstm_rec, atomic_lists, slot_rows, decide_two,
+ *             joint_wide and pred_mfma_min_batch at their defaults where there are more than two utterances), and,
+ *             for one or two utterances of other one-layer models or options, with at most 32 window rows,
+ *             workgroups over one XCD or the chip that meet at grid barriers.  Calls with a resident kernel take
+ *             turns on a GPU: one from another thread or stream waits for the one before it
  *   "loop_fused"  1 (default): with at most 16 window rows and a joint hidden size that is a multiple of 128,
  *             at most 640, that kernel builds the window rows directly as matrix-core operands; 0: it
  *             stages them in LDS (the form for every other shape)

@@ -61,6 +61,8 @@ float host_bf16_to_f32(uint16_t b) {
 }
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+struct GroupInstance;
+
 struct GraphKey {
   CallDev call;
   int unroll;
@@ -129,6 +131,7 @@ struct wind_model {
   bool have_call_times = false;
   // an asynchronous decode that wind_get_stats has not completed yet
   bool async_pending = false, async_loop = false;
+  const GroupInstance *async_group = nullptr;
   hipStream_t async_stream = nullptr;
   unsigned *async_bar = nullptr;
   int opt_pred_mfma_min_batch = kPredMfmaMinBatch;
@@ -143,6 +146,7 @@ struct wind_model {
   int opt_decide_two = 1;       // rows of 65 .. 128 key parts: both halves of a row's keys in the decision kernel's first round trip
   bool fma_pred_step = false;   // this call's prediction-network steps keep their state in fp32 (the resident loop kernel reads it)
   LoopDev loop{};
+  GroupDev group{};
   int *dbg_len = nullptr, *dbg_out = nullptr;   // lengths and outputs of the debug entry points (inside the workspace)
   void *beam_ws = nullptr;   // workspace of the beam scoring step
   BeamPool beam_pool{};
@@ -152,6 +156,7 @@ struct wind_model {
   double wnorm_max = 0.0;
   int *h_flag = nullptr;  // pinned
   unsigned long long *h_stats = nullptr;   // pinned, behind h_flag in the same allocation: the call's counters
+  int device = -1;
   int cu_count = 0;            // CUs of the device the model was loaded on (the resident loop kernel wants one per workgroup)
   int loop_info[2] = {0, 0};   // last decode call: workgroups of the resident loop kernel (0: not used), whether they shared one L2
   long long prev_iters = 0;
@@ -208,7 +213,7 @@ struct WsLayout {
   bool big_enc;
   int slot_stride, nparts, nparts_tiny;
   size_t o_e, o_encb, o_len, o_nact, o_eidx, o_eltok, o_slot, o_slotc, o_rst, o_raux, o_nemit, o_ticket, o_h, o_c, o_hn, o_hb,
-      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts;
+      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder;
 };
 
 WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
@@ -252,6 +257,11 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_lbar = take((size_t)(1 + 256) * kLoopFlagStride * 4); w.o_lh = take((size_t)kLoopMaxB * d.Hp * 4);
   w.o_lp = take((size_t)kLoopMaxB * d.Hj * 4);
   w.o_lparts = take((size_t)2 * kLoopRows * w.nparts_tiny * 8);
+  const bool grouped = d.start_p != nullptr;   // models that decode in resident groups
+  w.o_gbar = take(grouped ? (size_t)kGroups * kGroupBarInts * 4 : 0);
+  w.o_gx = take(grouped ? (size_t)2 * kGroups * kGroupSlots * d.Hp * 8 : 0);
+  w.o_gkeys = take(grouped ? (size_t)kGroups * 2 * kGroupRows * (w.nparts_tiny + 1) * 8 : 0);
+  w.o_gorder = take(grouped ? (size_t)(kGroupMaxB + 1) * 4 : 0);
   w.total = off;
   return w;
 }
@@ -327,6 +337,12 @@ void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B) {
   m->loop.h_x = (float *)(base + o_lh);
   m->loop.p_x = (float *)(base + o_lp);
   m->loop.parts_x = (float2 *)(base + o_lparts);
+  m->group.bar = (unsigned *)(base + w.o_gbar);
+  m->group.h_x = (unsigned long long *)(base + w.o_gx);
+  m->group.p_x = m->group.h_x + (size_t)kGroups * kGroupSlots * d.Hp;
+  m->group.keys = (unsigned long long *)(base + w.o_gkeys);
+  m->group.order = (int *)(base + w.o_gorder);
+  m->group.n_order = m->group.order + kGroupMaxB;
 }
 
 int check_launch(const char *what) {
@@ -438,13 +454,10 @@ bool enc_wide_ok(const wind_model *m, int B, int T) {
   return ((unsigned long long)B * T + 256) * d.D * 2 < (1ull << 32);
 }
 
-int enqueue_prologue(wind_model *m, hipStream_t s) {
+// every frame of the call through the encoder projection (c.len must be set)
+void enqueue_enc_proj(wind_model *m, hipStream_t s) {
   const ModelDev &d = m->dev;
   const CallDev &c = m->call;
-  {
-    const size_t nstate = (size_t)d.L * c.B * d.Hp;
-    init_state_kernel<<<(unsigned)std::min<size_t>(64, (nstate + 4095) / 4096 + 1), 256, 0, s>>>(d, c);
-  }
   if (c.T > 0) {
     if (m->dtype == WIND_BF16 && c.enc_b) {
       const long long rows = (long long)c.B * c.T;
@@ -477,6 +490,16 @@ int enqueue_prologue(wind_model *m, hipStream_t s) {
              (size_t)d.D * 4, d, c);
     }
   }
+}
+
+int enqueue_prologue(wind_model *m, hipStream_t s) {
+  const ModelDev &d = m->dev;
+  const CallDev &c = m->call;
+  {
+    const size_t nstate = (size_t)d.L * c.B * d.Hp;
+    init_state_kernel<<<(unsigned)std::min<size_t>(64, (nstate + 4095) / 4096 + 1), 256, 0, s>>>(d, c);
+  }
+  enqueue_enc_proj(m, s);
   int rc = check_launch("prologue");
   if (rc) return rc;
   return enqueue_pred_step(m, s, false, true);
@@ -646,6 +669,84 @@ bool loop_kernel_shape(const wind_model *m, int B, int T, int W, LoopDev *lp, si
   return false;
 }
 
+// ---- resident groups (wind_group_kernel)
+struct GroupInstance {
+  void (*kernel)(ModelDev, CallDev, GroupDev);
+  size_t smem;
+  int ks, ct, gw;
+};
+template <int KS, int CT, int GW>
+constexpr GroupInstance group_instance() {
+  return {wind_group_kernel<KS, CT, GW>, GroupCfg<KS, CT, GW>::smem, KS, CT, GW};
+}
+const GroupInstance kGroupInstances[] = {
+    group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<1, 4, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(),
+    group_instance<2, 4, 32>(), group_instance<3, 1, 32>(), group_instance<3, 2, 32>(), group_instance<3, 4, 32>(), group_instance<4, 1, 32>(),
+    group_instance<4, 2, 32>(), group_instance<4, 4, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(), group_instance<5, 4, 32>(),
+    group_instance<5, 2, 20>()};
+
+// Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts).
+bool group_model(int dtype, const ModelDev &d) {
+  return dtype == WIND_BF16 && d.L == 1 && d.Hp == d.Hj && d.Hj % 128 == 0 && d.Hj <= 640 && d.V <= 1024 &&
+         (unsigned long long)(d.V + 1) * 4 * d.Hp < (1ull << 31);
+}
+
+// The resident groups of this call, or null if the call does not qualify.
+const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, GroupDev *gd) {
+  const ModelDev &d = m->dev;
+  if (!d.start_p || W > kGroupMaxW || B > kGroupMaxB || m->cu_count < kGroups * 32) return nullptr;
+  if ((unsigned long long)B * (unsigned long long)T * d.Hj >= (1ull << 31)) return nullptr;
+  if (!m->opt_loop_kernel || !m->opt_loop_fused || !m->opt_loop_one_xcd || m->opt_profile || !m->opt_graph || m->opt_host_sync || m->opt_debug_stamps) return nullptr;
+  // options that shape the graph of per-step kernels ask for that graph
+  if (B > kLoopMaxB && (!m->opt_lstm_rec || !m->opt_atomic_lists || !m->opt_slot_rows || !m->opt_decide_two || m->opt_joint_wide != 1 ||
+                        m->opt_pred_mfma_min_batch > B)) return nullptr;
+  // two utterances: two groups of 20 workgroups (the LSTM's 640 units divide by 20); else 32, the CUs of an XCD
+  const int gw = B == 2 && d.Hp == 640 ? 20 : 32;
+  const int nparts = (d.V + kTinyCols - 1) / kTinyCols;
+  gd->NG = std::min(kGroups, B);
+  gd->NS = std::min(kGroupSlots, (B + gd->NG - 1) / gd->NG);
+  gd->SPT = std::min(kGroupMaxW / W, gd->NS);
+  const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
+  gd->RG = tiles > 2 ? 4 : tiles;
+  const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
+  const int ct = gw == 20 ? 2 : parts > 2 ? 4 : parts;
+  if (parts > ct) return nullptr;
+  for (const GroupInstance &i : kGroupInstances)
+    if (i.ks == d.Hj / 128 && i.ct == ct && i.gw == gw) return &i;
+  return nullptr;
+}
+
+// Kernels that keep workgroups on the chip and have them wait for each other run one at a time per GPU: two of them,
+// launched from different streams, could each get some of the CUs and wait for the rest.  A call that
+// waits for its own end holds the gate until then; an asynchronous one leaves an event that later launches
+// wait for on the GPU.
+struct ResidentGate {
+  std::mutex mutex;
+  hipEvent_t pending = nullptr;
+  bool has_pending = false;
+};
+ResidentGate g_resident[kMaxDevices];
+
+int resident_enter(ResidentGate &g, hipStream_t s) {
+  if (!g.has_pending) return WIND_OK;
+  if (hipEventQuery(g.pending) == hipSuccess) g.has_pending = false;
+  else HIP_TRY(hipStreamWaitEvent(s, g.pending, 0));
+  return WIND_OK;
+}
+int resident_leave_pending(ResidentGate &g, hipStream_t s) {
+  if (!g.pending) HIP_TRY(hipEventCreateWithFlags(&g.pending, hipEventDisableTiming));
+  HIP_TRY(hipEventRecord(g.pending, s));
+  g.has_pending = true;
+  return WIND_OK;
+}
+
+int finish_group(wind_model *m, const GroupDev &gd, int gw) {
+  m->loop_info[0] = gd.NG * gw;
+  m->loop_info[1] = gd.NG == 1 && m->h_flag[2] == 2;
+  if (m->h_flag[1] != 0) return fail(WIND_ERR_HIP, "resident loop: a grid barrier timed out (workgroups not all resident?)");
+  return WIND_OK;
+}
+
 // One decode call.  ext_ws null: the model's own workspace, and the call returns when the decode has
 // finished.  ext_ws given: the caller's workspace, at most max_iters loop iterations are enqueued and
 // the call returns at once; wind_get_stats completes it (finish_async).
@@ -662,6 +763,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   if ((long long)B * T > (1ll << 31) - 1) return fail(WIND_ERR_ARG, "B*T too large");
   if (m->dtype == WIND_BF16 && m->dev.Hj > kDecideMaxHj) return fail(WIND_ERR_UNSUPPORTED, "Hj > 2048");
   hipStream_t s = (hipStream_t)stream;
+  struct { std::unique_lock<std::mutex> lock; } gate;   // held by calls with a resident kernel
   const bool async = ext_ws != nullptr;
   int rc = WIND_OK;
   if (async) {
@@ -691,6 +793,42 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   m->fma_pred_step = use_loop;   // the resident kernel starts from the fp32 state of the start-token step
   if (use_loop) { c.rec = nullptr; c.lists_atomic = 0; c.slot_rows = 0; }
   m->have_call_times = false;
+  GroupDev gd = m->group;
+  const GroupInstance *gi = group_shape(m, B, T, W, &gd);
+  if (gi || use_loop) {
+    if (m->device < 0 || m->device >= kMaxDevices) return fail(WIND_ERR_UNSUPPORTED, "device ordinal above 63");
+    gate.lock = std::unique_lock<std::mutex>(g_resident[m->device].mutex);
+    rc = resident_enter(g_resident[m->device], s);
+    if (rc) return rc;
+  }
+  if (gi) {
+    gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
+    gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
+    HIP_TRY(hipEventRecord(m->ev_call[0], s));
+    group_init_kernel<<<64, 256, 0, s>>>(m->dev, c, gd);
+    enqueue_enc_proj(m, s);
+    HIP_TRY(hipEventRecord(m->ev_call[1], s));
+    gi->kernel<<<(unsigned)(kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
+    rc = check_launch("resident groups");
+    if (rc) return rc;
+    HIP_TRY(hipEventRecord(m->ev_call[2], s));
+    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NG, c.stats, kNumStats, m->h_flag, m->h_stats);
+    rc = check_launch("resident groups' results");
+    if (rc) return rc;
+    if (async) {
+      m->async_pending = true; m->async_loop = false; m->async_group = gi; m->async_stream = s;
+      m->group.NG = gd.NG;
+      return resident_leave_pending(g_resident[m->device], s);
+    }
+    HIP_TRY(hipStreamSynchronize(s));
+    rc = finish_group(m, gd, gi->gw);
+    if (rc) return rc;
+    if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");
+    m->have_call_times = true;
+    rc = read_stats(m);
+    if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
+    return rc;
+  }
   HIP_TRY(hipEventRecord(m->ev_call[0], s));
   rc = enqueue_prologue(m, s);
   if (rc) return rc;
@@ -723,7 +861,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     if (async) {
       m->async_pending = true; m->async_loop = true; m->async_stream = s; m->async_bar = lp.bar;
       m->loop_info[0] = lp.G; m->loop_info[1] = 0;
-      return WIND_OK;
+      return resident_leave_pending(g_resident[m->device], s);
     }
     static_assert(kNumStats <= 128, "loop_collect_kernel: one thread per counter");
     loop_collect_kernel<<<1, 128, 0, s>>>(c.n_active, lp.bar, c.stats, kNumStats, m->h_flag, m->h_stats);   // one launch, one wait
@@ -857,8 +995,10 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
   m->load_stream = (hipStream_t)stream;
   {
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
       m->cu_count = cus;
+      m->device = dev;
+    }
   }
   ModelDev &d = m->dev;
   d.D = w->D; d.E = w->E; d.Hp = w->Hp; d.L = w->L; d.Hj = w->Hj; d.V = w->V;
@@ -965,6 +1105,20 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     m->wnorm_max = std::sqrt(wmax);
     set_tau(m);
   }
+  if (rc == WIND_OK && group_model(m->dtype, d)) {
+    // the state after the start token, for the resident groups: one allocation [Hp | Hj | 4Hp]
+    void *st = nullptr;
+    hipError_t e = hipMalloc(&st, (size_t)(5 * Hp + d.Hj) * sizeof(float));
+    if (e == hipSuccess) {
+      m->allocs.push_back(st);
+      float *sc = (float *)st, *sp = sc + Hp, *sr = sp + d.Hj;
+      group_start_kernel<<<(unsigned)((4 * Hp + d.Hj + 3) / 4), 256, (size_t)Hp * sizeof(float), m->load_stream>>>(d, sc, sp, sr);
+      chk(check_launch("start state"));
+      e = hipStreamSynchronize(m->load_stream);
+      d.start_c = sc; d.start_p = sp; d.start_rec = sr;
+    }
+    if (rc == WIND_OK && e != hipSuccess) rc = fail(WIND_ERR_HIP, std::string("start state: ") + hipGetErrorString(e));
+  }
   for (int i = 0; i < 3 && rc == WIND_OK; ++i) {
     hipError_t e = hipEventCreate(&m->ev_call[i]);
     if (e != hipSuccess) rc = fail(WIND_ERR_HIP, std::string("hipEventCreate: ") + hipGetErrorString(e));
@@ -983,6 +1137,8 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)joint_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWideSmemBytes);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)enc_proj_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWideSmemBytes);
     static_assert(kFusedSteps == 5, "one resident loop instance per number of fused K steps: here and at the launch");
+    for (const GroupInstance &i : kGroupInstances)
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     const void *loop_instances[] = {(const void *)wind_loop_kernel<0>, (const void *)wind_loop_kernel<1>, (const void *)wind_loop_kernel<2>,
                                     (const void *)wind_loop_kernel<3>, (const void *)wind_loop_kernel<4>, (const void *)wind_loop_kernel<5>};
     for (const void *k : loop_instances)
@@ -1126,6 +1282,19 @@ int wind_workspace_bytes(const wind_model *m, int B, int T, int W, size_t *bytes
 static int finish_async(wind_model *m) {
   hipStream_t s = m->async_stream;
   m->async_pending = false;
+  if (m->async_group) {
+    const GroupInstance *gi = m->async_group;
+    m->async_group = nullptr;
+    HIP_TRY(hipStreamSynchronize(s));
+    int rc = finish_group(m, m->group, gi->gw);
+    if (rc) return rc;
+    m->have_call_times = true;
+    rc = read_stats(m);
+    if (rc == WIND_OK && m->h_flag[0] != 0)
+      return fail(WIND_ERR_UNFINISHED, "the decode did not finish within max_iterations: outputs hold the labels found so far");
+    if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
+    return rc;
+  }
   m->h_flag[0] = m->h_flag[1] = 0;
   HIP_TRY(hipMemcpyAsync(m->h_flag, m->call.n_active, sizeof(int), hipMemcpyDeviceToHost, s));
   if (m->async_loop) HIP_TRY(hipMemcpyAsync(m->h_flag + 2, m->async_bar, 2 * sizeof(int), hipMemcpyDeviceToHost, s));

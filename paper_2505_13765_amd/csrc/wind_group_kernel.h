@@ -1,0 +1,756 @@
+// The whole decode loop of a small batch as resident groups of workgroups, one group per XCD.
+#pragma once
+#include "wind_types.h"
+#include "wind_decide_kernels.h"
+#include "wind_pred_kernels.h"
+
+namespace wind {
+
+// ---------------------------------------------------------------------------------------------
+// Utterances are independent, so a batch needs no hand-over between the chip's eight XCDs: every XCD decodes
+// its own utterances with a resident group of GW workgroups (one per CU), and what the group's
+// workgroups tell each other stays in that XCD's L2.  A group holds up to four utterances at a time
+// (slots); when one is done the slot takes the next of the group's list.  Utterances are dealt by falling
+// length, back and forth over the slots.
+//
+// All weights the loop needs sit in registers, as matrix-core operands: per workgroup CT parts of 32
+// columns of W_out (waves 0-3, K split in four), the recurrent rows of UPW LSTM units and PPW rows of W_pred
+// (waves 4-7, K split in four).  LDS holds the projected frames of the windows: two windows' worth per
+// slot, loaded straight from memory a whole iteration before they are read.
+//
+// An iteration, and what bounds it (a chain of short steps; nothing here is long enough to be bound by bytes or flops):
+//   waves 0-3  window rows as matrix-core operands from LDS, products with W_out, partial sums to LDS
+//   all        keys of the workgroup's rows and columns -> exchange 1; every workgroup takes every slot's
+//              decision from the keys (near-ties in fp32, only in rows before the first certain label)
+//   waves 4-7  a label's LSTM step for this workgroup's units -> exchange 2 (hidden vector) -> projection
+//              rows -> exchange 3 (projection); then, off the chain, the recurrent sums of the next step
+//              and the frames of the window after next
+// The three exchanges have no barrier and no flags: every 8-byte word carries its iteration (the keys: its
+// parity), and a reader asks for the words it needs until all are this iteration's.  A writer can only
+// overtake a reader by an iteration it cannot reach without that reader's own keys.
+// Every wait is bounded: after spin_limit polls, or when the group's abort word is set, a wave sets that word and
+// marks the workgroup failed, which then leaves at its next decision; the host reports the error.
+//
+// W <= 16.  A workgroup's row tile holds SPT = 16 / W slots; with more slots than that the group's workgroups
+// are cut into RG row groups, each covering all columns with GW / RG workgroups.
+constexpr int kGroups = 8;              // XCDs
+constexpr int kGroupSlots = 4;          // utterances a group decodes at a time, at most
+constexpr int kGroupRows = 64;          // window rows of a group, at most
+constexpr int kGroupMaxW = 16;
+constexpr int kGroupMaxB = 256;         // utterances of a call (group_init_kernel ranks them in one workgroup)
+constexpr int kGroupBarInts = 33 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 (1 + g): XCD number + 1 of workgroup g
+
+struct GroupDev {
+  unsigned *bar;                        // [kGroups][kGroupBarInts], zero at launch
+  unsigned long long *h_x;              // [kGroups][kGroupSlots][H] new hidden vectors: bf16 hi | lo << 16, iteration + 1 above
+  unsigned long long *p_x;              // [kGroups][kGroupSlots][H] new projections: fp32, iteration + 1 above
+  unsigned long long *keys;             // [kGroups][2][kGroupRows][nparts + 1] two keys per part; last: (blank logit, norm)
+  int *order, *n_order;                 // utterances with frames by falling length, and their number
+  int NG, NS, RG, SPT;
+  int max_iters;                        // windows an utterance may take
+  unsigned spin_limit;
+};
+
+template <int KS, int CT, int GW>
+struct GroupCfg {
+  static constexpr int H = 128 * KS;                      // = Hp = Hj
+  static constexpr int UPW = H / GW, NR = 4 * UPW, PPW = H / GW;
+  static constexpr int LT = NR / 16, PT = (PPW + 15) / 16;   // tiles of 16 weight rows
+  static constexpr int QK = H / 4, QL = (QK + 63) / 64;      // a wave's quarter of K, and its loads per lane
+  static constexpr int EST = H + 4, HST = H + 8;             // row strides in LDS (16 bytes of padding: banks)
+  static constexpr int NI = (4 * CT + 7) / 8;                // (row quad, part) items of the key step per wave
+  static_assert(H % GW == 0 && NR % 16 == 0, "units per workgroup");
+  static constexpr size_t oE = 0;                                         // float [32][EST]
+  static constexpr size_t oFred = oE + (size_t)32 * EST * 4;              // float [4][2 CT][4][80]
+  static constexpr size_t oFbn = oFred + (size_t)4 * 2 * CT * 4 * 80 * 4; // float [4][2][16]
+  static constexpr size_t oP = oFbn + 512;                                // float [slots][H]
+  static constexpr size_t oHb = oP + (size_t)kGroupSlots * H * 4;         // bf16 [8][HST]
+  static constexpr size_t oPred = oHb + (size_t)8 * HST * 2;              // float [4][16 PT][4]
+  static constexpr size_t oRecp = oPred + (size_t)4 * 16 * PT * 4 * 4;    // float [4][NR][4]
+  static constexpr size_t oRec = oRecp + (size_t)4 * NR * 4 * 4;          // float [slots][NR]
+  static constexpr size_t oC = oRec + (size_t)kGroupSlots * NR * 4;       // float [slots][UPW]
+  static constexpr size_t oW = oC + (size_t)kGroupSlots * UPW * 4;        // float [H] blank column of W_out
+  static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], fail, near; float bp[UPW]
+  static constexpr size_t smem = (oI + (64 + 64 + kNumStats + 2 + PPW) * 4 + 15) / 16 * 16;
+  static_assert(smem <= 160 * 1024, "LDS");
+};
+
+__device__ __forceinline__ unsigned long long group_ld(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// near: the readers share this CU's L2, a store need only reach that; else it goes to the memory side
+__device__ __forceinline__ void group_st(unsigned long long *p, unsigned lo, unsigned hi, bool near) {
+  const unsigned long long u = (unsigned long long)lo | ((unsigned long long)hi << 32);
+  if (near) __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Workgroup barrier that waits for LDS only (outstanding loads and stores go on)
+__device__ __forceinline__ void group_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// A quarter of a wait: asks again through `ask` (which returns whether this lane has all it needs) until every
+// lane of the wave does.  False: gave up.
+template <class Ask>
+__device__ __forceinline__ bool group_poll(unsigned *abort_word, unsigned limit, const Ask &ask) {
+  unsigned spins = 0;
+  while (!__all(ask())) {
+    if (++spins > limit || ((spins & 15u) == 0 && __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+      if ((threadIdx.x & 63) == 0) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+  }
+  return true;
+}
+// 64 lanes x 16 bytes from memory to 1 KB of LDS.  Written as assembly so that the compiler does not make later LDS
+// reads of this wave wait for it: whoever reads the rows is a barrier and an explicit wait away.
+__device__ __forceinline__ void group_load_lds(const void *src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
+}
+
+// Everything the loop expects to find: clamped lengths, the utterances by falling length, zeroed counters and exchange words
+// (the keys all ones: their first iterations' tag is 0), in one launch.
+__global__ __launch_bounds__(256) void group_init_kernel(ModelDev m, CallDev c, GroupDev gd) {
+  __shared__ int lens[kGroupMaxB];
+  const int tid = threadIdx.x;
+  const size_t nbar = (size_t)gd.NG * kGroupBarInts, nx = (size_t)gd.NG * kGroupSlots * m.Hp;
+  const size_t nk = (size_t)gd.NG * 2 * kGroupRows * (c.nparts_tiny + 1);
+  for (size_t i = (size_t)blockIdx.x * 256 + tid; i < nbar + 2 * nx + nk; i += (size_t)gridDim.x * 256) {
+    if (i < nbar) gd.bar[i] = 0u;
+    else if (i < nbar + nx) gd.h_x[i - nbar] = 0ull;
+    else if (i < nbar + 2 * nx) gd.p_x[i - nbar - nx] = 0ull;
+    else gd.keys[i - nbar - 2 * nx] = ~0ull;
+  }
+  if (blockIdx.x != 0) return;
+  for (int i = tid; i < kNumStats; i += 256) c.stats[i] = 0ull;
+  for (int b = tid; b < c.B; b += 256) {
+    int len = c.lengths[b];
+    len = len < 0 ? 0 : (len > c.T ? c.T : len);
+    lens[b] = len;
+    c.len[b] = len;
+    c.out_counts[b] = 0;
+  }
+  if (tid == 0) { c.n_active[0] = 0; c.n_active[1] = 0; }
+  __syncthreads();
+  int n = 0;
+  for (int b = tid; b < c.B; b += 256) {
+    const int len = lens[b];
+    int rank = 0;
+    n = 0;
+    for (int o = 0; o < c.B; ++o) {
+      const int lo = lens[o];
+      rank += lo > len || (lo == len && o < b);
+      n += lo > 0;
+    }
+    if (len > 0) gd.order[rank] = b;
+  }
+  if (tid == 0) *gd.n_order = n;
+}
+
+// Load time: the state after the start token (its LSTM step from zero, projection, recurrent sums of the next
+// step), the same for every utterance.  Workgroup = 4 rows of [w_hh ; w_pred], one per wave.
+__global__ __launch_bounds__(256) void group_start_kernel(ModelDev m, float *start_c, float *start_p, float *start_rec) {
+  extern __shared__ float hs[];
+  const int Hp = m.Hp, tid = threadIdx.x;
+  for (int u = tid; u < Hp; u += 256) {
+    const float4 x = *reinterpret_cast<const float4 *>(m.emb_gates + (size_t)m.V * 4 * Hp + 4 * u);
+    const float ig = 1.f / (1.f + expf(-x.x)), og = 1.f / (1.f + expf(-x.w));
+    const float cn = ig * tanhf(x.z);
+    hs[u] = og * tanhf(cn);
+    if (blockIdx.x == 0) start_c[u] = cn;
+  }
+  __syncthreads();
+  const int lane = tid & 63, row = (int)blockIdx.x * 4 + (tid >> 6);
+  if (row >= 4 * Hp + m.Hj) return;
+  const bf16_t *w = row < 4 * Hp ? reinterpret_cast<const bf16_t *>(m.w_cat[0]) + (size_t)row * Hp
+                                 : reinterpret_cast<const bf16_t *>(m.w_pred) + (size_t)(row - 4 * Hp) * Hp;
+  float a = 0.f;
+  for (int k = 2 * lane; k < Hp; k += 128) {
+    const float2 x = ldw2(w, k);
+    a = fmaf(x.x, hs[k], a);
+    a = fmaf(x.y, hs[k + 1], a);
+  }
+  a = wave_sum(a);
+  if (lane == 0) {
+    if (row < 4 * Hp) start_rec[row] = a;
+    else start_p[row - 4 * Hp] = a + m.b_pred[row - 4 * Hp];
+  }
+}
+
+// What the host reads after the loop, in one launch, straight into pinned memory.
+__global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active, const unsigned *bar, int NG, const unsigned long long *stats,
+                                                            int n_stats, int *h_flag, unsigned long long *h_stats) {
+  const int i = threadIdx.x;
+  if (i == 0) {
+    unsigned gave_up = 0u, near = 2u;
+    for (int g = 0; g < NG; ++g) {
+      gave_up |= bar[g * kGroupBarInts];
+      near = min(near, bar[g * kGroupBarInts + 1]);
+    }
+    h_flag[0] = n_active[0];
+    h_flag[1] = (int)gave_up;
+    h_flag[2] = (int)near;
+  }
+  if (i < n_stats) h_stats[i] = stats[i];
+}
+
+// The part of the loop's state that every wave keeps for itself: lane a holds slot a.
+struct GroupLane {
+  int b, t, len, sym, cnt;   // utterance, frame, length, labels on the frame, labels so far (len = t = 0: slot empty)
+  int wc;                    // windows so far
+  int rpos;                  // t modulo 2 W: the frame's row in its ring of projected frames
+  int ld0, ld;               // frames loaded (or asked for) before the last decision, and now
+  int nb, nlen, round;       // the slot's next utterance (-1: none)
+};
+
+template <int KS, int CT, int GW, int ROLE>
+__device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, const GroupDev &gd, unsigned char *smem, int grp, int g) {
+  using Cfg = GroupCfg<KS, CT, GW>;
+  constexpr int H = Cfg::H, NR = Cfg::NR, QK = Cfg::QK, QL = Cfg::QL;
+  float *ecache = reinterpret_cast<float *>(smem + Cfg::oE), *fred = reinterpret_cast<float *>(smem + Cfg::oFred);
+  float *fbn = reinterpret_cast<float *>(smem + Cfg::oFbn), *pfull = reinterpret_cast<float *>(smem + Cfg::oP);
+  bf16_t *hbuf = reinterpret_cast<bf16_t *>(smem + Cfg::oHb);
+  float *predp = reinterpret_cast<float *>(smem + Cfg::oPred), *recp = reinterpret_cast<float *>(smem + Cfg::oRecp);
+  float *recs = reinterpret_cast<float *>(smem + Cfg::oRec), *cst = reinterpret_cast<float *>(smem + Cfg::oC);
+  float *wbl = reinterpret_cast<float *>(smem + Cfg::oW);
+  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *stat2 = stat + 64, *counts = stat2 + 64, *fail = counts + kNumStats, *near_w = fail + 1;
+  float *bpl = reinterpret_cast<float *>(near_w + 1);   // this workgroup's rows of b_pred
+
+  int lane = threadIdx.x & 63, tid1 = threadIdx.x & 255, l15 = lane & 15, l4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w4 = wave & 3;   // w4: the wave's quarter of K
+  const int W = c.W, V = m.V, NS = gd.NS, SPT = gd.SPT, W2 = 2 * W, R = NS * W, nparts = c.nparts_tiny, kstride = nparts + 1;
+  const int CG = GW / gd.RG, rt = g / CG, cg = g - rt * CG;
+  unsigned *abort_word = gd.bar + grp * kGroupBarInts;
+  unsigned long long *hx = gd.h_x + (size_t)grp * kGroupSlots * H, *px = gd.p_x + (size_t)grp * kGroupSlots * H;
+  unsigned long long *kbase = gd.keys + (size_t)grp * 2 * kGroupRows * kstride;
+  const int unit0 = g * Cfg::UPW, prow0 = g * Cfg::PPW;
+
+  // ---- the slots' first utterances
+  GroupLane sl;
+  const int VS = gd.NG * NS, n_order = *gd.n_order;
+  auto next_entry = [&](int round, int &b, int &len) {
+    const int v = lane * gd.NG + grp, rank = round * VS + ((round & 1) ? VS - 1 - v : v);
+    b = -1;
+    len = 0;
+    if (lane < NS && rank < n_order) {
+      b = gd.order[rank];
+      len = c.len[b];
+    }
+  };
+  next_entry(0, sl.b, sl.len);
+  next_entry(1, sl.nb, sl.nlen);
+  sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+  sl.round = 1;
+  if (sl.b < 0) sl.b = 0;
+  sl.ld = min(sl.len, W2);
+
+  // ---- weights into registers
+  bf16x8 wo[ROLE == 0 ? 2 * CT : 1][KS];                                   // W_out columns
+  bf16x8 wr[ROLE == 1 ? Cfg::LT : 1][KS], wp[ROLE == 1 ? Cfg::PT : 1][KS];   // recurrent rows, projection rows
+  if constexpr (ROLE == 0) {
+#pragma unroll
+    for (int t = 0; t < 2 * CT; ++t) {
+      const int col = min(((t >> 1) * CG + cg) * 32 + 16 * (t & 1) + l15, m.Vpad - 1);
+      const bf16_t *src = reinterpret_cast<const bf16_t *>(m.w_out) + (size_t)col * H + w4 * QK + l4 * 8;
+#pragma unroll
+      for (int i = 0; i < KS; ++i) wo[t][i] = *reinterpret_cast<const bf16x8 *>(src + i * 32);
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < Cfg::LT; ++t) {
+      const bf16_t *src = reinterpret_cast<const bf16_t *>(m.w_cat[0]) + (size_t)(unit0 * 4 + 16 * t + l15) * H + w4 * QK + l4 * 8;
+#pragma unroll
+      for (int i = 0; i < KS; ++i) wr[t][i] = *reinterpret_cast<const bf16x8 *>(src + i * 32);
+    }
+#pragma unroll
+    for (int t = 0; t < Cfg::PT; ++t) {
+      const bf16_t *src = reinterpret_cast<const bf16_t *>(m.w_pred) + (size_t)(prow0 + min(16 * t + l15, Cfg::PPW - 1)) * H + w4 * QK + l4 * 8;
+#pragma unroll
+      for (int i = 0; i < KS; ++i) wp[t][i] = *reinterpret_cast<const bf16x8 *>(src + i * 32);
+    }
+  }
+
+  // ---- frames of slot `a` (scalars) from its ring's `from` to `to`, one row per wave in turn
+  auto load_frames = [&]() {
+    const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) float *)ecache;
+    for (int q = 0; q < SPT; ++q) {
+      const int a = rt * SPT + q;
+      if (a >= NS) break;
+      const int f0 = __builtin_amdgcn_readlane(sl.ld0, a), f1 = __builtin_amdgcn_readlane(sl.ld, a);
+      const int t = __builtin_amdgcn_readlane(sl.t, a), rp = __builtin_amdgcn_readlane(sl.rpos, a), b = __builtin_amdgcn_readlane(sl.b, a);
+      for (int f = f0 + ((w4 - f0) & 3); f < f1; f += 4) {
+        int rr = rp + (f - t);
+        if (rr >= W2) rr -= W2;
+        const float *src = c.e + (size_t)((unsigned)b * (unsigned)c.T + (unsigned)f) * H + lane * 4;
+        const unsigned dst = lds0 + (unsigned)(q * W2 + rr) * (Cfg::EST * 4);
+#pragma unroll
+        for (int i = 0; i < (H + 255) / 256; ++i)
+          if (i * 256 + lane * 4 < H) group_load_lds(src + i * 256, dst + i * 1024);
+      }
+    }
+  };
+
+  // ---- state after the start token
+  if constexpr (ROLE == 0) {
+    for (int i = tid1; i < NS * H; i += 256) pfull[i] = m.start_p[i % H];
+    for (int i = tid1; i < H; i += 256) wbl[i] = m.w_blank[i];
+    if (tid1 == 0) *fail = 0;
+  } else {
+    for (int i = tid1; i < NS * NR; i += 256) recs[i] = m.start_rec[unit0 * 4 + i % NR];
+    for (int i = tid1; i < NS * Cfg::UPW; i += 256) cst[i] = m.start_c[unit0 + i % Cfg::UPW];
+    for (int i = tid1; i < kNumStats; i += 256) counts[i] = 0;
+    if (tid1 < Cfg::PPW) bpl[tid1] = m.b_pred[prow0 + tid1];
+    load_frames();
+  }
+  // ---- where the workgroups sit: XCD numbers, exchanged with device-wide stores
+  if (wave == 0) {
+    unsigned xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    xcc = (xcc & 15u) + 1u;
+    unsigned *bw = abort_word + 32;
+    if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned v = xcc;
+    const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+      if (lane < GW) v = __hip_atomic_load(bw + lane * 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return v != 0u;
+    });
+    const bool same = __all(v == xcc);
+    if (lane == 0) {
+      *near_w = same;
+      if (!got) *fail = 1;
+      if (g == 0) abort_word[1] = same ? 2u : 1u;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  group_barrier();
+  const bool near = *near_w != 0;
+
+  // ---- constants of this lane's places in the steps below
+  const float b_blank = m.b_out[V];
+  const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
+  auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
+  const int nq = 4 * wave >= R ? 0 : 4 * (wave + 8) >= R ? 1 : 2;   // row quads this wave decides
+  const unsigned segm = (1u << W) - 1u;
+  float bias[Cfg::NI][2];
+#pragma unroll
+  for (int k = 0; k < Cfg::NI; ++k)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int item = wave + 8 * k, part = (item >> 2) * CG + cg, col = part * 32 + 16 * t + l15;
+      bias[k][t] = item < 4 * CT && part < nparts && col < V ? m.b_out[col] : kKeyNone;   // what is added to kKeyNone vanishes in it
+    }
+  int pend = 0, pend_slot[kGroupSlots] = {0, 0, 0, 0};   // ROLE 1: slots whose recurrent sums wait for their partial sums
+
+  for (int it = 0;; ++it) {
+    // opaque: what follows from the lane's number is formed again in every iteration, where it is used, instead of being kept
+    // in registers over the loop (the weights need them)
+    asm volatile("" : "+v"(lane), "+v"(tid1));
+    l15 = lane & 15;
+    l4 = lane >> 4;
+    const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
+    if (!__any(nwin > 0)) break;
+    const int tag = (it >> 1) & 1;
+    const unsigned stamp = (unsigned)it + 1u;
+    unsigned long long *kp = kbase + (size_t)(it & 1) * kGroupRows * kstride;
+    if constexpr (ROLE == 0) {
+      // ---- window rows as matrix-core operands: lane (row l15, K group l4) takes 8 consecutive frames' projections
+      // per step of 32 of this wave's quarter of K, adds the prediction projection, applies the ReLU and rounds:
+      // its part of the first operand of a 16 x 16 x 32 product.  Blank logit and squared norm in fp32.
+      f32x4 acc[2 * CT];
+#pragma unroll
+      for (int t = 0; t < 2 * CT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int gq = div_w(l15), gl = gq < SPT ? gq : 0, gj = gq < SPT ? l15 - gl * W : 0;   // row l15 of the tile: slot, row of its window
+      const int ga = min(rt * SPT + gl, NS - 1), gloc = max(ga - rt * SPT, 0);
+      int rr = __shfl(sl.rpos, ga, kWave) + gj;
+      if (rr >= W2) rr -= W2;
+      const float *er = ecache + (gloc * W2 + rr) * Cfg::EST + w4 * QK + l4 * 8;
+      const float *pr = pfull + ga * H + w4 * QK + l4 * 8, *wr_ = wbl + w4 * QK + l4 * 8;
+      float dot = 0.f, nrm = 0.f;
+      // the LDS operands of a step are read one step ahead, into registers that take turns
+      float4 eo[2][2], po[2][2], bo[2][2];
+      auto read_ops = [&](int set, int i) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          eo[set][h] = *reinterpret_cast<const float4 *>(er + i * 32 + 4 * h);
+          po[set][h] = *reinterpret_cast<const float4 *>(pr + i * 32 + 4 * h);
+          bo[set][h] = *reinterpret_cast<const float4 *>(wr_ + i * 32 + 4 * h);
+        }
+      };
+      bf16x8 zf[KS];
+      read_ops(0, 0);
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        if (i + 1 < KS) read_ops((i + 1) & 1, i + 1);
+        float x[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = bo[i & 1][h];
+          float *y = x + 4 * h;
+          y[0] = fmaxf(e4.x + p4.x, 0.f); y[1] = fmaxf(e4.y + p4.y, 0.f); y[2] = fmaxf(e4.z + p4.z, 0.f); y[3] = fmaxf(e4.w + p4.w, 0.f);
+          dot = fmaf(y[0], b4.x, dot); dot = fmaf(y[1], b4.y, dot); dot = fmaf(y[2], b4.z, dot); dot = fmaf(y[3], b4.w, dot);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) nrm = fmaf(y[q], y[q], nrm);
+        }
+        const u32x4 zu = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+        zf[i] = __builtin_bit_cast(bf16x8, zu);
+        if constexpr (CT < 4) {
+#pragma unroll
+          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // keeps the reads at one step ahead: registers
+      }
+      if constexpr (CT == 4) {   // the products behind the row: operands of both at once would not fit the registers
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+#pragma unroll
+          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);
+      }
+      dot += __shfl_xor(dot, 16, kWave); nrm += __shfl_xor(nrm, 16, kWave);
+      dot += __shfl_xor(dot, 32, kWave); nrm += __shfl_xor(nrm, 32, kWave);
+      // register r of lane l: row 4 l4 + r, column l15 of tile t; 80 floats per r: the readers below hit different banks
+#pragma unroll
+      for (int t = 0; t < 2 * CT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) fred[((w4 * 2 * CT + t) * 4 + r) * 80 + lane] = acc[t][r];
+      if (lane < 16) {
+        fbn[(w4 * 2 + 0) * 16 + lane] = dot;
+        fbn[(w4 * 2 + 1) * 16 + lane] = nrm;
+      }
+    }
+    group_barrier();   // B1: partial sums of the logits (and, from the last step, of the recurrent rows) are in LDS
+    // ---- keys: item (row quad q4, part): lane = (row 4 q4 + l4, columns l15 and l15 + 16 of the part)
+#pragma unroll
+    for (int k = 0; k < Cfg::NI; ++k) {
+      const int item = wave + 8 * k;
+      if (item >= 4 * CT) continue;
+      const int q4 = item & 3, ct = item >> 2, part = ct * CG + cg;
+      float k1 = kKeyNone, k2 = kKeyNone;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        float v = bias[k][t];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += fred[((w * 2 * CT + 2 * ct + t) * 4 + l4) * 80 + 16 * q4 + l15];
+        push_top2(k1, k2, make_key(v, 16 * t + l15));
+      }
+      merge_top2(k1, k2, dpp_f32<kDppRowMirror>(k1), dpp_f32<kDppRowMirror>(k2));
+      merge_top2(k1, k2, dpp_f32<kDppRowHalfMirror>(k1), dpp_f32<kDppRowHalfMirror>(k2));
+      merge_top2(k1, k2, dpp_f32<kDppQuadXor2>(k1), dpp_f32<kDppQuadXor2>(k2));
+      merge_top2(k1, k2, dpp_f32<kDppQuadXor1>(k1), dpp_f32<kDppQuadXor1>(k2));
+      const int lr = 4 * q4 + l4, row = rt * SPT * W + lr;
+      if (part < nparts && l15 == 0 && lr < SPT * W && row < R)
+        group_st(kp + (size_t)row * kstride + part, __float_as_uint(k1), __float_as_uint(key_with_tag(k2, tag)), near);
+    }
+    if constexpr (ROLE == 1) {
+      if (wave == 4 && cg == 0 && lane < SPT * W && rt * SPT * W + lane < R) {   // SPT * W <= 16
+        float d2 = b_blank, n2 = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { d2 += fbn[(w * 2 + 0) * 16 + lane]; n2 += fbn[(w * 2 + 1) * 16 + lane]; }
+        group_st(kp + (size_t)(rt * SPT * W + lane) * kstride + nparts, __float_as_uint(d2), __float_as_uint(key_with_tag(sqrtf(n2), tag)), near);
+      }
+      for (int i = tid1; i < pend * NR; i += 256) {
+        const int e = i / NR, row = i - e * NR;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += recp[(w * NR + row) * 4 + e];
+        const int s = e == 0 ? pend_slot[0] : e == 1 ? pend_slot[1] : e == 2 ? pend_slot[2] : pend_slot[3];
+        recs[s * NR + row] = v;
+      }
+      pend = 0;
+    }
+    // ---- exchange 1: four rows per wave and pass, 16 lanes per row, lane s with the keys of parts s and s + 16
+    if (nq > 0) {
+      float2 kA[2], kB[2], kC[2];
+      bool valid[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int row = 4 * (wave + 8 * k) + l4, a = div_w(row);
+        valid[k] = k < nq && row - a * W < __shfl(nwin, a, kWave);
+        kA[k] = kB[k] = make_float2(kKeyNone, kKeyNone);
+        kC[k] = make_float2(0.f, 0.f);
+      }
+      auto pair = [](unsigned long long u) { return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32))); };
+      const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+        bool fresh = true;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (valid[k]) {
+            const unsigned long long *kr = kp + (size_t)(4 * (wave + 8 * k) + l4) * kstride;
+            if (l15 < nparts) kA[k] = pair(group_ld(kr + l15));
+            if (l15 + 16 < nparts) kB[k] = pair(group_ld(kr + l15 + 16));
+            kC[k] = pair(group_ld(kr + nparts));
+          }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (valid[k])
+            fresh = fresh && (l15 >= nparts || key_tag(kA[k].y) == tag) && (l15 + 16 >= nparts || key_tag(kB[k].y) == tag) && key_tag(kC[k].y) == tag;
+        return fresh;
+      });
+      if (!got && lane == 0) *fail = 1;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (k >= nq) continue;
+        const float a2 = l15 < nparts ? key_with_tag(kA[k].y, 0) : kKeyNone, b2 = l15 + 16 < nparts ? key_with_tag(kB[k].y, 0) : kKeyNone;
+        const float kbest = row16_max_f32(fmaxf(kA[k].x, kB[k].x));
+        const float vbest = key_val(kbest), top = fmaxf(vbest, kC[k].x);
+        const float thresh = top - (m.tau_scale * kC[k].y + 6.2e-5f * fabsf(top));
+        const int cnt = row16_sum_i32((key_val(kA[k].x) >= thresh) + (key_val(a2) >= thresh) + (key_val(kB[k].x) >= thresh) + (key_val(b2) >= thresh));
+        int col = -1;
+        if (kA[k].x == kbest) col = l15 * 32 + key_col(kbest);
+        if (kB[k].x == kbest) col = (l15 + 16) * 32 + key_col(kbest);
+        col = row16_max_i32(col);
+        int label = V;
+        if (valid[k] && !(vbest < thresh)) label = cnt == 1 && kC[k].x < thresh ? col : -1;   // -1: near-tie
+        if (l15 == 0) stat[4 * (wave + 8 * k) + l4] = label;
+      }
+    }
+    if constexpr (ROLE == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
+    group_barrier();   // B2: every row's label, or that it is a near-tie
+    if (*fail) return;
+    int lab = lane < R ? stat[lane] : V;
+    unsigned long long m_nb = __ballot(lab >= 0 && lab != V);
+    // near-ties before the first certain label of their window: fp32 logits, one row per wave
+    const int oa = div_w(lane), oj = lane - oa * W;
+    const unsigned long long need = __ballot(lab < 0 && ((m_nb >> (oa * W)) & ((1ull << oj) - 1ull)) == 0ull);
+    if (need) {
+      unsigned long long todo = need;
+      // the waves with the fuller registers leave these to the others
+      constexpr bool mine = ROLE == 0 ? CT < 4 : NR <= 80;
+      constexpr int turns = CT < 4 && NR <= 80 ? 8 : 4;
+      for (int k = 0; mine && todo; ++k, todo &= todo - 1) {
+        if ((k & (turns - 1)) != (wave & (turns - 1))) continue;
+        const int row = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1), a = __builtin_amdgcn_readlane(oa, row), j = __builtin_amdgcn_readlane(oj, row);
+        const int b = __builtin_amdgcn_readlane(sl.b, a), t = __builtin_amdgcn_readlane(sl.t, a);
+        float4 kk0 = no_keys();
+        const unsigned long long *kr = kp + (size_t)row * kstride;
+        const unsigned long long uc = group_ld(kr + nparts);
+        if (lane < nparts) {
+          const unsigned long long u = group_ld(kr + lane);
+          kk0.x = __uint_as_float((unsigned)u);
+          kk0.y = key_with_tag(__uint_as_float((unsigned)(u >> 32)), 0);
+        }
+        const float vblank = __uint_as_float((unsigned)uc), znorm = __uint_as_float((unsigned)(uc >> 32));
+        const float top = fmaxf(key_val(wave_max_f32(kk0.x)), vblank);
+        const float thresh = top - (m.tau_scale * znorm + 6.2e-5f * fabsf(top));
+        CallDev cl = c;
+        cl.p = pfull + ((long long)a - b) * H;   // recheck_row looks at row b
+        int none = -1;
+        float unused = 0.f;
+        const int l = recheck_row<KS, 2>(m, cl, row, b, t + j, nparts, nparts, 32, vblank, thresh, kk0, false, no_keys(), false, none, unused);
+        if (lane == 0) stat2[row] = l;
+      }
+      group_barrier();
+      if ((need >> lane) & 1ull) lab = stat2[lane];
+      m_nb = __ballot(lab >= 0 && lab != V);
+    }
+    const int oshift = lane < NS ? lane * W : 0;
+    // ---- outcome of every slot's window, in every wave alike; one wave of workgroup 0 writes the outputs
+    const unsigned seg = lane < NS ? (unsigned)(m_nb >> oshift) & segm : 0u;
+    const int first = seg ? __ffs((int)seg) - 1 : -1;
+    int tok = __shfl(lab, oshift + max(first, 0), kWave);
+    tok = min(max(tok, 0), V);
+    bool emits = false, fresh_slot = false;
+    if (nwin > 0) {
+      const bool writer = ROLE == 1 && wave == 7 && g == 0;
+      const int rech = __popc((unsigned)(need >> oshift) & segm);
+      const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, rech, writer);
+      const int adv = wo.slot.y - sl.t;
+      sl.t = wo.slot.y; sl.sym = wo.slot.w; sl.cnt = wo.cnt;
+      sl.rpos += adv;
+      if (sl.rpos >= W2) sl.rpos -= W2;
+      ++sl.wc;
+      sl.ld0 = sl.ld;
+      sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
+      const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
+      if (writer) {   // the call's counters: additions that nobody waits for (fewer than 2^31 each: B T (S + 1) is an int)
+        const unsigned ev = wo.ev;
+        atomicAdd(&counts[ST_WINDOWS], 1);
+        atomicAdd(&counts[ST_ROWS], (int)(ev & 127u));
+        atomicAdd(&counts[ST_USEFUL], (int)((ev >> 7) & 127u));
+        if ((ev >> 21) & 127u) atomicAdd(&counts[ST_RECHECK], (int)((ev >> 21) & 127u));
+        if (ev >> 28) {
+          atomicAdd(&counts[ST_LABELS], (int)((ev >> 28) & 1u));
+          atomicAdd(&counts[ST_FORCED], (int)((ev >> 29) & 1u));
+          atomicAdd(&counts[ST_OVERFLOW], (int)((ev >> 30) & 1u));
+        }
+        atomicAdd(&counts[kStatJump0 + ((ev >> 14) & 127u)], 1);
+        if (done) atomicMax(&counts[ST_ITER], sl.wc);
+        if (cut) atomicAdd(&c.n_active[0], 1);
+      }
+      emits = (wo.flag & 2) && !done;
+      if (done) {   // the slot's next utterance, or nothing
+        fresh_slot = sl.nb >= 0;
+        sl.b = fresh_slot ? sl.nb : 0;
+        sl.len = fresh_slot ? sl.nlen : 0;
+        sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+        sl.ld = min(sl.len, W2);
+        if (fresh_slot) {
+          ++sl.round;
+          next_entry(sl.round, sl.nb, sl.nlen);
+        }
+      }
+    } else {
+      sl.ld0 = sl.ld;
+    }
+    const unsigned long long em = __ballot(emits), rf = __ballot(fresh_slot);
+    if (em) {
+      const int n_em = __popcll(em);
+      int es[kGroupSlots] = {0, 0, 0, 0}, et[kGroupSlots] = {0, 0, 0, 0};
+      {
+        unsigned long long todo = em;
+#pragma unroll
+        for (int e = 0; e < kGroupSlots; ++e)
+          if (todo) {
+            es[e] = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+            et[e] = __builtin_amdgcn_readlane(tok, es[e]);
+            todo &= todo - 1;
+          }
+      }
+      // ---- LSTM step: thread (emitting slot le, gate row li of this workgroup's units)
+      const int lvt = ROLE == 1 ? tid1 : tid1 + 256, le = lvt / NR, li = lvt - le * NR;
+      if (le < n_em) {
+        const int s = le == 0 ? es[0] : le == 1 ? es[1] : le == 2 ? es[2] : es[3], tk = le == 0 ? et[0] : le == 1 ? et[1] : le == 2 ? et[2] : et[3];
+        const float pre = recs[s * NR + li] + m.emb_gates[(unsigned)tk * (4u * H) + (unsigned)(unit0 * 4 + li)];   // fits 32 bits: checked by the host
+        const float act = (li & 3) == 2 ? tanhf(pre) : 1.f / (1.f + expf(-pre));
+        const float ig = dpp_f32<0x00>(act), fg = dpp_f32<0x55>(act), gg = dpp_f32<0xAA>(act), og = dpp_f32<0xFF>(act);   // the unit's four gates
+        if ((li & 3) == 0) {
+          const int u = li >> 2;
+          const float cn = fg * cst[s * Cfg::UPW + u] + ig * gg;
+          cst[s * Cfg::UPW + u] = cn;
+          const float hv = og * tanhf(cn);
+          const unsigned hb = f32_to_bf16_bits(hv), lb = f32_to_bf16_bits(hv - bf16_bits_to_f32(hb));
+          group_st(hx + s * H + unit0 + u, hb | (lb << 16), stamp, near);
+        }
+      }
+      if constexpr (ROLE == 1) {
+        // ---- exchange 2: this wave's quarter of the new hidden vectors, as bf16 hi and lo rows
+        unsigned long long u[kGroupSlots][QL];
+        const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+#pragma unroll
+          for (int e = 0; e < kGroupSlots; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) u[e][q] = group_ld(hx + es[e] * H + w4 * QK + min(lane + 64 * q, QK - 1));
+            }
+          bool fresh = true;
+#pragma unroll
+          for (int e = 0; e < kGroupSlots; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) fresh = fresh && (unsigned)(u[e][q] >> 32) == stamp;
+            }
+          return fresh;
+        });
+        if (!got && lane == 0) *fail = 1;
+#pragma unroll
+        for (int e = 0; e < kGroupSlots; ++e)
+          if (e < n_em) {
+#pragma unroll
+            for (int q = 0; q < QL; ++q)
+              if (lane + 64 * q < QK) {
+                bf16_t *d = hbuf + 2 * e * Cfg::HST + w4 * QK + lane + 64 * q;
+                d[0] = (bf16_t)u[e][q];
+                d[Cfg::HST] = (bf16_t)(u[e][q] >> 16);
+              }
+          }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's own rows: no barrier
+        bf16x8 hf[KS];   // first operand: rows 2 e and 2 e + 1 = hi and lo of the e-th emitting slot (rows of others: not looked at)
+        const bf16_t *hsrc = hbuf + (l15 & 7) * Cfg::HST + w4 * QK + l4 * 8;
+#pragma unroll
+        for (int i = 0; i < KS; ++i) hf[i] = *reinterpret_cast<const bf16x8 *>(hsrc + i * 32);
+        f32x4 pacc[Cfg::PT];
+#pragma unroll
+        for (int t = 0; t < Cfg::PT; ++t) {
+          pacc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < KS; ++i) pacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hf[i], wp[t][i], pacc[t], 0, 0, 0);
+          // lane (weight row l15, first-operand rows 4 l4 ..): slots 2 l4 and 2 l4 + 1, hi + lo
+          if (lane < 32)
+            *reinterpret_cast<float2 *>(&predp[(w4 * 16 * Cfg::PT + 16 * t + l15) * 4 + 2 * l4]) = make_float2(pacc[t][0] + pacc[t][1], pacc[t][2] + pacc[t][3]);
+        }
+        group_barrier();   // B3: partial sums of the projection rows
+        if (tid1 < n_em * Cfg::PPW) {
+          const int e = tid1 / Cfg::PPW, row = tid1 - e * Cfg::PPW;
+          float v = 0.f;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) v += predp[(w * 16 * Cfg::PT + row) * 4 + e];
+          const int s = e == 0 ? es[0] : e == 1 ? es[1] : e == 2 ? es[2] : es[3];
+          group_st(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp, near);
+        }
+        // ---- off the chain: the recurrent sums of the next step (their partial sums are added behind the next barrier)
+#pragma unroll
+        for (int t = 0; t < Cfg::LT; ++t) {
+          f32x4 racc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < KS; ++i) racc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hf[i], wr[t][i], racc, 0, 0, 0);
+          if (lane < 32) *reinterpret_cast<float2 *>(&recp[(w4 * NR + 16 * t + l15) * 4 + 2 * l4]) = make_float2(racc[0] + racc[1], racc[2] + racc[3]);
+        }
+        pend = n_em;
+#pragma unroll
+        for (int e = 0; e < kGroupSlots; ++e) pend_slot[e] = es[e];
+      } else {
+        group_barrier();   // B3
+        // ---- exchange 3: this wave's quarter of the new projections
+        unsigned long long u[kGroupSlots][QL];
+        const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+#pragma unroll
+          for (int e = 0; e < kGroupSlots; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) u[e][q] = group_ld(px + es[e] * H + w4 * QK + min(lane + 64 * q, QK - 1));
+            }
+          bool fresh = true;
+#pragma unroll
+          for (int e = 0; e < kGroupSlots; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) fresh = fresh && (unsigned)(u[e][q] >> 32) == stamp;
+            }
+          return fresh;
+        });
+        if (!got && lane == 0) *fail = 1;
+#pragma unroll
+        for (int e = 0; e < kGroupSlots; ++e)
+          if (e < n_em) {
+#pragma unroll
+            for (int q = 0; q < QL; ++q)
+              if (lane + 64 * q < QK) pfull[es[e] * H + w4 * QK + lane + 64 * q] = __uint_as_float((unsigned)u[e][q]);
+          }
+      }
+    }
+    if constexpr (ROLE == 1) load_frames();
+    if (rf) {   // slots that took a new utterance: the state after the start token, their first frames
+      unsigned long long todo = rf;
+      while (todo) {
+        const int a = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+        todo &= todo - 1;
+        if constexpr (ROLE == 0) {
+          for (int i = tid1; i < H; i += 256) pfull[a * H + i] = m.start_p[i];
+        } else {
+          for (int i = tid1; i < NR; i += 256) recs[a * NR + i] = m.start_rec[unit0 * 4 + i];
+          for (int i = tid1; i < Cfg::UPW; i += 256) cst[a * Cfg::UPW + i] = m.start_c[unit0 + i];
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      group_barrier();
+    }
+  }
+  if constexpr (ROLE == 1) {
+    if (g == 0 && wave == 7)   // the group's counters
+      for (int j = lane; j < kNumStats; j += 64) {
+        if (j == ST_ITER) atomicMax(&c.stats[j], (unsigned long long)counts[j]);
+        else if (counts[j]) atomicAdd(&c.stats[j], (unsigned long long)counts[j]);
+      }
+  }
+}
+
+template <int KS, int CT, int GW>
+__global__ __launch_bounds__(512) void wind_group_kernel(ModelDev m, CallDev c, GroupDev gd) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;   // workgroups go to the XCDs in turn
+  if (grp >= gd.NG) return;
+  if (threadIdx.x < 256) group_loop<KS, CT, GW, 0>(m, c, gd, smem_raw, grp, g);
+  else group_loop<KS, CT, GW, 1>(m, c, gd, smem_raw, grp, g);
+}
+
+}  // namespace wind

@@ -23,8 +23,9 @@
 // implementations: MFMA tiles with the hidden state split into bf16 hi + lo, low-latency
 // wave-per-unit kernels (the start-token step of the resident loop kernel), generic FMA (fp32
 // models).  fp32 models replace build_z + joint by joint_exact (fp32 FMA, argmax taken directly).
-// One or two utterances of a one-layer model run the whole loop as one resident kernel
-// (wind_loop_kernel).
+// Small batches of a one-layer model run the whole loop as one resident kernel: a group of workgroups per
+// XCD, each with utterances of its own (wind_group_kernel), or, for one or two utterances of the shapes
+// that one does not take, workgroups over the whole chip (wind_loop_kernel).
 #pragma once
 #include "wind_types.h"
 #include "wind_enc_kernels.h"
@@ -32,3 +33,4 @@
 #include "wind_decide_kernels.h"
 #include "wind_pred_kernels.h"
 #include "wind_loop_kernel.h"
+#include "wind_group_kernel.h"

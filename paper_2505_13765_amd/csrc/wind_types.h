@@ -37,6 +37,8 @@ struct ModelDev {
   const void *w_out_slab;       // bf16 models: the same matrix in slabs of 32 K values, [Hj / 32][Vpad][32] (wide joint tiles)
   const float *b_out;           // [V+1]
   const float *w_blank;         // [Hj] fp32 copy of row V
+  const float *start_c, *start_p, *start_rec;   // one-layer models that decode in resident groups: the state after the start token (cell state
+                                //   [Hp], projection [Hj], recurrent gate sums [4Hp]), the same for every utterance; else null
   float tau_scale;              // near-tie band = tau_scale * |z|_2 (+ key truncation)
 };
 
