@@ -485,6 +485,10 @@ void enqueue_enc_proj(wind_model *m, hipStream_t s) {
         launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_mfma_kernel<EncCfg>, grid, dim3(EncCfg::NT), EncCfg::SMEM_BYTES, d, c,
                tiles_per_utt);
       }
+    } else if (d.D % 4 == 0 && (uintptr_t)c.enc % 16 == 0) {   // the tiles load four inputs at a time
+      const int tiles_per_utt = (c.T + 63) / 64;
+      launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_f32_tile_kernel, dim3((unsigned)(c.B * tiles_per_utt), (unsigned)((d.Hj + 63) / 64)), dim3(256), 0,
+             d, c, tiles_per_utt);
     } else {
       launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_f32_kernel, dim3((unsigned)c.T, (unsigned)c.B), dim3(256),
              (size_t)d.D * 4, d, c);
@@ -669,26 +673,35 @@ bool loop_kernel_shape(const wind_model *m, int B, int T, int W, LoopDev *lp, si
   return false;
 }
 
-// ---- resident groups (wind_group_kernel)
+// ---- resident groups (wind_group_kernel, wind_group_f32_kernel)
 struct GroupInstance {
   void (*kernel)(ModelDev, CallDev, GroupDev);
   size_t smem;
-  int ks, ct, gw;
+  int dtype, H, ct, gw;
 };
 template <int KS, int CT, int GW>
 constexpr GroupInstance group_instance() {
-  return {wind_group_kernel<KS, CT, GW>, GroupCfg<KS, CT, GW>::smem, KS, CT, GW};
+  return {wind_group_kernel<KS, CT, GW>, GroupCfg<KS, CT, GW>::smem, WIND_BF16, GroupCfg<KS, CT, GW>::H, CT, GW};
+}
+template <int NK, int CT, int GW>
+constexpr GroupInstance group_f32_instance() {
+  return {wind_group_f32_kernel<NK, CT, GW>, GroupF32Cfg<NK, CT, GW>::smem, WIND_F32, GroupF32Cfg<NK, CT, GW>::H, CT, GW};
 }
 const GroupInstance kGroupInstances[] = {
     group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<1, 4, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(),
     group_instance<2, 4, 32>(), group_instance<3, 1, 32>(), group_instance<3, 2, 32>(), group_instance<3, 4, 32>(), group_instance<4, 1, 32>(),
     group_instance<4, 2, 32>(), group_instance<4, 4, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(), group_instance<5, 4, 32>(),
-    group_instance<5, 2, 20>()};
+    group_instance<5, 2, 20>(),
+    group_f32_instance<2, 4, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
+    group_f32_instance<8, 1, 32>(), group_f32_instance<12, 1, 32>(), group_f32_instance<16, 1, 32>(), group_f32_instance<20, 1, 32>()};
 
-// Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts).
+// Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts), a width
+// that some instance has.
 bool group_model(int dtype, const ModelDev &d) {
-  return dtype == WIND_BF16 && d.L == 1 && d.Hp == d.Hj && d.Hj % 128 == 0 && d.Hj <= 640 && d.V <= 1024 &&
-         (unsigned long long)(d.V + 1) * 4 * d.Hp < (1ull << 31);
+  if (d.L != 1 || d.Hp != d.Hj || d.V > 1024 || (unsigned long long)(d.V + 1) * 4 * d.Hp >= (1ull << 31)) return false;
+  for (const GroupInstance &i : kGroupInstances)
+    if (i.dtype == dtype && i.H == d.Hj) return true;
+  return false;
 }
 
 // The resident groups of this call, or null if the call does not qualify.
@@ -700,19 +713,30 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
   // options that shape the graph of per-step kernels ask for that graph
   if (B > kLoopMaxB && (!m->opt_lstm_rec || !m->opt_atomic_lists || !m->opt_slot_rows || !m->opt_decide_two || m->opt_joint_wide != 1 ||
                         m->opt_pred_mfma_min_batch > B)) return nullptr;
-  // two utterances: two groups of 20 workgroups (the LSTM's 640 units divide by 20); else 32, the CUs of an XCD
-  const int gw = B == 2 && d.Hp == 640 ? 20 : 32;
   const int nparts = (d.V + kTinyCols - 1) / kTinyCols;
-  gd->NG = std::min(kGroups, B);
-  gd->NS = std::min(kGroupSlots, (B + gd->NG - 1) / gd->NG);
-  gd->SPT = std::min(kGroupMaxW / W, gd->NS);
-  const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
-  gd->RG = tiles > 2 ? 4 : tiles;
-  const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
-  const int ct = gw == 20 ? 2 : parts > 2 ? 4 : parts;
-  if (parts > ct) return nullptr;
+  int gw, ct;
+  if (m->dtype == WIND_F32 && d.Hj <= 128 && nparts <= 4) {
+    // a model that fits one CU: a workgroup per utterance
+    gw = 1;
+    ct = 4;
+    gd->NG = B;
+    gd->NX = 0;
+    gd->NS = gd->SPT = gd->RG = 1;
+  } else {
+    // two utterances of 640 units: two groups of 20 workgroups (640 divides by 20); else 32, the CUs of an XCD
+    gw = m->dtype == WIND_BF16 && B == 2 && d.Hp == 640 ? 20 : 32;
+    gd->NG = gd->NX = std::min(kGroups, B);
+    gd->NS = std::min(kGroupSlots, (B + gd->NG - 1) / gd->NG);
+    if (m->dtype == WIND_F32) gd->NS = std::min(gd->NS, kGroupMaxW / W);   // one row tile: registers hold one part of W_out
+    gd->SPT = std::min(kGroupMaxW / W, gd->NS);
+    const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
+    gd->RG = tiles > 2 ? 4 : tiles;
+    const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
+    ct = gw == 20 ? 2 : parts > 2 ? 4 : parts;
+    if (parts > ct) return nullptr;
+  }
   for (const GroupInstance &i : kGroupInstances)
-    if (i.ks == d.Hj / 128 && i.ct == ct && i.gw == gw) return &i;
+    if (i.dtype == m->dtype && i.H == d.Hj && i.ct == ct && i.gw == gw) return &i;
   return nullptr;
 }
 
@@ -808,11 +832,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     group_init_kernel<<<64, 256, 0, s>>>(m->dev, c, gd);
     enqueue_enc_proj(m, s);
     HIP_TRY(hipEventRecord(m->ev_call[1], s));
-    gi->kernel<<<(unsigned)(kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
+    gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
     HIP_TRY(hipEventRecord(m->ev_call[2], s));
-    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NG, c.stats, kNumStats, m->h_flag, m->h_stats);
+    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, kNumStats, m->h_flag, m->h_stats);
     rc = check_launch("resident groups' results");
     if (rc) return rc;
     if (async) {
@@ -1112,7 +1136,9 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     if (e == hipSuccess) {
       m->allocs.push_back(st);
       float *sc = (float *)st, *sp = sc + Hp, *sr = sp + d.Hj;
-      group_start_kernel<<<(unsigned)((4 * Hp + d.Hj + 3) / 4), 256, (size_t)Hp * sizeof(float), m->load_stream>>>(d, sc, sp, sr);
+      const unsigned blocks = (unsigned)((4 * Hp + d.Hj + 3) / 4);
+      if (m->dtype == WIND_BF16) group_start_kernel<bf16_t><<<blocks, 256, (size_t)Hp * sizeof(float), m->load_stream>>>(d, sc, sp, sr);
+      else group_start_kernel<float><<<blocks, 256, (size_t)Hp * sizeof(float), m->load_stream>>>(d, sc, sp, sr);
       chk(check_launch("start state"));
       e = hipStreamSynchronize(m->load_stream);
       d.start_c = sc; d.start_p = sp; d.start_rec = sr;

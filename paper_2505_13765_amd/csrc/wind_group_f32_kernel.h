@@ -1,0 +1,437 @@
+// Resident groups for fp32 models: the loop of wind_group_kernel.h with fp32 weights and products.
+#pragma once
+#include "wind_group_kernel.h"
+
+namespace wind {
+
+// ---------------------------------------------------------------------------------------------
+// The same loop and the same exchanges; what differs:
+//   - every logit is an fp32 matrix-core product (16 x 16 x 4), so a row's argmax is taken from the exchanged (value,
+//     column) words and no near-tie is decided again;
+//   - weights are twice as wide: all eight waves share them (K split in eight), W_out as matrix-core operands, the
+//     recurrent and the projection rows one row per lane (a matrix-vector product per emitting slot: the hidden
+//     vector is read from LDS as a broadcast, nothing is summed over lanes).  One row tile per group: slots x W <= 16;
+//   - small models (GW = 1: a whole model fits one CU's registers) run one workgroup per utterance, which
+//     tells itself through LDS, behind workgroup barriers.
+// Bound by the chain of steps like the bf16 groups; of 640 units the products of a 16-row tile take 1.2 us (fp32 rate).
+template <int NK, int CT, int GW>
+struct GroupF32Cfg {
+  static constexpr int H = 32 * NK, KW = H / 8;             // = Hp = Hj; a wave's part of K
+  static constexpr int UPW = H / GW, NR = 4 * UPW, PPW = H / GW, NSET = (NR + PPW + 63) / 64;
+  static constexpr int SL = GW == 1 ? 1 : kGroupSlots;
+  static constexpr int EST = H + 4, QL = (KW + 63) / 64, NI = (4 * CT + 7) / 8;
+  static_assert(PPW <= 64 || GW == 1, "the projection rows come first");
+  static constexpr int PSET = (PPW + 63) / 64;               // sets of 64 rows that hold projection rows
+  static constexpr size_t oE = 0;                                          // float [32][EST]
+  static constexpr size_t oFred = oE + (size_t)32 * EST * 4;               // float [8][2 CT][4][80]
+  static constexpr size_t oFbn = oFred + (size_t)8 * 2 * CT * 4 * 80 * 4;  // float [8][16]
+  static constexpr size_t oP = oFbn + 512;                                 // float [SL][H]
+  static constexpr size_t oHb = oP + (size_t)SL * H * 4;                   // float [SL][H]
+  static constexpr size_t oPart = oHb + (size_t)SL * H * 4;                // float [8][SL][64 NSET]
+  static constexpr size_t oRec = oPart + (size_t)8 * SL * 64 * NSET * 4;   // float [SL][NR]
+  static constexpr size_t oC = oRec + (size_t)SL * NR * 4;                 // float [SL][UPW]
+  static constexpr size_t oW = oC + (size_t)SL * UPW * 4;                  // float [H] blank column of W_out
+  static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1], [H], [H]
+  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], fail, near; float bp[PPW]
+  static constexpr size_t smem = (oI + (64 + kNumStats + 2 + PPW) * 4 + 15) / 16 * 16;
+  static_assert(smem <= 160 * 1024, "LDS");
+};
+
+template <int NK, int CT, int GW>
+__global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev c, GroupDev gd) {
+  using Cfg = GroupF32Cfg<NK, CT, GW>;
+  constexpr int H = Cfg::H, KW = Cfg::KW, NR = Cfg::NR, PPW = Cfg::PPW, QL = Cfg::QL, NSET = Cfg::NSET, SL = Cfg::SL;
+  constexpr bool SOLO = GW == 1;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int grp = SOLO ? (int)blockIdx.x : (int)blockIdx.x % kGroups, g = SOLO ? 0 : (int)blockIdx.x / kGroups;
+  if (grp >= gd.NG) return;
+  float *ecache = reinterpret_cast<float *>(smem + Cfg::oE), *fred = reinterpret_cast<float *>(smem + Cfg::oFred);
+  float *fbn = reinterpret_cast<float *>(smem + Cfg::oFbn), *pfull = reinterpret_cast<float *>(smem + Cfg::oP);
+  float *hbuf = reinterpret_cast<float *>(smem + Cfg::oHb), *partl = reinterpret_cast<float *>(smem + Cfg::oPart);
+  float *recs = reinterpret_cast<float *>(smem + Cfg::oRec), *cst = reinterpret_cast<float *>(smem + Cfg::oC);
+  float *wbl = reinterpret_cast<float *>(smem + Cfg::oW);
+  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *counts = stat + 64, *fail = counts + kNumStats, *near_w = fail + 1;
+  float *bpl = reinterpret_cast<float *>(near_w + 1);
+
+  int lane = threadIdx.x & 63, tid = threadIdx.x, l15 = lane & 15, l4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int W = c.W, V = m.V, NS = gd.NS, W2 = 2 * W, R = NS * W, nparts = c.nparts_tiny, kstride = nparts + 1;
+  unsigned *abort_word = SOLO ? nullptr : gd.bar + grp * kGroupBarInts;
+  unsigned long long *xs = reinterpret_cast<unsigned long long *>(smem + Cfg::oX);
+  unsigned long long *hx = SOLO ? xs + 16 * (CT + 1) : gd.h_x + (size_t)grp * kGroupSlots * H;
+  unsigned long long *px = SOLO ? hx + H : gd.p_x + (size_t)grp * kGroupSlots * H;
+  unsigned long long *kbase = SOLO ? xs : gd.keys + (size_t)grp * 2 * kGroupRows * kstride;
+  const int unit0 = g * Cfg::UPW, prow0 = g * PPW;
+  const int n_order = *gd.n_order;
+  GroupLane sl = group_first_slots(c, gd, grp, lane, n_order);
+
+  // ---- weights into registers
+  float wo[2 * CT][NK], wv[NSET][KW];
+#pragma unroll
+  for (int t = 0; t < 2 * CT; ++t) {
+    const int col = min(((t >> 1) * GW + g) * 32 + 16 * (t & 1) + l15, m.Vpad - 1);
+    const float *src = reinterpret_cast<const float *>(m.w_out) + (size_t)col * H + wave * KW + l4 * NK;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) wo[t][i] = src[i];
+  }
+#pragma unroll
+  for (int t = 0; t < NSET; ++t) {
+    const int r = t * 64 + lane;
+    const float *src = (r < PPW ? reinterpret_cast<const float *>(m.w_pred) + (size_t)(prow0 + r) * H
+                                : reinterpret_cast<const float *>(m.w_cat[0]) + (size_t)(unit0 * 4 + min(r - PPW, NR - 1)) * H) + wave * KW;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) wv[t][i] = src[i];
+  }
+  auto load_frames = [&]() { group_load_frames<H, Cfg::EST>(c, gd, sl, ecache, 0, lane, wave, 8); };
+
+  // ---- state after the start token
+  for (int i = tid; i < NS * H; i += 512) pfull[i] = m.start_p[i % H];
+  for (int i = tid; i < H; i += 512) wbl[i] = m.w_blank[i];
+  for (int i = tid; i < NS * NR; i += 512) recs[i] = m.start_rec[unit0 * 4 + i % NR];
+  for (int i = tid; i < NS * Cfg::UPW; i += 512) cst[i] = m.start_c[unit0 + i % Cfg::UPW];
+  for (int i = tid; i < kNumStats; i += 512) counts[i] = 0;
+  for (int i = tid; i < PPW; i += 512) bpl[i] = m.b_pred[prow0 + i];
+  load_frames();
+  if (tid == 0) { *fail = 0; *near_w = 1; }
+  // ---- where the workgroups sit: XCD numbers, exchanged with device-wide stores
+  if (!SOLO && wave == 0) {
+    unsigned xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    xcc = (xcc & 15u) + 1u;
+    unsigned *bw = abort_word + 32;
+    if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned v = xcc;
+    const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+      if (lane < GW) v = __hip_atomic_load(bw + lane * 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return v != 0u;
+    });
+    const bool same = __all(v == xcc);
+    if (lane == 0) {
+      *near_w = same;
+      if (!got) *fail = 1;
+      if (g == 0) abort_word[1] = same ? 2u : 1u;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  group_barrier();
+  const bool near = *near_w != 0;
+  auto put = [&](unsigned long long *p, unsigned lo, unsigned hi) {
+    if constexpr (SOLO) *p = (unsigned long long)lo | ((unsigned long long)hi << 32);
+    else group_st(p, lo, hi, near);
+  };
+  auto get = [&](const unsigned long long *p) {
+    if constexpr (SOLO) return *p;
+    else return group_ld(p);
+  };
+  auto wait = [&](const auto &ask) {   // SOLO: the words are behind a workgroup barrier
+    if constexpr (SOLO) { ask(); return true; }
+    else return group_poll(abort_word, gd.spin_limit, ask);
+  };
+
+  const float b_blank = m.b_out[V];
+  const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
+  auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
+  float bias[Cfg::NI][2];
+#pragma unroll
+  for (int k = 0; k < Cfg::NI; ++k)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int item = wave + 8 * k, part = (item >> 2) * GW + g, col = part * 32 + 16 * t + l15;
+      bias[k][t] = item < 4 * CT && part < nparts && col < V ? m.b_out[col] : kKeyNone;   // what is added to kKeyNone vanishes in it
+    }
+  int pend = 0, pend_slot[kGroupSlots] = {0, 0, 0, 0};
+
+  for (int it = 0;; ++it) {
+    asm volatile("" : "+v"(lane), "+v"(tid));   // see group_loop
+    l15 = lane & 15;
+    l4 = lane >> 4;
+    const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
+    if (!__any(nwin > 0)) break;
+    const unsigned stamp = (unsigned)it + 1u, stamp16 = stamp & 0xFFFFu;
+    unsigned long long *kp = SOLO ? kbase : kbase + (size_t)(it & 1) * kGroupRows * kstride;
+    {
+      // ---- window rows as matrix-core operands: lane (row l15, K group l4), NK consecutive units of this wave's part of K
+      f32x4 acc[2 * CT];
+#pragma unroll
+      for (int t = 0; t < 2 * CT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int gq = div_w(l15), ga = gq < NS ? gq : 0, gj = gq < NS ? l15 - ga * W : 0;
+      int rr = __shfl(sl.rpos, ga, kWave) + gj;
+      if (rr >= W2) rr -= W2;
+      const float *er = ecache + (ga * W2 + rr) * Cfg::EST + wave * KW + l4 * NK;
+      const float *pr = pfull + ga * H + wave * KW + l4 * NK, *br = wbl + wave * KW + l4 * NK;
+      float dot = 0.f;
+      constexpr int VEC = NK % 4 == 0 ? 4 : 2;
+#pragma unroll
+      for (int i = 0; i < NK; i += VEC) {
+        float ev[VEC], pv[VEC], bv[VEC];
+        if constexpr (VEC == 4) {
+          const float4 e4 = *reinterpret_cast<const float4 *>(er + i), p4 = *reinterpret_cast<const float4 *>(pr + i), b4 = *reinterpret_cast<const float4 *>(br + i);
+          ev[0] = e4.x; ev[1] = e4.y; ev[2] = e4.z; ev[3] = e4.w;
+          pv[0] = p4.x; pv[1] = p4.y; pv[2] = p4.z; pv[3] = p4.w;
+          bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
+        } else {
+          const float2 e2 = *reinterpret_cast<const float2 *>(er + i), p2 = *reinterpret_cast<const float2 *>(pr + i), b2 = *reinterpret_cast<const float2 *>(br + i);
+          ev[0] = e2.x; ev[1] = e2.y; pv[0] = p2.x; pv[1] = p2.y; bv[0] = b2.x; bv[1] = b2.y;
+        }
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+          const float z = fmaxf(ev[q] + pv[q], 0.f);
+          dot = fmaf(z, bv[q], dot);
+#pragma unroll
+          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(z, wo[t][i + q], acc[t], 0, 0, 0);
+        }
+      }
+      dot += __shfl_xor(dot, 16, kWave);
+      dot += __shfl_xor(dot, 32, kWave);
+#pragma unroll
+      for (int t = 0; t < 2 * CT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) fred[((wave * 2 * CT + t) * 4 + r) * 80 + lane] = acc[t][r];
+      if (lane < 16) fbn[wave * 16 + lane] = dot;
+    }
+    group_barrier();   // B1
+    // ---- best label of every (row, part): item (row quad q4, part): lane = (row 4 q4 + l4, columns l15 and l15 + 16)
+#pragma unroll
+    for (int k = 0; k < Cfg::NI; ++k) {
+      const int item = wave + 8 * k;
+      if (item >= 4 * CT) continue;
+      const int q4 = item & 3, ct = item >> 2, part = ct * GW + g;
+      float v[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        v[t] = bias[k][t];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v[t] += fred[((w * 2 * CT + 2 * ct + t) * 4 + l4) * 80 + 16 * q4 + l15];
+      }
+      const bool second = v[1] > v[0];   // ties: the lower column
+      const float b = second ? v[1] : v[0], bm = row16_max_f32(b);
+      const int col = 0xFFFF - row16_max_i32(b == bm ? 0xFFFF - (part * 32 + (second ? 16 : 0) + l15) : 0);
+      const int row = 4 * q4 + l4;
+      if (part < nparts && l15 == 0 && row < R) put(kp + row * kstride + part, __float_as_uint(bm), (unsigned)(col & 0xFFFF) | (stamp16 << 16));
+    }
+    if (wave == 4 && g == 0 && lane < R) {   // R <= 16
+      float d2 = b_blank;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) d2 += fbn[w * 16 + lane];
+      put(kp + lane * kstride + nparts, __float_as_uint(d2), stamp16 << 16);
+    }
+    if (wave >= 4)   // the recurrent sums of the last step
+      for (int i = tid - 256; i < pend * NR; i += 256) {
+        const int e = i / NR, row = i - e * NR;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += partl[(w * SL + e) * 64 * NSET + PPW + row];
+        const int s = e == 0 ? pend_slot[0] : e == 1 ? pend_slot[1] : e == 2 ? pend_slot[2] : pend_slot[3];
+        recs[s * NR + row] = v;
+      }
+    pend = 0;
+    // ---- exchange 1: four rows per wave, 16 lanes per row
+    if constexpr (SOLO) group_barrier();
+    if (4 * wave < R) {
+      const int row = 4 * wave + l4, a = div_w(row);
+      const bool valid = row - a * W < __shfl(nwin, a, kWave);
+      unsigned long long kA = 0ull, kB = 0ull, kC = 0ull;
+      const bool got = wait([&]() {
+        if (!valid) return true;
+        const unsigned long long *kr = kp + row * kstride;
+        if (l15 < nparts) kA = get(kr + l15);
+        if (l15 + 16 < nparts) kB = get(kr + l15 + 16);
+        kC = get(kr + nparts);
+        return (l15 >= nparts || (unsigned)(kA >> 48) == stamp16) && (l15 + 16 >= nparts || (unsigned)(kB >> 48) == stamp16) &&
+               (unsigned)(kC >> 48) == stamp16;
+      });
+      if (!got && lane == 0) *fail = 1;
+      float b = valid && l15 < nparts ? __uint_as_float((unsigned)kA) : kKeyNone;
+      int col = (int)(kA >> 32) & 0xFFFF;
+      if (valid && l15 + 16 < nparts && __uint_as_float((unsigned)kB) > b) {   // ties: the lower column
+        b = __uint_as_float((unsigned)kB);
+        col = (int)(kB >> 32) & 0xFFFF;
+      }
+      const float bm = row16_max_f32(b);
+      col = 0xFFFF - row16_max_i32(b == bm ? 0xFFFF - col : 0);
+      if (l15 == 0) stat[row] = !valid || __uint_as_float((unsigned)kC) > bm ? V : col;   // blank has the highest id: it wins only if strictly larger
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
+    group_barrier();   // B2
+    if (*fail) return;
+    const int lab = lane < R ? stat[lane] : V;
+    const unsigned long long m_nb = __ballot(lab != V);
+    int tok;
+    bool emits, fresh_slot;
+    group_outcome(c, gd, sl, grp, lane, n_order, nwin, V, m_nb, 0ull, lab, wave == 7 && g == 0, counts, tok, emits, fresh_slot);
+    const unsigned long long em = __ballot(emits), rf = __ballot(fresh_slot);
+    if (em) {
+      const int n_em = __popcll(em);
+      int es[kGroupSlots] = {0, 0, 0, 0}, et[kGroupSlots] = {0, 0, 0, 0};
+      {
+        unsigned long long todo = em;
+#pragma unroll
+        for (int e = 0; e < SL; ++e)
+          if (todo) {
+            es[e] = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+            et[e] = __builtin_amdgcn_readlane(tok, es[e]);
+            todo &= todo - 1;
+          }
+      }
+      // ---- LSTM step: thread (emitting slot, gate row of this workgroup's units)
+      for (int i = tid; i < n_em * NR; i += 512) {
+        const int le = i / NR, li = i - le * NR;
+        const int s = le == 0 ? es[0] : le == 1 ? es[1] : le == 2 ? es[2] : es[3], tk = le == 0 ? et[0] : le == 1 ? et[1] : le == 2 ? et[2] : et[3];
+        const float pre = recs[s * NR + li] + m.emb_gates[(unsigned)tk * (4u * H) + (unsigned)(unit0 * 4 + li)];   // fits 32 bits: checked by the host
+        const float act = (li & 3) == 2 ? tanhf(pre) : 1.f / (1.f + expf(-pre));
+        const float ig = dpp_f32<0x00>(act), fg = dpp_f32<0x55>(act), gg = dpp_f32<0xAA>(act), og = dpp_f32<0xFF>(act);   // the unit's four gates
+        if ((li & 3) == 0) {
+          const int u = li >> 2;
+          const float cn = fg * cst[s * Cfg::UPW + u] + ig * gg;
+          cst[s * Cfg::UPW + u] = cn;
+          put(hx + s * H + unit0 + u, __float_as_uint(og * tanhf(cn)), stamp);
+        }
+      }
+      // ---- exchange 2 / 3: this wave's part of the emitting slots' vectors, into its part of `to`
+      auto fetch = [&](const unsigned long long *from, float *to, bool by_slot) {
+        unsigned long long u[SL][QL];
+        const bool got = wait([&]() {
+          bool fresh = true;
+#pragma unroll
+          for (int e = 0; e < SL; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) u[e][q] = get(from + es[e] * H + wave * KW + min(lane + 64 * q, KW - 1));
+            }
+#pragma unroll
+          for (int e = 0; e < SL; ++e)
+            if (e < n_em) {
+#pragma unroll
+              for (int q = 0; q < QL; ++q) fresh = fresh && (unsigned)(u[e][q] >> 32) == stamp;
+            }
+          return fresh;
+        });
+        if (!got && lane == 0) *fail = 1;
+#pragma unroll
+        for (int e = 0; e < SL; ++e)
+          if (e < n_em) {
+#pragma unroll
+            for (int q = 0; q < QL; ++q)
+              if (lane + 64 * q < KW) to[(by_slot ? es[e] : e) * H + wave * KW + lane + 64 * q] = __uint_as_float((unsigned)u[e][q]);
+          }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back by this wave only
+      };
+      // rows of set `t` times the e-th new hidden vector, over this wave's part of K
+      auto row_sums = [&](int t, int e) {
+        const float *hr = hbuf + e * H + wave * KW;   // the same address in every lane
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+#pragma unroll
+        for (int k = 0; k < KW; k += 4) {
+          const float4 h4 = *reinterpret_cast<const float4 *>(hr + k);
+          a0 = fmaf(wv[t][k], h4.x, a0); a1 = fmaf(wv[t][k + 1], h4.y, a1); a2 = fmaf(wv[t][k + 2], h4.z, a2); a3 = fmaf(wv[t][k + 3], h4.w, a3);
+        }
+        partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = (a0 + a1) + (a2 + a3);
+      };
+      if constexpr (SOLO) group_barrier();
+      fetch(hx, hbuf, false);
+      for (int e = 0; e < n_em; ++e) {
+#pragma unroll
+        for (int t = 0; t < Cfg::PSET; ++t) row_sums(t, e);
+      }
+      group_barrier();   // B3: partial sums of the projection rows
+      for (int i = tid; i < n_em * PPW; i += 512) {
+        const int e = i / PPW, row = i - e * PPW;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += partl[(w * SL + e) * 64 * NSET + row];
+        const int s = e == 0 ? es[0] : e == 1 ? es[1] : e == 2 ? es[2] : es[3];
+        put(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp);
+      }
+      // ---- while the projections travel: the recurrent sums of the next step (added behind the next barrier)
+      for (int e = 0; e < n_em; ++e) {
+#pragma unroll
+        for (int t = Cfg::PSET; t < NSET; ++t) row_sums(t, e);
+      }
+      pend = n_em;
+#pragma unroll
+      for (int e = 0; e < SL; ++e) pend_slot[e] = es[e];
+      if constexpr (SOLO) group_barrier();
+      fetch(px, pfull, true);
+    }
+    load_frames();
+    if (rf) {   // slots that took a new utterance: the state after the start token, their first frames
+      unsigned long long todo = rf;
+      while (todo) {
+        const int a = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+        todo &= todo - 1;
+        for (int i = tid; i < H; i += 512) pfull[a * H + i] = m.start_p[i];
+        for (int i = tid; i < NR; i += 512) recs[a * NR + i] = m.start_rec[unit0 * 4 + i];
+        for (int i = tid; i < Cfg::UPW; i += 512) cst[a * Cfg::UPW + i] = m.start_c[unit0 + i];
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      group_barrier();
+    }
+  }
+  if (g == 0 && wave == 7) group_add_counters(c, counts, lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// e = W_enc enc + b_enc of fp32 models: 64 x 64 tiles, fp32 matrix-core products (32 x 32 x 2), one 32 x 32 block per wave,
+// both operands through LDS in stages of 32 inputs, the next stage's loads in flight during a stage's
+// products.  D a multiple of 4 (other models: enc_proj_f32_kernel).  A row tile is 64 frames of one utterance.
+__global__ __launch_bounds__(256) void enc_proj_f32_tile_kernel(ModelDev m, CallDev c, int tiles_per_utt) {
+  constexpr int BK = 32, ST = BK + 4;
+  __shared__ __attribute__((aligned(16))) float as[64 * ST], bs[64 * ST];
+  const int b = blockIdx.x / tiles_per_utt, t0 = (blockIdx.x % tiles_per_utt) * 64, n0 = blockIdx.y * 64, D = m.D;
+  const int len = c.len[b];
+  if (t0 >= len) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+  // thread: rows tid / 8 and tid / 8 + 32 of both tiles, inputs 4 (tid & 7) ..
+  const int lr = tid >> 3, lk = (tid & 7) * 4;
+  const float *ap[2], *bp[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    ap[h] = c.enc + ((size_t)b * c.T + min(t0 + lr + 32 * h, len - 1)) * D + lk;
+    bp[h] = reinterpret_cast<const float *>(m.w_enc) + (size_t)(n0 + lr + 32 * h) * D + lk;   // rows up to a multiple of 256 exist
+  }
+  float4 av[2], bv[2];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      av[h] = bv[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k0 + lk < D) {
+        av[h] = *reinterpret_cast<const float4 *>(ap[h] + k0);
+        bv[h] = *reinterpret_cast<const float4 *>(bp[h] + k0);
+      }
+    }
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  fetch(0);
+  for (int k0 = 0; k0 < D; k0 += BK) {
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      *reinterpret_cast<float4 *>(&as[(lr + 32 * h) * ST + lk]) = av[h];
+      *reinterpret_cast<float4 *>(&bs[(lr + 32 * h) * ST + lk]) = bv[h];
+    }
+    __syncthreads();
+    if (k0 + BK < D) fetch(k0 + BK);
+    // lane (row or column lane & 31, half lane >> 5) takes inputs 16 half + 0 .. 15 of the stage, two per product step
+    const float *ar = &as[(wm * 32 + (lane & 31)) * ST + (lane >> 5) * 16], *br = &bs[(wn * 32 + (lane & 31)) * ST + (lane >> 5) * 16];
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) {
+      const float4 a4 = *reinterpret_cast<const float4 *>(ar + i), b4 = *reinterpret_cast<const float4 *>(br + i);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, acc, 0, 0, 0);
+    }
+  }
+  const int col = n0 + wn * 32 + (lane & 31);
+  if (col >= m.Hj) return;
+  const float bias = m.b_enc[col];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int t = t0 + wm * 32 + acc_row(0, r, lane);
+    if (t < len) c.e[((size_t)b * c.T + t) * m.Hj + col] = acc[r] + bias;
+  }
+}
+
+}  // namespace wind

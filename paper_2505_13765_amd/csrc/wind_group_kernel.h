@@ -46,7 +46,8 @@ struct GroupDev {
   unsigned long long *p_x;              // [kGroups][kGroupSlots][H] new projections: fp32, iteration + 1 above
   unsigned long long *keys;             // [kGroups][2][kGroupRows][nparts + 1] two keys per part; last: (blank logit, norm)
   int *order, *n_order;                 // utterances with frames by falling length, and their number
-  int NG, NS, RG, SPT;
+  int NG, NS, RG, SPT;                  // groups, slots per group, row tiles per group, slots per row tile
+  int NX;                               // groups whose workgroups exchange words in memory
   int max_iters;                        // windows an utterance may take
   unsigned spin_limit;
 };
@@ -114,8 +115,8 @@ __device__ __forceinline__ void group_load_lds(const void *src, unsigned lds) {
 __global__ __launch_bounds__(256) void group_init_kernel(ModelDev m, CallDev c, GroupDev gd) {
   __shared__ int lens[kGroupMaxB];
   const int tid = threadIdx.x;
-  const size_t nbar = (size_t)gd.NG * kGroupBarInts, nx = (size_t)gd.NG * kGroupSlots * m.Hp;
-  const size_t nk = (size_t)gd.NG * 2 * kGroupRows * (c.nparts_tiny + 1);
+  const size_t nbar = (size_t)gd.NX * kGroupBarInts, nx = (size_t)gd.NX * kGroupSlots * m.Hp;
+  const size_t nk = (size_t)gd.NX * 2 * kGroupRows * (c.nparts_tiny + 1);
   for (size_t i = (size_t)blockIdx.x * 256 + tid; i < nbar + 2 * nx + nk; i += (size_t)gridDim.x * 256) {
     if (i < nbar) gd.bar[i] = 0u;
     else if (i < nbar + nx) gd.h_x[i - nbar] = 0ull;
@@ -150,6 +151,7 @@ __global__ __launch_bounds__(256) void group_init_kernel(ModelDev m, CallDev c, 
 
 // Load time: the state after the start token (its LSTM step from zero, projection, recurrent sums of the next
 // step), the same for every utterance.  Workgroup = 4 rows of [w_hh ; w_pred], one per wave.
+template <class WT>
 __global__ __launch_bounds__(256) void group_start_kernel(ModelDev m, float *start_c, float *start_p, float *start_rec) {
   extern __shared__ float hs[];
   const int Hp = m.Hp, tid = threadIdx.x;
@@ -163,8 +165,8 @@ __global__ __launch_bounds__(256) void group_start_kernel(ModelDev m, float *sta
   __syncthreads();
   const int lane = tid & 63, row = (int)blockIdx.x * 4 + (tid >> 6);
   if (row >= 4 * Hp + m.Hj) return;
-  const bf16_t *w = row < 4 * Hp ? reinterpret_cast<const bf16_t *>(m.w_cat[0]) + (size_t)row * Hp
-                                 : reinterpret_cast<const bf16_t *>(m.w_pred) + (size_t)(row - 4 * Hp) * Hp;
+  const WT *w = row < 4 * Hp ? reinterpret_cast<const WT *>(m.w_cat[0]) + (size_t)row * Hp
+                             : reinterpret_cast<const WT *>(m.w_pred) + (size_t)(row - 4 * Hp) * Hp;
   float a = 0.f;
   for (int k = 2 * lane; k < Hp; k += 128) {
     const float2 x = ldw2(w, k);
@@ -179,12 +181,12 @@ __global__ __launch_bounds__(256) void group_start_kernel(ModelDev m, float *sta
 }
 
 // What the host reads after the loop, in one launch, straight into pinned memory.
-__global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active, const unsigned *bar, int NG, const unsigned long long *stats,
+__global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active, const unsigned *bar, int NX, const unsigned long long *stats,
                                                             int n_stats, int *h_flag, unsigned long long *h_stats) {
   const int i = threadIdx.x;
   if (i == 0) {
     unsigned gave_up = 0u, near = 2u;
-    for (int g = 0; g < NG; ++g) {
+    for (int g = 0; g < NX; ++g) {
       gave_up |= bar[g * kGroupBarInts];
       near = min(near, bar[g * kGroupBarInts + 1]);
     }
@@ -203,6 +205,114 @@ struct GroupLane {
   int ld0, ld;               // frames loaded (or asked for) before the last decision, and now
   int nb, nlen, round;       // the slot's next utterance (-1: none)
 };
+
+// The entry of order `round` of this lane's slot: utterances by falling length, dealt back and forth over the slots.
+__device__ __forceinline__ void group_next(const CallDev &c, const GroupDev &gd, int grp, int lane, int n_order, int round, int &b, int &len) {
+  const int VS = gd.NG * gd.NS, v = lane * gd.NG + grp, rank = round * VS + ((round & 1) ? VS - 1 - v : v);
+  b = -1;
+  len = 0;
+  if (lane < gd.NS && rank < n_order) {
+    b = gd.order[rank];
+    len = c.len[b];
+  }
+}
+__device__ __forceinline__ GroupLane group_first_slots(const CallDev &c, const GroupDev &gd, int grp, int lane, int n_order) {
+  GroupLane sl;
+  group_next(c, gd, grp, lane, n_order, 0, sl.b, sl.len);
+  group_next(c, gd, grp, lane, n_order, 1, sl.nb, sl.nlen);
+  sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+  sl.round = 1;
+  if (sl.b < 0) sl.b = 0;
+  sl.ld = min(sl.len, 2 * c.W);
+  return sl;
+}
+
+// The frames that the slots of row tile rt have come to need (from ld0 to ld), into their rings of 2 W rows, one frame per wave
+// in turn (part of nparts).
+template <int H, int EST>
+__device__ __forceinline__ void group_load_frames(const CallDev &c, const GroupDev &gd, const GroupLane &sl, const float *ecache, int rt, int lane,
+                                                  int part, int nparts) {
+  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) const float *)ecache;
+  const int W2 = 2 * c.W;
+  for (int q = 0; q < gd.SPT; ++q) {
+    const int a = rt * gd.SPT + q;
+    if (a >= gd.NS) break;
+    const int f0 = __builtin_amdgcn_readlane(sl.ld0, a), f1 = __builtin_amdgcn_readlane(sl.ld, a);
+    const int t = __builtin_amdgcn_readlane(sl.t, a), rp = __builtin_amdgcn_readlane(sl.rpos, a), b = __builtin_amdgcn_readlane(sl.b, a);
+    for (int f = f0 + ((part - f0) & (nparts - 1)); f < f1; f += nparts) {
+      int rr = rp + (f - t);
+      if (rr >= W2) rr -= W2;
+      const float *src = c.e + (size_t)((unsigned)b * (unsigned)c.T + (unsigned)f) * H + lane * 4;
+      const unsigned dst = lds0 + (unsigned)(q * W2 + rr) * (EST * 4);
+#pragma unroll
+      for (int i = 0; i < (H + 255) / 256; ++i)
+        if (i * 256 + lane * 4 < H) group_load_lds(src + i * 256, dst + i * 1024);
+    }
+  }
+}
+
+// What a decided iteration does to the slots, in every wave alike: m_nb = rows of the group whose label is not blank, lab = row
+// `lane`'s label, need = rows that were decided again in fp32.  `writer` (one wave of the group) writes the outputs and
+// counts.  Returns whether this lane's slot takes an LSTM step (for tok) and whether it took a new utterance.
+__device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &gd, GroupLane &sl, int grp, int lane, int n_order, int nwin, int V,
+                                              unsigned long long m_nb, unsigned long long need, int lab, bool writer, int *counts, int &tok,
+                                              bool &emits, bool &fresh_slot) {
+  const int W = c.W, W2 = 2 * W, oshift = lane < gd.NS ? lane * W : 0;
+  const unsigned segm = (1u << W) - 1u;
+  const unsigned seg = lane < gd.NS ? (unsigned)(m_nb >> oshift) & segm : 0u;
+  const int first = seg ? __ffs((int)seg) - 1 : -1;
+  tok = __shfl(lab, oshift + max(first, 0), kWave);
+  tok = min(max(tok, 0), V);
+  emits = false;
+  fresh_slot = false;
+  if (nwin > 0) {
+    const int rech = __popc((unsigned)(need >> oshift) & segm);
+    const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, rech, writer);
+    const int adv = wo.slot.y - sl.t;
+    sl.t = wo.slot.y; sl.sym = wo.slot.w; sl.cnt = wo.cnt;
+    sl.rpos += adv;
+    if (sl.rpos >= W2) sl.rpos -= W2;
+    ++sl.wc;
+    sl.ld0 = sl.ld;
+    sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
+    const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
+    if (writer) {   // the call's counters: additions that nobody waits for (fewer than 2^31 each: B T (S + 1) is an int)
+      const unsigned ev = wo.ev;
+      atomicAdd(&counts[ST_WINDOWS], 1);
+      atomicAdd(&counts[ST_ROWS], (int)(ev & 127u));
+      atomicAdd(&counts[ST_USEFUL], (int)((ev >> 7) & 127u));
+      if ((ev >> 21) & 127u) atomicAdd(&counts[ST_RECHECK], (int)((ev >> 21) & 127u));
+      if (ev >> 28) {
+        atomicAdd(&counts[ST_LABELS], (int)((ev >> 28) & 1u));
+        atomicAdd(&counts[ST_FORCED], (int)((ev >> 29) & 1u));
+        atomicAdd(&counts[ST_OVERFLOW], (int)((ev >> 30) & 1u));
+      }
+      atomicAdd(&counts[kStatJump0 + ((ev >> 14) & 127u)], 1);
+      if (done) atomicMax(&counts[ST_ITER], sl.wc);
+      if (cut) atomicAdd(&c.n_active[0], 1);
+    }
+    emits = (wo.flag & 2) && !done;
+    if (done) {   // the slot's next utterance, or nothing
+      fresh_slot = sl.nb >= 0;
+      sl.b = fresh_slot ? sl.nb : 0;
+      sl.len = fresh_slot ? sl.nlen : 0;
+      sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+      sl.ld = min(sl.len, W2);
+      if (fresh_slot) {
+        ++sl.round;
+        group_next(c, gd, grp, lane, n_order, sl.round, sl.nb, sl.nlen);
+      }
+    }
+  } else {
+    sl.ld0 = sl.ld;
+  }
+}
+__device__ __forceinline__ void group_add_counters(const CallDev &c, const int *counts, int lane) {
+  for (int j = lane; j < kNumStats; j += 64) {
+    if (j == ST_ITER) atomicMax(&c.stats[j], (unsigned long long)counts[j]);
+    else if (counts[j]) atomicAdd(&c.stats[j], (unsigned long long)counts[j]);
+  }
+}
 
 template <int KS, int CT, int GW, int ROLE>
 __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, const GroupDev &gd, unsigned char *smem, int grp, int g) {
@@ -227,23 +337,8 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
   const int unit0 = g * Cfg::UPW, prow0 = g * Cfg::PPW;
 
   // ---- the slots' first utterances
-  GroupLane sl;
-  const int VS = gd.NG * NS, n_order = *gd.n_order;
-  auto next_entry = [&](int round, int &b, int &len) {
-    const int v = lane * gd.NG + grp, rank = round * VS + ((round & 1) ? VS - 1 - v : v);
-    b = -1;
-    len = 0;
-    if (lane < NS && rank < n_order) {
-      b = gd.order[rank];
-      len = c.len[b];
-    }
-  };
-  next_entry(0, sl.b, sl.len);
-  next_entry(1, sl.nb, sl.nlen);
-  sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
-  sl.round = 1;
-  if (sl.b < 0) sl.b = 0;
-  sl.ld = min(sl.len, W2);
+  const int n_order = *gd.n_order;
+  GroupLane sl = group_first_slots(c, gd, grp, lane, n_order);
 
   // ---- weights into registers
   bf16x8 wo[ROLE == 0 ? 2 * CT : 1][KS];                                   // W_out columns
@@ -271,25 +366,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     }
   }
 
-  // ---- frames of slot `a` (scalars) from its ring's `from` to `to`, one row per wave in turn
-  auto load_frames = [&]() {
-    const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) float *)ecache;
-    for (int q = 0; q < SPT; ++q) {
-      const int a = rt * SPT + q;
-      if (a >= NS) break;
-      const int f0 = __builtin_amdgcn_readlane(sl.ld0, a), f1 = __builtin_amdgcn_readlane(sl.ld, a);
-      const int t = __builtin_amdgcn_readlane(sl.t, a), rp = __builtin_amdgcn_readlane(sl.rpos, a), b = __builtin_amdgcn_readlane(sl.b, a);
-      for (int f = f0 + ((w4 - f0) & 3); f < f1; f += 4) {
-        int rr = rp + (f - t);
-        if (rr >= W2) rr -= W2;
-        const float *src = c.e + (size_t)((unsigned)b * (unsigned)c.T + (unsigned)f) * H + lane * 4;
-        const unsigned dst = lds0 + (unsigned)(q * W2 + rr) * (Cfg::EST * 4);
-#pragma unroll
-        for (int i = 0; i < (H + 255) / 256; ++i)
-          if (i * 256 + lane * 4 < H) group_load_lds(src + i * 256, dst + i * 1024);
-      }
-    }
-  };
+  auto load_frames = [&]() { group_load_frames<H, Cfg::EST>(c, gd, sl, ecache, rt, lane, w4, 4); };
 
   // ---- state after the start token
   if constexpr (ROLE == 0) {
@@ -331,7 +408,6 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
   const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
   auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
   const int nq = 4 * wave >= R ? 0 : 4 * (wave + 8) >= R ? 1 : 2;   // row quads this wave decides
-  const unsigned segm = (1u << W) - 1u;
   float bias[Cfg::NI][2];
 #pragma unroll
   for (int k = 0; k < Cfg::NI; ++k)
@@ -543,55 +619,10 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       if ((need >> lane) & 1ull) lab = stat2[lane];
       m_nb = __ballot(lab >= 0 && lab != V);
     }
-    const int oshift = lane < NS ? lane * W : 0;
-    // ---- outcome of every slot's window, in every wave alike; one wave of workgroup 0 writes the outputs
-    const unsigned seg = lane < NS ? (unsigned)(m_nb >> oshift) & segm : 0u;
-    const int first = seg ? __ffs((int)seg) - 1 : -1;
-    int tok = __shfl(lab, oshift + max(first, 0), kWave);
-    tok = min(max(tok, 0), V);
-    bool emits = false, fresh_slot = false;
-    if (nwin > 0) {
-      const bool writer = ROLE == 1 && wave == 7 && g == 0;
-      const int rech = __popc((unsigned)(need >> oshift) & segm);
-      const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, rech, writer);
-      const int adv = wo.slot.y - sl.t;
-      sl.t = wo.slot.y; sl.sym = wo.slot.w; sl.cnt = wo.cnt;
-      sl.rpos += adv;
-      if (sl.rpos >= W2) sl.rpos -= W2;
-      ++sl.wc;
-      sl.ld0 = sl.ld;
-      sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
-      const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
-      if (writer) {   // the call's counters: additions that nobody waits for (fewer than 2^31 each: B T (S + 1) is an int)
-        const unsigned ev = wo.ev;
-        atomicAdd(&counts[ST_WINDOWS], 1);
-        atomicAdd(&counts[ST_ROWS], (int)(ev & 127u));
-        atomicAdd(&counts[ST_USEFUL], (int)((ev >> 7) & 127u));
-        if ((ev >> 21) & 127u) atomicAdd(&counts[ST_RECHECK], (int)((ev >> 21) & 127u));
-        if (ev >> 28) {
-          atomicAdd(&counts[ST_LABELS], (int)((ev >> 28) & 1u));
-          atomicAdd(&counts[ST_FORCED], (int)((ev >> 29) & 1u));
-          atomicAdd(&counts[ST_OVERFLOW], (int)((ev >> 30) & 1u));
-        }
-        atomicAdd(&counts[kStatJump0 + ((ev >> 14) & 127u)], 1);
-        if (done) atomicMax(&counts[ST_ITER], sl.wc);
-        if (cut) atomicAdd(&c.n_active[0], 1);
-      }
-      emits = (wo.flag & 2) && !done;
-      if (done) {   // the slot's next utterance, or nothing
-        fresh_slot = sl.nb >= 0;
-        sl.b = fresh_slot ? sl.nb : 0;
-        sl.len = fresh_slot ? sl.nlen : 0;
-        sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
-        sl.ld = min(sl.len, W2);
-        if (fresh_slot) {
-          ++sl.round;
-          next_entry(sl.round, sl.nb, sl.nlen);
-        }
-      }
-    } else {
-      sl.ld0 = sl.ld;
-    }
+    // ---- outcome of every slot's window; one wave of workgroup 0 writes the outputs
+    int tok;
+    bool emits, fresh_slot;
+    group_outcome(c, gd, sl, grp, lane, n_order, nwin, V, m_nb, need, lab, ROLE == 1 && wave == 7 && g == 0, counts, tok, emits, fresh_slot);
     const unsigned long long em = __ballot(emits), rf = __ballot(fresh_slot);
     if (em) {
       const int n_em = __popcll(em);
@@ -736,11 +767,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     }
   }
   if constexpr (ROLE == 1) {
-    if (g == 0 && wave == 7)   // the group's counters
-      for (int j = lane; j < kNumStats; j += 64) {
-        if (j == ST_ITER) atomicMax(&c.stats[j], (unsigned long long)counts[j]);
-        else if (counts[j]) atomicAdd(&c.stats[j], (unsigned long long)counts[j]);
-      }
+    if (g == 0 && wave == 7) group_add_counters(c, counts, lane);
   }
 }
 

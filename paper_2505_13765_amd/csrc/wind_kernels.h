@@ -34,3 +34,4 @@
 #include "wind_pred_kernels.h"
 #include "wind_loop_kernel.h"
 #include "wind_group_kernel.h"
+#include "wind_group_f32_kernel.h"
