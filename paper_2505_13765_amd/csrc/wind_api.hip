@@ -6,6 +6,7 @@
 #include <hip/hip_ext.h>
 #include <algorithm>
 
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -44,6 +45,7 @@ using EncSmallCfg = TileCfg<64, 64, 32, 32>;   // calls whose 128 x 128 tiles wo
 using PredCfg = DmaCfg<64, 64, 32, 32, 64, 4>;   // 32 utterances (hi and lo rows) x 64 columns, 4-stage ring
 constexpr int kPredMfmaMinBatch = 1;       // below this the FMA prediction network is used
 constexpr size_t kEncRing5MinRows = 16384;   // B * T from which the encoder projection uses 256 x 256 tiles
+constexpr long long kEncFewTiles = 1024;     // 32 x 32 tiles up to which the encoder projection runs on them (four workgroups per CU)
 constexpr int kIterRowsCap = 16384;   // iterations whose row counts profile mode records
 constexpr int kRowPad = 256;  // window-row buffers are padded to a multiple of every tile height, plus one block
 
@@ -129,6 +131,9 @@ struct wind_model {
   int opt_host_sync = 0;   // 1: kernels one by one and the host reads the active count after every iteration
   hipEvent_t ev_call[3] = {nullptr, nullptr, nullptr};   // last decode call: start, loop start, loop end
   bool have_call_times = false;
+  bool stamp_times = false;    // the last call's times are stamp_ms (device time stamps) instead of the events'
+  double stamp_ms[2] = {0.0, 0.0}, clock_khz = 1e5;
+  int call_number = 0;         // of the last call that ran in resident groups
   // an asynchronous decode that wind_get_stats has not completed yet
   bool async_pending = false, async_loop = false;
   const GroupInstance *async_group = nullptr;
@@ -249,7 +254,7 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_bl = take(w.Mpad * 4); w.o_zn = take(w.Mpad * 4);
   w.o_parts = take(w.Mpad * (size_t)std::max(w.nparts_tiny * 8, w.nparts * 16));   // two keys of 32 columns, or three (+ pad) of 64
   w.o_rl = take(w.Mpad * 4);
-  w.o_stats = take(kNumStats * 8);
+  w.o_stats = take(kStatWords * 8);
   w.o_dbg = take(128);
   w.o_iter = take((size_t)kIterRowsCap * 4);
   w.o_dbglen = take((size_t)B * 4);             // debug entry points: lengths and outputs of their own
@@ -454,15 +459,19 @@ bool enc_wide_ok(const wind_model *m, int B, int T) {
   return ((unsigned long long)B * T + 256) * d.D * 2 < (1ull << 32);
 }
 
-// every frame of the call through the encoder projection (c.len must be set)
-void enqueue_enc_proj(wind_model *m, hipStream_t s) {
+constexpr int kGroupInitBlocks = 64;   // workgroups that prepare the resident groups' words and lists
+// every frame of the call through the encoder projection; gd: also what the resident groups need before their launch
+void enqueue_enc_proj(wind_model *m, hipStream_t s, const GroupDev *group = nullptr) {
   const ModelDev &d = m->dev;
   const CallDev &c = m->call;
+  const int init = group ? kGroupInitBlocks : 0;
+  const GroupDev gd = group ? *group : GroupDev{};
+  if (c.T == 0 && group) group_init_kernel<<<init, 256, 0, s>>>(d, c, gd);
   if (c.T > 0) {
     if (m->dtype == WIND_BF16 && c.enc_b) {
       const long long rows = (long long)c.B * c.T;
       const bool wide = enc_wide_ok(m, c.B, c.T);
-      launch(m, s, WIND_K_ENC_PROJ, false, enc_round_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, d, c, wide ? 1 : 0);
+      launch(m, s, WIND_K_ENC_PROJ, false, enc_round_kernel, dim3((unsigned)((rows + 3) / 4 + init)), dim3(256), 0, d, c, wide ? 1 : 0, gd, init);
       if (wide) {
         const int tiles_per_utt = (c.T + 255) / 256, n_row_tiles = c.B * tiles_per_utt, n_col_tiles = (d.Hj + 255) / 256;
         launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_wide_kernel, dim3((unsigned)((n_row_tiles + 7) / 8 * 8 * n_col_tiles)), dim3(256),
@@ -474,22 +483,27 @@ void enqueue_enc_proj(wind_model *m, hipStream_t s) {
                EncBigCfg::SMEM_BYTES, d, c, tiles_per_utt);
       }
     } else if (m->dtype == WIND_BF16) {
-      const int tiles_per_utt = (c.T + EncCfg::BM - 1) / EncCfg::BM;
+      const int tiles_per_utt = (c.T + EncCfg::BM - 1) / EncCfg::BM, few_per_utt = (c.T + 31) / 32;
       dim3 grid((unsigned)(c.B * tiles_per_utt), (unsigned)((d.Hj + EncCfg::BN - 1) / EncCfg::BN));
-      if (grid.x * grid.y < 128) {   // a single short utterance: a quarter of the tile on four times the workgroups
+      if ((long long)c.B * few_per_utt * (d.Hj / 32) <= kEncFewTiles) {
+        launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_few_kernel, dim3((unsigned)(c.B * few_per_utt + init), (unsigned)(d.Hj / 32)), dim3(512), 0, d, c,
+               few_per_utt, gd, init);
+      } else if (grid.x * grid.y < 128) {   // a quarter of the tile on four times the workgroups
         const int small_per_utt = (c.T + EncSmallCfg::BM - 1) / EncSmallCfg::BM;
-        dim3 sgrid((unsigned)(c.B * small_per_utt), (unsigned)((d.Hj + EncSmallCfg::BN - 1) / EncSmallCfg::BN));
+        dim3 sgrid((unsigned)(c.B * small_per_utt + init), (unsigned)((d.Hj + EncSmallCfg::BN - 1) / EncSmallCfg::BN));
         launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_mfma_kernel<EncSmallCfg>, sgrid, dim3(EncSmallCfg::NT), EncSmallCfg::SMEM_BYTES,
-               d, c, small_per_utt);
+               d, c, small_per_utt, gd, init);
       } else {
+        grid.x += (unsigned)init;
         launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_mfma_kernel<EncCfg>, grid, dim3(EncCfg::NT), EncCfg::SMEM_BYTES, d, c,
-               tiles_per_utt);
+               tiles_per_utt, gd, init);
       }
     } else if (d.D % 4 == 0 && (uintptr_t)c.enc % 16 == 0) {   // the tiles load four inputs at a time
       const int tiles_per_utt = (c.T + 63) / 64;
-      launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_f32_tile_kernel, dim3((unsigned)(c.B * tiles_per_utt), (unsigned)((d.Hj + 63) / 64)), dim3(256), 0,
-             d, c, tiles_per_utt);
+      launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_f32_tile_kernel, dim3((unsigned)(c.B * tiles_per_utt + init), (unsigned)((d.Hj + 63) / 64)), dim3(256), 0,
+             d, c, tiles_per_utt, gd, init);
     } else {
+      if (group) group_init_kernel<<<init, 256, 0, s>>>(d, c, gd);
       launch(m, s, WIND_K_ENC_PROJ, false, enc_proj_f32_kernel, dim3((unsigned)c.T, (unsigned)c.B), dim3(256),
              (size_t)d.D * 4, d, c);
     }
@@ -764,10 +778,24 @@ int resident_leave_pending(ResidentGate &g, hipStream_t s) {
   return WIND_OK;
 }
 
-int finish_group(wind_model *m, const GroupDev &gd, int gw) {
+// Waits for the results of the resident groups' call `call_number` on stream s to arrive in pinned memory.
+int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s) {
+  for (unsigned spins = 1; __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number; ++spins) {
+    if ((spins & 0x3FFFu) == 0) {   // a kernel that failed never writes it
+      const hipError_t e = hipStreamQuery(s);
+      if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("resident groups: ") + hipGetErrorString(e));
+      if (e == hipSuccess && __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number)
+        return fail(WIND_ERR_HIP, "resident groups: the stream is done, the results have not arrived");
+    }
+    __builtin_ia32_pause();
+  }
   m->loop_info[0] = gd.NG * gw;
   m->loop_info[1] = gd.NG == 1 && m->h_flag[2] == 2;
   if (m->h_flag[1] != 0) return fail(WIND_ERR_HIP, "resident loop: a grid barrier timed out (workgroups not all resident?)");
+  const unsigned long long *h = m->h_stats;
+  m->stamp_ms[0] = (double)(h[kStatEnd] - h[kStatStart]) / m->clock_khz;
+  m->stamp_ms[1] = (double)(h[kStatEnd] - h[kStatLoop]) / m->clock_khz;
+  m->have_call_times = m->stamp_times = true;
   return WIND_OK;
 }
 
@@ -816,7 +844,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   m->loop_info[0] = m->loop_info[1] = 0;
   m->fma_pred_step = use_loop;   // the resident kernel starts from the fp32 state of the start-token step
   if (use_loop) { c.rec = nullptr; c.lists_atomic = 0; c.slot_rows = 0; }
-  m->have_call_times = false;
+  m->have_call_times = m->stamp_times = false;
   GroupDev gd = m->group;
   const GroupInstance *gi = group_shape(m, B, T, W, &gd);
   if (gi || use_loop) {
@@ -828,15 +856,12 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
-    HIP_TRY(hipEventRecord(m->ev_call[0], s));
-    group_init_kernel<<<64, 256, 0, s>>>(m->dev, c, gd);
-    enqueue_enc_proj(m, s);
-    HIP_TRY(hipEventRecord(m->ev_call[1], s));
+    enqueue_enc_proj(m, s, &gd);
     gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
-    HIP_TRY(hipEventRecord(m->ev_call[2], s));
-    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, kNumStats, m->h_flag, m->h_stats);
+    m->call_number = m->call_number == INT_MAX ? 1 : m->call_number + 1;
+    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, m->h_flag, m->h_stats, m->call_number);
     rc = check_launch("resident groups' results");
     if (rc) return rc;
     if (async) {
@@ -844,11 +869,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       m->group.NG = gd.NG;
       return resident_leave_pending(g_resident[m->device], s);
     }
-    HIP_TRY(hipStreamSynchronize(s));
-    rc = finish_group(m, gd, gi->gw);
+    rc = finish_group(m, gd, gi->gw, s);
     if (rc) return rc;
     if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");
-    m->have_call_times = true;
     rc = read_stats(m);
     if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
     return rc;
@@ -1022,6 +1045,8 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
       m->cu_count = cus;
       m->device = dev;
+      int khz = 0;
+      if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) m->clock_khz = khz;
     }
   }
   ModelDev &d = m->dev;
@@ -1154,9 +1179,13 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     rc = static_scratch_address(&unused);   // once per device, here rather than in a call that must not stall
   }
   if (rc == WIND_OK) {
-    hipError_t e = hipHostMalloc((void **)&m->h_flag, 64 + kNumStats * sizeof(unsigned long long), hipHostMallocDefault);
-    if (e != hipSuccess) rc = fail(WIND_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-    else m->h_stats = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(m->h_flag) + 64);
+    hipError_t e = hipHostMalloc((void **)&m->h_flag, 64 + kStatWords * sizeof(unsigned long long), hipHostMallocCoherent);
+    if (e != hipSuccess) {
+      rc = fail(WIND_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
+    } else {
+      std::memset(m->h_flag, 0, 64);
+      m->h_stats = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(m->h_flag) + 64);
+    }
   }
   if (rc == WIND_OK) {
     hipError_t e = hipFuncSetAttribute((const void *)joint_ws_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWsSmemBytes);
@@ -1311,10 +1340,8 @@ static int finish_async(wind_model *m) {
   if (m->async_group) {
     const GroupInstance *gi = m->async_group;
     m->async_group = nullptr;
-    HIP_TRY(hipStreamSynchronize(s));
-    int rc = finish_group(m, m->group, gi->gw);
+    int rc = finish_group(m, m->group, gi->gw, s);
     if (rc) return rc;
-    m->have_call_times = true;
     rc = read_stats(m);
     if (rc == WIND_OK && m->h_flag[0] != 0)
       return fail(WIND_ERR_UNFINISHED, "the decode did not finish within max_iterations: outputs hold the labels found so far");
@@ -1375,6 +1402,11 @@ int wind_get_kernel_times(wind_model *m, double *ms, int64_t *launches) {
 int wind_get_call_times(wind_model *m, double *total_ms, double *loop_ms) {
   if (!m || !total_ms || !loop_ms) return fail(WIND_ERR_ARG, "null argument");
   if (!m->have_call_times) return fail(WIND_ERR_ARG, "no completed decode call yet");
+  if (m->stamp_times) {
+    *total_ms = m->stamp_ms[0];
+    *loop_ms = m->stamp_ms[1];
+    return WIND_OK;
+  }
   float a = 0.f, b = 0.f;
   HIP_TRY(hipEventElapsedTime(&a, m->ev_call[0], m->ev_call[2]));
   HIP_TRY(hipEventElapsedTime(&b, m->ev_call[1], m->ev_call[2]));

@@ -9,6 +9,12 @@ __global__ __launch_bounds__(256) void fill_int_kernel(int *p, int n, int v) {
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) p[i] = v;
 }
 
+// the length of utterance b as the call uses it
+__device__ __forceinline__ int utt_len(const CallDev &c, int b) {
+  const int len = c.lengths[b];
+  return len < 0 ? 0 : (len > c.T ? c.T : len);
+}
+
 __global__ __launch_bounds__(256) void init_state_kernel(ModelDev m, CallDev c) {
   const int tid = threadIdx.x;
   // every workgroup zeroes its share of the prediction-network state; the first also builds the lists
@@ -20,9 +26,7 @@ __global__ __launch_bounds__(256) void init_state_kernel(ModelDev m, CallDev c) 
   if (blockIdx.x != 0) return;
   for (int i = tid; i < kNumStats; i += 256) c.stats[i] = 0ull;
   for (int b = tid; b < c.B; b += 256) {
-    int len = c.lengths[b];
-    len = len < 0 ? 0 : (len > c.T ? c.T : len);
-    c.len[b] = len;
+    c.len[b] = utt_len(c, b);
     c.out_counts[b] = 0;
     c.emit_idx[b] = b;         // the first prediction-network step runs on every utterance
     c.emit_list_tok[b] = m.V;  // on the start token
@@ -52,13 +56,81 @@ __global__ __launch_bounds__(256) void init_state_kernel(ModelDev m, CallDev c) 
 }
 
 // ---------------------------------------------------------------------------------------------
+// Resident groups (wind_group_kernel.h): what a call hands to them.
+constexpr int kGroups = 8;              // XCDs
+constexpr int kGroupSlots = 4;          // utterances a group decodes at a time, at most
+constexpr int kGroupRows = 64;          // window rows of a group, at most
+constexpr int kGroupMaxW = 16;
+constexpr int kGroupMaxB = 256;         // utterances of a call (group_init_kernel ranks them in one workgroup)
+constexpr int kGroupBarInts = 33 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 (1 + g): XCD number + 1 of workgroup g
+
+struct GroupDev {
+  unsigned *bar;                        // [kGroups][kGroupBarInts], zero at launch
+  unsigned long long *h_x;              // [kGroups][kGroupSlots][H] new hidden vectors: bf16 hi | lo << 16, iteration + 1 above
+  unsigned long long *p_x;              // [kGroups][kGroupSlots][H] new projections: fp32, iteration + 1 above
+  unsigned long long *keys;             // [kGroups][2][kGroupRows][nparts + 1] two keys per part; last: (blank logit, norm)
+  int *order, *n_order;                 // utterances with frames by falling length, and their number
+  int NG, NS, RG, SPT;                  // groups, slots per group, row tiles per group, slots per row tile
+  int NX;                               // groups whose workgroups exchange words in memory
+  int max_iters;                        // windows an utterance may take
+  unsigned spin_limit;
+};
+
+// Everything the resident groups expect to find: clamped lengths, the utterances by falling length, zeroed counters and
+// exchange words (the keys all ones: their first iterations' tag is 0).  Done by `nblocks` workgroups of 256 threads at the front of the
+// call's first launch (a launch of its own costs 5 us at the front of every call).  lens: LDS for kGroupMaxB ints.
+__device__ __forceinline__ void group_init(const ModelDev &m, const CallDev &c, const GroupDev &gd, int block, int nblocks, int *lens) {
+  const int tid = threadIdx.x;
+  const size_t nbar = (size_t)gd.NX * kGroupBarInts, nx = (size_t)gd.NX * kGroupSlots * m.Hp;
+  const size_t nk = (size_t)gd.NX * 2 * kGroupRows * (c.nparts_tiny + 1);
+  for (size_t i = (size_t)block * 256 + tid; i < nbar + 2 * nx + nk; i += (size_t)nblocks * 256) {
+    if (i < nbar) gd.bar[i] = 0u;
+    else if (i < nbar + nx) gd.h_x[i - nbar] = 0ull;
+    else if (i < nbar + 2 * nx) gd.p_x[i - nbar - nx] = 0ull;
+    else gd.keys[i - nbar - 2 * nx] = ~0ull;
+  }
+  if (block != 0) return;
+  if (tid == 0) c.stats[kStatStart] = (unsigned long long)wall_clock64();
+  for (int i = tid; i < kNumStats; i += 256) c.stats[i] = 0ull;
+  for (int b = tid; b < c.B; b += 256) {
+    const int len = utt_len(c, b);
+    lens[b] = len;
+    c.len[b] = len;
+    c.out_counts[b] = 0;
+  }
+  if (tid == 0) { c.n_active[0] = 0; c.n_active[1] = 0; }
+  __syncthreads();
+  int n = 0;
+  for (int b = tid; b < c.B; b += 256) {
+    const int len = lens[b];
+    int rank = 0;
+    n = 0;
+    for (int o = 0; o < c.B; ++o) {
+      const int lo = lens[o];
+      rank += lo > len || (lo == len && o < b);
+      n += lo > 0;
+    }
+    if (len > 0) gd.order[rank] = b;
+  }
+  if (tid == 0) *gd.n_order = n;
+}
+__global__ __launch_bounds__(256) void group_init_kernel(ModelDev m, CallDev c, GroupDev gd) {   // calls without a single frame
+  __shared__ int lens[kGroupMaxB];
+  group_init(m, c, gd, (int)blockIdx.x, (int)gridDim.x, lens);
+}
+
+// ---------------------------------------------------------------------------------------------
 // e[b,t,:] = W_enc enc_out[b,t,:] + b_enc for t < len[b]: bf16 MFMA, fp32 accumulate, fp32 out.
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::NT) void enc_proj_mfma_kernel(ModelDev m, CallDev c, int tiles_per_utt) {
+__global__ __launch_bounds__(Cfg::NT) void enc_proj_mfma_kernel(ModelDev m, CallDev c, int tiles_per_utt, GroupDev gd, int init_blocks) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  if ((int)blockIdx.x < init_blocks) {
+    if (blockIdx.y == 0) group_init(m, c, gd, (int)blockIdx.x, init_blocks, reinterpret_cast<int *>(smem_raw));
+    return;
+  }
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
-  const int b = blockIdx.x / tiles_per_utt, t0 = (blockIdx.x % tiles_per_utt) * Cfg::BM;
-  const int len = c.len[b];
+  const int tile = (int)blockIdx.x - init_blocks, b = tile / tiles_per_utt, t0 = (tile % tiles_per_utt) * Cfg::BM;
+  const int len = utt_len(c, b);
   if (t0 >= len) return;
   const int n0 = blockIdx.y * Cfg::BN, D = m.D;
   const float *base = c.enc + (size_t)b * c.T * D;
@@ -91,15 +163,70 @@ __global__ __launch_bounds__(Cfg::NT) void enc_proj_mfma_kernel(ModelDev m, Call
   }
 }
 
+// The same for calls of few frames, whose tiles above would leave most CUs idle in front of a long chain of stages (14 us for one
+// utterance of 125 frames): 32 x 32 outputs per workgroup, K dealt to its eight waves in steps of 16, every
+// operand straight from memory into registers with up to eight steps in flight, the waves' partial tiles added through LDS.
+__global__ __launch_bounds__(512) void enc_proj_few_kernel(ModelDev m, CallDev c, int tiles_per_utt, GroupDev gd, int init_blocks) {
+  __shared__ __attribute__((aligned(16))) float part[8][16][64];
+  if ((int)blockIdx.x < init_blocks) {
+    if (blockIdx.y == 0 && threadIdx.x < 256) group_init(m, c, gd, (int)blockIdx.x, init_blocks, reinterpret_cast<int *>(&part[0][0][0]));
+    return;
+  }
+  const int tile = (int)blockIdx.x - init_blocks, b = tile / tiles_per_utt, t0 = (tile % tiles_per_utt) * 32;
+  const int len = utt_len(c, b);
+  if (t0 >= len) return;
+  const int n0 = blockIdx.y * 32, D = m.D, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float *ar = c.enc + ((size_t)b * c.T + min(t0 + (lane & 31), len - 1)) * D + (lane >> 5) * 8;
+  const bf16_t *br = reinterpret_cast<const bf16_t *>(m.w_enc) + (size_t)(n0 + (lane & 31)) * D + (lane >> 5) * 8;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int steps = D / 16;
+  for (int s0 = wave; s0 < steps; s0 += 64) {
+    f32x4 a[8][2];
+    bf16x8 w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int k = min(s0 + 8 * i, steps - 1) * 16;   // past the end: the last step again, not used
+      a[i][0] = *reinterpret_cast<const f32x4 *>(ar + k);
+      a[i][1] = *reinterpret_cast<const f32x4 *>(ar + k + 4);
+      w[i] = *reinterpret_cast<const bf16x8 *>(br + k);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (s0 + 8 * i < steps) {
+        const u32x4 o = u32x4{pack_bf16x2(a[i][0].x, a[i][0].y), pack_bf16x2(a[i][0].z, a[i][0].w), pack_bf16x2(a[i][1].x, a[i][1].y),
+                              pack_bf16x2(a[i][1].z, a[i][1].w)};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o), w[i], acc, 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[wave][r][lane] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = 2 * wave + h, col = n0 + (lane & 31), t = t0 + acc_row(0, r, lane);
+    float v = m.b_enc[col];   // Hj is a multiple of 64: every column exists
+#pragma unroll
+    for (int w2 = 0; w2 < 8; ++w2) v += part[w2][r][lane];
+    if (t < len) c.e[((size_t)b * c.T + t) * m.Hj + col] = v;
+  }
+}
+
 // Large calls: the encoder outputs are first rounded to bf16 rows (valid frames only), so that the
 // projection can use the direct-to-LDS tile core at full tile size.
 // (slab: in slabs of 32 inputs, [D / 32][B*T + 256][32], for enc_proj_wide_kernel)
-__global__ __launch_bounds__(256) void enc_round_kernel(ModelDev m, CallDev c, int slab) {
+__global__ __launch_bounds__(256) void enc_round_kernel(ModelDev m, CallDev c, int slab, GroupDev gd, int init_blocks) {
+  __shared__ int lens[kGroupMaxB];
+  if ((int)blockIdx.x < init_blocks) {
+    group_init(m, c, gd, (int)blockIdx.x, init_blocks, lens);
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long row = (long long)blockIdx.x * 4 + wave;
+  const long long row = (long long)((int)blockIdx.x - init_blocks) * 4 + wave;
   if (row >= (long long)c.B * c.T) return;
   const int b = (int)(row / c.T), t = (int)(row - (long long)b * c.T);
-  if (t >= c.len[b]) return;
+  if (t >= utt_len(c, b)) return;
   const float *src = c.enc + (size_t)row * m.D;
   const size_t slab_elems = ((size_t)c.B * c.T + 256) * 32;
   bf16_t *dst = slab ? c.enc_b + (size_t)row * 32 : c.enc_b + (size_t)row * m.D;
@@ -116,7 +243,7 @@ template <class Cfg>
 __global__ __launch_bounds__(Cfg::NT) void enc_proj_ring5_kernel(ModelDev m, CallDev c, int tiles_per_utt) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int b = blockIdx.x / tiles_per_utt, t0 = (blockIdx.x % tiles_per_utt) * Cfg::BM;
-  const int len = c.len[b];
+  const int len = utt_len(c, b);
   if (t0 >= len) return;
   const int n0 = blockIdx.y * Cfg::BN, D = m.D;
   f32x16 acc[Cfg::MI][Cfg::NI];
@@ -197,7 +324,7 @@ __global__ __launch_bounds__(256) void enc_proj_wide_kernel(ModelDev m, CallDev 
   const int rt = (q / n_col_tiles) * 8 + (id & 7), ct = q % n_col_tiles;
   if (rt >= n_row_tiles) return;
   const int b = rt / tiles_per_utt, t0 = (rt % tiles_per_utt) * 256;
-  const int len = c.len[b];
+  const int len = utt_len(c, b);
   if (t0 >= len) return;
   const int mi = (min(len - t0, 256) + 63) / 64;
   switch (mi) {
@@ -212,7 +339,7 @@ __global__ __launch_bounds__(256) void enc_proj_wide_kernel(ModelDev m, CallDev 
 __global__ __launch_bounds__(256) void enc_proj_f32_kernel(ModelDev m, CallDev c) {
   extern __shared__ float xs[];
   const int b = blockIdx.y, t = blockIdx.x;
-  if (t >= c.len[b]) return;
+  if (t >= utt_len(c, b)) return;
   const float *x = c.enc + ((size_t)b * c.T + t) * m.D;
   for (int k = threadIdx.x; k < m.D; k += 256) xs[k] = x[k];
   __syncthreads();

@@ -45,6 +45,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int grp = SOLO ? (int)blockIdx.x : (int)blockIdx.x % kGroups, g = SOLO ? 0 : (int)blockIdx.x / kGroups;
   if (grp >= gd.NG) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) c.stats[kStatLoop] = (unsigned long long)wall_clock64();
   float *ecache = reinterpret_cast<float *>(smem + Cfg::oE), *fred = reinterpret_cast<float *>(smem + Cfg::oFred);
   float *fbn = reinterpret_cast<float *>(smem + Cfg::oFbn), *pfull = reinterpret_cast<float *>(smem + Cfg::oP);
   float *hbuf = reinterpret_cast<float *>(smem + Cfg::oHb), *partl = reinterpret_cast<float *>(smem + Cfg::oPart);
@@ -374,11 +375,15 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
 // e = W_enc enc + b_enc of fp32 models: 64 x 64 tiles, fp32 matrix-core products (32 x 32 x 2), one 32 x 32 block per wave,
 // both operands through LDS in stages of 32 inputs, the next stage's loads in flight during a stage's
 // products.  D a multiple of 4 (other models: enc_proj_f32_kernel).  A row tile is 64 frames of one utterance.
-__global__ __launch_bounds__(256) void enc_proj_f32_tile_kernel(ModelDev m, CallDev c, int tiles_per_utt) {
+__global__ __launch_bounds__(256) void enc_proj_f32_tile_kernel(ModelDev m, CallDev c, int tiles_per_utt, GroupDev gd, int init_blocks) {
   constexpr int BK = 32, ST = BK + 4;
   __shared__ __attribute__((aligned(16))) float as[64 * ST], bs[64 * ST];
-  const int b = blockIdx.x / tiles_per_utt, t0 = (blockIdx.x % tiles_per_utt) * 64, n0 = blockIdx.y * 64, D = m.D;
-  const int len = c.len[b];
+  if ((int)blockIdx.x < init_blocks) {
+    if (blockIdx.y == 0) group_init(m, c, gd, (int)blockIdx.x, init_blocks, reinterpret_cast<int *>(as));
+    return;
+  }
+  const int tile = (int)blockIdx.x - init_blocks, b = tile / tiles_per_utt, t0 = (tile % tiles_per_utt) * 64, n0 = blockIdx.y * 64, D = m.D;
+  const int len = utt_len(c, b);
   if (t0 >= len) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
   // thread: rows tid / 8 and tid / 8 + 32 of both tiles, inputs 4 (tid & 7) ..

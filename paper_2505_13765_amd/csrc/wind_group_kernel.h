@@ -33,25 +33,6 @@ namespace wind {
 //
 // W <= 16.  A workgroup's row tile holds SPT = 16 / W slots; with more slots than that the group's workgroups
 // are cut into RG row groups, each covering all columns with GW / RG workgroups.
-constexpr int kGroups = 8;              // XCDs
-constexpr int kGroupSlots = 4;          // utterances a group decodes at a time, at most
-constexpr int kGroupRows = 64;          // window rows of a group, at most
-constexpr int kGroupMaxW = 16;
-constexpr int kGroupMaxB = 256;         // utterances of a call (group_init_kernel ranks them in one workgroup)
-constexpr int kGroupBarInts = 33 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 (1 + g): XCD number + 1 of workgroup g
-
-struct GroupDev {
-  unsigned *bar;                        // [kGroups][kGroupBarInts], zero at launch
-  unsigned long long *h_x;              // [kGroups][kGroupSlots][H] new hidden vectors: bf16 hi | lo << 16, iteration + 1 above
-  unsigned long long *p_x;              // [kGroups][kGroupSlots][H] new projections: fp32, iteration + 1 above
-  unsigned long long *keys;             // [kGroups][2][kGroupRows][nparts + 1] two keys per part; last: (blank logit, norm)
-  int *order, *n_order;                 // utterances with frames by falling length, and their number
-  int NG, NS, RG, SPT;                  // groups, slots per group, row tiles per group, slots per row tile
-  int NX;                               // groups whose workgroups exchange words in memory
-  int max_iters;                        // windows an utterance may take
-  unsigned spin_limit;
-};
-
 template <int KS, int CT, int GW>
 struct GroupCfg {
   static constexpr int H = 128 * KS;                      // = Hp = Hj
@@ -110,45 +91,6 @@ __device__ __forceinline__ void group_load_lds(const void *src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
 }
 
-// Everything the loop expects to find: clamped lengths, the utterances by falling length, zeroed counters and exchange words
-// (the keys all ones: their first iterations' tag is 0), in one launch.
-__global__ __launch_bounds__(256) void group_init_kernel(ModelDev m, CallDev c, GroupDev gd) {
-  __shared__ int lens[kGroupMaxB];
-  const int tid = threadIdx.x;
-  const size_t nbar = (size_t)gd.NX * kGroupBarInts, nx = (size_t)gd.NX * kGroupSlots * m.Hp;
-  const size_t nk = (size_t)gd.NX * 2 * kGroupRows * (c.nparts_tiny + 1);
-  for (size_t i = (size_t)blockIdx.x * 256 + tid; i < nbar + 2 * nx + nk; i += (size_t)gridDim.x * 256) {
-    if (i < nbar) gd.bar[i] = 0u;
-    else if (i < nbar + nx) gd.h_x[i - nbar] = 0ull;
-    else if (i < nbar + 2 * nx) gd.p_x[i - nbar - nx] = 0ull;
-    else gd.keys[i - nbar - 2 * nx] = ~0ull;
-  }
-  if (blockIdx.x != 0) return;
-  for (int i = tid; i < kNumStats; i += 256) c.stats[i] = 0ull;
-  for (int b = tid; b < c.B; b += 256) {
-    int len = c.lengths[b];
-    len = len < 0 ? 0 : (len > c.T ? c.T : len);
-    lens[b] = len;
-    c.len[b] = len;
-    c.out_counts[b] = 0;
-  }
-  if (tid == 0) { c.n_active[0] = 0; c.n_active[1] = 0; }
-  __syncthreads();
-  int n = 0;
-  for (int b = tid; b < c.B; b += 256) {
-    const int len = lens[b];
-    int rank = 0;
-    n = 0;
-    for (int o = 0; o < c.B; ++o) {
-      const int lo = lens[o];
-      rank += lo > len || (lo == len && o < b);
-      n += lo > 0;
-    }
-    if (len > 0) gd.order[rank] = b;
-  }
-  if (tid == 0) *gd.n_order = n;
-}
-
 // Load time: the state after the start token (its LSTM step from zero, projection, recurrent sums of the next
 // step), the same for every utterance.  Workgroup = 4 rows of [w_hh ; w_pred], one per wave.
 template <class WT>
@@ -180,9 +122,11 @@ __global__ __launch_bounds__(256) void group_start_kernel(ModelDev m, float *sta
   }
 }
 
-// What the host reads after the loop, in one launch, straight into pinned memory.
+// What the host reads after the loop, in one launch, straight into pinned memory; the call's number last: the host
+// watches for it instead of waiting for the stream (a wait costs 10 us and more after the work is done, and events between the
+// kernels 6 us each; the call's times are the device's time stamps).
 __global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active, const unsigned *bar, int NX, const unsigned long long *stats,
-                                                            int n_stats, int *h_flag, unsigned long long *h_stats) {
+                                                            int *h_flag, unsigned long long *h_stats, int number) {
   const int i = threadIdx.x;
   if (i == 0) {
     unsigned gave_up = 0u, near = 2u;
@@ -194,7 +138,10 @@ __global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active,
     h_flag[1] = (int)gave_up;
     h_flag[2] = (int)near;
   }
-  if (i < n_stats) h_stats[i] = stats[i];
+  if (i < kStatWords) h_stats[i] = i == kStatEnd ? (unsigned long long)wall_clock64() : stats[i];
+  __threadfence_system();
+  __syncthreads();
+  if (i == 0) __hip_atomic_store(h_flag + 8, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The part of the loop's state that every wave keeps for itself: lane a holds slot a.
@@ -776,6 +723,7 @@ __global__ __launch_bounds__(512) void wind_group_kernel(ModelDev m, CallDev c, 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;   // workgroups go to the XCDs in turn
   if (grp >= gd.NG) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) c.stats[kStatLoop] = (unsigned long long)wall_clock64();
   if (threadIdx.x < 256) group_loop<KS, CT, GW, 0>(m, c, gd, smem_raw, grp, g);
   else group_loop<KS, CT, GW, 1>(m, c, gd, smem_raw, grp, g);
 }

@@ -12,6 +12,8 @@ constexpr int kMaxWindow = 64;
 constexpr int kTinyRows = 64;   // slots the resident loop kernel keeps in LDS (it runs far fewer)
 constexpr int kStatJump0 = 9;  // index of jump_hist[0] in the device counter array
 constexpr int kNumStats = kStatJump0 + kMaxWindow + 1;
+// behind the counters, in the same array: device time stamps of the resident groups' calls (start of the call, start of the loop, end)
+constexpr int kStatStart = kNumStats, kStatLoop = kNumStats + 1, kStatEnd = kNumStats + 2, kStatWords = kNumStats + 3;
 enum { ST_ITER = 0, ST_WINDOWS, ST_ROWS, ST_USEFUL, ST_LABELS, ST_FORCED, ST_RECHECK, ST_OVERFLOW, ST_WIDE };   // ST_WIDE: iterations with more window rows than the gather kernel was told
 
 // Weights on the device.  WT-typed matrices are bf16 (bf16 models) or fp32 (fp32 models).
