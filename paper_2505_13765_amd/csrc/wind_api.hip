@@ -706,7 +706,7 @@ const GroupInstance kGroupInstances[] = {
     group_instance<2, 4, 32>(), group_instance<3, 1, 32>(), group_instance<3, 2, 32>(), group_instance<3, 4, 32>(), group_instance<4, 1, 32>(),
     group_instance<4, 2, 32>(), group_instance<4, 4, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(), group_instance<5, 4, 32>(),
     group_instance<5, 2, 20>(),
-    group_f32_instance<2, 4, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
+    group_f32_instance<2, 1, 1>(), group_f32_instance<2, 4, 1>(), group_f32_instance<4, 1, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
     group_f32_instance<8, 1, 32>(), group_f32_instance<12, 1, 32>(), group_f32_instance<16, 1, 32>(), group_f32_instance<20, 1, 32>()};
 
 // Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts), a width
@@ -732,7 +732,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
   if (m->dtype == WIND_F32 && d.Hj <= 128 && nparts <= 4) {
     // a model that fits one CU: a workgroup per utterance
     gw = 1;
-    ct = 4;
+    ct = nparts > 1 ? 4 : 1;
     gd->NG = B;
     gd->NX = 0;
     gd->NS = gd->SPT = gd->RG = 1;

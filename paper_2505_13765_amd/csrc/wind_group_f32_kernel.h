@@ -33,9 +33,38 @@ struct GroupF32Cfg {
   static constexpr size_t oW = oC + (size_t)SL * UPW * 4;                  // float [H] blank column of W_out
   static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1], [H], [H]
   static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], fail, near; float bp[PPW]
-  static constexpr size_t smem = (oI + (64 + kNumStats + 2 + PPW) * 4 + 15) / 16 * 16;
+  static constexpr size_t oT = (oI + (64 + kNumStats + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
+  static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
 };
+
+// a += w[16 i + n] h[n] for n = 0 .. N - 1, h[n] from lane n of the lane's row of 16 (DPP row_newbcast).  One block of
+// assembly: the compiler keeps the broadcasts as moves of their own, which doubles the instructions; the no-op in
+// front keeps the required distance from whatever wrote h.
+template <int N>
+__device__ __forceinline__ void group_row_products(float &a, float h, const float *w) {
+#define WIND_FMAC(n) "v_fmac_f32_dpp %0, %1, %" #n " row_newbcast:"
+  if constexpr (N == 16)
+    asm("s_nop 1\n\t" WIND_FMAC(2) "0 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(3) "1 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(4) "2 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(5) "3 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(6) "4 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(7) "5 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(8) "6 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(9) "7 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(10) "8 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(11) "9 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(12) "10 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(13) "11 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(14) "12 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(15) "13 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(16) "14 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(17) "15 row_mask:0xf bank_mask:0xf"
+        : "+v"(a)
+        : "v"(h), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9]), "v"(w[10]), "v"(w[11]),
+          "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+  else
+    asm("s_nop 1\n\t" WIND_FMAC(2) "0 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(3) "1 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(4) "2 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(5) "3 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(6) "4 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(7) "5 row_mask:0xf bank_mask:0xf\n\t"
+        WIND_FMAC(8) "6 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(9) "7 row_mask:0xf bank_mask:0xf"
+        : "+v"(a)
+        : "v"(h), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]));
+#undef WIND_FMAC
+}
 
 template <int NK, int CT, int GW>
 __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev c, GroupDev gd) {
@@ -130,6 +159,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   };
 
   const float b_blank = m.b_out[V];
+  const unsigned touch_lds = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char *)(smem + Cfg::oT);
   const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
   auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
   float bias[Cfg::NI][2];
@@ -226,6 +256,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         recs[s * NR + row] = v;
       }
     pend = 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
     // ---- exchange 1: four rows per wave, 16 lanes per row
     if constexpr (SOLO) group_barrier();
     if (4 * wave < R) {
@@ -250,9 +281,11 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       }
       const float bm = row16_max_f32(b);
       col = 0xFFFF - row16_max_i32(b == bm ? 0xFFFF - col : 0);
-      if (l15 == 0) stat[row] = !valid || __uint_as_float((unsigned)kC) > bm ? V : col;   // blank has the highest id: it wins only if strictly larger
+      const int label = !valid || __uint_as_float((unsigned)kC) > bm ? V : col;   // blank has the highest id: it wins only if strictly larger
+      if (l15 == 0) stat[row] = label;
+      if (label < V && l15 < min((NR * 4 + 127) / 128 + 1, 16))   // see group_loop
+        group_touch(m.emb_gates + (unsigned)label * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
     group_barrier();   // B2
     if (*fail) return;
     const int lab = lane < R ? stat[lane] : V;
@@ -317,20 +350,26 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back by this wave only
       };
-      // rows of set `t` times the e-th new hidden vector, over this wave's part of K
-      auto row_sums = [&](int t, int e) {
-        const float *hr = hbuf + e * H + wave * KW;   // the same address in every lane
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+      // rows of set `t` times the e-th new hidden vector, over this wave's part of K.  The vector sits in registers, 16 values
+      // to a register in every row of 16 lanes, and each product takes its value from its row's lane n (as an LDS
+      // broadcast per value the reads bound this: 0.75 us for 80 values)
+      float hv[(KW + 15) / 16];
+      auto take_vector = [&](int e) {
 #pragma unroll
-        for (int k = 0; k < KW; k += 4) {
-          const float4 h4 = *reinterpret_cast<const float4 *>(hr + k);
-          a0 = fmaf(wv[t][k], h4.x, a0); a1 = fmaf(wv[t][k + 1], h4.y, a1); a2 = fmaf(wv[t][k + 2], h4.z, a2); a3 = fmaf(wv[t][k + 3], h4.w, a3);
-        }
-        partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = (a0 + a1) + (a2 + a3);
+        for (int i = 0; i < (KW + 15) / 16; ++i) hv[i] = hbuf[e * H + wave * KW + min(16 * i + l15, KW - 1)];
+      };
+      auto row_sums = [&](int t, int e) {
+        float a0 = 0.f, a1 = 0.f;
+        constexpr int BLK = KW % 16 == 0 ? 16 : 8;
+        static_assert(KW == 8 || KW % 16 == 0, "whole blocks");
+#pragma unroll
+        for (int i = 0; i < KW; i += BLK) group_row_products<BLK>((i & 16) ? a1 : a0, hv[i / 16], wv[t] + i);
+        partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = a0 + a1;
       };
       if constexpr (SOLO) group_barrier();
       fetch(hx, hbuf, false);
       for (int e = 0; e < n_em; ++e) {
+        take_vector(e);
 #pragma unroll
         for (int t = 0; t < Cfg::PSET; ++t) row_sums(t, e);
       }
@@ -345,6 +384,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       }
       // ---- while the projections travel: the recurrent sums of the next step (added behind the next barrier)
       for (int e = 0; e < n_em; ++e) {
+        take_vector(e);
 #pragma unroll
         for (int t = Cfg::PSET; t < NSET; ++t) row_sums(t, e);
       }

@@ -53,7 +53,8 @@ struct GroupCfg {
   static constexpr size_t oC = oRec + (size_t)kGroupSlots * NR * 4;       // float [slots][UPW]
   static constexpr size_t oW = oC + (size_t)kGroupSlots * UPW * 4;        // float [H] blank column of W_out
   static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], fail, near; float bp[UPW]
-  static constexpr size_t smem = (oI + (64 + 64 + kNumStats + 2 + PPW) * 4 + 15) / 16 * 16;
+  static constexpr size_t oT = (oI + (64 + 64 + kNumStats + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
+  static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
 };
 
@@ -144,6 +145,11 @@ __global__ __launch_bounds__(128) void group_collect_kernel(const int *n_active,
   if (i == 0) __hip_atomic_store(h_flag + 8, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// 64 lanes x 4 bytes to LDS nobody reads: brings the lines they lie in into this CU's cache
+__device__ __forceinline__ void group_touch(const void *src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory");
+}
+
 // The part of the loop's state that every wave keeps for itself: lane a holds slot a.
 struct GroupLane {
   int b, t, len, sym, cnt;   // utterance, frame, length, labels on the frame, labels so far (len = t = 0: slot empty)
@@ -223,19 +229,26 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
     sl.ld0 = sl.ld;
     sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
     const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
-    if (writer) {   // the call's counters: additions that nobody waits for (fewer than 2^31 each: B T (S + 1) is an int)
+    if (writer) {
+      // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
+      // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
       const unsigned ev = wo.ev;
-      atomicAdd(&counts[ST_WINDOWS], 1);
-      atomicAdd(&counts[ST_ROWS], (int)(ev & 127u));
-      atomicAdd(&counts[ST_USEFUL], (int)((ev >> 7) & 127u));
-      if ((ev >> 21) & 127u) atomicAdd(&counts[ST_RECHECK], (int)((ev >> 21) & 127u));
-      if (ev >> 28) {
-        atomicAdd(&counts[ST_LABELS], (int)((ev >> 28) & 1u));
-        atomicAdd(&counts[ST_FORCED], (int)((ev >> 29) & 1u));
-        atomicAdd(&counts[ST_OVERFLOW], (int)((ev >> 30) & 1u));
+      auto add = [&](int which, unsigned v) {
+        const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + which);
+        asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(v) : "memory");
+      };
+      add(ST_WINDOWS, 1u);
+      add(ST_ROWS, ev & 127u);
+      add(ST_USEFUL, (ev >> 7) & 127u);
+      add(ST_RECHECK, (ev >> 21) & 127u);
+      add(ST_LABELS, (ev >> 28) & 1u);
+      add(ST_FORCED, (ev >> 29) & 1u);
+      add(ST_OVERFLOW, (ev >> 30) & 1u);
+      add(kStatJump0 + (int)((ev >> 14) & 127u), 1u);
+      if (done) {
+        const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + ST_ITER);
+        asm volatile("ds_max_u32 %0, %1" ::"v"(at), "v"(sl.wc) : "memory");
       }
-      atomicAdd(&counts[kStatJump0 + ((ev >> 14) & 127u)], 1);
-      if (done) atomicMax(&counts[ST_ITER], sl.wc);
       if (cut) atomicAdd(&c.n_active[0], 1);
     }
     emits = (wo.flag & 2) && !done;
@@ -255,6 +268,7 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
   }
 }
 __device__ __forceinline__ void group_add_counters(const CallDev &c, const int *counts, int lane) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's additions are in
   for (int j = lane; j < kNumStats; j += 64) {
     if (j == ST_ITER) atomicMax(&c.stats[j], (unsigned long long)counts[j]);
     else if (counts[j]) atomicAdd(&c.stats[j], (unsigned long long)counts[j]);
@@ -352,6 +366,16 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
 
   // ---- constants of this lane's places in the steps below
   const float b_blank = m.b_out[V];
+  // the blank column's part that this lane needs, kept in registers where there is room (the row's LDS reads bound that step)
+  constexpr bool BREG = ROLE == 0 && CT < 4;
+  float4 breg[BREG ? KS : 1][2];
+  if constexpr (BREG) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) breg[i][h] = *reinterpret_cast<const float4 *>(wbl + w4 * QK + l4 * 8 + i * 32 + 4 * h);
+  }
+  const unsigned touch_lds = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char *)(smem + Cfg::oT);
   const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
   auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
   const int nq = 4 * wave >= R ? 0 : 4 * (wave + 8) >= R ? 1 : 2;   // row quads this wave decides
@@ -391,13 +415,13 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       const float *pr = pfull + ga * H + w4 * QK + l4 * 8, *wr_ = wbl + w4 * QK + l4 * 8;
       float dot = 0.f, nrm = 0.f;
       // the LDS operands of a step are read one step ahead, into registers that take turns
-      float4 eo[2][2], po[2][2], bo[2][2];
+      float4 eo[2][2], po[2][2], bo[BREG ? 1 : 2][2];
       auto read_ops = [&](int set, int i) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           eo[set][h] = *reinterpret_cast<const float4 *>(er + i * 32 + 4 * h);
           po[set][h] = *reinterpret_cast<const float4 *>(pr + i * 32 + 4 * h);
-          bo[set][h] = *reinterpret_cast<const float4 *>(wr_ + i * 32 + 4 * h);
+          if constexpr (!BREG) bo[set][h] = *reinterpret_cast<const float4 *>(wr_ + i * 32 + 4 * h);
         }
       };
       bf16x8 zf[KS];
@@ -408,15 +432,15 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         float x[8];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = bo[i & 1][h];
+          const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = BREG ? breg[BREG ? i : 0][h] : bo[BREG ? 0 : i & 1][h];
           float *y = x + 4 * h;
           y[0] = fmaxf(e4.x + p4.x, 0.f); y[1] = fmaxf(e4.y + p4.y, 0.f); y[2] = fmaxf(e4.z + p4.z, 0.f); y[3] = fmaxf(e4.w + p4.w, 0.f);
           dot = fmaf(y[0], b4.x, dot); dot = fmaf(y[1], b4.y, dot); dot = fmaf(y[2], b4.z, dot); dot = fmaf(y[3], b4.w, dot);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) nrm = fmaf(y[q], y[q], nrm);
         }
         const u32x4 zu = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
         zf[i] = __builtin_bit_cast(bf16x8, zu);
+        // the norm only sets the width of the near-tie band: the rounded row's will do
+        nrm = dot2_bf16(zu.x, zu.x, nrm); nrm = dot2_bf16(zu.y, zu.y, nrm); nrm = dot2_bf16(zu.z, zu.z, nrm); nrm = dot2_bf16(zu.w, zu.w, nrm);
         if constexpr (CT < 4) {
 #pragma unroll
           for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);
@@ -481,6 +505,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       }
       pend = 0;
     }
+    if constexpr (ROLE == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
     // ---- exchange 1: four rows per wave and pass, 16 lanes per row, lane s with the keys of parts s and s + 16
     if (nq > 0) {
       float2 kA[2], kB[2], kC[2];
@@ -525,9 +550,12 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         int label = V;
         if (valid[k] && !(vbest < thresh)) label = cnt == 1 && kC[k].x < thresh ? col : -1;   // -1: near-tie
         if (l15 == 0) stat[4 * (wave + 8 * k) + l4] = label;
+        // The step of a label starts with its row of input sums, from a table that no L2 holds: a row that may be the window's first
+        // label asks for its lines now, while the decision is completed (step 0.94 -> 0.7 us)
+        if (label != V && l15 < (NR * 4 + 127) / 128 + 1)
+          group_touch(m.emb_gates + (unsigned)max(col, 0) * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
       }
     }
-    if constexpr (ROLE == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
     group_barrier();   // B2: every row's label, or that it is a near-tie
     if (*fail) return;
     int lab = lane < R ? stat[lane] : V;
@@ -584,8 +612,8 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
             todo &= todo - 1;
           }
       }
-      // ---- LSTM step: thread (emitting slot le, gate row li of this workgroup's units)
-      const int lvt = ROLE == 1 ? tid1 : tid1 + 256, le = lvt / NR, li = lvt - le * NR;
+      // ---- LSTM step: thread (emitting slot le, gate row li of this workgroup's units); waves 0-3 first, which get here earlier
+      const int lvt = ROLE == 0 ? tid1 : tid1 + 256, le = lvt / NR, li = lvt - le * NR;
       if (le < n_em) {
         const int s = le == 0 ? es[0] : le == 1 ? es[1] : le == 2 ? es[2] : es[3], tk = le == 0 ? et[0] : le == 1 ? et[1] : le == 2 ? et[2] : et[3];
         const float pre = recs[s * NR + li] + m.emb_gates[(unsigned)tk * (4u * H) + (unsigned)(unit0 * 4 + li)];   // fits 32 bits: checked by the host
