@@ -1202,8 +1202,9 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
       e = hipFuncSetAttribute((const void *)joint_mfma_store_kernel<JointCfg>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, JointCfg::SMEM_BYTES);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)beam_logits_tiny_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              2 * 32 * (kBeamTinyMaxHj + 8) * 2);
+      for (auto k : {beam_logits_tiny_kernel<1>, beam_logits_tiny_kernel<2>, beam_logits_tiny_kernel<3>, beam_logits_tiny_kernel<4>})
+        if (e == hipSuccess)
+          e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)beam_tiny_smem(kBeamTinyMaxHj, 1));
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void *)enc_proj_ring5_kernel<EncBigCfg>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               EncBigCfg::SMEM_BYTES);
