@@ -29,7 +29,8 @@ namespace wind {
 // parity), and a reader asks for the words it needs until all are this iteration's.  A writer can only
 // overtake a reader by an iteration it cannot reach without that reader's own keys.
 // Every wait is bounded: after spin_limit polls, or when the group's abort word is set, a wave sets that word and
-// marks the workgroup failed, which then leaves at its next decision; the host reports the error.
+// marks the workgroup failed, which then leaves at its next decision; the host
+// then has the call decoded by the per-step kernels, or reports the error.
 //
 // W <= 16.  A workgroup's row tile holds SPT = 16 / W slots; with more slots than that the group's workgroups
 // are cut into RG row groups, each covering all columns with GW / RG workgroups.
@@ -551,9 +552,10 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         if (valid[k] && !(vbest < thresh)) label = cnt == 1 && kC[k].x < thresh ? col : -1;   // -1: near-tie
         if (l15 == 0) stat[4 * (wave + 8 * k) + l4] = label;
         // The step of a label starts with its row of input sums, from a table that no L2 holds: a row that may be the window's first
-        // label asks for its lines now, while the decision is completed (step 0.94 -> 0.7 us)
+        // label asks for its lines now, while the decision is completed (step 0.94 -> 0.7 us).  The
+        // column is clamped: with NaN logits no key is a label's
         if (label != V && l15 < (NR * 4 + 127) / 128 + 1)
-          group_touch(m.emb_gates + (unsigned)max(col, 0) * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
+          group_touch(m.emb_gates + (unsigned)min(max(col, 0), V) * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
       }
     }
     group_barrier();   // B2: every row's label, or that it is a near-tie
