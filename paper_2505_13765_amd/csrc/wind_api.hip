@@ -765,21 +765,29 @@ struct ResidentGate {
 };
 ResidentGate g_resident[kMaxDevices];
 
+// Asynchronous calls under stream capture: the event has no place in another graph, and what is captured runs when the caller
+// launches it, so its turn is the caller's to keep.
+bool stream_capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
 int resident_enter(ResidentGate &g, hipStream_t s) {
-  if (!g.has_pending) return WIND_OK;
+  if (!g.has_pending || stream_capturing(s)) return WIND_OK;
   if (hipEventQuery(g.pending) == hipSuccess) g.has_pending = false;
   else HIP_TRY(hipStreamWaitEvent(s, g.pending, 0));
   return WIND_OK;
 }
 int resident_leave_pending(ResidentGate &g, hipStream_t s) {
+  if (stream_capturing(s)) return WIND_OK;
   if (!g.pending) HIP_TRY(hipEventCreateWithFlags(&g.pending, hipEventDisableTiming));
   HIP_TRY(hipEventRecord(g.pending, s));
   g.has_pending = true;
   return WIND_OK;
 }
 
-// Waits for the results of the resident groups' call `call_number` on stream s to arrive in pinned memory.
-int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s) {
+// Waits for the results of the resident groups' call `call_number` on stream s to arrive in pinned memory.  gave_up: whether the
+// error is that a wait of the groups timed out.
+int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s, bool *gave_up = nullptr) {
   for (unsigned spins = 1; __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number; ++spins) {
     if ((spins & 0x3FFFu) == 0) {   // a kernel that failed never writes it
       const hipError_t e = hipStreamQuery(s);
@@ -791,6 +799,7 @@ int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s) {
   }
   m->loop_info[0] = gd.NG * gw;
   m->loop_info[1] = gd.NG == 1 && m->h_flag[2] == 2;
+  if (gave_up) *gave_up = m->h_flag[1] != 0;
   if (m->h_flag[1] != 0) return fail(WIND_ERR_HIP, "resident loop: a grid barrier timed out (workgroups not all resident?)");
   const unsigned long long *h = m->h_stats;
   m->stamp_ms[0] = (double)(h[kStatEnd] - h[kStatStart]) / m->clock_khz;
@@ -869,12 +878,20 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       m->group.NG = gd.NG;
       return resident_leave_pending(g_resident[m->device], s);
     }
-    rc = finish_group(m, gd, gi->gw, s);
-    if (rc) return rc;
-    if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");
-    rc = read_stats(m);
-    if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
-    return rc;
+    bool gave_up = false;
+    rc = finish_group(m, gd, gi->gw, s, &gave_up);
+    // Something else holds the chip (another process, a long kernel of another stream).  The graph of per-step kernels needs no
+    // two workgroups at once: it decodes this call from the start.
+    if (!gave_up || use_loop) {
+      if (rc) return rc;
+      if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");
+      rc = read_stats(m);
+      if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
+      return rc;
+    }
+    m->loop_info[0] = m->loop_info[1] = 0;
+    HIP_TRY(hipStreamSynchronize(s));   // the collecting kernel has left
+    gate.lock.unlock();
   }
   HIP_TRY(hipEventRecord(m->ev_call[0], s));
   rc = enqueue_prologue(m, s);
@@ -1341,6 +1358,7 @@ static int finish_async(wind_model *m) {
   if (m->async_group) {
     const GroupInstance *gi = m->async_group;
     m->async_group = nullptr;
+    HIP_TRY(hipStreamSynchronize(s));   // the stream, not just the results: whatever the caller put behind the decode is done too
     int rc = finish_group(m, m->group, gi->gw, s);
     if (rc) return rc;
     rc = read_stats(m);

@@ -85,3 +85,51 @@ def test_two_streams_and_threads_take_turns():
     assert not bad
     for m in models:
         m.close()
+
+
+@pytest.mark.parametrize("H,V,B", [(640, 1024, 5), (128, 31, 8)])
+def test_groups_that_cannot_meet_leave_the_call_to_the_per_step_kernels(H, V, B):
+    """Workgroups that wait for each other too long (here: not at all, set from the host) give up, and the call is decoded by the
+    graph of per-step kernels, which needs no two workgroups on the chip at once."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("groups", 40 + B, B, 1, 75, 64, 64, 1, H, H, V, "bf16", (8,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=2.0, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    m.set_option("loop_kernel", 0)
+    want = m.decode(d_enc, d_len, 8, cfg.S)
+    m.set_option("loop_kernel", 1)
+    for limit, resident in ((0, False), (1 << 21, True)):
+        m.set_option("loop_spin_limit", limit)
+        got = m.decode(d_enc, d_len, 8, cfg.S)
+        assert (m.loop_info()[0] > 0) == resident
+        if not resident:   # the same kernels
+            assert all(a.tolist() == b.tolist() for k in (0, 1) for a, b in zip(got[k], want[k]))
+    m.close()
+
+
+def test_completing_an_asynchronous_decode_waits_for_the_stream():
+    """wind_get_stats waits for the stream, so work that the caller put behind the decode is done too."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.scaled(wi.CONFIGS["batch32"], 4, 30, 60)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg))
+    enc, lens = wi.make_batch(cfg)
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    B, T = enc.shape[:2]
+    out = [torch.zeros(s, dtype=torch.int32, device="cuda") for s in ((B, T * cfg.S), (B, T * cfg.S), (B,))]
+    ws = torch.empty(m.workspace_bytes(B, T, 8) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:][: m.workspace_bytes(B, T, 8)]
+    a = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    m.greedy_decode_async(d_enc, d_len, 8, cfg.S, *out, ws, T * (cfg.S + 1) + 2)
+    for _ in range(8):
+        a = a @ a * 1e-2
+    behind = torch.cuda.Event()
+    behind.record()
+    m.stats()
+    assert behind.query()
+    m.close()
