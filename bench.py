@@ -196,6 +196,7 @@ def graph_ablation(torch, wi, WindModel, steps, warmup):
     out = (torch.zeros((B, cap), dtype=torch.int32, device="cuda"),
            torch.zeros((B, cap), dtype=torch.int32, device="cuda"),
            torch.zeros((B,), dtype=torch.int32, device="cuda"))
+    model.set_option("loop_kernel", 0)   # the per-step kernels in all three: batches of this size would decode in resident groups
     res = {"workload": f"batch32 model, B=16, {int(lens.sum())} frames", "unit": "ms per decode call",
            "paper_table5_decoder_only_s": {"standard": {"eager": 12.45, "graph": 4.23}, "wind_w8": {"eager": 6.45, "graph": 2.10},
                                            "hardware": "2x A6000, Parakeet-RNNT-1.1b, real audio"}}
