@@ -45,7 +45,9 @@ using EncSmallCfg = TileCfg<64, 64, 32, 32>;   // calls whose 128 x 128 tiles wo
 using PredCfg = DmaCfg<64, 64, 32, 32, 64, 4>;   // 32 utterances (hi and lo rows) x 64 columns, 4-stage ring
 constexpr int kPredMfmaMinBatch = 1;       // below this the FMA prediction network is used
 constexpr size_t kEncRing5MinRows = 16384;   // B * T from which the encoder projection uses 256 x 256 tiles
-constexpr long long kEncFewTiles = 1024;     // 32 x 32 tiles up to which the encoder projection runs on them (four workgroups per CU)
+// 32 x 32 tiles up to which the encoder projection runs on them.  Against 64 x 64 tiles, D = 1024: 80 tiles 9.5 us (14.5), 160 to 380 the
+// same 14.5, 640 tiles 21.8 us (15.5)
+constexpr long long kEncFewTiles = 384;
 constexpr int kIterRowsCap = 16384;   // iterations whose row counts profile mode records
 constexpr int kRowPad = 256;  // window-row buffers are padded to a multiple of every tile height, plus one block
 
@@ -459,12 +461,14 @@ bool enc_wide_ok(const wind_model *m, int B, int T) {
   return ((unsigned long long)B * T + 256) * d.D * 2 < (1ull << 32);
 }
 
-constexpr int kGroupInitBlocks = 64;   // workgroups that prepare the resident groups' words and lists
+constexpr int kGroupInitBlocks = 8;   // workgroups per group that prepare the resident groups' words and lists
 // every frame of the call through the encoder projection; gd: also what the resident groups need before their launch
 void enqueue_enc_proj(wind_model *m, hipStream_t s, const GroupDev *group = nullptr) {
   const ModelDev &d = m->dev;
   const CallDev &c = m->call;
-  const int init = group ? kGroupInitBlocks : 0;
+  // few where there are few groups: the launch's grid has them once per column tile, and all but the first row's leave at once, in front
+  // of the tiles (64 workgroups for a single group: 14 us instead of 9.5 for 125 frames)
+  const int init = group ? kGroupInitBlocks * std::max(1, group->NX) : 0;
   const GroupDev gd = group ? *group : GroupDev{};
   if (c.T == 0 && group) group_init_kernel<<<init, 256, 0, s>>>(d, c, gd);
   if (c.T > 0) {
