@@ -276,7 +276,7 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
 void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B);
 
 // The model's own workspace: allocated on first use, regrown when a call needs more.
-int ensure_workspace(wind_model *m, int B, int T, int W) {
+int ensure_workspace(wind_model *m, int B, int T, int W, hipStream_t s) {
   const WsLayout w = workspace_layout(m, B, T, W);
   if (w.total > m->ws_bytes) {
     HIP_TRY(hipDeviceSynchronize());
@@ -286,8 +286,9 @@ int ensure_workspace(wind_model *m, int B, int T, int W) {
     m->graph_valid = false;
     HIP_TRY(hipMalloc(&m->ws, w.total));
     m->ws_bytes = w.total;
-    // window-row buffers are read tile-wide: start them defined
-    HIP_TRY(hipMemset(m->ws, 0, w.total));
+    // window-row buffers are read tile-wide: start them defined.  On the call's stream: the default stream is not ordered against it, and
+    // what it has queued would put the clearing behind the call's first kernels
+    HIP_TRY(hipMemsetAsync(m->ws, 0, w.total, s));
   }
   carve_workspace(m, w, (char *)m->ws, B);
   return WIND_OK;
@@ -842,7 +843,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     const size_t zi = w.Mpad * (size_t)m->dev.Hj / 2;
     fill_int_kernel<<<(unsigned)std::min<size_t>((zi + 255) / 256, 2048), 256, 0, s>>>((int *)m->call.z, (int)zi, 0);
   } else {
-    rc = ensure_workspace(m, B, T, W);
+    rc = ensure_workspace(m, B, T, W, s);
     if (rc) return rc;
   }
   CallDev &c = m->call;
@@ -1312,7 +1313,7 @@ int wind_beam_window_scores(wind_model *m, const float *enc_window, int n, const
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
   BeamWs ws;
-  rc = beam_workspace(m, (size_t)n, (size_t)Bh, (size_t)Bh * n, &ws);
+  rc = beam_workspace(m, (size_t)n, (size_t)Bh, (size_t)Bh * n, &ws, s);
   if (rc) return rc;
   rc = beam_scores_enqueue(m, ws, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
   if (rc) return rc;
@@ -1537,7 +1538,7 @@ int wind_set_option(wind_model *m, const char *key, int64_t value) {
 // Common start of the debug entry points: workspace for the shape, the call's fields, and a decode
 // prologue (state, encoder projection, start-token step) with the library's own outputs.
 static int debug_prologue(wind_model *m, const float *enc_out, const int32_t *lengths, int B, int T, int W, hipStream_t s) {
-  int rc = ensure_workspace(m, B, T, W);
+  int rc = ensure_workspace(m, B, T, W, s);
   if (rc) return rc;
   CallDev &c = m->call;
   c.B = B; c.T = T; c.W = W; c.S = 1; c.cap = 1;

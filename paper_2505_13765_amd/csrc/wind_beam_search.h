@@ -47,7 +47,7 @@ size_t beam_carve(const wind_model *m, size_t n, size_t Bh, size_t rows, char *b
 }
 
 // The model's own scoring workspace, allocated on first use and regrown on demand.
-int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws) {
+int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws, hipStream_t s) {
   const size_t off = beam_carve(m, n, Bh, rows, nullptr, nullptr);
   if (off > m->beam_ws_bytes) {
     HIP_TRY(hipDeviceSynchronize());
@@ -56,7 +56,7 @@ int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws) 
     m->beam_ws_bytes = 0;
     HIP_TRY(hipMalloc(&m->beam_ws, off));
     m->beam_ws_bytes = off;
-    HIP_TRY(hipMemset(m->beam_ws, 0, off));   // the MFMA pass reads whole row tiles
+    HIP_TRY(hipMemsetAsync(m->beam_ws, 0, off, s));   // the MFMA pass reads whole row tiles; on the stream that the pass runs on
   }
   beam_carve(m, n, Bh, rows, (char *)m->beam_ws, ws);
   return WIND_OK;
@@ -221,7 +221,7 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
   BeamPool &bp = m->beam_pool;
   const int V = d.V, V1 = V + 1;
   BeamWs ws;
-  int rc = beam_workspace(m, (size_t)window, (size_t)kBeamMaxK, (size_t)std::max(kBeamMaxK * window, kBeamCompRows), &ws);
+  int rc = beam_workspace(m, (size_t)window, (size_t)kBeamMaxK, (size_t)std::max(kBeamMaxK * window, kBeamCompRows), &ws, s);
   if (rc) return rc;
   rc = beam_pool_reserve(m, 1024, s);
   if (rc) return rc;
