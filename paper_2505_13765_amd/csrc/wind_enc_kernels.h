@@ -62,7 +62,8 @@ constexpr int kGroupSlots = 4;          // utterances a group decodes at a time,
 constexpr int kGroupRows = 64;          // window rows of a group, at most
 constexpr int kGroupMaxW = 16;
 constexpr int kGroupMaxB = 256;         // utterances of a call (group_init_kernel ranks them in one workgroup)
-constexpr int kGroupBarInts = 33 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 (1 + g): XCD number + 1 of workgroup g
+constexpr int kGroupBarInts = 34 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 + g: iterations workgroup g has
+                                        //   decided, word 32 (2 + g): its XCD number + 1
 
 struct GroupDev {
   unsigned *bar;                        // [kGroups][kGroupBarInts], zero at launch

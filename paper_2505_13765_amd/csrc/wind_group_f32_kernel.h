@@ -128,7 +128,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     unsigned xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     xcc = (xcc & 15u) + 1u;
-    unsigned *bw = abort_word + 32;
+    unsigned *bw = abort_word + 64;
     if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned v = xcc;
     const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
@@ -137,14 +137,15 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     });
     const bool same = __all(v == xcc);
     if (lane == 0) {
-      *near_w = same;
+      *near_w = (same ? 1 : 0) | (group_keys_suffice(nparts, GW, 1) ? 0 : 2);
       if (!got) *fail = 1;
       if (g == 0) abort_word[1] = same ? 2u : 1u;
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   group_barrier();
-  const bool near = *near_w != 0;
+  const int flags = __builtin_amdgcn_readfirstlane(*near_w);
+  const bool near = flags & 1, publishes = flags & 2;
   auto put = [&](unsigned long long *p, unsigned lo, unsigned hi) {
     if constexpr (SOLO) *p = (unsigned long long)lo | ((unsigned long long)hi << 32);
     else group_st(p, lo, hi, near);
@@ -179,7 +180,11 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
     const unsigned stamp = (unsigned)it + 1u, stamp16 = stamp & 0xFFFFu;
-    unsigned long long *kp = SOLO ? kbase : kbase + (size_t)(it & 1) * kGroupRows * kstride;
+    unsigned long long *kp = SOLO ? kbase : kbase + (size_t)group_key_buffer(it) * kGroupRows * kstride;
+    if constexpr (!SOLO) {   // the keys that this iteration's replace have been read by everybody
+      if (publishes && wave == 6 && group_keys_need(it) > 0 &&
+          !group_poll(abort_word, gd.spin_limit, [&]() { return group_decided<GW>(abort_word + 32, lane, group_keys_need(it)); }) && lane == 0) *fail = 1;
+    }
     {
       // ---- window rows as matrix-core operands: lane (row l15, K group l4), NK consecutive units of this wave's part of K
       f32x4 acc[2 * CT];
@@ -288,6 +293,9 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     }
     group_barrier();   // B2
     if (*fail) return;
+    if constexpr (!SOLO) {
+      if (publishes && wave == 6 && lane == 0) group_publish(abort_word + 32 + g, stamp, near);   // this workgroup's reads of the keys are done
+    }
     const int lab = lane < R ? stat[lane] : V;
     const unsigned long long m_nb = __ballot(lab != V);
     int tok;

@@ -2,6 +2,7 @@
 #pragma once
 #include "wind_types.h"
 #include "wind_decide_kernels.h"
+#include "wind_group_protocol.h"
 #include "wind_pred_kernels.h"
 
 namespace wind {
@@ -26,8 +27,10 @@ namespace wind {
 //              rows -> exchange 3 (projection); then, off the chain, the recurrent sums of the next step
 //              and the frames of the window after next
 // The three exchanges have no barrier and no flags: every 8-byte word carries its iteration (the keys: its
-// parity), and a reader asks for the words it needs until all are this iteration's.  A writer can only
-// overtake a reader by an iteration it cannot reach without that reader's own keys.
+// parity), and a reader asks for the words it needs until all are this iteration's.  No word is overwritten before everybody
+// has read it: new hidden vectors and projections come from every workgroup, so none can start a step that another has not
+// finished.  Keys need not, and where some workgroup has none every workgroup also publishes the iterations it has decided
+// (wind_group_protocol.h; looked at by a wave that idles during the window products.  Always doing so cost 2 to 6 %).
 // Every wait is bounded: after spin_limit polls, or when the group's abort word is set, a wave sets that word and
 // marks the workgroup failed, which then leaves at its next decision; the host
 // then has the call decoded by the per-step kernels, or reports the error.
@@ -53,7 +56,7 @@ struct GroupCfg {
   static constexpr size_t oRec = oRecp + (size_t)4 * NR * 4 * 4;          // float [slots][NR]
   static constexpr size_t oC = oRec + (size_t)kGroupSlots * NR * 4;       // float [slots][UPW]
   static constexpr size_t oW = oC + (size_t)kGroupSlots * UPW * 4;        // float [H] blank column of W_out
-  static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], fail, near; float bp[UPW]
+  static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], fail, flags; float bp[UPW]
   static constexpr size_t oT = (oI + (64 + 64 + kNumStats + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
   static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
@@ -73,6 +76,16 @@ __device__ __forceinline__ void group_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+// Whether every workgroup of the group has decided `need` iterations (progress: their counts, one word each, one line in all)
+template <int GW>
+__device__ __forceinline__ bool group_decided(const unsigned *progress, int lane, int need) {
+  const unsigned v = lane < GW ? __hip_atomic_load(progress + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0x7FFFFFFFu;
+  return (int)v >= need;
+}
+__device__ __forceinline__ void group_publish(unsigned *word, unsigned v, bool near) {
+  if (near) __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // A quarter of a wait: asks again through `ask` (which returns whether this lane has all it needs) until every
 // lane of the wave does.  False: gave up.
@@ -347,7 +360,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     unsigned xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     xcc = (xcc & 15u) + 1u;
-    unsigned *bw = abort_word + 32;
+    unsigned *bw = abort_word + 64;
     if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned v = xcc;
     const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
@@ -356,14 +369,15 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     });
     const bool same = __all(v == xcc);
     if (lane == 0) {
-      *near_w = same;
+      *near_w = (same ? 1 : 0) | (group_keys_suffice(nparts, CG, gd.RG) ? 0 : 2);
       if (!got) *fail = 1;
       if (g == 0) abort_word[1] = same ? 2u : 1u;
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   group_barrier();
-  const bool near = *near_w != 0;
+  const int flags = __builtin_amdgcn_readfirstlane(*near_w);   // one register for both
+  const bool near = flags & 1, publishes = flags & 2;
 
   // ---- constants of this lane's places in the steps below
   const float b_blank = m.b_out[V];
@@ -398,9 +412,15 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     l4 = lane >> 4;
     const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
-    const int tag = (it >> 1) & 1;
+    const int tag = group_key_tag(it);
     const unsigned stamp = (unsigned)it + 1u;
-    unsigned long long *kp = kbase + (size_t)(it & 1) * kGroupRows * kstride;
+    unsigned long long *kp = kbase + (size_t)group_key_buffer(it) * kGroupRows * kstride;
+    if constexpr (ROLE == 1) {
+      // the keys that this iteration's replace have been read by everybody: nearly always so at once, and looked at while waves 0-3
+      // form the window products
+      if (publishes && wave == 6 && group_keys_need(it) > 0 &&
+          !group_poll(abort_word, gd.spin_limit, [&]() { return group_decided<GW>(abort_word + 32, lane, group_keys_need(it)); }) && lane == 0) *fail = 1;
+    }
     if constexpr (ROLE == 0) {
       // ---- window rows as matrix-core operands: lane (row l15, K group l4) takes 8 consecutive frames' projections
       // per step of 32 of this wave's quarter of K, adds the prediction projection, applies the ReLU and rounds:
@@ -596,6 +616,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       if ((need >> lane) & 1ull) lab = stat2[lane];
       m_nb = __ballot(lab >= 0 && lab != V);
     }
+    if (ROLE == 1 && publishes && wave == 6 && lane == 0) group_publish(abort_word + 32 + g, stamp, near);   // this workgroup's reads of the keys are done
     // ---- outcome of every slot's window; one wave of workgroup 0 writes the outputs
     int tok;
     bool emits, fresh_slot;
