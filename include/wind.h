@@ -123,7 +123,13 @@ int wind_greedy_decode(wind_model *m, const float *enc_out, const int32_t *lengt
  * Completion: the next wind_get_stats on the model waits for `stream`, and returns WIND_OK, or
  * WIND_ERR_OVERFLOW (as wind_greedy_decode), or WIND_ERR_UNFINISHED if utterances were still active
  * after max_iterations (outputs and counts then hold the labels found up to there).  Until then the
- * model accepts no other decode call.  Other arguments as wind_greedy_decode.  Returns WIND_ERR_ARG for
+ * model accepts no other decode call.  The loop is the graph of per-step kernels, except that calls of one or two
+ * utterances may run as one resident kernel (option "loop_kernel"), whose workgroups have to be on the chip
+ * together: if something keeps them apart for longer than "loop_spin_limit" polls, wind_get_stats returns
+ * WIND_ERR_HIP and the outputs are incomplete; and that small fp32 models run as one workgroup per utterance, which wait for
+ * nobody.  Under stream capture the kernels become part of the caller's graph (captured per-step
+ * kernels: max_iterations times five or so nodes); launches of such graphs that hold a resident kernel are the caller's to keep
+ * apart, from each other and from other calls with one.  Other arguments as wind_greedy_decode.  Returns WIND_ERR_ARG for
  * a null, misaligned or too small workspace (the message names both sizes) and max_iterations < 1,
  * WIND_ERR_UNSUPPORTED with options "graph" = 0, "profile" or "host_sync".  The first call of a shape
  * captures and instantiates its graph (host-side work and runtime allocations).
@@ -364,8 +370,7 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             device-wide stores if it is not as expected.  0: spread over the chip
  *   "loop_spin_limit"  polls a workgroup of a resident kernel waits for the others before it gives up
  *             (default 2^21, about a second); the decode then returns WIND_ERR_HIP, or, where the alternative to the
- *             groups is the graph of per-step kernels, is done again by that graph (wind_greedy_decode and
- *             wind_sequential_decode; the asynchronous form reports the error).  Tests set it
+ *             groups is the graph of per-step kernels, is done again by that graph.  Tests set it
  *             to 0 to exercise that path: every workgroup still leaves the kernel normally
  *   "atomic_lists"  1 (default): in the graph of per-step kernels of bf16 models, every workgroup of the
  *             decision kernel claims its utterance's place in the next iteration's list of active

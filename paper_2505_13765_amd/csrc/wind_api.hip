@@ -137,7 +137,7 @@ struct wind_model {
   double stamp_ms[2] = {0.0, 0.0}, clock_khz = 1e5;
   int call_number = 0;         // of the last call that ran in resident groups
   // an asynchronous decode that wind_get_stats has not completed yet
-  bool async_pending = false, async_loop = false;
+  bool async_pending = false, async_loop = false, async_timed = false;   // async_timed: its events were recorded (not into a graph)
   const GroupInstance *async_group = nullptr;
   hipStream_t async_stream = nullptr;
   unsigned *async_bar = nullptr;
@@ -154,6 +154,7 @@ struct wind_model {
   bool fma_pred_step = false;   // this call's prediction-network steps keep their state in fp32 (the resident loop kernel reads it)
   LoopDev loop{};
   GroupDev group{};
+  int *group_out = nullptr;    // kGroupOutBytes in the workspace
   int *dbg_len = nullptr, *dbg_out = nullptr;   // lengths and outputs of the debug entry points (inside the workspace)
   void *beam_ws = nullptr;   // workspace of the beam scoring step
   BeamPool beam_pool{};
@@ -214,13 +215,14 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
+constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {
   size_t total, Mpad, st;
   bool big_enc;
   int slot_stride, nparts, nparts_tiny;
   size_t o_e, o_encb, o_len, o_nact, o_eidx, o_eltok, o_slot, o_slotc, o_rst, o_raux, o_nemit, o_ticket, o_h, o_c, o_hn, o_hb,
-      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder;
+      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder, o_gout;
 };
 
 WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
@@ -269,6 +271,7 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_gx = take(grouped ? (size_t)2 * kGroups * kGroupSlots * d.Hp * 8 : 0);
   w.o_gkeys = take(grouped ? (size_t)kGroups * 2 * kGroupRows * (w.nparts_tiny + 1) * 8 : 0);
   w.o_gorder = take(grouped ? (size_t)(kGroupMaxB + 1) * 4 : 0);
+  w.o_gout = take(grouped ? kGroupOutBytes : 0);   // an asynchronous call's flags and counters
   w.total = off;
   return w;
 }
@@ -351,6 +354,7 @@ void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B) {
   m->group.keys = (unsigned long long *)(base + w.o_gkeys);
   m->group.order = (int *)(base + w.o_gorder);
   m->group.n_order = m->group.order + kGroupMaxB;
+  m->group_out = (int *)(base + w.o_gout);
 }
 
 int check_launch(const char *what) {
@@ -790,18 +794,8 @@ int resident_leave_pending(ResidentGate &g, hipStream_t s) {
   return WIND_OK;
 }
 
-// Waits for the results of the resident groups' call `call_number` on stream s to arrive in pinned memory.  gave_up: whether the
-// error is that a wait of the groups timed out.
-int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s, bool *gave_up = nullptr) {
-  for (unsigned spins = 1; __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number; ++spins) {
-    if ((spins & 0x3FFFu) == 0) {   // a kernel that failed never writes it
-      const hipError_t e = hipStreamQuery(s);
-      if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("resident groups: ") + hipGetErrorString(e));
-      if (e == hipSuccess && __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number)
-        return fail(WIND_ERR_HIP, "resident groups: the stream is done, the results have not arrived");
-    }
-    __builtin_ia32_pause();
-  }
+// What the resident groups' results in pinned memory say.  gave_up: whether the error is that a wait of the groups timed out.
+int group_results(wind_model *m, const GroupDev &gd, int gw, bool *gave_up = nullptr) {
   m->loop_info[0] = gd.NG * gw;
   m->loop_info[1] = gd.NG == 1 && m->h_flag[2] == 2;
   if (gave_up) *gave_up = m->h_flag[1] != 0;
@@ -811,6 +805,19 @@ int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s, bool 
   m->stamp_ms[1] = (double)(h[kStatEnd] - h[kStatLoop]) / m->clock_khz;
   m->have_call_times = m->stamp_times = true;
   return WIND_OK;
+}
+// Waits for the results of the resident groups' call `call_number` on stream s to arrive in pinned memory.
+int finish_group(wind_model *m, const GroupDev &gd, int gw, hipStream_t s, bool *gave_up) {
+  for (unsigned spins = 1; __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number; ++spins) {
+    if ((spins & 0x3FFFu) == 0) {   // a kernel that failed never writes it
+      const hipError_t e = hipStreamQuery(s);
+      if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("resident groups: ") + hipGetErrorString(e));
+      if (e == hipSuccess && __atomic_load_n(&m->h_flag[8], __ATOMIC_ACQUIRE) != m->call_number)
+        return fail(WIND_ERR_HIP, "resident groups: the stream is done, the results have not arrived");
+    }
+    __builtin_ia32_pause();
+  }
+  return group_results(m, gd, gw, gave_up);
 }
 
 // One decode call.  ext_ws null: the model's own workspace, and the call returns when the decode has
@@ -861,6 +868,10 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   m->have_call_times = m->stamp_times = false;
   GroupDev gd = m->group;
   const GroupInstance *gi = group_shape(m, B, T, W, &gd);
+  // Behind an asynchronous call no host decodes it again if the groups cannot meet: it takes them only where no two workgroups have to
+  // (one per utterance), or where the other choice is a kernel whose workgroups have to meet as well.
+  if (async && gi && gi->gw != 1 && !use_loop) gi = nullptr;
+  const bool capturing = async && stream_capturing(s);
   if (gi || use_loop) {
     if (m->device < 0 || m->device >= kMaxDevices) return fail(WIND_ERR_UNSUPPORTED, "device ordinal above 63");
     gate.lock = std::unique_lock<std::mutex>(g_resident[m->device].mutex);
@@ -874,8 +885,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
-    m->call_number = m->call_number == INT_MAX ? 1 : m->call_number + 1;
-    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, m->h_flag, m->h_stats, m->call_number);
+    // An asynchronous call's results stay in its workspace until it is completed: it may be part of a graph that the caller launches
+    // again at any time, beside a later call that watches the pinned words.
+    if (!async) m->call_number = m->call_number == INT_MAX ? 1 : m->call_number + 1;
+    int *flags = async ? m->group_out : m->h_flag;
+    group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, flags, (unsigned long long *)(flags + 16), async ? 0 : m->call_number);
     rc = check_launch("resident groups' results");
     if (rc) return rc;
     if (async) {
@@ -884,7 +898,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       return resident_leave_pending(g_resident[m->device], s);
     }
     bool gave_up = false;
-    rc = finish_group(m, gd, gi->gw, s, &gave_up);
+    rc = finish_group(m, gd, gi->gw, s, &gave_up);   // flags and counters: h_flag, and h_stats 64 bytes on
     // Something else holds the chip (another process, a long kernel of another stream).  The graph of per-step kernels needs no
     // two workgroups at once: it decodes this call from the start.
     if (!gave_up || use_loop) {
@@ -898,10 +912,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     HIP_TRY(hipStreamSynchronize(s));   // the collecting kernel has left
     gate.lock.unlock();
   }
-  HIP_TRY(hipEventRecord(m->ev_call[0], s));
+  auto call_event = [&](int i) { return capturing ? hipSuccess : hipEventRecord(m->ev_call[i], s); };   // times are of calls that ran
+  HIP_TRY(call_event(0));
   rc = enqueue_prologue(m, s);
   if (rc) return rc;
-  HIP_TRY(hipEventRecord(m->ev_call[1], s));   // the loop starts here: state set up, every frame projected
+  HIP_TRY(call_event(1));   // the loop starts here: state set up, every frame projected
   if (use_loop) {
     // the whole loop as one resident kernel
     lp.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
@@ -926,9 +941,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     }
     rc = check_launch("resident loop");
     if (rc) return rc;
-    HIP_TRY(hipEventRecord(m->ev_call[2], s));
+    HIP_TRY(call_event(2));
     if (async) {
-      m->async_pending = true; m->async_loop = true; m->async_stream = s; m->async_bar = lp.bar;
+      m->async_pending = true; m->async_loop = true; m->async_timed = !capturing; m->async_stream = s; m->async_bar = lp.bar;
       m->loop_info[0] = lp.G; m->loop_info[1] = 0;
       return resident_leave_pending(g_resident[m->device], s);
     }
@@ -961,7 +976,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   };
   m->joint_us.clear();
   m->joint_rows.clear();
-  if (use_graph) {
+  if (use_graph && !capturing) {
     rc = ensure_graph(m);
     if (rc) return rc;
   }
@@ -970,9 +985,18 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     // end of the decode find no active utterance and leave at once
     if (!use_graph) return fail(WIND_ERR_UNSUPPORTED, "the asynchronous decode needs graph replay (options graph, profile, host_sync)");
     const long long replays = (std::min(async_iters, max_iters) + U - 1) / U;
-    for (long long i = 0; i < replays; ++i) HIP_TRY(hipGraphLaunch(m->graph_exec[wide_by_history(i) ? 1 : 0], s));
-    HIP_TRY(hipEventRecord(m->ev_call[2], s));
-    m->async_pending = true; m->async_loop = false; m->async_stream = s;
+    for (long long i = 0; i < replays; ++i) {
+      if (!capturing) {
+        HIP_TRY(hipGraphLaunch(m->graph_exec[wide_by_history(i) ? 1 : 0], s));
+      } else {   // into the caller's graph: the kernels themselves
+        for (int it = 0; it < U; ++it) {
+          rc = enqueue_iteration(m, s, it & 1, true, wide_by_history(i));
+          if (rc) return rc;
+        }
+      }
+    }
+    HIP_TRY(call_event(2));
+    m->async_pending = true; m->async_loop = false; m->async_timed = !capturing; m->async_stream = s;
     return WIND_OK;
   }
   if (m->opt_host_sync) {
@@ -1201,7 +1225,7 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     rc = static_scratch_address(&unused);   // once per device, here rather than in a call that must not stall
   }
   if (rc == WIND_OK) {
-    hipError_t e = hipHostMalloc((void **)&m->h_flag, 64 + kStatWords * sizeof(unsigned long long), hipHostMallocCoherent);
+    hipError_t e = hipHostMalloc((void **)&m->h_flag, kGroupOutBytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
       rc = fail(WIND_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
     } else {
@@ -1363,8 +1387,9 @@ static int finish_async(wind_model *m) {
   if (m->async_group) {
     const GroupInstance *gi = m->async_group;
     m->async_group = nullptr;
-    HIP_TRY(hipStreamSynchronize(s));   // the stream, not just the results: whatever the caller put behind the decode is done too
-    int rc = finish_group(m, m->group, gi->gw, s);
+    HIP_TRY(hipMemcpyAsync(m->h_flag, m->group_out, kGroupOutBytes, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));   // whatever the caller put behind the decode is done too
+    int rc = group_results(m, m->group, gi->gw);
     if (rc) return rc;
     rc = read_stats(m);
     if (rc == WIND_OK && m->h_flag[0] != 0)
@@ -1380,7 +1405,7 @@ static int finish_async(wind_model *m) {
   if (m->async_loop && m->h_flag[2] != 0)
     return fail(WIND_ERR_HIP, "resident loop: a grid barrier timed out (workgroups not all resident?)");
   int rc = fetch_stats(m, s);
-  m->have_call_times = true;
+  m->have_call_times = m->async_timed;
   m->prev_B = m->call.B; m->prev_T = m->call.T; m->prev_W = m->call.W;
   m->prev_iters = m->last_stats.iterations;
   // whole replays are an even number of iterations, so the last one left its count in the first slot
