@@ -14,6 +14,7 @@ namespace wind {
 //   - small models (GW = 1: a whole model fits one CU's registers) run one workgroup per utterance, which
 //     tells itself through LDS, behind workgroup barriers.
 // Bound by the chain of steps like the bf16 groups; of 640 units the products of a 16-row tile take 1.2 us (fp32 rate).
+constexpr int kGroupNoLabel = 0xFFFF;   // in a word's column field; above every column
 template <int NK, int CT, int GW>
 struct GroupF32Cfg {
   static constexpr int H = 32 * NK, KW = H / 8;             // = Hp = Hj; a wave's part of K
@@ -239,9 +240,10 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
 #pragma unroll
         for (int w = 0; w < 8; ++w) v[t] += fred[((w * 2 * CT + 2 * ct + t) * 4 + l4) * 80 + 16 * q4 + l15];
       }
-      const bool second = v[1] > v[0];   // ties: the lower column
-      const float b = second ? v[1] : v[0], bm = row16_max_f32(b);
-      const int col = 0xFFFF - row16_max_i32(b == bm ? 0xFFFF - (part * 32 + (second ? 16 : 0) + l15) : 0);
+      // a NaN (from infinite frames) is no label's: the maxima pass over it, and a part of nothing else has column kGroupNoLabel
+      const float b = fmaxf(v[0], v[1]), bm = row16_max_f32(b);
+      const int at = part * 32 + l15 + (v[0] == b ? 0 : 16);   // ties: the lower column
+      const int col = kGroupNoLabel - row16_max_i32(b == bm ? kGroupNoLabel - at : 0);
       const int row = 4 * q4 + l4;
       if (part < nparts && l15 == 0 && row < R) put(kp + row * kstride + part, __float_as_uint(bm), (unsigned)(col & 0xFFFF) | (stamp16 << 16));
     }
@@ -278,15 +280,20 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
                (unsigned)(kC >> 48) == stamp16;
       });
       if (!got && lane == 0) *fail = 1;
-      float b = valid && l15 < nparts ? __uint_as_float((unsigned)kA) : kKeyNone;
-      int col = (int)(kA >> 32) & 0xFFFF;
-      if (valid && l15 + 16 < nparts && __uint_as_float((unsigned)kB) > b) {   // ties: the lower column
+      float b = kKeyNone;
+      int col = kGroupNoLabel;
+      if (valid && l15 < nparts) {
+        b = __uint_as_float((unsigned)kA);
+        col = (int)(kA >> 32) & 0xFFFF;
+      }
+      if (valid && l15 + 16 < nparts && (__uint_as_float((unsigned)kB) > b || b != b)) {   // ties: the lower column
         b = __uint_as_float((unsigned)kB);
         col = (int)(kB >> 32) & 0xFFFF;
       }
       const float bm = row16_max_f32(b);
-      col = 0xFFFF - row16_max_i32(b == bm ? 0xFFFF - col : 0);
-      const int label = !valid || __uint_as_float((unsigned)kC) > bm ? V : col;   // blank has the highest id: it wins only if strictly larger
+      col = kGroupNoLabel - row16_max_i32(b == bm ? kGroupNoLabel - col : 0);
+      // blank has the highest id: it wins only if strictly larger, and where no label has a logit
+      const int label = !valid || col >= V || __uint_as_float((unsigned)kC) > bm ? V : col;
       if (l15 == 0) stat[row] = label;
       if (label < V && l15 < min((NR * 4 + 127) / 128 + 1, 16))   // see group_loop
         group_touch(m.emb_gates + (unsigned)label * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);

@@ -392,7 +392,7 @@ __global__ __launch_bounds__(256) void joint_exact_kernel(ModelDev m, CallDev c,
     int bi = s_idx[0];
     for (int w2 = 1; w2 < 4; ++w2)
       if (s_val[w2] > bv || (s_val[w2] == bv && s_idx[w2] < bi)) { bv = s_val[w2]; bi = s_idx[w2]; }
-    c.row_label[row] = valid ? bi : m.V;
+    c.row_label[row] = valid ? min(bi, m.V) : m.V;   // no logit is a number (infinite frames): blank, as from keys
   }
 }
 

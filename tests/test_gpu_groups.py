@@ -54,6 +54,39 @@ def test_resident_groups(dtype, H, V, B, W):
     m.close()
 
 
+@pytest.mark.parametrize("dtype,H,V,B,W", [("bf16", 640, 1024, 3, 8), ("bf16", 128, 31, 8, 16), ("bf16", 512, 77, 1, 5), ("f32", 640, 1000, 2, 16),
+                                           ("f32", 384, 31, 5, 4), ("f32", 128, 97, 3, 4), ("f32", 64, 32, 2, 7), ("f32", 64, 128, 1, 4)])
+def test_frames_that_are_not_finite(dtype, H, V, B, W):
+    """A NaN frame projects to a hidden row of zeros (the ReLU's maximum passes over NaN) and is decided by the biases; an infinite input gives
+    hidden units of infinity and NaN logits, a row without any label: blank, on every route.  No id outside the vocabulary is ever written."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    D = 64 if dtype == "bf16" else 68
+    cfg = wi.WindConfig("groups", 60 + B, B, 30, 75, D, 64, 1, H, H, V, dtype, (W,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=2.0, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    bad = []
+    for b in range(B):
+        enc[b, 4] = np.nan
+        bad.append({5, 6, 7, 20, int(lens[b]) - 1})
+        for t in bad[b]:
+            enc[b, t, t % D] = np.inf if t % 2 else -np.inf
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    res = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        toks, frs = m.decode(d_enc, d_len, W, cfg.S)
+        assert (m.loop_info()[0] > 0) == bool(loop)
+        assert all(((0 <= t) & (t < V)).all() for t in toks) and sum(map(len, toks)) > 0
+        assert not any(bad[b] & set(f.tolist()) for b, f in enumerate(frs))
+        st = m.stats()
+        res.append((toks, frs, (st.iterations, st.windows, st.rows, st.useful_rows, st.labels, st.forced_advances, list(st.jump_hist))))
+    assert all(a.tolist() == b.tolist() for k in (0, 1) for a, b in zip(res[0][k], res[1][k]))
+    assert res[0][2] == res[1][2]
+    m.close()
+
+
 def test_two_streams_and_threads_take_turns():
     """Resident kernels of several models, called from several threads on streams of their own, must not wait for each other's CUs."""
     import threading
