@@ -457,11 +457,10 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
           float *y = x + 4 * h;
           y[0] = fmaxf(e4.x + p4.x, 0.f); y[1] = fmaxf(e4.y + p4.y, 0.f); y[2] = fmaxf(e4.z + p4.z, 0.f); y[3] = fmaxf(e4.w + p4.w, 0.f);
           dot = fmaf(y[0], b4.x, dot); dot = fmaf(y[1], b4.y, dot); dot = fmaf(y[2], b4.z, dot); dot = fmaf(y[3], b4.w, dot);
+          nrm = fmaf(y[0], y[0], nrm); nrm = fmaf(y[1], y[1], nrm); nrm = fmaf(y[2], y[2], nrm); nrm = fmaf(y[3], y[3], nrm);
         }
         const u32x4 zu = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
         zf[i] = __builtin_bit_cast(bf16x8, zu);
-        // the norm only sets the width of the near-tie band: the rounded row's will do
-        nrm = dot2_bf16(zu.x, zu.x, nrm); nrm = dot2_bf16(zu.y, zu.y, nrm); nrm = dot2_bf16(zu.z, zu.z, nrm); nrm = dot2_bf16(zu.w, zu.w, nrm);
         if constexpr (CT < 4) {
 #pragma unroll
           for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);

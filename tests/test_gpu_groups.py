@@ -87,6 +87,38 @@ def test_frames_that_are_not_finite(dtype, H, V, B, W):
     m.close()
 
 
+@pytest.mark.parametrize("H,V,B,W", [(128, 31, 3, 8), (640, 1000, 1, 16), (512, 77, 40, 4)])
+def test_the_near_tie_band_is_that_of_the_unrounded_row(H, V, B, W):
+    """Which rows are decided again in fp32 depends on the norm of the hidden row before it is rounded to bf16.  Every hidden unit here is just below
+    1 + 2^-8, which rounds to 1: a norm of rounded values is 0.4 % short, and a label 0.2 % inside the edge of the band would be missed."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("groups", 80 + B, B, 20, 40, 64, 64, 1, H, H, V, "bf16", (W,), 3, 0.7)
+    w = wi.make_weights(cfg)
+    x, wn = float(np.float32(1 + 2.0 ** -8 - 2.0 ** -20)), 4.0
+    for k in ("w_enc", "w_pred", "b_pred", "w_out"):
+        w[k][:] = 0.0
+    w["b_enc"][:] = x
+    w["w_out"][0, 0] = wn   # the longest weight row: with |z| = x sqrt(H), the band is kappa * 2.1e-3 * wn * x
+    w["b_out"][:] = -50.0
+    w["b_out"][1] = 1.0
+    tau = 8.0 * 2.1e-3 * wn * x + 6.2e-5
+    enc, lens = wi.make_batch(cfg)
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    for gap, inside in ((0.998 * tau, True), (1.002 * tau, False)):   # keys are truncated by 2^-15 of the logit: 0.05 % of the band
+        w["b_out"][2] = 1.0 - gap
+        m = WindModel.from_config(cfg, w)
+        for loop in (0, 1):
+            m.set_option("loop_kernel", loop)
+            toks, _ = m.decode(d_enc, d_len, W, cfg.S)
+            assert (m.loop_info()[0] > 0) == bool(loop)
+            st = m.stats()
+            assert st.rechecks == (st.rows if inside else 0)
+            assert all((t == 1).all() for t in toks) and st.labels == 3 * int(lens.sum())
+        m.close()
+
+
 def test_two_streams_and_threads_take_turns():
     """Resident kernels of several models, called from several threads on streams of their own, must not wait for each other's CUs."""
     import threading
