@@ -764,13 +764,15 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
 }
 
 // Kernels that keep workgroups on the chip and have them wait for each other run one at a time per GPU: two of them,
-// launched from different streams, could each get some of the CUs and wait for the rest.  A call that
-// waits for its own end holds the gate until then; an asynchronous one leaves an event that later launches
-// wait for on the GPU.
+// launched from different streams, could each get some of the CUs and wait for the rest.  Every such launch leaves an event behind it that
+// the next one's stream waits for, on the GPU.  The mutex is held while a call puts its kernel on its stream and no longer: a
+// host thread does not wait for what another's stream has queued.  (A call that waits for its own results takes its event back
+// once it has them, so that calls one after another wait for no event.)
 struct ResidentGate {
   std::mutex mutex;
   hipEvent_t pending = nullptr;
   bool has_pending = false;
+  unsigned long long turn = 0;   // of the launch that `pending` stands for
 };
 ResidentGate g_resident[kMaxDevices];
 
@@ -786,12 +788,19 @@ int resident_enter(ResidentGate &g, hipStream_t s) {
   else HIP_TRY(hipStreamWaitEvent(s, g.pending, 0));
   return WIND_OK;
 }
-int resident_leave_pending(ResidentGate &g, hipStream_t s) {
+// The kernel is on stream s: its turn, for resident_done
+int resident_leave(ResidentGate &g, hipStream_t s, unsigned long long *turn) {
+  *turn = 0;
   if (stream_capturing(s)) return WIND_OK;
   if (!g.pending) HIP_TRY(hipEventCreateWithFlags(&g.pending, hipEventDisableTiming));
   HIP_TRY(hipEventRecord(g.pending, s));
   g.has_pending = true;
+  *turn = ++g.turn;
   return WIND_OK;
+}
+void resident_done(ResidentGate &g, unsigned long long turn) {
+  std::lock_guard<std::mutex> lock(g.mutex);
+  if (g.turn == turn) g.has_pending = false;
 }
 
 // What the resident groups' results in pinned memory say.  gave_up: whether the error is that a wait of the groups timed out.
@@ -836,7 +845,6 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   if ((long long)B * T > (1ll << 31) - 1) return fail(WIND_ERR_ARG, "B*T too large");
   if (m->dtype == WIND_BF16 && m->dev.Hj > kDecideMaxHj) return fail(WIND_ERR_UNSUPPORTED, "Hj > 2048");
   hipStream_t s = (hipStream_t)stream;
-  struct { std::unique_lock<std::mutex> lock; } gate;   // held by calls with a resident kernel
   const bool async = ext_ws != nullptr;
   int rc = WIND_OK;
   if (async) {
@@ -874,14 +882,20 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   const bool capturing = async && stream_capturing(s);
   if (gi || use_loop) {
     if (m->device < 0 || m->device >= kMaxDevices) return fail(WIND_ERR_UNSUPPORTED, "device ordinal above 63");
-    gate.lock = std::unique_lock<std::mutex>(g_resident[m->device].mutex);
-    rc = resident_enter(g_resident[m->device], s);
-    if (rc) return rc;
   }
+  ResidentGate &gate = g_resident[std::max(m->device, 0)];
+  std::unique_lock<std::mutex> gate_lock(gate.mutex, std::defer_lock);
+  unsigned long long turn = 0;
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
     enqueue_enc_proj(m, s, &gd);
+    const bool meets = gi->gw != 1;   // one workgroup per utterance: waits for nobody
+    if (meets) {
+      gate_lock.lock();
+      rc = resident_enter(gate, s);
+      if (rc) return rc;
+    }
     gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
@@ -892,13 +906,19 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     group_collect_kernel<<<1, 128, 0, s>>>(c.n_active, gd.bar, gd.NX, c.stats, flags, (unsigned long long *)(flags + 16), async ? 0 : m->call_number);
     rc = check_launch("resident groups' results");
     if (rc) return rc;
+    if (meets) {
+      rc = resident_leave(gate, s, &turn);
+      gate_lock.unlock();
+      if (rc) return rc;
+    }
     if (async) {
       m->async_pending = true; m->async_loop = false; m->async_group = gi; m->async_stream = s;
       m->group.NG = gd.NG;
-      return resident_leave_pending(g_resident[m->device], s);
+      return WIND_OK;
     }
     bool gave_up = false;
     rc = finish_group(m, gd, gi->gw, s, &gave_up);   // flags and counters: h_flag, and h_stats 64 bytes on
+    if (turn && (rc == WIND_OK || gave_up)) resident_done(gate, turn);
     // Something else holds the chip (another process, a long kernel of another stream).  The graph of per-step kernels needs no
     // two workgroups at once: it decodes this call from the start.
     if (!gave_up || use_loop) {
@@ -910,7 +930,6 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     }
     m->loop_info[0] = m->loop_info[1] = 0;
     HIP_TRY(hipStreamSynchronize(s));   // the collecting kernel has left
-    gate.lock.unlock();
   }
   auto call_event = [&](int i) { return capturing ? hipSuccess : hipEventRecord(m->ev_call[i], s); };   // times are of calls that ran
   HIP_TRY(call_event(0));
@@ -921,6 +940,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     // the whole loop as one resident kernel
     lp.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
     lp.spin_limit = (unsigned)m->opt_loop_spin_limit;
+    gate_lock.lock();
+    rc = resident_enter(gate, s);
+    if (rc) return rc;
     {
       const int bar_ints = (1 + lp.G) * kLoopFlagStride;
       // the key exchange starts out as "two iterations old": all tag bits set, the first iterations' tag is 0
@@ -945,13 +967,17 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     if (async) {
       m->async_pending = true; m->async_loop = true; m->async_timed = !capturing; m->async_stream = s; m->async_bar = lp.bar;
       m->loop_info[0] = lp.G; m->loop_info[1] = 0;
-      return resident_leave_pending(g_resident[m->device], s);
+      return resident_leave(gate, s, &turn);
     }
     static_assert(kNumStats <= 128, "loop_collect_kernel: one thread per counter");
     loop_collect_kernel<<<1, 128, 0, s>>>(c.n_active, lp.bar, c.stats, kNumStats, m->h_flag, m->h_stats);   // one launch, one wait
     rc = check_launch("resident loop results");
     if (rc) return rc;
+    rc = resident_leave(gate, s, &turn);
+    gate_lock.unlock();
+    if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(s));
+    resident_done(gate, turn);
     m->loop_info[0] = lp.G; m->loop_info[1] = m->h_flag[2] == 2;
     if (m->h_flag[1] != 0) return fail(WIND_ERR_HIP, "resident loop: a grid barrier timed out (workgroups not all resident?)");
     if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");

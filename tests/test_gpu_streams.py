@@ -126,3 +126,57 @@ def test_captured_asynchronous_decode(torch_cuda, name, B, W):
         assert same(taken(out), want)
         assert same(m.decode(e2, l2, W, cfg.S), want2)
     m.close()
+
+
+def backlog(torch, stream):
+    """Some 0.4 s of matrix products on the stream, and an event behind them."""
+    a = torch.ones((8192, 8192), device="cuda")
+    with torch.cuda.stream(stream):
+        for _ in range(40):
+            a = a @ a * 1e-9
+        behind = torch.cuda.Event()
+        behind.record()
+    return behind
+
+
+def test_no_host_thread_waits_for_anothers_stream(torch_cuda):
+    """Resident kernels take turns on the GPU.  While a synchronous call waits behind the work that its stream has queued, an asynchronous
+    call of another model on another stream returns at once, and a small fp32 model, whose workgroups wait for nobody, decodes."""
+    import time
+
+    torch = torch_cuda
+    cfg, enc, lens, make = load("greedy_b1", 1, 60, 60)
+    tiny_cfg, tiny_enc, tiny_lens, make_tiny = load("tiny", 2, 30, 60)
+    m, other, tiny = make(), make(), make_tiny()
+    d_enc, d_len, t_enc, t_len = (torch.from_numpy(x).cuda() for x in (enc, lens, tiny_enc, tiny_lens))
+    want, want_tiny = m.decode(d_enc, d_len, 16, cfg.S), tiny.decode(t_enc, t_len, 4, tiny_cfg.S)
+    assert same(other.decode(d_enc, d_len, 16, cfg.S), want)
+    out, ws = async_buffers(torch, other, 1, enc.shape[1], 16, cfg.S)
+    torch.cuda.synchronize()
+    beside = 0
+    for _ in range(6):   # streams may share a hardware queue, and the tiny decode then comes behind the products after all
+        s1, s2, s3, got = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream(), []
+        behind = backlog(torch, s1)
+
+        def work():
+            with torch.cuda.stream(s1):
+                got.append(m.decode(d_enc, d_len, 16, cfg.S))
+
+        t = threading.Thread(target=work)
+        t.start()
+        time.sleep(0.02)   # it has put its kernels on its stream
+        with torch.cuda.stream(s2):
+            other.greedy_decode_async(d_enc, d_len, 16, cfg.S, *out, ws, enc.shape[1] * (cfg.S + 1) + 2)
+        assert not behind.query()
+        with torch.cuda.stream(s3):
+            assert same(tiny.decode(t_enc, t_len, 4, tiny_cfg.S), want_tiny)
+        beside += not behind.query()
+        t.join()
+        assert other.stats().labels == sum(map(len, want[0]))
+        assert same(got[0], want) and same(taken(out), want)
+        assert m.loop_info()[0] == other.loop_info()[0] == 32
+        if beside:
+            break
+    assert beside
+    for x in (m, other, tiny):
+        x.close()
