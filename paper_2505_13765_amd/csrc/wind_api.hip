@@ -215,6 +215,7 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
+constexpr unsigned kGroupStartPolls = 1u << 14;   // about 10 ms
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {
@@ -888,7 +889,10 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   unsigned long long turn = 0;
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
+    // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where the per-step kernels
+    // can decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
+    gd.start_limit = use_loop ? gd.spin_limit : std::min(gd.spin_limit, kGroupStartPolls);
     enqueue_enc_proj(m, s, &gd);
     const bool meets = gi->gw != 1;   // one workgroup per utterance: waits for nobody
     if (meets) {

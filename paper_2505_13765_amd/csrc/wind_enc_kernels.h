@@ -74,7 +74,7 @@ struct GroupDev {
   int NG, NS, RG, SPT;                  // groups, slots per group, row tiles per group, slots per row tile
   int NX;                               // groups whose workgroups exchange words in memory
   int max_iters;                        // windows an utterance may take
-  unsigned spin_limit;
+  unsigned spin_limit, start_limit;     // polls of a wait, and of the first one: until all workgroups of the group are on the chip
 };
 
 // Everything the resident groups expect to find: clamped lengths, the utterances by falling length, zeroed counters and

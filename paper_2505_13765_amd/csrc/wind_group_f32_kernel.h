@@ -132,7 +132,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     unsigned *bw = abort_word + 64;
     if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned v = xcc;
-    const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+    const bool got = group_poll(abort_word, gd.start_limit, [&]() {
       if (lane < GW) v = __hip_atomic_load(bw + lane * 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return v != 0u;
     });

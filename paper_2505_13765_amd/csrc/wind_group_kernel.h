@@ -31,8 +31,8 @@ namespace wind {
 // has read it: new hidden vectors and projections come from every workgroup, so none can start a step that another has not
 // finished.  Keys need not, and where some workgroup has none every workgroup also publishes the iterations it has decided
 // (wind_group_protocol.h; looked at by a wave that idles during the window products.  Always doing so cost 2 to 6 %).
-// Every wait is bounded: after spin_limit polls, or when the group's abort word is set, a wave sets that word and
-// marks the workgroup failed, which then leaves at its next decision; the host
+// Every wait is bounded: after spin_limit polls (the first one, for all to be on the chip: start_limit), or when the group's abort word is
+// set, a wave sets that word and marks the workgroup failed, which then leaves at its next decision; the host
 // then has the call decoded by the per-step kernels, or reports the error.
 //
 // W <= 16.  A workgroup's row tile holds SPT = 16 / W slots; with more slots than that the group's workgroups
@@ -363,7 +363,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     unsigned *bw = abort_word + 64;
     if (lane == 0) __hip_atomic_store(bw + g * 32, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned v = xcc;
-    const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
+    const bool got = group_poll(abort_word, gd.start_limit, [&]() {
       if (lane < GW) v = __hip_atomic_load(bw + lane * 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return v != 0u;
     });

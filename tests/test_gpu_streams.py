@@ -180,3 +180,48 @@ def test_no_host_thread_waits_for_anothers_stream(torch_cuda):
     assert beside
     for x in (m, other, tiny):
         x.close()
+
+
+def test_groups_do_not_wait_long_for_their_places(torch_cuda):
+    """While a kernel that outlasts the call (here: a captured asynchronous decode of one utterance, whose launches the caller keeps
+    apart or not) holds some CUs of every XCD, a batch is decoded by the per-step kernels, not after it."""
+    import time
+
+    torch = torch_cuda
+    from paper_2505_13765_amd import WindModel
+
+    one = wi.scaled(wi.CONFIGS["greedy_b1"], 1, 5000, 5000)
+    m = WindModel.from_config(one, wi.make_weights(one, blank_bias=-50.0))   # labels on every frame: some 0.3 s
+    d_one, l_one = torch.randn((1, 5000, one.D), device="cuda"), torch.full((1,), 5000, dtype=torch.int32, device="cuda")
+    out, ws = async_buffers(torch, m, 1, 5000, 32, one.S)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        m.greedy_decode_async(d_one, l_one, 32, one.S, *out, ws, 5000 * (one.S + 1) + 2)
+    cfg, enc, lens, make = load("batch32", 12, 30, 60)
+    batch = make()
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    batch.set_option("loop_kernel", 0)
+    want = batch.decode(d_enc, d_len, 8, cfg.S)
+    batch.set_option("loop_kernel", 1)
+    assert same(batch.decode(d_enc, d_len, 8, cfg.S), want) and batch.loop_info()[0] == 256
+    beside = False
+    for _ in range(6):   # streams may share a hardware queue, and the batch then comes behind the other kernel
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(s1):
+            g.replay()
+            behind = torch.cuda.Event()
+            behind.record()
+        time.sleep(0.02)
+        assert not behind.query()
+        with torch.cuda.stream(s2):
+            assert same(batch.decode(d_enc, d_len, 8, cfg.S), want)
+        beside = not behind.query()
+        torch.cuda.synchronize()
+        assert m.stats().labels == 5000 * one.S == int(out[2][0])   # the other kernel was not disturbed
+        if beside:
+            break
+    assert beside and batch.loop_info()[0] == 0
+    assert same(batch.decode(d_enc, d_len, 8, cfg.S), want) and batch.loop_info()[0] == 256
+    m.close()
+    batch.close()
