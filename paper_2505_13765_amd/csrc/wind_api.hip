@@ -215,7 +215,7 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
-constexpr unsigned kGroupStartPolls = 1u << 14;   // about 10 ms
+constexpr unsigned kGroupStartPolls = 1u << 14;   // about 3 ms
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {

@@ -191,7 +191,7 @@ def test_groups_do_not_wait_long_for_their_places(torch_cuda):
     from paper_2505_13765_amd import WindModel
 
     one = wi.scaled(wi.CONFIGS["greedy_b1"], 1, 5000, 5000)
-    m = WindModel.from_config(one, wi.make_weights(one, blank_bias=-50.0))   # labels on every frame: some 0.3 s
+    m = WindModel.from_config(one, wi.make_weights(one, blank_bias=-50.0))   # labels on every frame: 1.3 s
     d_one, l_one = torch.randn((1, 5000, one.D), device="cuda"), torch.full((1,), 5000, dtype=torch.int32, device="cuda")
     out, ws = async_buffers(torch, m, 1, 5000, 32, one.S)
     torch.cuda.synchronize()
@@ -215,13 +215,15 @@ def test_groups_do_not_wait_long_for_their_places(torch_cuda):
         time.sleep(0.02)
         assert not behind.query()
         with torch.cuda.stream(s2):
+            start = time.perf_counter()
             assert same(batch.decode(d_enc, d_len, 8, cfg.S), want)
+            took = time.perf_counter() - start
         beside = not behind.query()
         torch.cuda.synchronize()
         assert m.stats().labels == 5000 * one.S == int(out[2][0])   # the other kernel was not disturbed
         if beside:
             break
-    assert beside and batch.loop_info()[0] == 0
+    assert beside and took < 0.1 and batch.loop_info()[0] == 0   # 5 ms; the limit of the later waits is 0.4 s
     assert same(batch.decode(d_enc, d_len, 8, cfg.S), want) and batch.loop_info()[0] == 256
     m.close()
     batch.close()
