@@ -715,7 +715,6 @@ const GroupInstance kGroupInstances[] = {
     group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<1, 4, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(),
     group_instance<2, 4, 32>(), group_instance<3, 1, 32>(), group_instance<3, 2, 32>(), group_instance<3, 4, 32>(), group_instance<4, 1, 32>(),
     group_instance<4, 2, 32>(), group_instance<4, 4, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(), group_instance<5, 4, 32>(),
-    group_instance<5, 2, 20>(),
     group_f32_instance<2, 1, 1>(), group_f32_instance<2, 4, 1>(), group_f32_instance<4, 1, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
     group_f32_instance<8, 1, 32>(), group_f32_instance<12, 1, 32>(), group_f32_instance<16, 1, 32>(), group_f32_instance<20, 1, 32>()};
 
@@ -738,7 +737,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
   if (B > kLoopMaxB && (!m->opt_lstm_rec || !m->opt_atomic_lists || !m->opt_slot_rows || !m->opt_decide_two || m->opt_joint_wide != 1 ||
                         m->opt_pred_mfma_min_batch > B)) return nullptr;
   const int nparts = (d.V + kTinyCols - 1) / kTinyCols;
-  int gw, ct;
+  int gw = 32, ct;   // workgroups of a group: the CUs of an XCD
   if (m->dtype == WIND_F32 && d.Hj <= 128 && nparts <= 4) {
     // a model that fits one CU: a workgroup per utterance
     gw = 1;
@@ -747,8 +746,6 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     gd->NX = 0;
     gd->NS = gd->SPT = gd->RG = 1;
   } else {
-    // two utterances of 640 units: two groups of 20 workgroups (640 divides by 20); else 32, the CUs of an XCD
-    gw = m->dtype == WIND_BF16 && B == 2 && d.Hp == 640 ? 20 : 32;
     gd->NG = gd->NX = std::min(kGroups, B);
     gd->NS = std::min(kGroupSlots, (B + gd->NG - 1) / gd->NG);
     if (m->dtype == WIND_F32) gd->NS = std::min(gd->NS, kGroupMaxW / W);   // one row tile: registers hold one part of W_out
@@ -756,7 +753,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
     gd->RG = tiles > 2 ? 4 : tiles;
     const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
-    ct = gw == 20 ? 2 : parts > 2 ? 4 : parts;
+    ct = parts > 2 ? 4 : parts;
     if (parts > ct) return nullptr;
   }
   for (const GroupInstance &i : kGroupInstances)

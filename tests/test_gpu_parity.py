@@ -174,17 +174,21 @@ def test_prediction_network_on_mfma_tiles(torch_cuda, name, B, lo, hi, W):
     m.close()
 
 
-@pytest.mark.parametrize("name,B,lo,hi,W,near", [("greedy_b1", 1, 150, 150, 16, True), ("greedy_b1", 1, 130, 130, 1, True),
-                                                 ("greedy_b1", 1, 120, 120, 32, False), ("greedy_b1", 1, 90, 90, 5, True),
-                                                 ("greedy_b1", 2, 60, 120, 16, False), ("batch32", 2, 50, 90, 3, False)])
-def test_resident_loop_kernel(torch_cuda, name, B, lo, hi, W, near):
+@pytest.mark.parametrize("name,Hp,B,lo,hi,W,near", [("greedy_b1", 640, 1, 150, 150, 16, True), ("greedy_b1", 640, 1, 130, 130, 1, True),
+                                                    ("greedy_b1", 640, 1, 120, 120, 32, False), ("greedy_b1", 640, 1, 90, 90, 5, True),
+                                                    ("greedy_b1", 640, 2, 60, 120, 16, False), ("batch32", 640, 2, 50, 90, 3, False),
+                                                    ("greedy_b1", 512, 1, 150, 150, 16, True), ("greedy_b1", 512, 1, 90, 90, 5, True),
+                                                    ("greedy_b1", 512, 2, 60, 120, 16, True)])
+def test_resident_loop_kernel(torch_cuda, name, Hp, B, lo, hi, W, near):
     """One or two utterances with at most 32 window rows decode in one resident kernel whose
     workgroups exchange keys, hidden vectors and projections behind grid barriers; it must agree
     with the oracle and, label for label and counter for counter, with the graph of per-step
     kernels (loop_kernel = 0).  Both placements of its workgroups are run: 32 on one XCD, exchanging
     through its L2 (shapes marked `near`: their larger weight slices and the window rows fit LDS),
-    and spread over the chip; the library reports which one a call used."""
-    cfg = wi.scaled(wi.CONFIGS[name], B, lo, hi)
+    and spread over the chip; the library reports which one a call used.  With all options on, models as wide in the
+    LSTM as in the joiner take the resident groups instead (windows of at most 16 rows; a group of 32 per
+    utterance); a narrower LSTM brings those options to this kernel."""
+    cfg = wi.scaled(wi.CONFIGS[name], B, lo, hi).replace(Hp=Hp)
     m, o, _ = load(cfg)
     enc, lens = wi.make_batch(cfg)
     d_enc, d_len = to_dev(torch_cuda, enc, lens)
@@ -197,6 +201,8 @@ def test_resident_loop_kernel(torch_cuda, name, B, lo, hi, W, near):
         g, one_l2 = m.loop_info()
         if lk == 0:
             assert (g, one_l2) == (0, False)
+        elif one and fused and Hp == cfg.Hj and W <= 16 and B == 2:
+            assert (g, one_l2) == (64, False)
         elif one and near:
             assert g == 32
             if not one_l2:   # the kernel found its workgroups on several XCDs and kept the device-wide stores: slower, not wrong
