@@ -305,7 +305,8 @@ typedef enum {
 int wind_get_kernel_times(wind_model *m, double *ms, int64_t *launches);
 
 /*
- * Device time of the last decode call on a model, from events on the call's stream: the whole call,
+ * Device time of the last decode call on a model, from events on the call's stream, or, for calls in resident groups
+ * (option "loop_kernel"), from time stamps that their kernels take (first start, start of the loop, results written): the whole call,
  * and the loop alone, i.e. without the once-per-call set-up (state, encoder projection of every frame,
  * start-token step) — the "decoder-only" kind of time of Table 5, whose total also holds the encoder.
  * In milliseconds; HOST pointers.  The loop's end is the last launch the call made (with graph replay
@@ -359,8 +360,9 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             64, 128, 256, 384, 512 or 640, at most 1024 labels; the options lstm_rec, atomic_lists, slot_rows, decide_two,
  *             joint_wide and pred_mfma_min_batch at their defaults where there are more than two utterances), and,
  *             for one or two utterances of other one-layer models or options, with at most 32 window rows,
- *             workgroups over one XCD or the chip that meet at grid barriers.  Calls with a resident kernel take
- *             turns on a GPU: one from another thread or stream waits for the one before it
+ *             workgroups over one XCD or the chip that meet at grid barriers.  Resident kernels whose
+ *             workgroups wait for each other (all but those of fp32 models of at most 128 units and 128 labels) take turns on a
+ *             GPU: a call's kernel waits on its stream until that of the call before it, of any thread, stream or model, is done
  *   "loop_fused"  1 (default): with at most 16 window rows and a joint hidden size that is a multiple of 128,
  *             at most 640, that kernel builds the window rows directly as matrix-core operands; 0: it
  *             stages them in LDS (the form for every other shape)
@@ -371,7 +373,7 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *   "loop_spin_limit"  polls a workgroup of a resident kernel waits for the others before it gives up
  *             (default 2^21, about half a second); the decode then returns WIND_ERR_HIP, or, where the alternative to the
  *             groups is the graph of per-step kernels, is done again by that graph (groups that are not all on the chip
- *             within 2^14 polls, about 3 ms, leave it to the graph then).  Tests set it
+ *             within 2^16 polls, about 12 ms, leave it to the graph then).  Tests set it
  *             to 0 to exercise that path: every workgroup still leaves the kernel normally
  *   "atomic_lists"  1 (default): in the graph of per-step kernels of bf16 models, every workgroup of the
  *             decision kernel claims its utterance's place in the next iteration's list of active

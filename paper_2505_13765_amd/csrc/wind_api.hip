@@ -45,8 +45,8 @@ using EncSmallCfg = TileCfg<64, 64, 32, 32>;   // calls whose 128 x 128 tiles wo
 using PredCfg = DmaCfg<64, 64, 32, 32, 64, 4>;   // 32 utterances (hi and lo rows) x 64 columns, 4-stage ring
 constexpr int kPredMfmaMinBatch = 1;       // below this the FMA prediction network is used
 constexpr size_t kEncRing5MinRows = 16384;   // B * T from which the encoder projection uses 256 x 256 tiles
-// 32 x 32 tiles up to which the encoder projection runs on them.  Against 64 x 64 tiles, D = 1024: 80 tiles 9.5 us (14.5), 160 to 380 the
-// same 14.5, 640 tiles 21.8 us (15.5)
+// 32 x 32 tiles up to which the encoder projection runs on them.  Against 64 x 64 tiles, D = 1024: 80 tiles 9.5 us (14.5), from 160 to 380 no
+// difference (14.5), 640 tiles 21.8 us (15.5): the line is where they begin to lose
 constexpr long long kEncFewTiles = 384;
 constexpr int kIterRowsCap = 16384;   // iterations whose row counts profile mode records
 constexpr int kRowPad = 256;  // window-row buffers are padded to a multiple of every tile height, plus one block
@@ -215,7 +215,7 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
-constexpr unsigned kGroupStartPolls = 1u << 14;   // about 3 ms
+constexpr unsigned kGroupStartPolls = 1u << 16;   // about 12 ms, what a batch of 32 takes with the per-step kernels
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {

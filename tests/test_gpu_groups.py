@@ -139,7 +139,8 @@ def test_two_streams_and_threads_take_turns():
         with torch.cuda.stream(torch.cuda.Stream()):
             for _ in range(4):
                 toks, frs = m.decode(d_enc, d_len, 8, cfg.S)
-                if not all(a.tolist() == b.tolist() for r, g in zip(ref, (toks, frs)) for a, b in zip(r, g)):
+                # a call whose groups did not meet is decoded by the per-step kernels, with the same labels
+                if m.loop_info()[0] != 256 or not all(a.tolist() == b.tolist() for r, g in zip(ref, (toks, frs)) for a, b in zip(r, g)):
                     bad.append(m)
 
     threads = [threading.Thread(target=work, args=(m,)) for m in models]
