@@ -371,9 +371,9 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             shortens every grid barrier; the kernel checks the placement itself and falls back to
  *             device-wide stores if it is not as expected.  0: spread over the chip
  *   "loop_spin_limit"  polls a workgroup of a resident kernel waits for the others before it gives up
- *             (default 2^21, about half a second); the decode then returns WIND_ERR_HIP, or, where the alternative to the
- *             groups is the graph of per-step kernels, is done again by that graph (groups that are not all on the chip
- *             within 2^16 polls, about 12 ms, leave it to the graph then).  Tests set it
+ *             (default 2^21, about half a second); the decode then returns WIND_ERR_HIP.  Groups that are not all on the chip
+ *             within 2^16 polls, about 12 ms, leave the call to the kernels that take it without them (an asynchronous
+ *             call: the whole limit, and the error).  Tests set it
  *             to 0 to exercise that path: every workgroup still leaves the kernel normally
  *   "atomic_lists"  1 (default): in the graph of per-step kernels of bf16 models, every workgroup of the
  *             decision kernel claims its utterance's place in the next iteration's list of active

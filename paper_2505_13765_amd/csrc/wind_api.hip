@@ -881,15 +881,15 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   if (gi || use_loop) {
     if (m->device < 0 || m->device >= kMaxDevices) return fail(WIND_ERR_UNSUPPORTED, "device ordinal above 63");
   }
-  ResidentGate &gate = g_resident[std::max(m->device, 0)];
+  ResidentGate &gate = g_resident[gi || use_loop ? m->device : 0];   // calls of neither kind take no turn
   std::unique_lock<std::mutex> gate_lock(gate.mutex, std::defer_lock);
   unsigned long long turn = 0;
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
-    // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where the per-step kernels
-    // can decode the call, it waits for no more than about the time that takes.
+    // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where another kernel can
+    // decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
-    gd.start_limit = use_loop ? gd.spin_limit : std::min(gd.spin_limit, kGroupStartPolls);
+    gd.start_limit = async ? gd.spin_limit : std::min(gd.spin_limit, kGroupStartPolls);
     enqueue_enc_proj(m, s, &gd);
     const bool meets = gi->gw != 1;   // one workgroup per utterance: waits for nobody
     if (meets) {
@@ -921,8 +921,8 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     rc = finish_group(m, gd, gi->gw, s, &gave_up);   // flags and counters: h_flag, and h_stats 64 bytes on
     if (turn && (rc == WIND_OK || gave_up)) resident_done(gate, turn);
     // Something else holds the chip (another process, a long kernel of another stream).  The graph of per-step kernels needs no
-    // two workgroups at once: it decodes this call from the start.
-    if (!gave_up || use_loop) {
+    // two workgroups at once, and the resident loop kernel fewer, anywhere on the chip: they decode this call from the start.
+    if (!gave_up) {
       if (rc) return rc;
       if (m->h_flag[0] != 0) return fail(WIND_ERR_HIP, "decode loop did not terminate");
       rc = read_stats(m);

@@ -10,7 +10,8 @@ namespace wind {
 //     column) words and no near-tie is decided again;
 //   - weights are twice as wide: all eight waves share them (K split in eight), W_out as matrix-core operands, the
 //     recurrent and the projection rows one row per lane (a matrix-vector product per emitting slot: the hidden
-//     vector is read from LDS as a broadcast, nothing is summed over lanes).  One row tile per group: slots x W <= 16;
+//     vector is read from LDS as a broadcast, nothing is summed over lanes).  One row tile per group: slots x W <= 16.
+//     640 units do not quite fit (36 vector registers in scratch memory), nor 128 units with 128 labels on one CU (62);
 //   - small models (GW = 1: a whole model fits one CU's registers) run one workgroup per utterance, which
 //     tells itself through LDS, behind workgroup barriers.
 // Bound by the chain of steps like the bf16 groups; of 640 units the products of a 16-row tile take 1.2 us (fp32 rate).

@@ -14,7 +14,8 @@ namespace wind {
 // (slots); when one is done the slot takes the next of the group's list.  Utterances are dealt by falling
 // length, back and forth over the slots.
 //
-// All weights the loop needs sit in registers, as matrix-core operands: per workgroup CT parts of 32
+// The weights the loop needs sit in registers, as matrix-core operands (all but <5, 4, 32>, 640 units and three or four row tiles: 17
+// vector registers in scratch memory; all instances keep 100 to 140 scalars in lanes of vector registers): per workgroup CT parts of 32
 // columns of W_out (waves 0-3, K split in four), the recurrent rows of UPW LSTM units and PPW rows of W_pred
 // (waves 4-7, K split in four).  LDS holds the projected frames of the windows: two windows' worth per
 // slot, loaded straight from memory a whole iteration before they are read.

@@ -205,6 +205,11 @@ def test_groups_do_not_wait_long_for_their_places(torch_cuda):
     want = batch.decode(d_enc, d_len, 8, cfg.S)
     batch.set_option("loop_kernel", 1)
     assert same(batch.decode(d_enc, d_len, 8, cfg.S), want) and batch.loop_info()[0] == 256
+    pair_cfg, p_enc, p_len, make_pair = load("greedy_b1", 2, 30, 60)
+    pair = make_pair()
+    p_enc, p_len = torch.from_numpy(p_enc).cuda(), torch.from_numpy(p_len).cuda()
+    want_pair = pair.decode(p_enc, p_len, 16, pair_cfg.S)
+    assert pair.loop_info()[0] == 64
     beside = False
     for _ in range(6):   # streams may share a hardware queue, and the batch then comes behind the other kernel
         s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
@@ -218,15 +223,18 @@ def test_groups_do_not_wait_long_for_their_places(torch_cuda):
             start = time.perf_counter()
             assert same(batch.decode(d_enc, d_len, 8, cfg.S), want)
             took = time.perf_counter() - start
+            # two utterances: the loop kernel, which meets at grid barriers, finds places for its 40 workgroups
+            assert same(pair.decode(p_enc, p_len, 16, pair_cfg.S), want_pair)
         beside = not behind.query()
         torch.cuda.synchronize()
         assert m.stats().labels == 5000 * one.S == int(out[2][0])   # the other kernel was not disturbed
         if beside:
             break
-    assert beside and took < 0.1 and batch.loop_info()[0] == 0   # 14 ms; the limit of the later waits is 0.4 s
+    assert beside and pair.loop_info()[0] == 40
+    assert took < 0.1 and batch.loop_info()[0] == 0   # 14 ms; the limit of the later waits is 0.4 s
     assert same(batch.decode(d_enc, d_len, 8, cfg.S), want) and batch.loop_info()[0] == 256
-    m.close()
-    batch.close()
+    for x in (m, batch, pair):
+        x.close()
 
 
 def test_a_call_waits_on_the_gpu_for_an_asynchronous_one(torch_cuda):
