@@ -215,6 +215,10 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
+// Utterances up to which groups of four row tiles (windows of more than 8 rows) take a call: each round of 32 costs them the same, while the
+// per-step kernels' launches hardly grow.  640 units, W = 16, 200 to 1500 frames, against those: 192 utterances 11.8 ms (14.6),
+// 224 12.7 ms (14.1), 256 15.3 ms (13.7).  With fewer row tiles 256 still win or break even (W = 8 14.8 ms (15.0), W = 4 17.2 ms (19.4))
+constexpr int kGroupMaxB4 = 224;
 constexpr unsigned kGroupStartPolls = 1u << 16;   // about 12 ms, what a batch of 32 takes with the per-step kernels
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
@@ -752,6 +756,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     gd->SPT = std::min(kGroupMaxW / W, gd->NS);
     const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
     gd->RG = tiles > 2 ? 4 : tiles;
+    if (gd->RG == 4 && B > kGroupMaxB4) return nullptr;
     const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
     ct = parts > 2 ? 4 : parts;
     if (parts > ct) return nullptr;
