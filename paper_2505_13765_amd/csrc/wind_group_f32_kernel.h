@@ -11,7 +11,7 @@ namespace wind {
 //   - weights are twice as wide: all eight waves share them (K split in eight), W_out as matrix-core operands, the
 //     recurrent and the projection rows one row per lane (a matrix-vector product per emitting slot: the hidden
 //     vector is read from LDS as a broadcast, nothing is summed over lanes).  One row tile per group: slots x W <= 16.
-//     640 units do not quite fit (36 vector registers in scratch memory), nor 128 units with 128 labels on one CU (62);
+//     640 units do not quite fit (19 vector registers in scratch memory), nor 128 units with 128 labels on one CU (21);
 //   - small models (GW = 1: a whole model fits one CU's registers) run one workgroup per utterance, which
 //     tells itself through LDS, behind workgroup barriers.
 // Bound by the chain of steps like the bf16 groups; of 640 units the products of a 16-row tile take 1.2 us (fp32 rate).
@@ -34,38 +34,41 @@ struct GroupF32Cfg {
   static constexpr size_t oC = oRec + (size_t)SL * NR * 4;                 // float [SL][UPW]
   static constexpr size_t oW = oC + (size_t)SL * UPW * 4;                  // float [H] blank column of W_out
   static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1], [H], [H]
-  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], fail, near; float bp[PPW]
-  static constexpr size_t oT = (oI + (64 + kNumStats + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
+  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], fail, near; float bp[PPW], bo[32 CT + 1]
+  static constexpr size_t oT = (oI + (64 + kNumStats + 2 + PPW + 32 * CT + 1) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
   static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
 };
 
-// a += w[16 i + n] h[n] for n = 0 .. N - 1, h[n] from lane n of the lane's row of 16 (DPP row_newbcast).  One block of
+// fp32 sums of many products are kept short: what is added one after another loses half a unit in the last place of the running sum each
+// time, and the per-row kernels, whose 64 lanes take a tenth of a sum each and add in a tree, set the measure.  Blocks of 8
+// products, added in pairs, then over the wave's part of K, the eight waves' parts as a tree, the bias last.  Logits of
+// 640 units against 64 bits: one chain per wave 2.6e-7 rms, the per-row kernels 1.2e-7, the blocks 1.3e-7
+// (batch of 8, 600 frames: 1.44 -> 1.55 ms)
+template <class F>
+__device__ __forceinline__ float group_sum8(const F &f) {
+  return ((f(0) + f(1)) + (f(2) + f(3))) + ((f(4) + f(5)) + (f(6) + f(7)));
+}
+// Sum of w[n] h[FROM + n] for n = 0 .. 7, h[m] from lane m of the lane's row of 16 (DPP row_newbcast).  One block of
 // assembly: the compiler keeps the broadcasts as moves of their own, which doubles the instructions; the no-op in
 // front keeps the required distance from whatever wrote h.
-template <int N>
-__device__ __forceinline__ void group_row_products(float &a, float h, const float *w) {
-#define WIND_FMAC(n) "v_fmac_f32_dpp %0, %1, %" #n " row_newbcast:"
-  if constexpr (N == 16)
-    asm("s_nop 1\n\t" WIND_FMAC(2) "0 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(3) "1 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(4) "2 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(5) "3 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(6) "4 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(7) "5 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(8) "6 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(9) "7 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(10) "8 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(11) "9 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(12) "10 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(13) "11 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(14) "12 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(15) "13 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(16) "14 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(17) "15 row_mask:0xf bank_mask:0xf"
+template <int FROM>
+__device__ __forceinline__ float group_row_products(float h, const float *w) {
+  static_assert(FROM == 0 || FROM == 8, "half a row of lanes");
+  float a = 0.f;
+#define WIND_FMAC(n, lane) "v_fmac_f32_dpp %0, %1, %" #n " row_newbcast:" #lane " row_mask:0xf bank_mask:0xf"
+  if constexpr (FROM == 0)
+    asm("s_nop 1\n\t" WIND_FMAC(2, 0) "\n\t" WIND_FMAC(3, 1) "\n\t" WIND_FMAC(4, 2) "\n\t" WIND_FMAC(5, 3) "\n\t" WIND_FMAC(6, 4) "\n\t"
+        WIND_FMAC(7, 5) "\n\t" WIND_FMAC(8, 6) "\n\t" WIND_FMAC(9, 7)
         : "+v"(a)
-        : "v"(h), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9]), "v"(w[10]), "v"(w[11]),
-          "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+        : "v"(h), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]));
   else
-    asm("s_nop 1\n\t" WIND_FMAC(2) "0 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(3) "1 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(4) "2 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(5) "3 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(6) "4 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(7) "5 row_mask:0xf bank_mask:0xf\n\t"
-        WIND_FMAC(8) "6 row_mask:0xf bank_mask:0xf\n\t" WIND_FMAC(9) "7 row_mask:0xf bank_mask:0xf"
+    asm("s_nop 1\n\t" WIND_FMAC(2, 8) "\n\t" WIND_FMAC(3, 9) "\n\t" WIND_FMAC(4, 10) "\n\t" WIND_FMAC(5, 11) "\n\t" WIND_FMAC(6, 12) "\n\t"
+        WIND_FMAC(7, 13) "\n\t" WIND_FMAC(8, 14) "\n\t" WIND_FMAC(9, 15)
         : "+v"(a)
         : "v"(h), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]));
 #undef WIND_FMAC
+  return a;
 }
 
 template <int NK, int CT, int GW>
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   float *recs = reinterpret_cast<float *>(smem + Cfg::oRec), *cst = reinterpret_cast<float *>(smem + Cfg::oC);
   float *wbl = reinterpret_cast<float *>(smem + Cfg::oW);
   int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *counts = stat + 64, *fail = counts + kNumStats, *near_w = fail + 1;
-  float *bpl = reinterpret_cast<float *>(near_w + 1);
+  float *bpl = reinterpret_cast<float *>(near_w + 1), *bol = bpl + PPW;   // this workgroup's rows of b_pred, columns of b_out and blank's
 
   int lane = threadIdx.x & 63, tid = threadIdx.x, l15 = lane & 15, l4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -123,6 +126,10 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   for (int i = tid; i < NS * Cfg::UPW; i += 512) cst[i] = m.start_c[unit0 + i % Cfg::UPW];
   for (int i = tid; i < kNumStats; i += 512) counts[i] = 0;
   for (int i = tid; i < PPW; i += 512) bpl[i] = m.b_pred[prow0 + i];
+  for (int i = tid; i <= 32 * CT; i += 512) {
+    const int part = (i >> 5) * GW + g, col = i < 32 * CT ? part * 32 + (i & 31) : V;
+    bol[i] = i == 32 * CT || (part < nparts && col < V) ? m.b_out[col] : kKeyNone;   // what is added to kKeyNone vanishes in it
+  }
   load_frames();
   if (tid == 0) { *fail = 0; *near_w = 1; }
   // ---- where the workgroups sit: XCD numbers, exchanged with device-wide stores
@@ -161,18 +168,9 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     else return group_poll(abort_word, gd.spin_limit, ask);
   };
 
-  const float b_blank = m.b_out[V];
   const unsigned touch_lds = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char *)(smem + Cfg::oT);
   const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
   auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
-  float bias[Cfg::NI][2];
-#pragma unroll
-  for (int k = 0; k < Cfg::NI; ++k)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int item = wave + 8 * k, part = (item >> 2) * GW + g, col = part * 32 + 16 * t + l15;
-      bias[k][t] = item < 4 * CT && part < nparts && col < V ? m.b_out[col] : kKeyNone;   // what is added to kKeyNone vanishes in it
-    }
   int pend = 0, pend_slot[kGroupSlots] = {0, 0, 0, 0};
 
   for (int it = 0;; ++it) {
@@ -211,13 +209,21 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
           const float2 e2 = *reinterpret_cast<const float2 *>(er + i), p2 = *reinterpret_cast<const float2 *>(pr + i), b2 = *reinterpret_cast<const float2 *>(br + i);
           ev[0] = e2.x; ev[1] = e2.y; pv[0] = p2.x; pv[1] = p2.y; bv[0] = b2.x; bv[1] = b2.y;
         }
+        constexpr int NB = CT == 1 ? 2 : 1, STEPS = VEC / NB;   // blocks of 8 products (VEC 2: 4); 16 where the registers hold four parts of W_out
+        f32x4 blk[NB][2 * CT];                                  // a matrix-core product adds four of a row's
+        float d = 0.f;
 #pragma unroll
         for (int q = 0; q < VEC; ++q) {
           const float z = fmaxf(ev[q] + pv[q], 0.f);
-          dot = fmaf(z, bv[q], dot);
+          d = fmaf(z, bv[q], d);
 #pragma unroll
-          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(z, wo[t][i + q], acc[t], 0, 0, 0);
+          for (int t = 0; t < 2 * CT; ++t)
+            blk[q / STEPS][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(z, wo[t][i + q], q % STEPS ? blk[q / STEPS][t] : f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         }
+        dot += d;
+#pragma unroll
+        for (int t = 0; t < 2 * CT; ++t) acc[t] += NB == 2 ? blk[0][t] + blk[NB - 1][t] : blk[0][t];
+        __builtin_amdgcn_sched_barrier(0);   // a block's LDS operands at a time: registers
       }
       dot += __shfl_xor(dot, 16, kWave);
       dot += __shfl_xor(dot, 32, kWave);
@@ -237,9 +243,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       float v[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        v[t] = bias[k][t];
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v[t] += fred[((w * 2 * CT + 2 * ct + t) * 4 + l4) * 80 + 16 * q4 + l15];
+        v[t] = group_sum8([&](int w) { return fred[((w * 2 * CT + 2 * ct + t) * 4 + l4) * 80 + 16 * q4 + l15]; }) + bol[ct * 32 + 16 * t + l15];
       }
       // a NaN (from infinite frames) is no label's: the maxima pass over it, and a part of nothing else has column kGroupNoLabel
       const float b = fmaxf(v[0], v[1]), bm = row16_max_f32(b);
@@ -249,17 +253,13 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       if (part < nparts && l15 == 0 && row < R) put(kp + row * kstride + part, __float_as_uint(bm), (unsigned)(col & 0xFFFF) | (stamp16 << 16));
     }
     if (wave == 4 && g == 0 && lane < R) {   // R <= 16
-      float d2 = b_blank;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) d2 += fbn[w * 16 + lane];
+      const float d2 = group_sum8([&](int w) { return fbn[w * 16 + lane]; }) + bol[32 * CT];
       put(kp + lane * kstride + nparts, __float_as_uint(d2), stamp16 << 16);
     }
     if (wave >= 4)   // the recurrent sums of the last step
       for (int i = tid - 256; i < pend * NR; i += 256) {
         const int e = i / NR, row = i - e * NR;
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v += partl[(w * SL + e) * 64 * NSET + PPW + row];
+        const float v = group_sum8([&](int w) { return partl[(w * SL + e) * 64 * NSET + PPW + row]; });
         const int s = e == 0 ? pend_slot[0] : e == 1 ? pend_slot[1] : e == 2 ? pend_slot[2] : pend_slot[3];
         recs[s * NR + row] = v;
       }
@@ -375,12 +375,12 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         for (int i = 0; i < (KW + 15) / 16; ++i) hv[i] = hbuf[e * H + wave * KW + min(16 * i + l15, KW - 1)];
       };
       auto row_sums = [&](int t, int e) {
-        float a0 = 0.f, a1 = 0.f;
-        constexpr int BLK = KW % 16 == 0 ? 16 : 8;
         static_assert(KW == 8 || KW % 16 == 0, "whole blocks");
+        float a = group_row_products<0>(hv[0], wv[t]);
+        if constexpr (KW > 8) a += group_row_products<8>(hv[0], wv[t] + 8);
 #pragma unroll
-        for (int i = 0; i < KW; i += BLK) group_row_products<BLK>((i & 16) ? a1 : a0, hv[i / 16], wv[t] + i);
-        partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = a0 + a1;
+        for (int i = 16; i < KW; i += 16) a += group_row_products<0>(hv[i / 16], wv[t] + i) + group_row_products<8>(hv[i / 16], wv[t] + i + 8);
+        partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = a;
       };
       if constexpr (SOLO) group_barrier();
       fetch(hx, hbuf, false);
@@ -392,9 +392,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       group_barrier();   // B3: partial sums of the projection rows
       for (int i = tid; i < n_em * PPW; i += 512) {
         const int e = i / PPW, row = i - e * PPW;
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v += partl[(w * SL + e) * 64 * NSET + row];
+        const float v = group_sum8([&](int w) { return partl[(w * SL + e) * 64 * NSET + row]; });
         const int s = e == 0 ? es[0] : e == 1 ? es[1] : e == 2 ? es[2] : es[3];
         put(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp);
       }
@@ -461,9 +459,11 @@ __global__ __launch_bounds__(256) void enc_proj_f32_tile_kernel(ModelDev m, Call
       }
     }
   };
-  f32x16 acc;
+  // sums as short as above: blocks of 8 inputs (part), in pairs over a stage of 32, over four stages (run), over those.  D = 1024, rms
+  // against 64 bits: one chain 5.7e-7, the per-row kernel 1.0e-7, the blocks 1.0e-7 (8 x 600 frames: 63 -> 85 us)
+  f32x16 acc, run, zero;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = run[r] = zero[r] = 0.f;
   fetch(0);
   for (int k0 = 0; k0 < D; k0 += BK) {
     __syncthreads();
@@ -476,15 +476,22 @@ __global__ __launch_bounds__(256) void enc_proj_f32_tile_kernel(ModelDev m, Call
     if (k0 + BK < D) fetch(k0 + BK);
     // lane (row or column lane & 31, half lane >> 5) takes inputs 16 half + 0 .. 15 of the stage, two per product step
     const float *ar = &as[(wm * 32 + (lane & 31)) * ST + (lane >> 5) * 16], *br = &bs[(wn * 32 + (lane & 31)) * ST + (lane >> 5) * 16];
+    f32x16 part[4];
 #pragma unroll
-    for (int i = 0; i < 16; i += 4) {
-      const float4 a4 = *reinterpret_cast<const float4 *>(ar + i), b4 = *reinterpret_cast<const float4 *>(br + i);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, acc, 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+      const float4 a4 = *reinterpret_cast<const float4 *>(ar + 4 * i), b4 = *reinterpret_cast<const float4 *>(br + 4 * i);
+      part[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, zero, 0, 0, 0);
+      part[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, part[i], 0, 0, 0);
+      part[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, part[i], 0, 0, 0);
+      part[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, part[i], 0, 0, 0);
+    }
+    run += (part[0] + part[1]) + (part[2] + part[3]);
+    if (((k0 / BK) & 3) == 3) {
+      acc += run;
+      run = zero;
     }
   }
+  acc += run;
   const int col = n0 + wn * 32 + (lane & 31);
   if (col >= m.Hj) return;
   const float bias = m.b_enc[col];

@@ -120,6 +120,73 @@ def test_the_near_tie_band_is_that_of_the_unrounded_row(H, V, B, W):
         m.close()
 
 
+def test_fp32_encoder_projection_sums_are_short():
+    """Error of the projection of fp32 models against 64 bits: no more than that of 64 interleaved sums added in a tree (a row over a wave's
+    lanes), emulated here; one running sum over 1024 inputs is off five times as much.  15 %: sampling of the two errors."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    for D in (64, 132, 1024):
+        cfg = wi.WindConfig("groups", 5, 1, 24, 24, D, 64, 1, 128, 640, 32, "f32", (4,), 3, 0.7)
+        w = wi.make_weights(cfg)
+        m = WindModel.from_config(cfg, w)
+        enc, lens = wi.make_batch(cfg)
+        got = np.asarray(m.debug_enc_proj(torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()))[0].astype(np.float64)
+        m.close()
+        x, we = enc[0].astype(np.float64), w["w_enc"].astype(np.float64)
+        exact = x @ we.T + w["b_enc"]
+        s = np.zeros((24, 640, 64), np.float32)
+        for k in range(0, D, 64):
+            n = min(64, D - k)
+            s[:, :, :n] = (x[:, None, k:k + n] * we[None, :, k:k + n] + s[:, :, :n]).astype(np.float32)
+        for h in (32, 16, 8, 4, 2, 1):
+            s = s[:, :, :h] + s[:, :, h:2 * h]
+        rms = [float(np.sqrt(((v - exact) ** 2).mean())) for v in (got, s[:, :, 0] + w["b_enc"])]
+        print(f"encoder projection, {D} inputs: rms error {rms[0]:.2e}, lanes and tree {rms[1]:.2e}")
+        assert rms[0] <= 1.15 * rms[1]
+
+
+@pytest.mark.parametrize("H", [64, 256, 640])
+def test_fp32_logit_sums_are_short(H):
+    """Error of the groups' logits against 64 bits, no more than the per-row kernels'.  A decode tells whether a label's logit beats the
+    blank's; the blank's is made, frame by frame, what halving needs, until the label's is known to the last bit."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    B, T = 4, 400
+    rng = np.random.default_rng(H)
+    cfg = wi.WindConfig("groups", 5, B, T, T, H, 64, 1, H, H, 1, "f32", (1,), 1, 0.7)
+    w = wi.make_weights(cfg)
+    for k in ("w_enc", "b_enc", "w_pred", "b_pred", "w_out", "b_out"):
+        w[k][:] = 0.0
+    w["w_enc"][:] = np.eye(H, dtype=np.float32)   # hidden row = frame
+    w["w_out"][0, 1:] = rng.standard_normal(H - 1) / np.sqrt(H)
+    w["w_out"][1, 0] = 1.0                        # blank's logit = the frame's first value
+    z = np.abs(rng.standard_normal((B, T, H))).astype(np.float32)
+    exact = z[:, :, 1:].astype(np.float64) @ w["w_out"][0, 1:].astype(np.float64)
+    w["b_out"][0] = np.ceil(1 - exact.min())
+    exact += w["b_out"][0]
+    m = WindModel.from_config(cfg, w)
+    lens = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    rms = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        lo, hi = np.zeros((B, T), np.int32), np.full((B, T), np.float32(64.0).view(np.int32), np.int32)   # bits: the label wins at lo
+        while (hi - lo > 1).any():
+            mid = lo + (hi - lo) // 2
+            z[:, :, 0] = mid.view(np.float32)
+            _, frames = m.decode(torch.from_numpy(z).cuda(), lens, 1, 1)
+            wins = np.zeros((B, T), bool)
+            for b in range(B):
+                wins[b, frames[b]] = True
+            lo, hi = np.where(wins, mid, lo), np.where(wins, hi, mid)
+        assert (m.loop_info()[0] > 0) == bool(loop)
+        rms.append(float(np.sqrt(((lo.view(np.float32) - exact) ** 2).mean())))
+    print(f"logits of {H} units: rms error {rms[0]:.2e}, per-row kernels {rms[1]:.2e}")
+    assert rms[0] <= 1.15 * rms[1]   # 1600 samples: 2.5 % each
+    m.close()
+
+
 def test_two_streams_and_threads_take_turns():
     """Resident kernels of several models, called from several threads on streams of their own, must not wait for each other's CUs."""
     import threading
