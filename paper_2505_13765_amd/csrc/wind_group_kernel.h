@@ -451,15 +451,16 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
 #pragma unroll
       for (int i = 0; i < KS; ++i) {
         if (i + 1 < KS) read_ops((i + 1) & 1, i + 1);
-        float x[8];
+        float x[8], d = 0.f;   // the blank logit's sum in blocks of 8 products, a step's: as short as the other kernels' (lanes and a tree)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = BREG ? breg[BREG ? i : 0][h] : bo[BREG ? 0 : i & 1][h];
           float *y = x + 4 * h;
           y[0] = fmaxf(e4.x + p4.x, 0.f); y[1] = fmaxf(e4.y + p4.y, 0.f); y[2] = fmaxf(e4.z + p4.z, 0.f); y[3] = fmaxf(e4.w + p4.w, 0.f);
-          dot = fmaf(y[0], b4.x, dot); dot = fmaf(y[1], b4.y, dot); dot = fmaf(y[2], b4.z, dot); dot = fmaf(y[3], b4.w, dot);
+          d = fmaf(y[0], b4.x, d); d = fmaf(y[1], b4.y, d); d = fmaf(y[2], b4.z, d); d = fmaf(y[3], b4.w, d);
           nrm = fmaf(y[0], y[0], nrm); nrm = fmaf(y[1], y[1], nrm); nrm = fmaf(y[2], y[2], nrm); nrm = fmaf(y[3], y[3], nrm);
         }
+        dot += d;
         const u32x4 zu = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
         zf[i] = __builtin_bit_cast(bf16x8, zu);
         if constexpr (CT < 4) {
@@ -511,9 +512,10 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     }
     if constexpr (ROLE == 1) {
       if (wave == 4 && cg == 0 && lane < SPT * W && rt * SPT * W + lane < R) {   // SPT * W <= 16
-        float d2 = b_blank, n2 = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) { d2 += fbn[(w * 2 + 0) * 16 + lane]; n2 += fbn[(w * 2 + 1) * 16 + lane]; }
+        auto sum4 = [&](int which) {
+          return (fbn[(0 + which) * 16 + lane] + fbn[(2 + which) * 16 + lane]) + (fbn[(4 + which) * 16 + lane] + fbn[(6 + which) * 16 + lane]);
+        };
+        const float d2 = sum4(0) + b_blank, n2 = sum4(1);
         group_st(kp + (size_t)(rt * SPT * W + lane) * kstride + nparts, __float_as_uint(d2), __float_as_uint(key_with_tag(sqrtf(n2), tag)), near);
       }
       for (int i = tid1; i < pend * NR; i += 256) {

@@ -187,6 +187,52 @@ def test_fp32_logit_sums_are_short(H):
     m.close()
 
 
+@pytest.mark.parametrize("H", [128, 640])
+def test_blank_logit_sums_are_short(H):
+    """The blank logit of bf16 models is an fp32 sum that near-ties are decided against: its error against 64 bits is no more than
+    in the per-step kernels.  Found as above, by halving the logit of a label, here the sum of three bf16 inputs."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    B, T = 4, 400
+    rng = np.random.default_rng(H)
+    cfg = wi.WindConfig("groups", 5, B, T, T, H, 64, 1, H, H, 1, "bf16", (1,), 1, 0.7)
+    w = wi.make_weights(cfg)
+    for k in ("w_enc", "b_enc", "w_pred", "b_pred", "w_out", "b_out"):
+        w[k][:] = 0.0
+    w["w_enc"][:] = np.eye(H, dtype=np.float32)
+    w["w_enc"][0, :3] = 1.0
+    w["w_enc"][1, 1] = w["w_enc"][2, 2] = 0.0     # hidden unit 0 = inputs 0 + 1 + 2, units 1 and 2 unused
+    w["w_out"][0, 0] = 1.0                        # the label's logit = hidden unit 0
+    w["w_out"][1, 3:] = wi.round_to_bf16((rng.standard_normal(H - 3) / np.sqrt(H)).astype(np.float32))
+    z = wi.round_to_bf16(np.abs(rng.standard_normal((B, T, H))).astype(np.float32))
+    exact = z[:, :, 3:].astype(np.float64) @ w["w_out"][1, 3:].astype(np.float64)
+    w["b_out"][1] = np.ceil(1 - exact.min())
+    exact += w["b_out"][1]
+    m = WindModel.from_config(cfg, w)
+    lens = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    rms = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        lo, hi = np.zeros((B, T), np.int32), np.full((B, T), np.float32(64.0).view(np.int32), np.int32)   # bits: the blank wins at lo
+        while (hi - lo > 1).any():
+            mid = lo + (hi - lo) // 2
+            rest = mid.view(np.float32)
+            for i in range(3):   # cut, not rounded: 8 + 8 + 8 bits of the same sign
+                z[:, :, i] = (rest.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+                rest = rest - z[:, :, i]
+            _, frames = m.decode(torch.from_numpy(z).cuda(), lens, 1, 1)
+            label = np.zeros((B, T), bool)
+            for b in range(B):
+                label[b, frames[b]] = True
+            lo, hi = np.where(label, lo, mid), np.where(label, mid, hi)
+        assert (m.loop_info()[0] > 0) == bool(loop)
+        rms.append(float(np.sqrt(((hi.view(np.float32) - exact) ** 2).mean())))
+    print(f"blank logit of {H} units: rms error {rms[0]:.2e}, per-step kernels {rms[1]:.2e}")
+    assert rms[0] <= 1.15 * rms[1]   # 1600 samples: 2.5 % each
+    m.close()
+
+
 def test_two_streams_and_threads_take_turns():
     """Resident kernels of several models, called from several threads on streams of their own, must not wait for each other's CUs."""
     import threading
