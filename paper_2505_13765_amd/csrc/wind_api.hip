@@ -5,7 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <algorithm>
-
+#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdio>
@@ -19,6 +19,7 @@
 
 #include "wind_kernels.h"
 #include "wind_beam.h"
+#include "wind_beam_resident.h"
 
 using namespace wind;
 
@@ -111,6 +112,16 @@ struct BeamPool {
   void *h_res = nullptr, *d_res = nullptr;      // results of a pass: pinned host memory and its device address
 };
 
+// Beam search on resident workgroups (wind_beam_resident.h): what they exchange in, and the words they share with the host.
+struct BeamResident {
+  BeamGroupMem *mem = nullptr;                  // [kGroups]
+  struct Host {
+    unsigned long long cmd[kBeamCmdWords], res[kBeamResultWords];
+    unsigned exit;
+  } *host = nullptr, *dev = nullptr;            // pinned, and its device address
+  unsigned session = 0, seq = 0;                // numbers of the last launch and of the last command
+};
+
 struct wind_model {
   ModelDev dev{};
   int dtype = WIND_BF16;
@@ -158,6 +169,7 @@ struct wind_model {
   int *dbg_len = nullptr, *dbg_out = nullptr;   // lengths and outputs of the debug entry points (inside the workspace)
   void *beam_ws = nullptr;   // workspace of the beam scoring step
   BeamPool beam_pool{};
+  BeamResident beam_res{};
   int opt_beam_exact = 0;
   size_t beam_ws_bytes = 0;
   double kappa = 8.0;
@@ -775,7 +787,7 @@ struct ResidentGate {
   std::mutex mutex;
   hipEvent_t pending = nullptr;
   bool has_pending = false;
-  unsigned long long turn = 0;   // of the launch that `pending` stands for
+  std::atomic<unsigned long long> turn{0};   // of the launch that `pending` stands for
 };
 ResidentGate g_resident[kMaxDevices];
 
@@ -1272,6 +1284,8 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     static_assert(kFusedSteps == 5, "one resident loop instance per number of fused K steps: here and at the launch");
     for (const GroupInstance &i : kGroupInstances)
       if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
+    for (const auto &i : kBeamSearchInstances)
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.second);
     const void *loop_instances[] = {(const void *)wind_loop_kernel<0>, (const void *)wind_loop_kernel<1>, (const void *)wind_loop_kernel<2>,
                                     (const void *)wind_loop_kernel<3>, (const void *)wind_loop_kernel<4>, (const void *)wind_loop_kernel<5>};
     for (const void *k : loop_instances)
@@ -1324,6 +1338,8 @@ int wind_free(wind_model *m) {
   if (m->ws) (void)hipFree(m->ws);
   if (m->beam_ws) (void)hipFree(m->beam_ws);
   beam_pool_free(m);
+  if (m->beam_res.mem) (void)hipFree(m->beam_res.mem);
+  if (m->beam_res.host) (void)hipHostFree(m->beam_res.host);
   if (m->h_flag) (void)hipHostFree(m->h_flag);
   for (hipEvent_t e : m->ev_pool) (void)hipEventDestroy(e);
   for (hipEvent_t e : m->ev_call) if (e) (void)hipEventDestroy(e);

@@ -354,31 +354,36 @@ __device__ __forceinline__ unsigned beam_order_bits(float s) {
 __device__ __forceinline__ float beam_score_of(unsigned hi) {
   return __uint_as_float((hi & 0x80000000u) ? (hi & 0x7FFFFFFFu) : ~hi);
 }
-// Largest (hi, lo) pair of the wave, in every lane.  The pair is compared as one 64-bit integer.  DPP
-// row permutations inside the rows of 16, then the four row winners by v_readlane: no trip through
-// the LDS crossbar.
+// Largest (hi, lo) pair of each group of WIDTH lanes (64: the wave, 16: a row of lanes, 4: a quad), in every lane of the group.
+// The largest hi by DPP permutations (one instruction a step, no trip through the LDS crossbar), then the lo of the lane that has
+// it; only where several do (equal scores, or nothing left) are their lo words compared as well.  As one 64-bit comparison per
+// step a round took three times the instructions.
+template <int WIDTH>
+__device__ __forceinline__ unsigned lanes_max_u32(unsigned v) {
+  if (WIDTH > 4) {
+    v = max(v, (unsigned)dpp_i32<kDppRowMirror>((int)v));
+    v = max(v, (unsigned)dpp_i32<kDppRowHalfMirror>((int)v));
+  }
+  v = max(v, (unsigned)dpp_i32<kDppQuadXor2>((int)v));
+  v = max(v, (unsigned)dpp_i32<kDppQuadXor1>((int)v));
+  if (WIDTH == 64)
+    v = max(max((unsigned)__builtin_amdgcn_readlane((int)v, 0), (unsigned)__builtin_amdgcn_readlane((int)v, 16)),
+            max((unsigned)__builtin_amdgcn_readlane((int)v, 32), (unsigned)__builtin_amdgcn_readlane((int)v, 48)));
+  return v;
+}
+template <int WIDTH = 64>
 __device__ __forceinline__ void wave_max_pair(unsigned &hi, unsigned &lo) {
-  unsigned long long v = ((unsigned long long)hi << 32) | lo;
-#define WIND_PAIR_STEP(CTRL)                                                                                   \
-  {                                                                                                             \
-    const unsigned oh = (unsigned)dpp_i32<CTRL>((int)(v >> 32)), ol = (unsigned)dpp_i32<CTRL>((int)(unsigned)v); \
-    const unsigned long long o = ((unsigned long long)oh << 32) | ol;                                           \
-    v = o > v ? o : v;                                                                                          \
+  const unsigned best = lanes_max_u32<WIDTH>(hi);
+  const bool mine = hi == best;
+  hi = best;
+  if (WIDTH == 64) {
+    const unsigned long long who = __ballot(mine);
+    if (__popcll(who) == 1) {
+      lo = (unsigned)__builtin_amdgcn_readlane((int)lo, __ffsll((long long)who) - 1);
+      return;
+    }
   }
-  WIND_PAIR_STEP(kDppRowMirror)
-  WIND_PAIR_STEP(kDppRowHalfMirror)
-  WIND_PAIR_STEP(kDppQuadXor2)
-  WIND_PAIR_STEP(kDppQuadXor1)
-#undef WIND_PAIR_STEP
-#pragma unroll
-  for (int row = 0; row < 64; row += 16) {
-    const unsigned oh = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), row);
-    const unsigned ol = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, row);
-    const unsigned long long o = ((unsigned long long)oh << 32) | ol;
-    v = o > v ? o : v;
-  }
-  hi = (unsigned)(v >> 32);
-  lo = (unsigned)v;
+  lo = lanes_max_u32<WIDTH>(mine ? lo : 0u);
 }
 
 // One workgroup per hypothesis.  Pass 1: log-sum-exp of every row, blank log-probabilities and their

@@ -183,6 +183,127 @@ void beam_enqueue_decoder_step(wind_model *m, int rows, const int *parent, const
   else beam_pred_kernel<float, R><<<pb, 256, 0, s>>>(d, bp.h, bp.p, rows, ch);
 }
 
+// ---- the search on resident workgroups
+template <int KS>
+constexpr std::pair<void (*)(ModelDev, BeamResDev), size_t> beam_search_instance() { return {beam_search_kernel<KS>, BeamResCfg<KS>::smem}; }
+const std::pair<void (*)(ModelDev, BeamResDev), size_t> kBeamSearchInstances[] = {beam_search_instance<1>(), beam_search_instance<2>(), beam_search_instance<3>(),
+                                                                                  beam_search_instance<4>(), beam_search_instance<5>()};
+// Models that resident workgroups hold: bf16, one LSTM layer as wide as the joiner and of up to 640 units, up to 1024 labels, as the
+// resident groups of the decoder; and the options that ask for those
+bool beam_resident_model(const wind_model *m) {
+  const ModelDev &d = m->dev;
+  return m->dtype == WIND_BF16 && d.start_p && d.Hj <= 640 && m->cu_count >= kGroups * 32 && m->device >= 0 && m->device < kMaxDevices && m->opt_loop_kernel &&
+         m->opt_loop_fused && m->opt_loop_one_xcd && !m->opt_profile && m->opt_graph && !m->opt_host_sync && !m->opt_debug_stamps;
+}
+int beam_resident_reserve(wind_model *m, hipStream_t s) {
+  BeamResident &br = m->beam_res;
+  if (!br.mem || br.seq > 0xF0000000u || br.session > 0x0F000000u) {   // numbers that no word in the buffers has
+    HIP_TRY(hipDeviceSynchronize());
+    if (!br.mem) HIP_TRY(hipMalloc((void **)&br.mem, sizeof(BeamGroupMem) * kGroups));
+    HIP_TRY(hipMemsetAsync(br.mem, 0, sizeof(BeamGroupMem) * kGroups, s));
+    br.seq = br.session = 0;
+  }
+  if (!br.host) {
+    HIP_TRY(hipHostMalloc((void **)&br.host, sizeof(BeamResident::Host), hipHostMallocCoherent));
+    std::memset(br.host, 0, sizeof(BeamResident::Host));
+    HIP_TRY(hipHostGetDevicePointer((void **)&br.dev, br.host, 0));
+  }
+  return WIND_OK;
+}
+
+constexpr unsigned kBeamSessionCommands = 256;    // commands of one launch: whatever else waits for the stream gets its turn
+constexpr double kBeamIdleMs = 1.0;               // without a command for this long the workgroups leave (a callback may take any time)
+
+// The resident workgroups as one search uses them.  They stay from open() to close(), or until they have been idle, have
+// had their number of commands, or another call waits for its turn; the next command launches them again.
+struct BeamSession {
+  wind_model *m;
+  hipStream_t s;
+  bool usable = false, is_open = false;   // usable: shape and options allow it, and nothing has gone wrong so far
+  unsigned long long turn = 0;
+  unsigned commands = 0;
+
+  BeamSession(wind_model *m_, hipStream_t s_) : m(m_), s(s_) {}
+  ~BeamSession() { close(); }
+  BeamSession(const BeamSession &) = delete;
+  BeamSession &operator=(const BeamSession &) = delete;
+
+  int open() {
+    BeamResident &br = m->beam_res;
+    BeamPool &bp = m->beam_pool;
+    ResidentGate &gate = g_resident[m->device];
+    BeamResDev r{};
+    r.host_cmd = br.dev->cmd; r.host_res = br.dev->res; r.host_exit = &br.dev->exit;
+    r.mem = br.mem;
+    r.h = bp.h; r.c = bp.c; r.p = bp.p; r.e_all = bp.e_all;
+    r.session = ++br.session;
+    r.first = br.seq;
+    r.spin_limit = (unsigned)m->opt_loop_spin_limit;
+    r.start_limit = std::min(r.spin_limit, kGroupStartPolls);
+    r.idle_ticks = (unsigned long long)(kBeamIdleMs * m->clock_khz);
+    std::lock_guard<std::mutex> lock(gate.mutex);
+    int rc = resident_enter(gate, s);
+    if (rc) return rc;
+    const auto &k = kBeamSearchInstances[m->dev.Hj / 128 - 1];
+    k.first<<<kGroups * kBeamResWgs, 512, k.second, s>>>(m->dev, r);
+    rc = check_launch("beam search on resident workgroups");
+    if (rc) return rc;
+    is_open = true;   // also if the event fails: the kernel is there
+    commands = 0;
+    return resident_leave(gate, s, &turn);
+  }
+  void post(const unsigned (&words)[kBeamCmdWords]) {
+    BeamResident &br = m->beam_res;
+    for (int i = 0; i < kBeamCmdWords; ++i)
+      __atomic_store_n(&br.host->cmd[i], (unsigned long long)words[i] | ((unsigned long long)br.seq << 32), __ATOMIC_RELAXED);
+  }
+  // Sends everybody away; they leave within microseconds, and whoever waits for this stream or for its turn goes on behind them
+  void close() {
+    if (!is_open) return;
+    const unsigned quit[kBeamCmdWords] = {kBeamCmdQuit};
+    ++m->beam_res.seq;
+    post(quit);
+    is_open = false;
+  }
+  // One command: true in `done` once `arrived` says that all its results are in pinned memory.  Not done: the workgroups could not
+  // meet or gave up, nothing of them runs any more, and the caller takes the launches from here on.
+  template <class Arrived>
+  int run(const unsigned (&words)[kBeamCmdWords], int nres, const Arrived &arrived, bool *done) {
+    BeamResident &br = m->beam_res;
+    *done = false;
+    if (is_open && (commands >= kBeamSessionCommands || g_resident[m->device].turn.load(std::memory_order_relaxed) != turn)) close();
+    for (;;) {
+      ++br.seq;   // a number of its own for every try: under the last one idle workgroups have been told to leave
+      for (int i = 0; i < nres; ++i) __atomic_store_n(&br.host->res[i], 0ull, __ATOMIC_RELAXED);
+      post(words);
+      if (!is_open) {
+        const int rc = open();
+        if (rc) return rc;
+      }
+      ++commands;
+      bool left = false;
+      for (unsigned spins = 1; !left; ++spins) {
+        if (arrived()) { *done = true; return WIND_OK; }
+        left = __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == br.session;
+        if (!left && (spins & 0x3FFFu) == 0) {   // a kernel that failed never says that it has left
+          const hipError_t e = hipStreamQuery(s);
+          if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("beam search: ") + hipGetErrorString(e));
+          left = e == hipSuccess;
+        }
+        __builtin_ia32_pause();
+      }
+      is_open = false;
+      HIP_TRY(hipStreamSynchronize(s));
+      if (arrived()) { *done = true; return WIND_OK; }
+      if (__atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) != (br.session << 2 | kBeamExitIdle)) {
+        usable = false;
+        return WIND_OK;
+      }
+      // idle when the command came: the next launch takes it
+    }
+  }
+};
+
 struct BeamNode {
   int parent, token, depth, slot;
 };
@@ -249,8 +370,19 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
   }
   rc = check_launch("beam search set-up");
   if (rc) return rc;
-  HIP_TRY(hipStreamSynchronize(s));
   st.decoder_steps = 1;
+  BeamSession session(m, s);
+  if (K <= kBeamResHyps && window <= kBeamResFrames && beam_resident_model(m)) {
+    rc = beam_resident_reserve(m, s);
+    if (rc) return rc;
+    session.usable = true;
+  }
+  BeamResident &br = m->beam_res;
+  auto put = [](unsigned (&words)[kBeamCmdWords], int kind, int fresh, int Bh, int n, int t, int K, int split) {
+    words[kBeamAtHead] = (unsigned)(kind | fresh << 8 | Bh << 16 | n << 24);
+    words[kBeamAtFrame] = (unsigned)t;
+    words[kBeamAtK] = (unsigned)(K | split << 8);
+  };
 
   auto tokens_of = [&](int node) {
     std::vector<int> t((size_t)nodes[node].depth);
@@ -324,7 +456,32 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
       }
       if (!pairs.empty()) {
         std::vector<float> lp(row_node.size());
-        for (size_t r0 = 0; r0 < row_node.size(); r0 += kBeamCompRows) {
+        size_t r_done = 0;
+        while (session.usable && r_done < row_node.size()) {
+          const int rows = (int)std::min<size_t>(kBeamPrefixRows, row_node.size() - r_done);
+          unsigned words[kBeamCmdWords] = {0};
+          put(words, kBeamCmdComplete, 0, rows, 1, t, K, m->opt_beam_exact ? 1 : 0);
+          for (int r = 0; r < rows; ++r) {
+            const BeamNode &x = nodes[row_node[r_done + r]];
+            words[kBeamAtHyp + r] = (unsigned)nodes[x.parent].slot;
+            words[kBeamAtRowTok + r] = (unsigned)x.token;
+          }
+          bool done = false;
+          rc = session.run(words, rows, [&]() {
+            for (int r = 0; r < rows; ++r)
+              if (__atomic_load_n(&br.host->res[r], __ATOMIC_RELAXED) >> 32 != (br.seq | 0x80000000u)) return false;
+            return true;
+          }, &done);
+          if (rc) return rc;
+          if (!done) break;
+          for (int r = 0; r < rows; ++r) {
+            const unsigned bits = (unsigned)br.host->res[r];
+            std::memcpy(&lp[r_done + r], &bits, 4);
+          }
+          r_done += (size_t)rows;
+          st.completion_rows += rows;
+        }
+        for (size_t r0 = r_done; r0 < row_node.size(); r0 += kBeamCompRows) {
           const int rows = (int)std::min<size_t>(kBeamCompRows, row_node.size() - r0);
           int *slot = bp.h_stage, *tok = slot + kBeamCompRows;
           for (int r = 0; r < rows; ++r) {
@@ -390,41 +547,62 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     }
     const int Bh = (int)hyps.size();
 
-    // prediction-network step for the survivors whose label sequence is new
-    {
-      int rows = 0, parent[kBeamMaxK], child[kBeamMaxK], tok[kBeamMaxK];
-      for (const BeamHyp &h : hyps) {
-        BeamNode &nd = nodes[h.node];
-        if (nd.slot >= 0) continue;
+    // the survivors whose label sequence is new take a prediction-network step; then the scoring step: the window's joiner rows, P' and
+    // the K best pairs of every hypothesis
+    int fresh = 0, parent[kBeamMaxK], child[kBeamMaxK], tok[kBeamMaxK], slots[kBeamMaxK], fresh_of[kBeamMaxK];
+    for (int b = 0; b < Bh; ++b) {
+      BeamNode &nd = nodes[hyps[b].node];
+      fresh_of[b] = 0;
+      if (nd.slot < 0) {
         nd.slot = next_slot++;
-        parent[rows] = nodes[nd.parent].slot; child[rows] = nd.slot; tok[rows] = nd.token;
-        ++rows;
+        parent[fresh] = nodes[nd.parent].slot; child[fresh] = nd.slot; tok[fresh] = nd.token;
+        fresh_of[b] = ++fresh;
       }
-      if (rows) {
-        if (next_slot > bp.cap) {
-          rc = beam_pool_reserve(m, next_slot, s);
-          if (rc) return rc;
-        }
-        beam_enqueue_decoder_step(m, rows, parent, child, tok, s);
-        st.decoder_steps += rows;
-      }
+      slots[b] = nd.slot;
     }
-
-    // scoring step: the window's joiner rows, P' and the K best pairs of every hypothesis
+    if (next_slot > bp.cap) {
+      session.close();   // the pool moves
+      rc = beam_pool_reserve(m, next_slot, s);
+      if (rc) return rc;
+    }
+    if (next_slot >= 1 << kBeamSlotBits) { session.close(); session.usable = false; }
+    st.decoder_steps += fresh;
     const int n = std::min(window, T - t);
-    {
-      int slots[kBeamMaxK];
-      for (int b = 0; b < Bh; ++b) slots[b] = nodes[hyps[b].node].slot;
-      beam_enqueue_logits(m, ws, bp.e_all + (size_t)t * d.Hj, n, bp.p, beam_inline(slots, Bh), Bh, s);
-    }
-    beam_enqueue_topk(m, ws, n, Bh, K, (int32_t *)bp.d_res + kBeamResLabels, (int32_t *)bp.d_res + kBeamResJumps,
-                      (float *)bp.d_res + kBeamResScores, s);
-    rc = check_launch("beam scoring");
-    if (rc) return rc;
-    HIP_TRY(hipStreamSynchronize(s));
-    st.hyps_scored += Bh;
     const float *scores = (const float *)bp.h_res + kBeamResScores;
     const int32_t *labels = (const int32_t *)bp.h_res + kBeamResLabels, *jumps = (const int32_t *)bp.h_res + kBeamResJumps;
+    bool scored = false;
+    if (session.usable) {
+      unsigned words[kBeamCmdWords] = {0};
+      put(words, kBeamCmdScore, fresh, Bh, n, t, K, m->opt_beam_exact ? 1 : 0);
+      for (int i = 0; i < fresh; ++i) {
+        words[kBeamAtParent + i] = (unsigned)parent[i]; words[kBeamAtChild + i] = (unsigned)child[i]; words[kBeamAtToken + i] = (unsigned)tok[i];
+      }
+      for (int b = 0; b < Bh; ++b) words[kBeamAtHyp + b] = (unsigned)(slots[b] | fresh_of[b] << kBeamSlotBits);
+      rc = session.run(words, Bh * K, [&]() {
+        const unsigned tag = (br.seq & 0x7FFFu) | 0x8000u;
+        for (int i = 0; i < Bh * K; ++i)
+          if (__atomic_load_n(&br.host->res[i], __ATOMIC_RELAXED) >> 48 != tag) return false;
+        return true;
+      }, &scored);
+      if (rc) return rc;
+      for (int i = 0; i < Bh * K && scored; ++i) {
+        const unsigned long long w = br.host->res[i];
+        const unsigned bits = (unsigned)w, code = (unsigned)(w >> 32) & 0x7FFFu;
+        std::memcpy((float *)bp.h_res + kBeamResScores + i, &bits, 4);
+        ((int32_t *)bp.h_res)[kBeamResLabels + i] = code == (unsigned)kBeamCodeNone ? -1 : (int)(code & 0x7FFu);
+        ((int32_t *)bp.h_res)[kBeamResJumps + i] = code == (unsigned)kBeamCodeNone ? -1 : (int)(code >> 11);
+      }
+    }
+    if (!scored) {
+      if (fresh) beam_enqueue_decoder_step(m, fresh, parent, child, tok, s);
+      beam_enqueue_logits(m, ws, bp.e_all + (size_t)t * d.Hj, n, bp.p, beam_inline(slots, Bh), Bh, s);
+      beam_enqueue_topk(m, ws, n, Bh, K, (int32_t *)bp.d_res + kBeamResLabels, (int32_t *)bp.d_res + kBeamResJumps,
+                        (float *)bp.d_res + kBeamResScores, s);
+      rc = check_launch("beam scoring");
+      if (rc) return rc;
+      HIP_TRY(hipStreamSynchronize(s));
+    }
+    st.hyps_scored += Bh;
 
     if (on_round) {
       cb_len.clear(); cb_tok.clear(); cb_fr.clear(); cb_sym.clear(); cb_score.clear();

@@ -1,0 +1,101 @@
+"""Beam search on resident workgroups (models of one LSTM layer as wide as the joiner, up to 640 units and 1024 labels, K <= 8,
+windows of at most 16 frames): the replay protocol of test_gpu_beam_search.py at the edges of the workgroups' tiles, and the
+ways a search leaves them: waits that give up, workgroups that have gone idle, another call that takes its turn."""
+import threading
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+import wind_inputs as wi
+from test_gpu_beam_search import replay, torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def small(H, V, T, K, S):
+    cfg = wi.WindConfig("beam_resident", 40 + H, 1, T, T, 64, 64, 1, H, H, V, "bf16", (8,), S, 0.7)
+    return cfg, wi.sharpened(wi.make_weights(cfg, blank_bias=2.0, pred_gain=4.0), 4.0)
+
+
+# one column past a tile of 16, all tiles and the one past them, a single tile; one to 16 frames; one to eight hypotheses; every width
+@pytest.mark.parametrize("H,V,T,N,K,S,exact", [(128, 16, 20, 16, 8, 4, 1), (128, 1024, 18, 7, 5, 3, 1), (256, 31, 24, 1, 3, 2, 1), (384, 1023, 18, 16, 4, 3, 1),
+                                               (512, 1008, 17, 9, 8, 3, 0), (640, 1024, 16, 16, 8, 3, 1), (640, 1024, 21, 5, 1, 3, 1), (640, 300, 18, 13, 6, 4, 0)])
+def test_replay_at_the_edges(torch_cuda, H, V, T, N, K, S, exact):  # noqa: F811
+    from paper_2505_13765_amd import WindModel
+
+    cfg, w = small(H, V, T, K, S)
+    o = oracle.Oracle.from_config(cfg, w)
+    m = WindModel.from_config(cfg, w)
+    m.set_option("beam_exact", exact)
+    enc, _ = wi.make_batch(cfg)
+    stats = replay(o, m, torch_cuda, np.ascontiguousarray(enc[0]), N, K, S, "keep", (2e-4 if exact else 4e-2) * 4, free_run=False)
+    print(f"H={H} V={V} N={N} K={K} exact={exact}: {stats}")
+    m.close()
+
+
+def test_the_ways_out(torch_cuda):  # noqa: F811
+    """Launches only; a wait that gives up at once (the whole search then runs on launches); workgroups that go idle between two
+    passes: the same choices every time, scores to rounding."""
+    from paper_2505_13765_amd import WindModel
+
+    cfg, w = small(256, 100, 40, 4, 3)
+    m = WindModel.from_config(cfg, w)
+    m.set_option("beam_exact", 1)
+    e = torch_cuda.from_numpy(wi.make_batch(cfg)[0][0]).cuda()
+    here = m.beam_decode(e, 8, 4, 3)
+    m.set_option("loop_kernel", 0)
+    launches = m.beam_decode(e, 8, 4, 3)
+    m.set_option("loop_kernel", 1)
+    limit = 1 << 21
+    m.set_option("loop_spin_limit", 0)
+    given_up = m.beam_decode(e, 8, 4, 3)
+    m.set_option("loop_spin_limit", limit)
+
+    class Slow(list):
+        def append(self, x):
+            time.sleep(0.004 if len(self) % 5 == 0 else 0.0)
+            super().append(x)
+
+    idle = m.beam_decode(e, 8, 4, 3, trace=Slow())
+    again = m.beam_decode(e, 8, 4, 3)
+    for other in (launches, given_up, idle, again):
+        assert other[0].tolist() == here[0].tolist() and other[1].tolist() == here[1].tolist()
+        assert abs(other[2] - here[2]) < 1e-3 * max(1.0, abs(here[2]))
+    assert again[2] == here[2] and idle[2] == here[2] and given_up[2] == launches[2]
+    m.close()
+
+
+def test_other_calls_take_their_turn(torch_cuda):  # noqa: F811
+    """A greedy decode in resident groups on another thread and stream goes in between the search's passes, and both get their results."""
+    from paper_2505_13765_amd import WindModel
+
+    cfg, w = small(640, 1024, 120, 4, 3)
+    searcher, decoder = WindModel.from_config(cfg, w), WindModel.from_config(cfg, w)
+    enc = torch_cuda.from_numpy(wi.make_batch(cfg)[0]).cuda()
+    lens = torch_cuda.tensor([120], dtype=torch_cuda.int32, device="cuda")
+    want_b = searcher.beam_decode(enc[0], 16, 4, 3)
+    want_g = decoder.decode(enc, lens, 8, 3)
+    stop, wrong, calls = threading.Event(), [], [0]
+
+    def greedy():
+        with torch_cuda.cuda.stream(torch_cuda.cuda.Stream()):
+            while not stop.is_set():
+                got = decoder.decode(enc, lens, 8, 3)
+                calls[0] += 1
+                if got[0][0].tolist() != want_g[0][0].tolist():
+                    wrong.append(calls[0])
+
+    th = threading.Thread(target=greedy)
+    th.start()
+    try:
+        for _ in range(4):
+            got = searcher.beam_decode(enc[0], 16, 4, 3)
+            assert got[0].tolist() == want_b[0].tolist() and got[2] == want_b[2]
+    finally:
+        stop.set()
+        th.join()
+    assert not wrong and calls[0] > 4
+    searcher.close()
+    decoder.close()
