@@ -120,6 +120,7 @@ struct BeamResident {
     unsigned exit;
   } *host = nullptr, *dev = nullptr;            // pinned, and its device address
   unsigned session = 0, seq = 0;                // numbers of the last launch and of the last command
+  unsigned written = 0;                         // hypotheses of all scoring steps so far
 };
 
 struct wind_model {
@@ -1284,8 +1285,9 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     static_assert(kFusedSteps == 5, "one resident loop instance per number of fused K steps: here and at the launch");
     for (const GroupInstance &i : kGroupInstances)
       if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
-    for (const auto &i : kBeamSearchInstances)
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.second);
+    for (const BeamInstance &i : kBeamInstances)
+      for (auto k : {i.search, i.scores})
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     const void *loop_instances[] = {(const void *)wind_loop_kernel<0>, (const void *)wind_loop_kernel<1>, (const void *)wind_loop_kernel<2>,
                                     (const void *)wind_loop_kernel<3>, (const void *)wind_loop_kernel<4>, (const void *)wind_loop_kernel<5>};
     for (const void *k : loop_instances)
@@ -1384,6 +1386,9 @@ int wind_beam_window_scores(wind_model *m, const float *enc_window, int n, const
   int rc = beam_scores_check(m, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
+  bool done = false;
+  rc = beam_scores_resident(m, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s, &done);
+  if (rc || done) return rc;
   BeamWs ws;
   rc = beam_workspace(m, (size_t)n, (size_t)Bh, (size_t)Bh * n, &ws, s);
   if (rc) return rc;

@@ -44,11 +44,12 @@ constexpr int kBeamSlotBits = 24;
 
 // Exchange words of one group of 32 workgroups
 struct BeamGroupMem {
-  unsigned word[96];                              // 0: abort (the session's number), 32 + g: XCD number of workgroup g and session, 64 + g: commands done
+  unsigned word[96];                              // 0: abort (the session's number), 1: hypotheses written, 32 + g: XCD number of workgroup g
+                                                  //   and session, 64 + g: commands done
   unsigned long long cmd[kBeamCmdWords];
-  unsigned long long hx[kBeamResHyps * 640];      // new hidden vectors (one-shot: nothing)
+  unsigned long long hx[kBeamResHyps * 640];      // new hidden vectors
   unsigned long long px[kBeamResHyps * 640];      // new projections
-  unsigned long long ex[kBeamResFrames * 640];    // one-shot: projected frames
+  unsigned long long ex[kBeamResFrames * 640];    // one scoring step: projected frames
   unsigned long long lg[kBeamResRows * kBeamLgStride];
   unsigned long long row[kBeamResRows * kBeamRowWords];
 };
@@ -62,12 +63,12 @@ struct BeamResDev {
   unsigned session, first;              // number of this launch, and of the first command it takes
   unsigned spin_limit, start_limit;
   unsigned long long idle_ticks;
-  // one-shot
+  // one scoring step (beam_scores_kernel)
   const float *enc, *dec;               // [n, D], [Bh, Hp]
-  int n, Bh, K, NG, split;              // NG groups, hypothesis b in group b % NG
+  int n, Bh, K, split;
   int *out_labels, *out_jumps;
   float *out_scores;
-  unsigned *left;                       // workgroups that still have a hypothesis to write; host_exit gets `session` with the last one
+  unsigned written;                     // hypotheses written by all such launches (BeamGroupMem::word[1] of group 0) once this one is through
 };
 
 template <int KS>
@@ -84,7 +85,7 @@ struct BeamResCfg {
   static constexpr size_t oRecp = oF, oPredp = oRecp + (size_t)4 * NR * AST * 4,    //   float [4][NR][AST]; float [4][16 PT][AST]
                           oHst = oPredp + (size_t)4 * 16 * PT * AST * 4;            //   float [8][EST] new hidden vectors
   static constexpr size_t szNet = (size_t)4 * NR * AST * 4 + (size_t)4 * 16 * PT * AST * 4 + (size_t)kBeamResHyps * EST * 4;
-  static constexpr size_t szEnc = (size_t)8 * 16 * PT * 20 * 4;                     //   one-shot: float [8][16 PT][20]
+  static constexpr size_t szEnc = (size_t)8 * 16 * PT * 20 * 4;                     //   one scoring step: float [8][16 PT][20]
   static constexpr size_t oI = oF + (szLogits > szNet + szEnc ? szLogits : szNet + szEnc);
   static constexpr size_t oEncp = oF + szNet;
   static constexpr size_t smem = oI + 4 * (kBeamCmdWords + 32 + 2 * 2 * 4 * kBeamResHyps + kBeamResFrames * kBeamRowWords);
@@ -666,6 +667,107 @@ struct BeamRes {
       __hip_atomic_store(r.host_exit, r.session << 2 | why, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
+
+  // Rows of words (H each) into LDS: a half takes every other row, a wave its quarter
+  __device__ __forceinline__ void fetch_rows(const unsigned long long *src, float *dst, int count, unsigned seq) {
+    for (int b0 = HALF; b0 < count; b0 += 8) {
+      unsigned long long u[4][QL];
+      wait([&]() {
+        bool now = true;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int q = 0; q < QL; ++q) u[e][q] = group_ld(src + min(b0 + 2 * e, count - 1) * H + w4 * QK + min(lane + 64 * q, QK - 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int q = 0; q < QL; ++q) now = now && (unsigned)(u[e][q] >> 32) == seq;
+        return now;
+      });
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (b0 + 2 * e < count) {
+#pragma unroll
+          for (int q = 0; q < QL; ++q)
+            if (lane + 64 * q < QK) dst[(b0 + 2 * e) * EST + w4 * QK + lane + 64 * q] = __uint_as_float((unsigned)u[e][q]);
+        }
+    }
+  }
+
+  // One scoring step: group grp takes hypotheses grp, grp + kGroups, ...  Its workgroups project the window's frames and those hypotheses
+  // (every group all the frames: 26 MFLOP, less than telling the other XCDs), each its units, and go on as in a pass of the search.
+  __device__ __forceinline__ void score(int grp) {
+    const unsigned seq = r.first;
+    const int n = r.n, Bg = (r.Bh - grp + kGroups - 1) / kGroups, D = m.D, u0 = g * UPW;
+    float *encp = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ecache) + (Cfg::oEncp - Cfg::oE));
+    load_w_pred();
+    // frames: K split over the eight waves in steps of 32, frames rounded to bf16 as everywhere in bf16 models
+    f32x4 acc[Cfg::PT];
+#pragma unroll
+    for (int t = 0; t < Cfg::PT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float *er = r.enc + (size_t)min(l15, n - 1) * D + l4 * 8;
+    const bf16_t *wr0 = reinterpret_cast<const bf16_t *>(m.w_enc) + l4 * 8;
+#pragma unroll 4
+    for (int k = wave * 32; k < D; k += 256) {
+      const float4 a = *reinterpret_cast<const float4 *>(er + k), b = *reinterpret_cast<const float4 *>(er + k + 4);
+      const u32x4 xu = u32x4{pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w)};
+#pragma unroll
+      for (int t = 0; t < Cfg::PT; ++t) {
+        const bf16x8 w = *reinterpret_cast<const bf16x8 *>(wr0 + (size_t)(u0 + min(16 * t + l15, UPW - 1)) * D + k);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xu), w, acc[t], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < Cfg::PT; ++t)
+      *reinterpret_cast<float4 *>(&encp[((wave * Cfg::PT + t) * 16 + l15) * 20 + 4 * l4]) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    if constexpr (HALF == 0) {
+      const float *hp = r.dec + (size_t)(grp + kGroups * min(l15, Bg - 1)) * H + w4 * QK + l4 * 8;
+      float4 v[KS][2];
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        v[i][0] = *reinterpret_cast<const float4 *>(hp + 32 * i);
+        v[i][1] = *reinterpret_cast<const float4 *>(hp + 32 * i + 4);
+      }
+      f32x4 pacc[Cfg::PT];
+      products<Cfg::PT>(wp, v, pacc);
+      put_partial<Cfg::PT, Cfg::PT>(predp, 0, pacc);
+    }
+    load_w_out();   // on its way while the projections are exchanged
+    meet();         // a barrier: the partial sums are in LDS
+    if (!flags[0] || flags[1]) return;
+    for (int i = tid; i < (n + Bg) * UPW; i += 512) {
+      const int e = i / UPW, row = i - e * UPW;
+      if (e < n) {
+        float v[8];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v[w] = encp[(w * 16 * Cfg::PT + row) * 20 + e];
+        beam_st(&x.ex[e * H + u0 + row], __float_as_uint(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])) + m.b_enc[u0 + row]), seq);
+      } else {
+        beam_st(&x.px[(e - n) * H + u0 + row], __float_as_uint(sum4(predp, 16 * Cfg::PT, row, e - n) + m.b_pred[u0 + row]), seq);
+      }
+    }
+    // No wait of this launch may outlast its results, the words are the next one's then: whoever has no part in them leaves
+    if (32 * g > m.V && g >= Bg * n) return;   // no column, no row
+    fetch_rows(x.ex, ecache, n, seq);
+    fetch_rows(x.px, pfull, Bg, seq);
+    group_barrier();
+    logits(Bg * n, n, r.split, seq);
+    soft_max_rows(Bg * n, r.K, false, seq);
+    if (HALF == 1 && w4 == 1 && g < Bg) {
+      const int b = grp + kGroups * g;
+      bool put = false;
+      merge(g, n, r.K, seq, [&](int k, bool any, int label, int jump, float score) {
+        const size_t o = (size_t)b * r.K + k;
+        __hip_atomic_store(r.out_labels + o, any ? label : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(r.out_jumps + o, any ? jump : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(r.out_scores + o, score, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        put = true;
+      });
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // they are in memory: the last hypothesis of the launch tells the host
+      if (put && lane == 0 && __hip_atomic_fetch_add(&r.mem[0].word[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == r.written)
+        __hip_atomic_store(r.host_exit, r.session << 2 | kBeamExitAsked, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
 };
 
 template <int KS>
@@ -675,6 +777,17 @@ __global__ __launch_bounds__(512) void beam_search_kernel(ModelDev m, BeamResDev
   const int g = (int)blockIdx.x / kGroups;
   if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[0], smem_raw, g).search();
   else BeamRes<KS, 1>(m, r, r.mem[0], smem_raw, g).search();
+}
+
+// One scoring step for up to 64 hypotheses and 16 frames, a group of workgroups per XCD, a single launch.  As five launches (two
+// projections, logits, rows, merge) and a wait for the stream 16 hypotheses x 16 frames of 640 units and 1024 labels took 54 us.
+template <int KS>
+__global__ __launch_bounds__(512) void beam_scores_kernel(ModelDev m, BeamResDev r) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;
+  if (grp >= r.Bh) return;
+  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp], smem_raw, g).score(grp);
+  else BeamRes<KS, 1>(m, r, r.mem[grp], smem_raw, g).score(grp);
 }
 
 }  // namespace wind

@@ -183,11 +183,15 @@ void beam_enqueue_decoder_step(wind_model *m, int rows, const int *parent, const
   else beam_pred_kernel<float, R><<<pb, 256, 0, s>>>(d, bp.h, bp.p, rows, ch);
 }
 
-// ---- the search on resident workgroups
+// ---- resident workgroups
+struct BeamInstance {
+  void (*search)(ModelDev, BeamResDev);
+  void (*scores)(ModelDev, BeamResDev);
+  size_t smem;
+};
 template <int KS>
-constexpr std::pair<void (*)(ModelDev, BeamResDev), size_t> beam_search_instance() { return {beam_search_kernel<KS>, BeamResCfg<KS>::smem}; }
-const std::pair<void (*)(ModelDev, BeamResDev), size_t> kBeamSearchInstances[] = {beam_search_instance<1>(), beam_search_instance<2>(), beam_search_instance<3>(),
-                                                                                  beam_search_instance<4>(), beam_search_instance<5>()};
+constexpr BeamInstance beam_instance() { return {beam_search_kernel<KS>, beam_scores_kernel<KS>, BeamResCfg<KS>::smem}; }
+const BeamInstance kBeamInstances[] = {beam_instance<1>(), beam_instance<2>(), beam_instance<3>(), beam_instance<4>(), beam_instance<5>()};   // by width / 128
 // Models that resident workgroups hold: bf16, one LSTM layer as wide as the joiner and of up to 640 units, up to 1024 labels, as the
 // resident groups of the decoder; and the options that ask for those
 bool beam_resident_model(const wind_model *m) {
@@ -201,7 +205,7 @@ int beam_resident_reserve(wind_model *m, hipStream_t s) {
     HIP_TRY(hipDeviceSynchronize());
     if (!br.mem) HIP_TRY(hipMalloc((void **)&br.mem, sizeof(BeamGroupMem) * kGroups));
     HIP_TRY(hipMemsetAsync(br.mem, 0, sizeof(BeamGroupMem) * kGroups, s));
-    br.seq = br.session = 0;
+    br.seq = br.session = br.written = 0;
   }
   if (!br.host) {
     HIP_TRY(hipHostMalloc((void **)&br.host, sizeof(BeamResident::Host), hipHostMallocCoherent));
@@ -244,8 +248,8 @@ struct BeamSession {
     std::lock_guard<std::mutex> lock(gate.mutex);
     int rc = resident_enter(gate, s);
     if (rc) return rc;
-    const auto &k = kBeamSearchInstances[m->dev.Hj / 128 - 1];
-    k.first<<<kGroups * kBeamResWgs, 512, k.second, s>>>(m->dev, r);
+    const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
+    k.search<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
     rc = check_launch("beam search on resident workgroups");
     if (rc) return rc;
     is_open = true;   // also if the event fails: the kernel is there
@@ -303,6 +307,62 @@ struct BeamSession {
     }
   }
 };
+
+// One scoring step as a single launch.  `done`: the results are in the caller's buffers; else (the workgroups could not meet) nothing of it
+// runs any more and the caller takes the launches.
+int beam_scores_resident(wind_model *m, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
+                         int32_t *out_jumps, float *out_scores, hipStream_t s, bool *done) {
+  *done = false;
+  // the loads are 16 bytes wide; a captured call has nobody to wait for it
+  if (Bh > kGroups * kBeamResHyps || n > kBeamResFrames || K > kBeamResHyps || !beam_resident_model(m) || ((uintptr_t)enc_window | (uintptr_t)dec_out) % 16 ||
+      stream_capturing(s))
+    return WIND_OK;
+  int rc = beam_resident_reserve(m, s);
+  if (rc) return rc;
+  BeamResident &br = m->beam_res;
+  BeamResDev r{};
+  r.host_exit = &br.dev->exit;
+  r.mem = br.mem;
+  r.session = ++br.session;
+  r.first = ++br.seq;
+  r.spin_limit = (unsigned)m->opt_loop_spin_limit;
+  r.start_limit = std::min(r.spin_limit, kGroupStartPolls);
+  r.enc = enc_window; r.dec = dec_out;
+  r.n = n; r.Bh = Bh; r.K = K; r.split = m->opt_beam_exact ? 1 : 0;
+  r.out_labels = out_labels; r.out_jumps = out_jumps; r.out_scores = out_scores;
+  r.written = br.written += (unsigned)Bh;
+  ResidentGate &gate = g_resident[m->device];
+  unsigned long long turn = 0;
+  {
+    std::lock_guard<std::mutex> lock(gate.mutex);
+    rc = resident_enter(gate, s);
+    if (rc) return rc;
+    const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
+    k.scores<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
+    rc = check_launch("beam scoring step");
+    if (rc) return rc;
+    rc = resident_leave(gate, s, &turn);
+    if (rc) return rc;
+  }
+  const auto arrived = [&]() { return __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == r.session; };
+  for (unsigned spins = 1; !(*done = arrived()); ++spins) {
+    if ((spins & 0x3FFu) == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("beam scoring step: ") + hipGetErrorString(e));
+      if (e == hipSuccess) {
+        *done = arrived();
+        break;
+      }
+    }
+    __builtin_ia32_pause();
+  }
+  resident_done(gate, turn);
+  if (!*done) {   // some of its hypotheses may have been written: the count starts again
+    HIP_TRY(hipMemsetAsync(&br.mem[0].word[1], 0, sizeof(unsigned), s));
+    br.written = 0;
+  }
+  return WIND_OK;
+}
 
 struct BeamNode {
   int parent, token, depth, slot;

@@ -99,3 +99,43 @@ def test_other_calls_take_their_turn(torch_cuda):  # noqa: F811
     assert not wrong and calls[0] > 4
     searcher.close()
     decoder.close()
+
+
+# hypotheses that leave groups empty, fill one each, and fill all; windows of one to 16 frames; columns at the tiles' edges
+@pytest.mark.parametrize("H,V,n,Bh,K,exact", [(128, 16, 16, 1, 8, 1), (128, 1024, 5, 9, 4, 1), (256, 31, 1, 8, 1, 0), (384, 992, 16, 64, 8, 1),
+                                              (512, 1023, 11, 17, 5, 0), (640, 1024, 16, 16, 8, 1), (640, 1024, 16, 61, 8, 0)])
+def test_one_scoring_step(torch_cuda, H, V, n, Bh, K, exact):  # noqa: F811
+    """Against the oracle, and the same choices and scores (to rounding) as the launches that take every other shape; buffers that are
+    aligned to four bytes only take those."""
+    from oracle import beam_scores as bs
+    from paper_2505_13765_amd import WindModel
+    from test_gpu_beam_scores import check_against_oracle, hypotheses
+
+    torch = torch_cuda
+    cfg, w = small(H, V, 16, K, 4)
+    o = oracle.Oracle.from_config(cfg, w)
+    m = WindModel.from_config(cfg, w)
+    m.set_option("beam_exact", exact)
+    enc = wi.make_batch(cfg)[0][0, :n]
+    dec = hypotheses(o, cfg, np.random.default_rng(H + V), Bh, 4).astype(np.float32)
+    _, _, _, full = bs.beam_window(o, enc, dec.astype(np.float64), K)
+    e, d = torch.from_numpy(np.ascontiguousarray(enc)).cuda(), torch.from_numpy(dec).cuda()
+    tol = (2e-4 if exact else 4e-2) * 4
+    got = m.beam_window_scores(e, d, K)
+    check_against_oracle(cfg, full, K, *got, tol)
+    odd = torch.empty(d.numel() + 1, device="cuda")[1:].view(d.shape).copy_(d)
+    unaligned = m.beam_window_scores(e, odd, K)
+    m.set_option("loop_spin_limit", 0)
+    given_up = m.beam_window_scores(e, d, K)
+    m.set_option("loop_spin_limit", 1 << 21)
+    again = m.beam_window_scores(e, d, K)
+    # Other orders of the fp32 sums; without `exact` a hidden unit may also round to the other bf16 value: 2^-8 of a weight of the
+    # output layer (4 / sqrt(H)) times a unit of about one, 6e-4 at 640 units, a few at most
+    for other in (unaligned, given_up):
+        assert np.allclose(other[2], got[2], atol=2e-4 if exact else 4e-3, rtol=1e-5)
+    for a, b, c in zip(got, again, unaligned):
+        assert np.array_equal(a, b)
+    assert (unaligned[0] != got[0]).mean() <= 0.02   # near-ties
+    for a, b in zip(unaligned, given_up):
+        assert np.array_equal(a, b)
+    m.close()
