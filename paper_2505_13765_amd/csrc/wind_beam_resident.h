@@ -198,13 +198,18 @@ struct BeamRes {
   }
   // The number to publish under, once a barrier lies behind the waits of this workgroup
   __device__ __forceinline__ unsigned number(unsigned seq) const { return flags[1] ? 0u : seq; }
+  __device__ __forceinline__ unsigned place() const {
+    unsigned xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    return (r.session << 4) | (xcc & 15u);
+  }
+  __device__ __forceinline__ void announce() const {
+    if (tid == 0) __hip_atomic_store(&x.word[32 + g], place(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   // Whether all workgroups of the group are on the chip and share an L2 (wave 0; the result for everybody in flags)
   __device__ __forceinline__ void meet() {
     if (wave == 0) {
-      unsigned xcc;
-      asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-      const unsigned mine = (r.session << 4) | (xcc & 15u);
-      if (lane == 0) __hip_atomic_store(&x.word[32 + g], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned mine = place();
       unsigned v = mine;
       const bool got = beam_poll(abort_word(), r.session, r.start_limit, [&]() {
         if (lane < kBeamResWgs) v = __hip_atomic_load(&x.word[32 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -591,6 +596,7 @@ struct BeamRes {
   }
 
   __device__ __forceinline__ void search() {
+    announce();
     load_w_out();
     load_w_pred();
     load_w_rec();
@@ -700,39 +706,57 @@ struct BeamRes {
     const unsigned seq = r.first;
     const int n = r.n, Bg = (r.Bh - grp + kGroups - 1) / kGroups, D = m.D, u0 = g * UPW;
     float *encp = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ecache) + (Cfg::oEncp - Cfg::oE));
-    load_w_pred();
-    // frames: K split over the eight waves in steps of 32, frames rounded to bf16 as everywhere in bf16 models
+    announce();
+    // Everything the launch reads is asked for before any of it is looked at (start to the projections 8.9 -> 8.2 us).  Frames: K split over the
+    // eight waves in steps of 32, four at a time; rounded to bf16 as everywhere in bf16 models
     f32x4 acc[Cfg::PT];
 #pragma unroll
     for (int t = 0; t < Cfg::PT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float *er = r.enc + (size_t)min(l15, n - 1) * D + l4 * 8;
     const bf16_t *wr0 = reinterpret_cast<const bf16_t *>(m.w_enc) + l4 * 8;
-#pragma unroll 4
-    for (int k = wave * 32; k < D; k += 256) {
-      const float4 a = *reinterpret_cast<const float4 *>(er + k), b = *reinterpret_cast<const float4 *>(er + k + 4);
-      const u32x4 xu = u32x4{pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w)};
+    float4 ea[4], eb[4];
+    bf16x8 we[4][Cfg::PT];
+    auto ask_frames = [&](int k0) {
 #pragma unroll
-      for (int t = 0; t < Cfg::PT; ++t) {
-        const bf16x8 w = *reinterpret_cast<const bf16x8 *>(wr0 + (size_t)(u0 + min(16 * t + l15, UPW - 1)) * D + k);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xu), w, acc[t], 0, 0, 0);
+      for (int q = 0; q < 4; ++q) {
+        const int k = min(k0 + 256 * q, D - 32);
+        ea[q] = *reinterpret_cast<const float4 *>(er + k);
+        eb[q] = *reinterpret_cast<const float4 *>(er + k + 4);
+#pragma unroll
+        for (int t = 0; t < Cfg::PT; ++t) we[q][t] = *reinterpret_cast<const bf16x8 *>(wr0 + (size_t)(u0 + min(16 * t + l15, UPW - 1)) * D + k);
       }
-    }
-#pragma unroll
-    for (int t = 0; t < Cfg::PT; ++t)
-      *reinterpret_cast<float4 *>(&encp[((wave * Cfg::PT + t) * 16 + l15) * 20 + 4 * l4]) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    };
+    ask_frames(wave * 32);
+    float4 v[KS][2];
     if constexpr (HALF == 0) {
       const float *hp = r.dec + (size_t)(grp + kGroups * min(l15, Bg - 1)) * H + w4 * QK + l4 * 8;
-      float4 v[KS][2];
 #pragma unroll
       for (int i = 0; i < KS; ++i) {
         v[i][0] = *reinterpret_cast<const float4 *>(hp + 32 * i);
         v[i][1] = *reinterpret_cast<const float4 *>(hp + 32 * i + 4);
       }
+    }
+    load_w_pred();
+    load_w_out();
+    __builtin_amdgcn_sched_barrier(0);
+    for (int k0 = wave * 32; k0 < D; k0 += 1024) {
+      if (k0 >= 1024) ask_frames(k0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (k0 + 256 * q < D) {
+          const u32x4 xu = u32x4{pack_bf16x2(ea[q].x, ea[q].y), pack_bf16x2(ea[q].z, ea[q].w), pack_bf16x2(eb[q].x, eb[q].y), pack_bf16x2(eb[q].z, eb[q].w)};
+#pragma unroll
+          for (int t = 0; t < Cfg::PT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xu), we[q][t], acc[t], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < Cfg::PT; ++t)
+      *reinterpret_cast<float4 *>(&encp[((wave * Cfg::PT + t) * 16 + l15) * 20 + 4 * l4]) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    if constexpr (HALF == 0) {
       f32x4 pacc[Cfg::PT];
       products<Cfg::PT>(wp, v, pacc);
       put_partial<Cfg::PT, Cfg::PT>(predp, 0, pacc);
     }
-    load_w_out();   // on its way while the projections are exchanged
     meet();         // a barrier: the partial sums are in LDS
     if (!flags[0] || flags[1]) return;
     for (int i = tid; i < (n + Bg) * UPW; i += 512) {
@@ -780,7 +804,8 @@ __global__ __launch_bounds__(512) void beam_search_kernel(ModelDev m, BeamResDev
 }
 
 // One scoring step for up to 64 hypotheses and 16 frames, a group of workgroups per XCD, a single launch.  As five launches (two
-// projections, logits, rows, merge) and a wait for the stream 16 hypotheses x 16 frames of 640 units and 1024 labels took 54 us.
+// projections, logits, rows, merge) and a wait for the stream 16 hypotheses x 16 frames of 640 units and 1024 labels took 54 us, now 35.5: 20 in the kernel
+// (memory to projections 8.2, exchange and frames to LDS 3, logits 2, rows, merge and their exchanges 7), the rest launch and return.
 template <int KS>
 __global__ __launch_bounds__(512) void beam_scores_kernel(ModelDev m, BeamResDev r) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
