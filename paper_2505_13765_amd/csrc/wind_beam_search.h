@@ -370,8 +370,36 @@ struct BeamNode {
 struct BeamHyp {
   int node;
   double score;
-  int sym;                   // labels already placed on the frame the hypothesis rests on
-  std::vector<int> frames;   // frame of every label
+  int sym;      // labels already placed on the frame the hypothesis rests on
+  int stamps;   // time stamps of its labels: the last one's entry in a list of (frame, entry before), -1: no labels
+};
+struct BeamStamp {
+  int frame, before;
+};
+
+// (node, label) -> child node: open addressing, a power of two of places, at most half of them taken
+struct BeamChildren {
+  std::vector<std::pair<unsigned long long, int>> place{(size_t)1 << 12, {0ull, -1}};
+  size_t taken = 0;
+  // the child's node, or a place that holds -1 and that the caller fills
+  int &find(int parent, int token) {
+    if (2 * (taken + 1) > place.size()) {
+      std::vector<std::pair<unsigned long long, int>> old(place.size() * 2, {0ull, -1});
+      old.swap(place);
+      for (const auto &o : old)
+        if (o.second >= 0) at(o.first) = o;
+    }
+    const unsigned long long key = ((unsigned long long)(unsigned)parent << 32) | (unsigned)token;
+    auto &p = at(key);
+    p.first = key;
+    if (p.second < 0) ++taken;
+    return p.second;
+  }
+  std::pair<unsigned long long, int> &at(unsigned long long key) {
+    size_t i = (size_t)((key * 0x9E3779B97F4A7C15ull) >> 32) & (place.size() - 1);
+    while (place[i].second >= 0 && place[i].first != key) i = (i + 1) & (place.size() - 1);
+    return place[i];
+  }
 };
 
 double beam_logaddexp(double a, double b) {
@@ -418,7 +446,8 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
 
   // trie of label sequences; slot 0 holds the zero state, the empty sequence is one step from it on the start id
   std::vector<BeamNode> nodes;
-  std::unordered_map<unsigned long long, int> child_of;
+  BeamChildren children;
+  std::vector<BeamStamp> stamps;
   int next_slot = 2;
   nodes.push_back(BeamNode{-1, V, 0, 1});
   const size_t slot_sz = (size_t)d.L * d.Hp;
@@ -450,46 +479,78 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     return t;
   };
   auto child_node = [&](int parent, int token) {
-    const unsigned long long key = ((unsigned long long)(unsigned)parent << 32) | (unsigned)token;
-    auto it = child_of.find(key);
-    if (it != child_of.end()) return it->second;
-    nodes.push_back(BeamNode{parent, token, nodes[parent].depth + 1, -1});
-    child_of.emplace(key, (int)nodes.size() - 1);
-    return (int)nodes.size() - 1;
+    int &child = children.find(parent, token);
+    if (child < 0) {
+      child = (int)nodes.size();
+      nodes.push_back(BeamNode{parent, token, nodes[parent].depth + 1, -1});
+    }
+    return child;
+  };
+  auto frames_of = [&](const BeamHyp &h) {
+    std::vector<int> f((size_t)nodes[h.node].depth);
+    size_t i = f.size();
+    for (int q = h.stamps; q >= 0; q = stamps[q].before) f[--i] = stamps[q].frame;
+    return f;
+  };
+  // what a pass knows about a node: valid if its pass is the present one
+  struct Mark {
+    int64_t pass;
+    int value;
+  };
+  std::vector<Mark> hyp_at, row_at;
+  auto mark = [&](std::vector<Mark> &marks, int64_t pass, int node) -> int * {   // the node's value in this pass, or null
+    if ((size_t)node < marks.size() && marks[node].pass == pass) return &marks[node].value;
+    return nullptr;
+  };
+  auto set_mark = [&](std::vector<Mark> &marks, int64_t pass, int node, int value) {
+    if ((size_t)node >= marks.size()) marks.resize(nodes.size() + nodes.size() / 2 + 64, Mark{-1, 0});
+    marks[node] = Mark{pass, value};
   };
   // step 1: one entry per label sequence, probabilities added in list order; the time stamps and
   // label count of the most probable duplicate are kept (ties: smaller time stamps, then count)
+  int64_t look = 0;
+  std::vector<BeamHyp> merged;
+  std::vector<double> best_single;
   auto recombine = [&](std::vector<BeamHyp> &hyps) {
-    std::vector<BeamHyp> out;
-    std::unordered_map<int, size_t> at;
-    std::vector<double> best_single;
-    for (BeamHyp &h : hyps) {
-      auto it = at.find(h.node);
-      if (it == at.end()) {
-        at.emplace(h.node, out.size());
+    ++look;
+    merged.clear();
+    best_single.clear();
+    for (const BeamHyp &h : hyps) {
+      const int *at = mark(hyp_at, look, h.node);
+      if (!at) {
+        set_mark(hyp_at, look, h.node, (int)merged.size());
         best_single.push_back(h.score);
-        out.push_back(std::move(h));
+        merged.push_back(h);
         continue;
       }
-      BeamHyp &g = out[it->second];
-      double &bs = best_single[it->second];
+      BeamHyp &g = merged[*at];
+      double &bs = best_single[*at];
       const double total = beam_logaddexp(g.score, h.score);
-      const bool take = h.score > bs || (h.score == bs && (h.frames < g.frames || (h.frames == g.frames && h.sym < g.sym)));
-      if (take) { g.frames = std::move(h.frames); g.sym = h.sym; bs = h.score; }
+      bool take = h.score > bs;
+      if (h.score == bs) {
+        const std::vector<int> fh = frames_of(h), fg = frames_of(g);
+        take = fh < fg || (fh == fg && h.sym < g.sym);
+      }
+      if (take) { g.stamps = h.stamps; g.sym = h.sym; bs = h.score; }
       g.score = total;
     }
-    hyps.swap(out);
+    hyps.swap(merged);
   };
 
-  std::map<int, std::vector<BeamHyp>> resting;
-  resting[0].push_back(BeamHyp{0, 0.0, 0, {}});
+  std::vector<std::vector<BeamHyp>> resting((size_t)T + 1);   // by frame; T: finished
+  resting[0].push_back(BeamHyp{0, 0.0, 0, -1});
+  std::vector<BeamHyp> hyps, kept;
+  std::vector<int> order;
   std::vector<int> cb_len, cb_tok, cb_fr, cb_sym;
   std::vector<double> cb_score;
-  while (!resting.empty()) {
-    const int t = resting.begin()->first;
-    if (t == T) break;
-    std::vector<BeamHyp> hyps = std::move(resting.begin()->second);
-    resting.erase(resting.begin());
+  for (int t = 0; t < T;) {
+    if (resting[t].empty()) {
+      std::vector<BeamHyp>().swap(resting[t]);
+      ++t;
+      continue;
+    }
+    hyps.clear();
+    hyps.swap(resting[t]);   // new ones may come to rest on the same frame: the next pass
     ++st.rounds;
     st.max_pending = std::max<int64_t>(st.max_pending, (int64_t)hyps.size());
     recombine(hyps);
@@ -499,19 +560,19 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     if (prefix_mode != WIND_PREFIX_OFF && hyps.size() > 1) {
       struct Pair { size_t a, b; };
       std::vector<Pair> pairs;
-      std::unordered_map<int, int> row_of;   // child node X -> row holding log P(label(X) | t, decoder(parent(X)))
-      std::vector<int> row_node;
-      std::unordered_map<int, size_t> hyp_of;
-      for (size_t i = 0; i < hyps.size(); ++i) hyp_of.emplace(hyps[i].node, i);
+      std::vector<int> row_node;   // child nodes X by row, which holds log P(label(X) | t, decoder(parent(X))); row_at: the row of a node
       for (size_t b = 0; b < hyps.size(); ++b) {
         int q = hyps[b].node;
         for (int up = 1; up < S && nodes[q].parent >= 0; ++up) {
           q = nodes[q].parent;
-          auto it = hyp_of.find(q);
-          if (it == hyp_of.end() || hyps[it->second].sym + up >= S) continue;
-          pairs.push_back(Pair{it->second, b});
+          const int *at = mark(hyp_at, look, q);   // recombine's: every hypothesis has its place there
+          if (!at || hyps[*at].sym + up >= S) continue;
+          pairs.push_back(Pair{(size_t)*at, b});
           for (int x = hyps[b].node; x != q; x = nodes[x].parent)
-            if (row_of.emplace(x, (int)row_node.size()).second) row_node.push_back(x);
+            if (!mark(row_at, look, x)) {
+              set_mark(row_at, look, x, (int)row_node.size());
+              row_node.push_back(x);
+            }
         }
       }
       if (!pairs.empty()) {
@@ -573,15 +634,15 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
           // labels in sequence order: collect the chain from B up to A, then add from A's side
           chain.clear();
           for (int x = hyps[pr.b].node; x != hyps[pr.a].node; x = nodes[x].parent) chain.push_back(x);
-          for (size_t i = chain.size(); i-- > 0;) completion += (double)lp[(size_t)row_of[chain[i]]];
+          for (size_t i = chain.size(); i-- > 0;) completion += (double)lp[(size_t)row_at[chain[i]].value];
           hyps[pr.b].score = beam_logaddexp(hyps[pr.b].score, before[pr.a] + completion);
           removed[pr.a] = 1;
           ++st.completions;
         }
         if (prefix_mode == WIND_PREFIX_REMOVE) {
-          std::vector<BeamHyp> kept;
+          kept.clear();
           for (size_t i = 0; i < hyps.size(); ++i)
-            if (!removed[i]) kept.push_back(std::move(hyps[i]));
+            if (!removed[i]) kept.push_back(hyps[i]);
           hyps.swap(kept);
         }
       }
@@ -589,20 +650,18 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
 
     // step 3: the K most probable (ties: shorter, then lexicographically smaller label sequence)
     {
-      std::vector<std::vector<int>> toks(hyps.size());
-      std::vector<size_t> order(hyps.size());
-      for (size_t i = 0; i < hyps.size(); ++i) { order[i] = i; }
-      auto less = [&](size_t a, size_t b) {
+      order.resize(hyps.size());
+      for (size_t i = 0; i < hyps.size(); ++i) order[i] = (int)i;
+      auto less = [&](int a, int b) {
         if (hyps[a].score != hyps[b].score) return hyps[a].score > hyps[b].score;
         const int da = nodes[hyps[a].node].depth, db = nodes[hyps[b].node].depth;
         if (da != db) return da < db;
-        if (toks[a].empty() && da) toks[a] = tokens_of(hyps[a].node);
-        if (toks[b].empty() && db) toks[b] = tokens_of(hyps[b].node);
-        return toks[a] < toks[b];
+        return tokens_of(hyps[a].node) < tokens_of(hyps[b].node);
       };
-      std::sort(order.begin(), order.end(), less);
-      std::vector<BeamHyp> kept;
-      for (size_t i = 0; i < order.size() && i < (size_t)K; ++i) kept.push_back(std::move(hyps[order[i]]));
+      const size_t most = std::min(order.size(), (size_t)K);
+      std::partial_sort(order.begin(), order.begin() + most, order.end(), less);
+      kept.clear();
+      for (size_t i = 0; i < most; ++i) kept.push_back(hyps[order[i]]);
       hyps.swap(kept);
     }
     const int Bh = (int)hyps.size();
@@ -670,7 +729,8 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
         const std::vector<int> tk = tokens_of(h.node);
         cb_len.push_back((int)tk.size());
         cb_tok.insert(cb_tok.end(), tk.begin(), tk.end());
-        cb_fr.insert(cb_fr.end(), h.frames.begin(), h.frames.end());
+        const std::vector<int> fr = frames_of(h);
+        cb_fr.insert(cb_fr.end(), fr.begin(), fr.end());
         cb_sym.push_back(h.sym);
         cb_score.push_back(h.score);
       }
@@ -683,28 +743,28 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
       for (int k = 0; k < K; ++k) {
         const int label = labels[b * K + k], jump = jumps[b * K + k];
         if (label < 0) continue;
+        if (label > V || jump < 0 || jump >= n) return fail(WIND_ERR_HIP, "beam search: a pass returned a pair outside its window");
         BeamHyp nh;
         nh.score = hyps[b].score + (double)scores[b * K + k];
         if (label != V) {
           nh.node = child_node(hyps[b].node, label);
-          nh.frames = hyps[b].frames;
-          nh.frames.push_back(t + jump);
+          nh.stamps = (int)stamps.size();
+          stamps.push_back(BeamStamp{t + jump, hyps[b].stamps});
           nh.sym = jump == 0 ? hyps[b].sym + 1 : 1;
           int tn = t + jump;
           if (nh.sym >= S) { tn += 1; nh.sym = 0; }   // safeguard: leave the frame after S labels
-          resting[tn].push_back(std::move(nh));
+          resting[tn].push_back(nh);
         } else {
           nh.node = hyps[b].node;
-          nh.frames = hyps[b].frames;
+          nh.stamps = hyps[b].stamps;
           nh.sym = 0;
-          resting[t + n].push_back(std::move(nh));
+          resting[t + n].push_back(nh);
         }
       }
     }
   }
 
-  std::vector<BeamHyp> fin;
-  if (!resting.empty() && resting.begin()->first == T) fin = std::move(resting.begin()->second);
+  std::vector<BeamHyp> fin = std::move(resting[T]);
   if (fin.empty()) return fail(WIND_ERR_HIP, "beam search ended without a hypothesis");
   recombine(fin);
   size_t best = 0;
@@ -722,7 +782,8 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
   *out_score = fin[best].score;
   *out_count = (int32_t)best_tok.size();
   if ((int)best_tok.size() > cap) return fail(WIND_ERR_OVERFLOW, "the best hypothesis has more labels than cap");
-  for (size_t i = 0; i < best_tok.size(); ++i) { out_tokens[i] = best_tok[i]; out_frames[i] = fin[best].frames[i]; }
+  const std::vector<int> best_frames = frames_of(fin[best]);
+  for (size_t i = 0; i < best_tok.size(); ++i) { out_tokens[i] = best_tok[i]; out_frames[i] = best_frames[i]; }
   return WIND_OK;
 }
 
