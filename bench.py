@@ -44,6 +44,7 @@ def run_workload(torch, wi, WindModel, name, windows, steps, warmup, with_sequen
     enc, lens = wi.make_batch(cfg)
     frames = int(lens.sum())
     model = WindModel.from_config(cfg, w)
+    model.set_option("lookahead", 0)   # the sweep compares window sizes: no iteration looks beyond its window
     d_enc = torch.from_numpy(enc).cuda()
     d_len = torch.from_numpy(lens).cuda()
     B, T, _ = enc.shape
@@ -64,7 +65,11 @@ def run_workload(torch, wi, WindModel, name, windows, steps, warmup, with_sequen
             cold = (time.perf_counter() - t0) * 1e3
         sec = timed_decodes(torch, model, d_enc, d_len, W, cfg.S, steps, warmup, out)
         st = model.stats()
+        model.set_option("lookahead", 1)   # as a caller who sets no option has it
+        sec_default = timed_decodes(torch, model, d_enc, d_len, W, cfg.S, steps, warmup, out)
+        model.set_option("lookahead", 0)
         res["seq" if W is None else str(W)] = {
+            "ms_per_step_lookahead": sec_default * 1e3,
             **({"cold_first_call_ms": cold} if cold is not None else {}),
             "frames_per_s": frames / sec, "rtfx": frames * FRAME_SECONDS / sec, "ms_per_step": sec * 1e3,
             "iterations": int(st.iterations), "rows": int(st.rows), "useful_rows": int(st.useful_rows),
@@ -197,6 +202,7 @@ def graph_ablation(torch, wi, WindModel, steps, warmup):
            torch.zeros((B, cap), dtype=torch.int32, device="cuda"),
            torch.zeros((B,), dtype=torch.int32, device="cuda"))
     model.set_option("loop_kernel", 0)   # the per-step kernels in all three: batches of this size would decode in resident groups
+    model.set_option("lookahead", 0)
     res = {"workload": f"batch32 model, B=16, {int(lens.sum())} frames", "unit": "ms per decode call",
            "paper_table5_decoder_only_s": {"standard": {"eager": 12.45, "graph": 4.23}, "wind_w8": {"eager": 6.45, "graph": 2.10},
                                            "hardware": "2x A6000, Parakeet-RNNT-1.1b, real audio"}}

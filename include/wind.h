@@ -70,7 +70,8 @@ typedef struct {
   const float *w_out, *b_out;                  /* [V+1, Hj], [V+1]                 */
 } wind_weights;
 
-/* Counters of the last decode call on a model (Analysis, "Jump Distribution"). */
+/* Counters of the last decode call on a model (Analysis, "Jump Distribution"): those of windows of the caller's size, however many
+ * frames the kernels looked at a time (option "lookahead"). */
 typedef struct {
   int64_t iterations;       /* loop iterations that had at least one active utterance: the most windows of any utterance */
   int64_t windows;          /* (utterance, iteration) pairs = joiner calls on a window       */
@@ -141,7 +142,8 @@ int wind_greedy_decode_async(wind_model *m, const float *enc_out, const int32_t 
 
 /*
  * Method, Algorithm 1 (the standard frame-by-frame loop; Table 1's window-size-1 row), batched
- * the same way: one joiner row per utterance and iteration.  Same arguments without W.
+ * the same way: windows of one frame.  Same arguments without W.  With option "lookahead" = 0 the kernels
+ * evaluate one joiner row per utterance and iteration too.
  */
 int wind_sequential_decode(wind_model *m, const float *enc_out, const int32_t *lengths, int B, int T,
                            int max_symbols_per_step, int32_t *out_tokens, int32_t *out_frames,
@@ -363,6 +365,10 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             workgroups over one XCD or the chip that meet at grid barriers.  Resident kernels whose
  *             workgroups wait for each other (all but those of fp32 models of at most 128 units and 128 labels) take turns on a
  *             GPU: a call's kernel waits on its stream until that of the call before it, of any thread, stream or model, is done
+ *   "lookahead"  1 (default): an iteration of the resident groups looks at as many frames of an utterance as their row tiles
+ *             have rows for (16, or 8 with more than two utterances per XCD), also beyond the end of the caller's window: labels
+ *             and frames do not depend on how the frames are cut into windows, and the counters stay those of the
+ *             caller's.  0: never beyond it (what a window of that size costs; the standard loop frame by frame)
  *   "loop_fused"  1 (default): with at most 16 window rows and a joint hidden size that is a multiple of 128,
  *             at most 640, that kernel builds the window rows directly as matrix-core operands; 0: it
  *             stages them in LDS (the form for every other shape)

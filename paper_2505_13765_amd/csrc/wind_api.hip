@@ -156,6 +156,7 @@ struct wind_model {
   int opt_pred_mfma_min_batch = kPredMfmaMinBatch;
   int opt_loop_kernel = 1;
   int opt_loop_one_xcd = 1;
+  int opt_lookahead = 1;
   int opt_loop_fused = 1;
   long long opt_loop_spin_limit = 1ll << 21;
   int opt_debug_stamps = 0;
@@ -228,10 +229,11 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
-// Utterances up to which groups of four row tiles (windows of more than 8 rows) take a call: each round of 32 costs them the same, while the
-// per-step kernels' launches hardly grow.  640 units, W = 16, 200 to 1500 frames, against those: 192 utterances 11.8 ms (14.6),
-// 224 12.7 ms (14.1), 256 15.3 ms (13.7).  With fewer row tiles 256 still win or break even (W = 8 14.8 ms (15.0), W = 4 17.2 ms (19.4))
-constexpr int kGroupMaxB4 = 224;
+// Utterances up to which windows of more than 8 rows take groups: each round of 32 utterances costs them the same, while the per-step
+// kernels' launches hardly grow and half as many of those are needed as for short windows.  640 units, 200 to 1500 frames, groups / per-step kernels:
+// W = 16 192 utterances 10.6 / 13.8 ms, 224 12.7 / 14.2, 256 13.2 / 14.6; W = 4 256 utterances 13.2 / 20.2 ms.  Models of 128 units with a label on
+// almost every frame lose earlier (W = 16: from about 176 utterances).
+constexpr int kGroupMaxB16 = 224;
 constexpr unsigned kGroupStartPolls = 1u << 16;   // about 12 ms, what a batch of 32 takes with the per-step kernels
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
 // Where everything of a decode call lives inside the one workspace slab.
@@ -729,9 +731,8 @@ constexpr GroupInstance group_f32_instance() {
   return {wind_group_f32_kernel<NK, CT, GW>, GroupF32Cfg<NK, CT, GW>::smem, WIND_F32, GroupF32Cfg<NK, CT, GW>::H, CT, GW};
 }
 const GroupInstance kGroupInstances[] = {
-    group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<1, 4, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(),
-    group_instance<2, 4, 32>(), group_instance<3, 1, 32>(), group_instance<3, 2, 32>(), group_instance<3, 4, 32>(), group_instance<4, 1, 32>(),
-    group_instance<4, 2, 32>(), group_instance<4, 4, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(), group_instance<5, 4, 32>(),
+    group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(), group_instance<3, 1, 32>(),
+    group_instance<3, 2, 32>(), group_instance<4, 1, 32>(), group_instance<4, 2, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(),
     group_f32_instance<2, 1, 1>(), group_f32_instance<2, 4, 1>(), group_f32_instance<4, 1, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
     group_f32_instance<8, 1, 32>(), group_f32_instance<12, 1, 32>(), group_f32_instance<16, 1, 32>(), group_f32_instance<20, 1, 32>()};
 
@@ -762,18 +763,20 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     gd->NG = B;
     gd->NX = 0;
     gd->NS = gd->SPT = gd->RG = 1;
+    gd->reach = kGroupMaxW;
   } else {
     gd->NG = gd->NX = std::min(kGroups, B);
     gd->NS = std::min(kGroupSlots, (B + gd->NG - 1) / gd->NG);
-    if (m->dtype == WIND_F32) gd->NS = std::min(gd->NS, kGroupMaxW / W);   // one row tile: registers hold one part of W_out
-    gd->SPT = std::min(kGroupMaxW / W, gd->NS);
-    const int tiles = (gd->NS + gd->SPT - 1) / gd->SPT;
-    gd->RG = tiles > 2 ? 4 : tiles;
-    if (gd->RG == 4 && B > kGroupMaxB4) return nullptr;
-    const int parts = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // of W_out per workgroup
-    ct = parts > 2 ? 4 : parts;
-    if (parts > ct) return nullptr;
+    if (m->dtype == WIND_F32) gd->NS = std::min(gd->NS, kGroupMaxW / W);
+    gd->RG = m->dtype == WIND_F32 || gd->NS == 1 ? 1 : 2;   // row tiles: see wind_group_kernel.h; fp32: registers hold one part of W_out
+    gd->SPT = (gd->NS + gd->RG - 1) / gd->RG;
+    gd->reach = kGroupMaxW / gd->SPT;
+    if (W > 8 && B > kGroupMaxB16) return nullptr;
+    ct = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // parts of W_out per workgroup: one, or two
   }
+  gd->win = W;
+  gd->win_inv = 65536u / (unsigned)W + 1u;
+  if (!m->opt_lookahead) gd->reach = std::min(gd->reach, W);
   for (const GroupInstance &i : kGroupInstances)
     if (i.dtype == m->dtype && i.H == d.Hj && i.ct == ct && i.gw == gw) return &i;
   return nullptr;
@@ -915,7 +918,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       rc = resident_enter(gate, s);
       if (rc) return rc;
     }
-    gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, c, gd);
+    CallDev cr = c;
+    cr.W = gd.reach;
+    gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, cr, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
     // An asynchronous call's results stay in its workspace until it is completed: it may be part of a graph that the caller launches
@@ -1560,6 +1565,10 @@ int wind_set_option(wind_model *m, const char *key, int64_t value) {
   }
   if (!std::strcmp(key, "loop_one_xcd")) {
     m->opt_loop_one_xcd = value != 0;
+    return WIND_OK;
+  }
+  if (!std::strcmp(key, "lookahead")) {
+    m->opt_lookahead = value != 0;
     return WIND_OK;
   }
   if (!std::strcmp(key, "loop_spin_limit")) {

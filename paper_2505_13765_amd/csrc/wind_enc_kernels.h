@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void init_state_kernel(ModelDev m, CallDev c) 
 // Resident groups (wind_group_kernel.h): what a call hands to them.
 constexpr int kGroups = 8;              // XCDs
 constexpr int kGroupSlots = 4;          // utterances a group decodes at a time, at most
-constexpr int kGroupRows = 64;          // window rows of a group, at most
+constexpr int kGroupRows = 32;          // window rows of a group, at most
 constexpr int kGroupMaxW = 16;
 constexpr int kGroupMaxB = 256;         // utterances of a call (group_init_kernel ranks them in one workgroup)
 constexpr int kGroupBarInts = 34 * 32;  // per group: word 0 abort, word 1 placement (2: one L2, 1: not), word 32 + g: iterations workgroup g has
@@ -73,7 +73,10 @@ struct GroupDev {
   int *order, *n_order;                 // utterances with frames by falling length, and their number
   int NG, NS, RG, SPT;                  // groups, slots per group, row tiles per group, slots per row tile
   int NX;                               // groups whose workgroups exchange words in memory
-  int max_iters;                        // windows an utterance may take
+  int reach;                            // frames of an utterance that an iteration looks at
+  int win;                              // the caller's window (the kernels' CallDev::W is the reach)
+  unsigned win_inv;                     // 65536 / win + 1: x / win = x win_inv >> 16 for small x
+  int max_iters;                        // windows (of the caller's size) an utterance may take
   unsigned spin_limit, start_limit;     // polls of a wait, and of the first one: until all workgroups of the group are on the chip
 };
 

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     asm volatile("" : "+v"(lane), "+v"(tid));   // see group_loop
     l15 = lane & 15;
     l4 = lane >> 4;
-    const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
+    const int nwin = group_window(c, gd, sl);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
     const unsigned stamp = (unsigned)it + 1u, stamp16 = stamp & 0xFFFFu;
     unsigned long long *kp = SOLO ? kbase : kbase + (size_t)group_key_buffer(it) * kGroupRows * kstride;

@@ -14,8 +14,8 @@ namespace wind {
 // (slots); when one is done the slot takes the next of the group's list.  Utterances are dealt by falling
 // length, back and forth over the slots.
 //
-// The weights the loop needs sit in registers, as matrix-core operands (all but <5, 4, 32>, 640 units and three or four row tiles: 17
-// vector registers in scratch memory; all instances keep 100 to 140 scalars in lanes of vector registers): per workgroup CT parts of 32
+// The weights the loop needs sit in registers, as matrix-core operands (all instances keep 100 to 150 scalars in lanes of vector
+// registers): per workgroup CT parts of 32
 // columns of W_out (waves 0-3, K split in four), the recurrent rows of UPW LSTM units and PPW rows of W_pred
 // (waves 4-7, K split in four).  LDS holds the projected frames of the windows: two windows' worth per
 // slot, loaded straight from memory a whole iteration before they are read.
@@ -36,8 +36,13 @@ namespace wind {
 // set, a wave sets that word and marks the workgroup failed, which then leaves at its next decision; the host
 // then has the call decoded by the per-step kernels, or reports the error.
 //
-// W <= 16.  A workgroup's row tile holds SPT = 16 / W slots; with more slots than that the group's workgroups
-// are cut into RG row groups, each covering all columns with GW / RG workgroups.
+// How far an iteration looks (CallDev::W, the reach: frames of every slot) does not depend on the caller's window: a row tile has 16 rows,
+// which its SPT slots share, and whether a frame's label is found by one iteration or by the next changes neither
+// labels nor frames.  The counters stay those of windows of gd.win frames (group_outcome).  With several slots the group's workgroups
+// are cut into RG = 2 row groups, each covering all columns with GW / 2 workgroups.  640 units, 1024 labels, lengths 200 .. 1500: 13 utterances
+// (two slots), one tile of 2 x 8 rows 1.51 ms, two of 16 1.39; 20 (three slots), 3 x 5 rows 1.83, two tiles of 2 x 8 1.68, three
+// of 16 1.73; 32 (four), 4 x 4 2.90, two tiles of 2 x 8 2.47, four of 16 2.63.  As many frames as the caller's
+// window, before: one utterance of 1000 frames 2.94 / 1.26 / 0.98 / 0.84 ms at W = 1 / 4 / 8 / 16, now 0.84 at each.
 template <int KS, int CT, int GW>
 struct GroupCfg {
   static constexpr int H = 128 * KS;                      // = Hp = Hj
@@ -168,7 +173,8 @@ __device__ __forceinline__ void group_touch(const void *src, unsigned lds) {
 // The part of the loop's state that every wave keeps for itself: lane a holds slot a.
 struct GroupLane {
   int b, t, len, sym, cnt;   // utterance, frame, length, labels on the frame, labels so far (len = t = 0: slot empty)
-  int wc;                    // windows so far
+  int wc;                    // windows of the caller's size so far
+  int ph;                    // blank frames of the open one that earlier iterations have seen (0: none is open)
   int rpos;                  // t modulo 2 W: the frame's row in its ring of projected frames
   int ld0, ld;               // frames loaded (or asked for) before the last decision, and now
   int nb, nlen, round;       // the slot's next utterance (-1: none)
@@ -188,11 +194,17 @@ __device__ __forceinline__ GroupLane group_first_slots(const CallDev &c, const G
   GroupLane sl;
   group_next(c, gd, grp, lane, n_order, 0, sl.b, sl.len);
   group_next(c, gd, grp, lane, n_order, 1, sl.nb, sl.nlen);
-  sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+  sl.t = sl.sym = sl.cnt = sl.wc = sl.ph = sl.rpos = sl.ld0 = 0;
   sl.round = 1;
   if (sl.b < 0) sl.b = 0;
   sl.ld = min(sl.len, 2 * c.W);
   return sl;
+}
+
+// Frames of the slot's window in this iteration: up to c.W, the reach (see group_shape), which may hold several windows of the caller's
+// size, gd.win, or end inside one; no more of those than the call may take.
+__device__ __forceinline__ int group_window(const CallDev &c, const GroupDev &gd, const GroupLane &sl) {
+  return min(min(c.W, sl.len - sl.t), gd.win * min(gd.max_iters - sl.wc, kGroupMaxW) - sl.ph);
 }
 
 // The frames that the slots of row tile rt have come to need (from ld0 to ld), into their rings of 2 W rows, one frame per wave
@@ -234,32 +246,41 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
   emits = false;
   fresh_slot = false;
   if (nwin > 0) {
-    const int rech = __popc((unsigned)(need >> oshift) & segm);
-    const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, rech, writer);
+    // What that is in windows of the caller's size, which start where the last label or the last whole window left off: `full` blank ones,
+    // and one that a label or the last frame closes, `rem` blank frames into it, or that stays open
+    const int seen = sl.ph + (first < 0 ? nwin : first), full = (int)(((unsigned)seen * gd.win_inv) >> 16), rem = seen - full * gd.win;
+    const bool closes = first >= 0 || (rem > 0 && sl.t + nwin == sl.len);
+    const int n_last = first < 0 ? rem : min(gd.win, sl.len - (sl.t + first - rem));
+    const int looked = first < 0 ? W : min(W, (full + 1) * gd.win - sl.ph);   // rows of the frames up to the end of the window that decided
+    const int rech = __popc((unsigned)(need >> oshift) & segm & ((1u << looked) - 1u));
+    const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, 0, writer);
     const int adv = wo.slot.y - sl.t;
     sl.t = wo.slot.y; sl.sym = wo.slot.w; sl.cnt = wo.cnt;
     sl.rpos += adv;
     if (sl.rpos >= W2) sl.rpos -= W2;
-    ++sl.wc;
+    sl.wc += full + closes;
+    sl.ph = closes ? 0 : rem;
     sl.ld0 = sl.ld;
     sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
     const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
     if (writer) {
       // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
       // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
-      const unsigned ev = wo.ev;
+      const unsigned ev = wo.ev, forced = (ev >> 29) & 1u;
       auto add = [&](int which, unsigned v) {
         const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + which);
         asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(v) : "memory");
       };
-      add(ST_WINDOWS, 1u);
-      add(ST_ROWS, ev & 127u);
-      add(ST_USEFUL, (ev >> 7) & 127u);
-      add(ST_RECHECK, (ev >> 21) & 127u);
+      const int blanks = full * gd.win;
+      add(ST_WINDOWS, (unsigned)(full + closes));
+      add(ST_ROWS, (unsigned)(blanks + (closes ? n_last : 0)));
+      add(ST_USEFUL, (unsigned)(blanks + (first >= 0 ? rem + 1 : closes ? rem : 0)));
+      add(ST_RECHECK, (unsigned)rech);
       add(ST_LABELS, (ev >> 28) & 1u);
-      add(ST_FORCED, (ev >> 29) & 1u);
+      add(ST_FORCED, forced);
       add(ST_OVERFLOW, (ev >> 30) & 1u);
-      add(kStatJump0 + (int)((ev >> 14) & 127u), 1u);
+      add(kStatJump0 + gd.win, (unsigned)full);
+      add(kStatJump0 + rem + (int)forced, closes ? 1u : 0u);
       if (done) {
         const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + ST_ITER);
         asm volatile("ds_max_u32 %0, %1" ::"v"(at), "v"(sl.wc) : "memory");
@@ -271,7 +292,7 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
       fresh_slot = sl.nb >= 0;
       sl.b = fresh_slot ? sl.nb : 0;
       sl.len = fresh_slot ? sl.nlen : 0;
-      sl.t = sl.sym = sl.cnt = sl.wc = sl.rpos = sl.ld0 = 0;
+      sl.t = sl.sym = sl.cnt = sl.wc = sl.ph = sl.rpos = sl.ld0 = 0;
       sl.ld = min(sl.len, W2);
       if (fresh_slot) {
         ++sl.round;
@@ -382,10 +403,9 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
 
   // ---- constants of this lane's places in the steps below
   const float b_blank = m.b_out[V];
-  // the blank column's part that this lane needs, kept in registers where there is room (the row's LDS reads bound that step)
-  constexpr bool BREG = ROLE == 0 && CT < 4;
-  float4 breg[BREG ? KS : 1][2];
-  if constexpr (BREG) {
+  // the blank column's part that this lane needs (the row's LDS reads bound that step)
+  float4 breg[ROLE == 0 ? KS : 1][2];
+  if constexpr (ROLE == 0) {
 #pragma unroll
     for (int i = 0; i < KS; ++i)
 #pragma unroll
@@ -394,7 +414,6 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
   const unsigned touch_lds = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char *)(smem + Cfg::oT);
   const unsigned winv = 65536u / (unsigned)W + 1u;   // x / W for x < 64
   auto div_w = [&](int x) { return (int)(((unsigned)x * winv) >> 16); };
-  const int nq = 4 * wave >= R ? 0 : 4 * (wave + 8) >= R ? 1 : 2;   // row quads this wave decides
   float bias[Cfg::NI][2];
 #pragma unroll
   for (int k = 0; k < Cfg::NI; ++k)
@@ -411,7 +430,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     asm volatile("" : "+v"(lane), "+v"(tid1));
     l15 = lane & 15;
     l4 = lane >> 4;
-    const int nwin = min(W, sl.len - sl.t);   // lanes of empty slots: 0
+    const int nwin = group_window(c, gd, sl);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
     const int tag = group_key_tag(it);
     const unsigned stamp = (unsigned)it + 1u;
@@ -434,19 +453,17 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       int rr = __shfl(sl.rpos, ga, kWave) + gj;
       if (rr >= W2) rr -= W2;
       const float *er = ecache + (gloc * W2 + rr) * Cfg::EST + w4 * QK + l4 * 8;
-      const float *pr = pfull + ga * H + w4 * QK + l4 * 8, *wr_ = wbl + w4 * QK + l4 * 8;
+      const float *pr = pfull + ga * H + w4 * QK + l4 * 8;
       float dot = 0.f, nrm = 0.f;
       // the LDS operands of a step are read one step ahead, into registers that take turns
-      float4 eo[2][2], po[2][2], bo[BREG ? 1 : 2][2];
+      float4 eo[2][2], po[2][2];
       auto read_ops = [&](int set, int i) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           eo[set][h] = *reinterpret_cast<const float4 *>(er + i * 32 + 4 * h);
           po[set][h] = *reinterpret_cast<const float4 *>(pr + i * 32 + 4 * h);
-          if constexpr (!BREG) bo[set][h] = *reinterpret_cast<const float4 *>(wr_ + i * 32 + 4 * h);
         }
       };
-      bf16x8 zf[KS];
       read_ops(0, 0);
 #pragma unroll
       for (int i = 0; i < KS; ++i) {
@@ -454,7 +471,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         float x[8], d = 0.f;   // the blank logit's sum in blocks of 8 products, a step's: as short as the other kernels' (lanes and a tree)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = BREG ? breg[BREG ? i : 0][h] : bo[BREG ? 0 : i & 1][h];
+          const float4 e4 = eo[i & 1][h], p4 = po[i & 1][h], b4 = breg[i][h];
           float *y = x + 4 * h;
           y[0] = fmaxf(e4.x + p4.x, 0.f); y[1] = fmaxf(e4.y + p4.y, 0.f); y[2] = fmaxf(e4.z + p4.z, 0.f); y[3] = fmaxf(e4.w + p4.w, 0.f);
           d = fmaf(y[0], b4.x, d); d = fmaf(y[1], b4.y, d); d = fmaf(y[2], b4.z, d); d = fmaf(y[3], b4.w, d);
@@ -462,18 +479,9 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         }
         dot += d;
         const u32x4 zu = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
-        zf[i] = __builtin_bit_cast(bf16x8, zu);
-        if constexpr (CT < 4) {
 #pragma unroll
-          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);
-        }
+        for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, zu), wo[t][i], acc[t], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);   // keeps the reads at one step ahead: registers
-      }
-      if constexpr (CT == 4) {   // the products behind the row: operands of both at once would not fit the registers
-#pragma unroll
-        for (int i = 0; i < KS; ++i)
-#pragma unroll
-          for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[i], wo[t][i], acc[t], 0, 0, 0);
       }
       dot += __shfl_xor(dot, 16, kWave); nrm += __shfl_xor(nrm, 16, kWave);
       dot += __shfl_xor(dot, 32, kWave); nrm += __shfl_xor(nrm, 32, kWave);
@@ -529,56 +537,38 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       pend = 0;
     }
     if constexpr (ROLE == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
-    // ---- exchange 1: four rows per wave and pass, 16 lanes per row, lane s with the keys of parts s and s + 16
-    if (nq > 0) {
-      float2 kA[2], kB[2], kC[2];
-      bool valid[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int row = 4 * (wave + 8 * k) + l4, a = div_w(row);
-        valid[k] = k < nq && row - a * W < __shfl(nwin, a, kWave);
-        kA[k] = kB[k] = make_float2(kKeyNone, kKeyNone);
-        kC[k] = make_float2(0.f, 0.f);
-      }
+    // ---- exchange 1: four rows per wave, 16 lanes per row, lane s with the keys of parts s and s + 16
+    if (4 * wave < R) {
+      const int row = 4 * wave + l4, a = div_w(row);
+      const bool valid = row - a * W < __shfl(nwin, a, kWave);
+      float2 kA = make_float2(kKeyNone, kKeyNone), kB = kA, kC = make_float2(0.f, 0.f);
       auto pair = [](unsigned long long u) { return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32))); };
+      const unsigned long long *kr = kp + (size_t)row * kstride;
       const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
-        bool fresh = true;
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if (valid[k]) {
-            const unsigned long long *kr = kp + (size_t)(4 * (wave + 8 * k) + l4) * kstride;
-            if (l15 < nparts) kA[k] = pair(group_ld(kr + l15));
-            if (l15 + 16 < nparts) kB[k] = pair(group_ld(kr + l15 + 16));
-            kC[k] = pair(group_ld(kr + nparts));
-          }
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if (valid[k])
-            fresh = fresh && (l15 >= nparts || key_tag(kA[k].y) == tag) && (l15 + 16 >= nparts || key_tag(kB[k].y) == tag) && key_tag(kC[k].y) == tag;
-        return fresh;
+        if (!valid) return true;
+        if (l15 < nparts) kA = pair(group_ld(kr + l15));
+        if (l15 + 16 < nparts) kB = pair(group_ld(kr + l15 + 16));
+        kC = pair(group_ld(kr + nparts));
+        return (l15 >= nparts || key_tag(kA.y) == tag) && (l15 + 16 >= nparts || key_tag(kB.y) == tag) && key_tag(kC.y) == tag;
       });
       if (!got && lane == 0) *fail = 1;
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        if (k >= nq) continue;
-        const float a2 = l15 < nparts ? key_with_tag(kA[k].y, 0) : kKeyNone, b2 = l15 + 16 < nparts ? key_with_tag(kB[k].y, 0) : kKeyNone;
-        const float kbest = row16_max_f32(fmaxf(kA[k].x, kB[k].x));
-        const float vbest = key_val(kbest), top = fmaxf(vbest, kC[k].x);
-        const float thresh = top - (m.tau_scale * kC[k].y + 6.2e-5f * fabsf(top));
-        const int cnt = row16_sum_i32((key_val(kA[k].x) >= thresh) + (key_val(a2) >= thresh) + (key_val(kB[k].x) >= thresh) + (key_val(b2) >= thresh));
-        int col = -1;
-        if (kA[k].x == kbest) col = l15 * 32 + key_col(kbest);
-        if (kB[k].x == kbest) col = (l15 + 16) * 32 + key_col(kbest);
-        col = row16_max_i32(col);
-        int label = V;
-        if (valid[k] && !(vbest < thresh)) label = cnt == 1 && kC[k].x < thresh ? col : -1;   // -1: near-tie
-        if (l15 == 0) stat[4 * (wave + 8 * k) + l4] = label;
-        // The step of a label starts with its row of input sums, from a table that no L2 holds: a row that may be the window's first
-        // label asks for its lines now, while the decision is completed (step 0.94 -> 0.7 us).  The
-        // column is clamped: with NaN logits no key is a label's
-        if (label != V && l15 < (NR * 4 + 127) / 128 + 1)
-          group_touch(m.emb_gates + (unsigned)min(max(col, 0), V) * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
-      }
+      const float a2 = l15 < nparts ? key_with_tag(kA.y, 0) : kKeyNone, b2 = l15 + 16 < nparts ? key_with_tag(kB.y, 0) : kKeyNone;
+      const float kbest = row16_max_f32(fmaxf(kA.x, kB.x));
+      const float vbest = key_val(kbest), top = fmaxf(vbest, kC.x);
+      const float thresh = top - (m.tau_scale * kC.y + 6.2e-5f * fabsf(top));
+      const int cnt = row16_sum_i32((key_val(kA.x) >= thresh) + (key_val(a2) >= thresh) + (key_val(kB.x) >= thresh) + (key_val(b2) >= thresh));
+      int col = -1;
+      if (kA.x == kbest) col = l15 * 32 + key_col(kbest);
+      if (kB.x == kbest) col = (l15 + 16) * 32 + key_col(kbest);
+      col = row16_max_i32(col);
+      int label = V;
+      if (valid && !(vbest < thresh)) label = cnt == 1 && kC.x < thresh ? col : -1;   // -1: near-tie
+      if (l15 == 0) stat[row] = label;
+      // The step of a label starts with its row of input sums, from a table that no L2 holds: a row that may be the window's first
+      // label asks for its lines now, while the decision is completed (step 0.94 -> 0.7 us).  The
+      // column is clamped: with NaN logits no key is a label's
+      if (label != V && l15 < (NR * 4 + 127) / 128 + 1)
+        group_touch(m.emb_gates + (unsigned)min(max(col, 0), V) * (4u * H) + (unsigned)(unit0 * 4 + min(l15 * 32, NR - 1)), touch_lds);
     }
     group_barrier();   // B2: every row's label, or that it is a near-tie
     if (*fail) return;
@@ -590,8 +580,8 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     if (need) {
       unsigned long long todo = need;
       // the waves with the fuller registers leave these to the others
-      constexpr bool mine = ROLE == 0 ? CT < 4 : NR <= 80;
-      constexpr int turns = CT < 4 && NR <= 80 ? 8 : 4;
+      constexpr bool mine = ROLE == 0 || NR <= 80;
+      constexpr int turns = NR <= 80 ? 8 : 4;
       for (int k = 0; mine && todo; ++k, todo &= todo - 1) {
         if ((k & (turns - 1)) != (wave & (turns - 1))) continue;
         const int row = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1), a = __builtin_amdgcn_readlane(oa, row), j = __builtin_amdgcn_readlane(oj, row);

@@ -55,6 +55,41 @@ def test_resident_groups(dtype, H, V, B, W):
     m.close()
 
 
+# one to four slots per group, windows that the reach holds several of, that it cuts and that end inside it; a label on hardly
+# any and on almost every frame (blank bias)
+@pytest.mark.parametrize("bias", [1.0, 6.0])
+@pytest.mark.parametrize("dtype,H,V,B,Ws", [("bf16", 640, 1024, 1, (1, 3, 5, 16)), ("bf16", 128, 77, 13, (1, 6, 7, 11)), ("bf16", 256, 40, 19, (2, 9, 16)),
+                                            ("bf16", 384, 1000, 37, (1, 3, 12, 16)), ("f32", 640, 333, 9, (3, 5, 11)), ("f32", 64, 32, 5, (1, 6, 9))])
+def test_what_a_call_gives_does_not_depend_on_how_far_it_looks(dtype, H, V, B, Ws, bias):
+    """Labels, frames and every counter but the number of near-ties' lookups of option lookahead = 1 against 0, and of windows cut
+    by the last frame: lengths of every remainder."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    D = 64 if dtype == "bf16" else 68
+    cfg = wi.WindConfig("groups", 90 + B, B, 40, 95, D, 64, 1, H, H, V, dtype, (4,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=bias, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    lens[B // 2] = 1 if B > 4 else lens[B // 2]
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    labels = None
+    for W in Ws:
+        runs = []
+        for look in (0, 1):
+            m.set_option("lookahead", look)
+            toks, frs = m.decode(d_enc, d_len, W, cfg.S)
+            assert m.loop_info()[0] > 0
+            st = m.stats()
+            assert st.rechecks <= st.rows
+            runs.append(([t.tolist() for t in toks], [f.tolist() for f in frs], st.iterations, st.windows, st.rows, st.useful_rows, st.labels,
+                         st.forced_advances, list(st.jump_hist)))
+        assert runs[0] == runs[1]
+        assert sum(runs[0][8]) == runs[0][3] and sum(k * n for k, n in enumerate(runs[0][8])) == int(lens.sum())   # every frame is passed once
+        assert labels is None or labels == runs[0][:2]
+        labels = runs[0][:2]
+    m.close()
+
+
 @pytest.mark.parametrize("dtype,H,V,B,W", [("bf16", 640, 1024, 3, 8), ("bf16", 128, 31, 8, 16), ("bf16", 512, 77, 1, 5), ("f32", 640, 1000, 2, 16),
                                            ("f32", 384, 31, 5, 4), ("f32", 128, 97, 3, 4), ("f32", 64, 32, 2, 7), ("f32", 64, 128, 1, 4)])
 def test_frames_that_are_not_finite(dtype, H, V, B, W):
