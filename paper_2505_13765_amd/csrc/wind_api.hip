@@ -1291,7 +1291,7 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     for (const GroupInstance &i : kGroupInstances)
       if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     for (const BeamInstance &i : kBeamInstances)
-      for (auto k : {i.search, i.scores})
+      for (auto k : {i.search, i.scores, i.phases[0], i.phases[1], i.phases[2], i.phases[3]})
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     const void *loop_instances[] = {(const void *)wind_loop_kernel<0>, (const void *)wind_loop_kernel<1>, (const void *)wind_loop_kernel<2>,
                                     (const void *)wind_loop_kernel<3>, (const void *)wind_loop_kernel<4>, (const void *)wind_loop_kernel<5>};
@@ -1417,6 +1417,9 @@ int wind_beam_window_scores_static(wind_model *m, const float *enc_window, int n
   rc = static_scratch_address(&base);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
+  static_assert(sizeof(BeamGroupMem) <= WIND_STATIC_SCRATCH_BYTES, "one group at least");
+  if (beam_scores_shape(m, enc_window, n, dec_out, Bh, K))   // the sums of wind_beam_window_scores, which has the resident workgroups for these
+    return beam_scores_phases(m, reinterpret_cast<BeamGroupMem *>(base), WIND_STATIC_SCRATCH_BYTES, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
   BeamWs ws;
   beam_carve(m, (size_t)n, (size_t)Bh, rows, base, &ws);
   // The buffer keeps the last call's contents.  The one place read before it is written: the rows

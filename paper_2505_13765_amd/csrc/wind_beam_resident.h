@@ -68,6 +68,7 @@ struct BeamResDev {
   int n, Bh, K, split;
   int *out_labels, *out_jumps;
   float *out_scores;
+  int grp0, grp1;                       // as several launches: groups of this one, whose exchange words start at mem
   unsigned written;                     // hypotheses written by all such launches (BeamGroupMem::word[1] of group 0) once this one is through
 };
 
@@ -702,11 +703,20 @@ struct BeamRes {
 
   // One scoring step: group grp takes hypotheses grp, grp + kGroups, ...  Its workgroups project the window's frames and those hypotheses
   // (every group all the frames: 26 MFLOP, less than telling the other XCDs), each its units, and go on as in a pass of the search.
+  // PHASE 0 to 3: the same in four launches, each up to an exchange and then the next, for calls that nobody waits for: every word is there
+  // when it is asked for, no two workgroups have to meet, and every sum is the one launch's, to the bit
+  template <int PHASE>
   __device__ __forceinline__ void score(int grp) {
     const unsigned seq = r.first;
     const int n = r.n, Bg = (r.Bh - grp + kGroups - 1) / kGroups, D = m.D, u0 = g * UPW;
     float *encp = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ecache) + (Cfg::oEncp - Cfg::oE));
-    announce();
+    if constexpr (PHASE < 0) {
+      announce();
+    } else {
+      if (tid == 0) { flags[0] = 1; flags[1] = 0; }
+      group_barrier();
+    }
+    if constexpr (PHASE <= 0) {
     // Everything the launch reads is asked for before any of it is looked at (start to the projections 8.9 -> 8.2 us).  Frames: K split over the
     // eight waves in steps of 32, four at a time; rounded to bf16 as everywhere in bf16 models
     f32x4 acc[Cfg::PT];
@@ -737,7 +747,7 @@ struct BeamRes {
       }
     }
     load_w_pred();
-    load_w_out();
+    if constexpr (PHASE < 0) load_w_out();
     __builtin_amdgcn_sched_barrier(0);
     for (int k0 = wave * 32; k0 < D; k0 += 1024) {
       if (k0 >= 1024) ask_frames(k0);
@@ -757,7 +767,8 @@ struct BeamRes {
       products<Cfg::PT>(wp, v, pacc);
       put_partial<Cfg::PT, Cfg::PT>(predp, 0, pacc);
     }
-    meet();         // a barrier: the partial sums are in LDS
+    if constexpr (PHASE < 0) meet();   // a barrier: the partial sums are in LDS
+    else group_barrier();
     if (!flags[0] || flags[1]) return;
     for (int i = tid; i < (n + Bg) * UPW; i += 512) {
       const int e = i / UPW, row = i - e * UPW;
@@ -770,13 +781,19 @@ struct BeamRes {
         beam_st(&x.px[(e - n) * H + u0 + row], __float_as_uint(sum4(predp, 16 * Cfg::PT, row, e - n) + m.b_pred[u0 + row]), seq);
       }
     }
+    }
+    if constexpr (PHASE == 0) return;
     // No wait of this launch may outlast its results, the words are the next one's then: whoever has no part in them leaves
-    if (32 * g > m.V && g >= Bg * n) return;   // no column, no row
-    fetch_rows(x.ex, ecache, n, seq);
-    fetch_rows(x.px, pfull, Bg, seq);
-    group_barrier();
-    logits(Bg * n, n, r.split, seq);
-    soft_max_rows(Bg * n, r.K, false, seq);
+    if (PHASE < 0 && 32 * g > m.V && g >= Bg * n) return;   // no column, no row
+    if constexpr (PHASE < 0 || PHASE == 1) {
+      if constexpr (PHASE == 1) load_w_out();
+      fetch_rows(x.ex, ecache, n, seq);
+      fetch_rows(x.px, pfull, Bg, seq);
+      group_barrier();
+      logits(Bg * n, n, r.split, seq);
+    }
+    if constexpr (PHASE < 0 || PHASE == 2) soft_max_rows(Bg * n, r.K, false, seq);
+    if constexpr (PHASE == 1 || PHASE == 2) return;
     if (HALF == 1 && w4 == 1 && g < Bg) {
       const int b = grp + kGroups * g;
       bool put = false;
@@ -788,7 +805,7 @@ struct BeamRes {
         put = true;
       });
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // they are in memory: the last hypothesis of the launch tells the host
-      if (put && lane == 0 && __hip_atomic_fetch_add(&r.mem[0].word[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == r.written)
+      if (PHASE < 0 && put && lane == 0 && __hip_atomic_fetch_add(&r.mem[0].word[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == r.written)
         __hip_atomic_store(r.host_exit, r.session << 2 | kBeamExitAsked, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
@@ -811,8 +828,16 @@ __global__ __launch_bounds__(512) void beam_scores_kernel(ModelDev m, BeamResDev
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;
   if (grp >= r.Bh) return;
-  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp], smem_raw, g).score(grp);
-  else BeamRes<KS, 1>(m, r, r.mem[grp], smem_raw, g).score(grp);
+  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp], smem_raw, g).template score<-1>(grp);
+  else BeamRes<KS, 1>(m, r, r.mem[grp], smem_raw, g).template score<-1>(grp);
+}
+template <int KS, int PHASE>
+__global__ __launch_bounds__(512) void beam_scores_phase_kernel(ModelDev m, BeamResDev r) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;
+  if (grp >= r.Bh || grp < r.grp0 || grp >= r.grp1) return;
+  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp - r.grp0], smem_raw, g).template score<PHASE>(grp);
+  else BeamRes<KS, 1>(m, r, r.mem[grp - r.grp0], smem_raw, g).template score<PHASE>(grp);
 }
 
 }  // namespace wind

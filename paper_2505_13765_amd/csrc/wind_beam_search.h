@@ -187,10 +187,14 @@ void beam_enqueue_decoder_step(wind_model *m, int rows, const int *parent, const
 struct BeamInstance {
   void (*search)(ModelDev, BeamResDev);
   void (*scores)(ModelDev, BeamResDev);
+  void (*phases[4])(ModelDev, BeamResDev);
   size_t smem;
 };
 template <int KS>
-constexpr BeamInstance beam_instance() { return {beam_search_kernel<KS>, beam_scores_kernel<KS>, BeamResCfg<KS>::smem}; }
+constexpr BeamInstance beam_instance() { return {beam_search_kernel<KS>,
+                                                                   beam_scores_kernel<KS>,
+                                                                   {beam_scores_phase_kernel<KS, 0>, beam_scores_phase_kernel<KS, 1>, beam_scores_phase_kernel<KS, 2>, beam_scores_phase_kernel<KS, 3>},
+                                                                   BeamResCfg<KS>::smem}; }
 const BeamInstance kBeamInstances[] = {beam_instance<1>(), beam_instance<2>(), beam_instance<3>(), beam_instance<4>(), beam_instance<5>()};   // by width / 128
 // Models that resident workgroups hold: bf16, one LSTM layer as wide as the joiner and of up to 640 units, up to 1024 labels, as the
 // resident groups of the decoder; and the options that ask for those
@@ -308,15 +312,37 @@ struct BeamSession {
   }
 };
 
+// Scoring steps that the resident workgroups' kernel computes: the loads are 16 bytes wide
+bool beam_scores_shape(const wind_model *m, const float *enc_window, int n, const float *dec_out, int Bh, int K) {
+  return Bh <= kGroups * kBeamResHyps && n <= kBeamResFrames && K <= kBeamResHyps && beam_resident_model(m) && ((uintptr_t)enc_window | (uintptr_t)dec_out) % 16 == 0;
+}
+
+// The same sums in launches that wait for nobody (see BeamRes::score), with as many groups at a time as `mem` has room for
+int beam_scores_phases(wind_model *m, BeamGroupMem *mem, size_t bytes, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
+                       int32_t *out_jumps, float *out_scores, hipStream_t s) {
+  BeamResDev r{};
+  r.mem = mem;
+  r.session = r.first = 1;
+  r.spin_limit = kGroupStartPolls;
+  r.enc = enc_window; r.dec = dec_out;
+  r.n = n; r.Bh = Bh; r.K = K; r.split = m->opt_beam_exact ? 1 : 0;
+  r.out_labels = out_labels; r.out_jumps = out_jumps; r.out_scores = out_scores;
+  const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
+  const int step = (int)std::min<size_t>(bytes / sizeof(BeamGroupMem), kGroups);
+  for (r.grp0 = 0; r.grp0 < std::min(Bh, kGroups); r.grp0 = r.grp1) {
+    r.grp1 = r.grp0 + step;
+    for (auto phase : k.phases) phase<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
+  }
+  return check_launch("beam scoring step");
+}
+
 // One scoring step as a single launch.  `done`: the results are in the caller's buffers; else (the workgroups could not meet) nothing of it
 // runs any more and the caller takes the launches.
 int beam_scores_resident(wind_model *m, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
                          int32_t *out_jumps, float *out_scores, hipStream_t s, bool *done) {
   *done = false;
-  // the loads are 16 bytes wide; a captured call has nobody to wait for it
-  if (Bh > kGroups * kBeamResHyps || n > kBeamResFrames || K > kBeamResHyps || !beam_resident_model(m) || ((uintptr_t)enc_window | (uintptr_t)dec_out) % 16 ||
-      stream_capturing(s))
-    return WIND_OK;
+  // a captured call has nobody to wait for it
+  if (!beam_scores_shape(m, enc_window, n, dec_out, Bh, K) || stream_capturing(s)) return WIND_OK;
   int rc = beam_resident_reserve(m, s);
   if (rc) return rc;
   BeamResident &br = m->beam_res;
