@@ -134,8 +134,10 @@ struct wind_model {
   CallDev call{};
   // loop replay
   hipStream_t cap_stream = nullptr;
-  hipGraph_t graph[2] = {nullptr, nullptr};            // [1]: the iterations with joint_wide_kernel
-  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+  // [1], [3], [5]: the iterations with joint_wide_kernel; [2], [3]: windows of kShortReach rows, [4], [5]: windows of W rows in a call that has
+  // had the former (see decode())
+  hipGraph_t graph[6] = {};
+  hipGraphExec_t graph_exec[6] = {};
   GraphKey graph_key{};
   bool graph_valid = false;
   int opt_enc_wide = 1;         // large calls: encoder projection on the 256-column tile core (where the model allows)
@@ -340,6 +342,7 @@ void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B) {
   c.emit_idx = (int *)(base + o_eidx); c.n_emit = (int *)(base + o_nemit);
   c.emit_list_tok = (int *)(base + o_eltok);
   c.slot_state = (int4 *)(base + o_slot); c.slot_count = (int *)(base + o_slotc);
+  c.win = c.win0 = 0; c.slot_win = nullptr;
   c.ticket = (unsigned *)(base + o_ticket);
   c.h = (float *)(base + o_h); c.c = (float *)(base + o_c); c.hn = (float *)(base + o_hn);
   c.hb_hi = (bf16_t *)(base + o_hb); c.hb_lo = c.hb_hi + st / 4; c.hbn_hi = c.hb_lo + st / 4; c.hbn_lo = c.hbn_hi + st / 4;
@@ -565,6 +568,14 @@ int wide_threshold_rows(const wind_model *m, int B, int W) {
   return (long long)B * W > thr ? thr : -1;
 }
 
+// Window rows above which a call's windows may be cut: what fills the chip with two row tiles of 64 per workgroup of the joint kernel, which takes
+// hardly longer for those than for a few.
+long long cut_rows(const wind_model *m) {
+  const int NT = (m->dev.V + WsCfg<1>::BN - 1) / WsCfg<1>::BN, fill = NT >= 256 ? 1 : 256 / NT;
+  return 2 * 64 * fill;
+}
+constexpr long long kCutReplays = 16, kCutLead = 3;
+
 // the output contraction with its row argmax folded in, for the window rows build_z_kernel wrote
 // (wide: in slab layout, for joint_wide_kernel)
 void enqueue_joint(wind_model *m, hipStream_t s, int parity, bool capturing, bool wide) {
@@ -588,10 +599,14 @@ int enqueue_iteration(wind_model *m, hipStream_t s, int parity, bool capturing, 
   const int max_rows = c.B * c.W;
   const int decide_threads = 64 * (c.W < 16 ? c.W : 16);
   if (m->dtype == WIND_BF16) {
+    const bool two = d.Hj <= 1024 && c.nparts > 64 && c.nparts <= 128 && c.W <= 16 && m->opt_decide_two;   // one row per wave, two key loads per lane
     launch(m, s, WIND_K_BUILD_Z, capturing, build_z_kernel, dim3((unsigned)((max_rows + 3) / 4)), dim3(256), 0, d, c, parity,
            wide ? 1 : 0, wide_threshold_rows(m, c.B, c.W));
     enqueue_joint(m, s, parity, capturing, wide);
-    if (d.Hj <= 1024 && c.nparts > 64 && c.nparts <= 128 && c.W <= 16 && m->opt_decide_two)   // one row per wave, two key loads per lane
+    if (c.win) {
+      const auto k = two ? decide_kernel<bf16_t, false, true, true> : d.Hj <= 1024 ? decide_kernel<bf16_t, false, false, true> : decide_kernel<bf16_t, true, false, true>;
+      launch(m, s, WIND_K_DECIDE, capturing, k, dim3((unsigned)c.B), dim3(decide_threads), 0, d, c, parity, 0);
+    } else if (two)
       launch(m, s, WIND_K_DECIDE, capturing, decide_kernel<bf16_t, false, true>, dim3((unsigned)c.B), dim3(decide_threads), 0, d, c, parity, 0);
     else if (d.Hj <= 1024)
       launch(m, s, WIND_K_DECIDE, capturing, decide_kernel<bf16_t, false>, dim3((unsigned)c.B), dim3(decide_threads), 0, d, c, parity, 0);
@@ -607,6 +622,27 @@ int enqueue_iteration(wind_model *m, hipStream_t s, int parity, bool capturing, 
   return enqueue_pred_step(m, s, capturing, false, parity);
 }
 
+// One graph of the loop, by its place in wind_model::graph
+int capture_graph(wind_model *m, int w) {
+  const CallDev base = m->call;
+  if (w >= 2) {
+    m->call.win = base.W;
+    m->call.win0 = (int)kCutLead * m->opt_unroll;   // decode() has those replays at the caller's window first
+    if (w < 4) m->call.W = kShortReach;
+  }
+  int rc = WIND_OK;
+  hipError_t e = hipStreamBeginCapture(m->cap_stream, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) {
+    for (int it = 0; it < m->opt_unroll && rc == WIND_OK; ++it) rc = enqueue_iteration(m, m->cap_stream, it & 1, true, w & 1);
+    e = hipStreamEndCapture(m->cap_stream, &m->graph[w]);
+  }
+  m->call = base;
+  if (rc) return rc;
+  if (e != hipSuccess) return fail(WIND_ERR_HIP, std::string("capture of the decode loop: ") + hipGetErrorString(e));
+  HIP_TRY(hipGraphInstantiate(&m->graph_exec[w], m->graph[w], nullptr, nullptr, 0));
+  return WIND_OK;
+}
+
 // The loop's graphs: `unroll` iterations with joint_ws_kernel, and, where the call can have iterations
 // for joint_wide_kernel, the same with that kernel (either graph is right for any row count).
 int ensure_graph(wind_model *m) {
@@ -614,7 +650,7 @@ int ensure_graph(wind_model *m) {
   key.call = m->call;
   key.unroll = m->opt_unroll;
   if (m->graph_valid && key == m->graph_key) return WIND_OK;
-  for (int g = 0; g < 2; ++g) {
+  for (int g = 0; g < 6; ++g) {
     if (m->graph_exec[g]) { (void)hipGraphExecDestroy(m->graph_exec[g]); m->graph_exec[g] = nullptr; }
     if (m->graph[g]) { (void)hipGraphDestroy(m->graph[g]); m->graph[g] = nullptr; }
   }
@@ -624,15 +660,8 @@ int ensure_graph(wind_model *m) {
   const bool want[2] = {wide_rows != 0, wide_rows >= 0};
   for (int w = 0; w < 2; ++w) {
     if (!want[w]) continue;
-    HIP_TRY(hipStreamBeginCapture(m->cap_stream, hipStreamCaptureModeThreadLocal));
-    int rc = WIND_OK;
-    for (int it = 0; it < m->opt_unroll && rc == WIND_OK; ++it) rc = enqueue_iteration(m, m->cap_stream, it & 1, true, w == 1);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(m->cap_stream, &g);
-    if (rc != WIND_OK) { if (g) (void)hipGraphDestroy(g); return rc; }
-    if (e != hipSuccess) return fail(WIND_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-    m->graph[w] = g;
-    HIP_TRY(hipGraphInstantiate(&m->graph_exec[w], m->graph[w], nullptr, nullptr, 0));
+    const int rc = capture_graph(m, w);
+    if (rc) return rc;
   }
   m->graph_key = key;
   m->graph_valid = true;
@@ -898,6 +927,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   // Behind an asynchronous call no host decodes it again if the groups cannot meet: it takes them only where no two workgroups have to
   // (one per utterance), or where the other choice is a kernel whose workgroups have to meet as well.
   if (async && gi && gi->gw != 1 && !use_loop) gi = nullptr;
+  // Calls whose windows may be cut (see the loop below); res_state has no use there (lists_atomic) and the room.  An asynchronous call's caller
+  // counts iterations
+  if (!gi && !use_loop && !async && c.lists_atomic && m->opt_lookahead && m->opt_graph && !m->opt_profile && !m->opt_host_sync && W >= 2 * kShortReach &&
+      T >= 8 * m->opt_unroll && B == c.slot_stride && (long long)B * W > cut_rows(m))
+    c.slot_win = reinterpret_cast<int2 *>(c.res_state);
   const bool capturing = async && stream_capturing(s);
   if (gi || use_loop) {
     if (m->device < 0 || m->device >= kMaxDevices) return fail(WIND_ERR_UNSUPPORTED, "device ordinal above 63");
@@ -1011,6 +1045,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     return rc;
   }
   const int U = m->opt_unroll;
+  long long split_replays = 0;
   const bool use_graph = m->opt_graph && !m->opt_profile && !m->opt_host_sync;   // events cannot sit between graph nodes
   // Which joint kernel the iterations of a block of U run (either is right for any row count; the choice is
   // about speed): joint_wide_kernel while the call has more than wide_rows window rows per iteration.  The
@@ -1066,17 +1101,55 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     }
   } else {
     // Launch ahead by what the previous call of the same shape needed, then poll once per replay.
-    long long ahead = 1;
-    if (m->prev_B == B && m->prev_T == T && m->prev_W == W && m->prev_iters > 0) ahead = m->prev_iters / U;
+    long long ahead = same_shape ? m->prev_iters / U : 1;
     if (ahead < 1) ahead = 1;
+    // Windows of half the rows where most labels lie in those: rows behind a window's first label are thrown away, and the joint kernel of a large
+    // batch takes as long as its rows, while a window whose first kShortReach rows are blank takes a second iteration.  A call with rows enough for
+    // that is looked at after its first replay, with kCutLead replays queued so that the GPU has work meanwhile, and, once cut, every kCutReplays;
+    // `late` is the share of its windows since the last look that had no label in time.  Results and counters are those of the caller's
+    // window either way (decide_kernel<.., SPLIT>).  4096 labels, a label on every second
+    // evaluation, W = 16, 100 to 1000 frames: 256 utterances 33.5 -> 30.1 ms, 128 26.5 -> 26.1, 80 25.1 -> 25.2; not cut (8192 labels, blanks 85 %): 128
+    // utterances 31.7 -> 31.8, 70 13.0 -> 13.0.
+    const long long planned = ahead;
+    bool cut = false, split = false;   // cut: windows of kShortReach rows now; split: so some time in this call
+    unsigned long long seen_windows = 0, seen_late = 0;
+    const auto look = [&]() {
+      unsigned long long late = 0;
+      for (int j = kShortReach; j <= W; ++j) late += m->h_stats[kStatJump0 + j];
+      const unsigned long long windows = m->h_stats[ST_WINDOWS];
+      cut = (late - seen_late) * (cut ? 4 : 8) < windows - seen_windows && (long long)*m->h_flag * W > cut_rows(m);
+      split = split || cut;
+      seen_windows = windows;
+      seen_late = late;
+    };
     const long long max_launches = (max_iters + 2 * U) / U + 2;
     long long launches = 0;
     bool polled = false;
+    if (c.slot_win) {
+      for (; launches < kCutLead; ++launches) {
+        HIP_TRY(hipGraphLaunch(m->graph_exec[(same_shape ? wide_by_history(launches) : wide_by_count(B)) ? 1 : 0], s));
+        if (launches > 0) continue;
+        HIP_TRY(hipMemcpyAsync(m->h_flag, c.n_active, sizeof(int), hipMemcpyDeviceToHost, s));
+        rc = enqueue_stats_copy(m, s);
+        if (rc) return rc;
+        HIP_TRY(hipEventRecord(m->ev_call[2], s));
+      }
+      HIP_TRY(hipEventSynchronize(m->ev_call[2]));
+      look();
+      polled = split;
+      ahead = std::max(planned - launches, 1ll);
+      if (split) ahead = std::min(ahead, kCutReplays - launches);
+    }
     for (;;) {
       for (long long i = 0; i < ahead; ++i, ++launches) {
-        const bool wide = polled ? wide_by_count(*m->h_flag) : wide_by_history(launches);
+        const bool wide = polled ? wide_by_count(cut ? (long long)*m->h_flag * kShortReach / W : *m->h_flag) : wide_by_history(launches);
+        const int g = (wide ? 1 : 0) + (cut ? 2 : split ? 4 : 0);
         if (use_graph) {
-          HIP_TRY(hipGraphLaunch(m->graph_exec[wide ? 1 : 0], s));
+          if (!m->graph_exec[g]) {
+            rc = capture_graph(m, g);
+            if (rc) return rc;
+          }
+          HIP_TRY(hipGraphLaunch(m->graph_exec[g], s));
         } else {
           for (int it = 0; it < U; ++it) {
             rc = enqueue_iteration(m, s, it & 1, false, wide);
@@ -1092,7 +1165,14 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       if (rc) return rc;
       HIP_TRY(hipStreamSynchronize(s));
       prof_collect(m);
-      if (*m->h_flag == 0) break;
+      if (*m->h_flag == 0) {
+        if (split) split_replays = launches;
+        break;
+      }
+      if (split) {
+        if (launches % kCutReplays == 0) look();
+        if (launches < planned) ahead = std::min(planned - launches, kCutReplays - launches % kCutReplays);
+      }
       if (launches > max_launches) return fail(WIND_ERR_HIP, "decode loop did not terminate");
     }
   }
@@ -1104,7 +1184,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     if (n) HIP_TRY(hipMemcpy(m->joint_rows.data(), c.iter_rows, n * sizeof(int), hipMemcpyDeviceToHost));
   }
   m->prev_B = B; m->prev_T = T; m->prev_W = W;
-  m->prev_iters = m->last_stats.iterations;
+  m->prev_iters = split_replays ? std::max((split_replays - 1) * U, 1ll) : m->last_stats.iterations;   // iterations launched: windows may have taken two
   m->prev_wide_iters = m->last_wide_iters;
   if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
   return rc;
@@ -1336,7 +1416,7 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
 int wind_free(wind_model *m) {
   if (!m) return WIND_OK;
   (void)hipDeviceSynchronize();
-  for (int g = 0; g < 2; ++g) {
+  for (int g = 0; g < 6; ++g) {
     if (m->graph_exec[g]) (void)hipGraphExecDestroy(m->graph_exec[g]);
     if (m->graph[g]) (void)hipGraphDestroy(m->graph[g]);
   }

@@ -623,7 +623,9 @@ __device__ __forceinline__ void compact_lists(const CallDev &c, int parity, int 
 // WIDE: joint hidden sizes above 1024 (the near-tie path then keeps the hidden vector in more registers).
 // TWO: rows of 65 .. 128 column parts in windows of at most one row per wave: each wave asks for both halves
 // of its row's keys in the first round trip (and for no rows beyond its first, which it does not have).
-template <class WT, bool WIDE, bool TWO = false>
+// SPLIT: the iterations' window, W, is not the caller's, c.win: the counters are those of windows of the caller's size (an iteration may end
+// inside one), as resident groups have them.
+template <class WT, bool WIDE, bool TWO = false, bool SPLIT = false>
 __global__ __launch_bounds__(1024) void decide_kernel(ModelDev m, CallDev c, int parity, int exact_mode) {
   __shared__ DecideShared sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
@@ -634,6 +636,8 @@ __global__ __launch_bounds__(1024) void decide_kernel(ModelDev m, CallDev c, int
   const int na = c.n_active[parity];
   const int4 st = c.slot_state[parity * c.slot_stride + a];
   const int cnt = c.slot_count[parity * c.slot_stride + a];
+  int2 win = make_int2(0, 0);
+  if constexpr (SPLIT) win = c.slot_win[parity * c.slot_stride + a];
   using RA = RowsAheadT<TWO ? 1 : kRowsAhead, TWO>;
   RA ahead;
 #pragma unroll
@@ -705,10 +709,25 @@ __global__ __launch_bounds__(1024) void decide_kernel(ModelDev m, CallDev c, int
       const int flag = sh.flag[0];
       const unsigned ev = sh.event[0];
       const int k = threadIdx.x;
+      unsigned whole = 0u, closes = 1u, rows = ev & 127u, useful = (ev >> 7) & 127u, jump = (ev >> 14) & 127u;
+      if constexpr (SPLIT) {   // `whole` blank windows, and one that a label or the last frame closes, `rem` blank frames into it, or that stays open
+        const int n = (int)rows, first = (ev >> 28) & 1u ? (int)useful - 1 : -1, seen = win.y + (first < 0 ? n : first);
+        whole = seen >= c.win;
+        const int rem = seen - (whole ? c.win : 0);
+        closes = first >= 0 || (rem > 0 && st.y + n == st.z);
+        rows = first < 0 ? rem : min(c.win, st.z - (st.y + first - rem));
+        useful = first < 0 ? rem : rem + 1;
+        jump = rem + ((ev >> 29) & 1u);
+        win = make_int2(win.x + (int)(whole + closes), closes ? 0 : rem);
+        if (!closes) rows = useful = 0u;
+        rows += whole * c.win;
+        useful += whole * c.win;
+      }
       if (k == 0 && (flag & 1)) {
         const int pos = atomicAdd(&c.n_active[parity ^ 1], 1);
         c.slot_state[(parity ^ 1) * c.slot_stride + pos] = ns;
         c.slot_count[(parity ^ 1) * c.slot_stride + pos] = sh.cnt[0];
+        if constexpr (SPLIT) c.slot_win[(parity ^ 1) * c.slot_stride + pos] = win;
       }
       if (k == 1 && (flag & 2)) {
         const int pos = atomicAdd(c.n_emit, 1);
@@ -718,15 +737,21 @@ __global__ __launch_bounds__(1024) void decide_kernel(ModelDev m, CallDev c, int
       unsigned long long add = 0ull;
       int which = -1;
       switch (k) {
-        case 2: which = ST_WINDOWS; add = 1ull; break;
-        case 3: which = ST_ROWS; add = ev & 127u; break;
-        case 4: which = ST_USEFUL; add = (ev >> 7) & 127u; break;
+        case 2: which = ST_WINDOWS; add = whole + closes; break;
+        case 3: which = ST_ROWS; add = rows; break;
+        case 4: which = ST_USEFUL; add = useful; break;
         case 5: which = ST_RECHECK; add = (ev >> 21) & 127u; break;
         case 6: which = ST_LABELS; add = (ev >> 28) & 1u; break;
         case 7: which = ST_FORCED; add = (ev >> 29) & 1u; break;
         case 8: which = ST_OVERFLOW; add = (ev >> 30) & 1u; break;
-        case 9: which = kStatJump0 + (int)((ev >> 14) & 127u); add = 1ull; break;
-        case 10: which = ST_ITER; add = a == 0 ? 1ull : 0ull; break;
+        case 9: which = kStatJump0 + (int)jump; add = closes; break;
+        case 10:
+          if constexpr (!SPLIT) { which = ST_ITER; add = a == 0 ? 1ull : 0ull; }
+          else if (!(flag & 1)) atomicMax(&c.stats[ST_ITER], (unsigned long long)(c.win0 + win.x));
+          break;
+        case 11:
+          if constexpr (SPLIT) { which = kStatJump0 + c.win; add = whole; }
+          break;
         default: break;
       }
       if (which >= 0 && add) atomicAdd(&c.stats[which], add);

@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void init_state_kernel(ModelDev m, CallDev c) 
         const int pos = na + __popcll(mk & ((1ull << tid) - 1ull));
         c.slot_state[pos] = make_int4(b, 0, len, 0);
         c.slot_count[pos] = 0;
+        if (c.slot_win) c.slot_win[pos] = c.slot_win[c.slot_stride + pos] = make_int2(0, 0);
       }
       na += __popcll(mk);
     }

@@ -11,6 +11,7 @@ constexpr int kMaxLayers = 4;
 constexpr int kMaxWindow = 64;
 constexpr int kTinyRows = 64;   // slots the resident loop kernel keeps in LDS (it runs far fewer)
 constexpr int kStatJump0 = 9;  // index of jump_hist[0] in the device counter array
+constexpr int kShortReach = 8;              // see decode()
 constexpr int kNumStats = kStatJump0 + kMaxWindow + 1;
 // behind the counters, in the same array: device time stamps of the resident groups' calls (start of the call, start of the loop, end)
 constexpr int kStatStart = kNumStats, kStatLoop = kNumStats + 1, kStatEnd = kNumStats + 2, kStatWords = kNumStats + 3;
@@ -47,6 +48,9 @@ struct ModelDev {
 // One decode call: caller buffers, sizes, and the library's state arrays.
 struct CallDev {
   int B, T, W, S, cap;
+  int win, win0;                // decide_kernel<.., SPLIT>: the caller's window where an iteration's, W, is another; windows of every
+                                //   active utterance before the first such iteration
+  int2 *slot_win;               // [2][slot_stride] (windows since then, blank frames of the open one)
   const float *enc;             // [B,T,D]
   const int *lengths;           // [B] as given
   int *out_tokens, *out_frames, *out_counts;

@@ -348,3 +348,31 @@ def test_completing_an_asynchronous_decode_waits_for_the_stream():
     m.stats()
     assert behind.query()
     m.close()
+
+
+# large batches of models that are not in groups: half windows where most labels lie early (bias 1: a label on almost every frame), whole ones elsewhere, and
+# both in one call (frames of silence behind the first part)
+@pytest.mark.parametrize("V,B,W,bias,silent", [(4100, 70, 16, 1.0, False), (4100, 70, 16, 6.0, False), (4100, 80, 17, 2.0, True), (8200, 64, 16, 1.0, True)])
+def test_large_batches_count_windows_of_the_callers_size(V, B, W, bias, silent):
+    """Labels, frames and every counter but the number of near-ties' lookups of option lookahead = 1 against 0, calls repeated."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("cut", 70 + B, B, 150, 700, 64, 64, 1, 128, 128, V, "bf16", (4,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=bias, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    if silent:
+        enc[:, 150:] = 0.0
+    lens[3] = 1
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    runs = []
+    for look in (0, 1, 1):
+        m.set_option("lookahead", look)
+        toks, frs = m.decode(d_enc, d_len, W, cfg.S)
+        assert m.loop_info()[0] == 0
+        st = m.stats()
+        runs.append(([t.tolist() for t in toks], [f.tolist() for f in frs], st.iterations, st.windows, st.rows, st.useful_rows, st.labels,
+                     st.forced_advances, list(st.jump_hist)))
+    print(f"{runs[0][3]} windows, late: {sum(runs[0][8][8:]) / runs[0][3]:.3f}", flush=True)
+    assert runs[0] == runs[1] == runs[2]
+    m.close()
