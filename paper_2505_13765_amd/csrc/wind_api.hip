@@ -941,6 +941,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   unsigned long long turn = 0;
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
+    gd.limited = gd.max_iters < max_iters;
     // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where another kernel can
     // decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;

@@ -173,7 +173,7 @@ __device__ __forceinline__ void group_touch(const void *src, unsigned lds) {
 // The part of the loop's state that every wave keeps for itself: lane a holds slot a.
 struct GroupLane {
   int b, t, len, sym, cnt;   // utterance, frame, length, labels on the frame, labels so far (len = t = 0: slot empty)
-  int wc;                    // windows of the caller's size so far
+  int wc;                    // windows of the caller's size so far (wc, ph: in the wave that writes, and in all of limited calls)
   int ph;                    // blank frames of the open one that earlier iterations have seen (0: none is open)
   int rpos;                  // t modulo 2 W: the frame's row in its ring of projected frames
   int ld0, ld;               // frames loaded (or asked for) before the last decision, and now
@@ -204,7 +204,8 @@ __device__ __forceinline__ GroupLane group_first_slots(const CallDev &c, const G
 // Frames of the slot's window in this iteration: up to c.W, the reach (see group_shape), which may hold several windows of the caller's
 // size, gd.win, or end inside one; no more of those than the call may take.
 __device__ __forceinline__ int group_window(const CallDev &c, const GroupDev &gd, const GroupLane &sl) {
-  return min(min(c.W, sl.len - sl.t), gd.win * min(gd.max_iters - sl.wc, kGroupMaxW) - sl.ph);
+  const int n = min(c.W, sl.len - sl.t);
+  return gd.limited ? min(n, gd.win * min(gd.max_iters - sl.wc, kGroupMaxW) - sl.ph) : n;
 }
 
 // The frames that the slots of row tile rt have come to need (from ld0 to ld), into their rings of 2 W rows, one frame per wave
@@ -246,47 +247,52 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
   emits = false;
   fresh_slot = false;
   if (nwin > 0) {
-    // What that is in windows of the caller's size, which start where the last label or the last whole window left off: `full` blank ones,
-    // and one that a label or the last frame closes, `rem` blank frames into it, or that stays open
-    const int seen = sl.ph + (first < 0 ? nwin : first), full = (int)(((unsigned)seen * gd.win_inv) >> 16), rem = seen - full * gd.win;
-    const bool closes = first >= 0 || (rem > 0 && sl.t + nwin == sl.len);
-    const int n_last = first < 0 ? rem : min(gd.win, sl.len - (sl.t + first - rem));
-    const int looked = first < 0 ? W : min(W, (full + 1) * gd.win - sl.ph);   // rows of the frames up to the end of the window that decided
-    const int rech = __popc((unsigned)(need >> oshift) & segm & ((1u << looked) - 1u));
+    const int t0 = sl.t;
     const WindowOutcome wo = window_outcome(c, make_int4(sl.b, sl.t, sl.len, sl.sym), sl.cnt, nwin, first, tok, V, 0, writer);
     const int adv = wo.slot.y - sl.t;
     sl.t = wo.slot.y; sl.sym = wo.slot.w; sl.cnt = wo.cnt;
     sl.rpos += adv;
     if (sl.rpos >= W2) sl.rpos -= W2;
-    sl.wc += full + closes;
-    sl.ph = closes ? 0 : rem;
     sl.ld0 = sl.ld;
     sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
-    const bool cut = (wo.flag & 1) && sl.wc >= gd.max_iters, done = !(wo.flag & 1) || cut;
-    if (writer) {
-      // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
-      // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
-      const unsigned ev = wo.ev, forced = (ev >> 29) & 1u;
-      auto add = [&](int which, unsigned v) {
-        const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + which);
-        asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(v) : "memory");
-      };
-      const int blanks = full * gd.win;
-      add(ST_WINDOWS, (unsigned)(full + closes));
-      add(ST_ROWS, (unsigned)(blanks + (closes ? n_last : 0)));
-      add(ST_USEFUL, (unsigned)(blanks + (first >= 0 ? rem + 1 : closes ? rem : 0)));
-      add(ST_RECHECK, (unsigned)rech);
-      add(ST_LABELS, (ev >> 28) & 1u);
-      add(ST_FORCED, forced);
-      add(ST_OVERFLOW, (ev >> 30) & 1u);
-      add(kStatJump0 + gd.win, (unsigned)full);
-      add(kStatJump0 + rem + (int)forced, closes ? 1u : 0u);
-      if (done) {
-        const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + ST_ITER);
-        asm volatile("ds_max_u32 %0, %1" ::"v"(at), "v"(sl.wc) : "memory");
+    bool cut = false;
+    if (writer || gd.limited) {   // behind the state that everybody waits for: 50 ns of an iteration where every wave did this first
+      // What that is in windows of the caller's size, which start where the last label or the last whole window left off: `full` blank ones,
+      // and one that a label or the last frame closes, `rem` blank frames into it, or that stays open
+      const int seen = sl.ph + (first < 0 ? nwin : first), full = (int)(((unsigned)seen * gd.win_inv) >> 16), rem = seen - full * gd.win;
+      const bool closes = first >= 0 || (rem > 0 && t0 + nwin == sl.len);
+      const int n_last = first < 0 ? rem : min(gd.win, sl.len - (t0 + first - rem));
+      const int looked = first < 0 ? W : min(W, (full + 1) * gd.win - sl.ph);   // rows of the frames up to the end of the window that decided
+      const int rech = __popc((unsigned)(need >> oshift) & segm & ((1u << looked) - 1u));
+      sl.wc += full + closes;
+      sl.ph = closes ? 0 : rem;
+      cut = gd.limited && (wo.flag & 1) && sl.wc >= gd.max_iters;
+      if (writer) {
+        // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
+        // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
+        const unsigned ev = wo.ev, forced = (ev >> 29) & 1u;
+        auto add = [&](int which, unsigned v) {
+          const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + which);
+          asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(v) : "memory");
+        };
+        const int blanks = full * gd.win;
+        add(ST_WINDOWS, (unsigned)(full + closes));
+        add(ST_ROWS, (unsigned)(blanks + (closes ? n_last : 0)));
+        add(ST_USEFUL, (unsigned)(blanks + (first >= 0 ? rem + 1 : closes ? rem : 0)));
+        add(ST_RECHECK, (unsigned)rech);
+        add(ST_LABELS, (ev >> 28) & 1u);
+        add(ST_FORCED, forced);
+        add(ST_OVERFLOW, (ev >> 30) & 1u);
+        add(kStatJump0 + gd.win, (unsigned)full);
+        add(kStatJump0 + rem + (int)forced, closes ? 1u : 0u);
+        if (!(wo.flag & 1) || cut) {
+          const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + ST_ITER);
+          asm volatile("ds_max_u32 %0, %1" ::"v"(at), "v"(sl.wc) : "memory");
+        }
+        if (cut) atomicAdd(&c.n_active[0], 1);
       }
-      if (cut) atomicAdd(&c.n_active[0], 1);
     }
+    const bool done = !(wo.flag & 1) || cut;
     emits = (wo.flag & 2) && !done;
     if (done) {   // the slot's next utterance, or nothing
       fresh_slot = sl.nb >= 0;
