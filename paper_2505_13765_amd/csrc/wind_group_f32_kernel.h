@@ -324,8 +324,12 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
           }
       }
       // ---- LSTM step: thread (emitting slot, gate row of this workgroup's units)
-      for (int i = tid; i < n_em * NR; i += 512) {
-        const int le = i / NR, li = i - le * NR;
+      // A thread has one at most.  As a loop over the threads' items it left by its last lane into a block where, with 640 units, the compiler
+      // put the constant 1 into a register before it took the lanes back: a wait that gave up then stored whatever was there
+      // as its failure
+      static_assert(SL * NR <= 512 && SL * PPW <= 512, "a thread each");
+      if (tid < n_em * NR) {
+        const int le = tid / NR, li = tid - le * NR;
         const int s = le == 0 ? es[0] : le == 1 ? es[1] : le == 2 ? es[2] : es[3], tk = le == 0 ? et[0] : le == 1 ? et[1] : le == 2 ? et[2] : et[3];
         const float pre = recs[s * NR + li] + m.emb_gates[(unsigned)tk * (4u * H) + (unsigned)(unit0 * 4 + li)];   // fits 32 bits: checked by the host
         const float act = (li & 3) == 2 ? tanhf(pre) : 1.f / (1.f + expf(-pre));
@@ -390,8 +394,8 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         for (int t = 0; t < Cfg::PSET; ++t) row_sums(t, e);
       }
       group_barrier();   // B3: partial sums of the projection rows
-      for (int i = tid; i < n_em * PPW; i += 512) {
-        const int e = i / PPW, row = i - e * PPW;
+      if (tid < n_em * PPW) {
+        const int e = tid / PPW, row = tid - e * PPW;
         const float v = group_sum8([&](int w) { return partl[(w * SL + e) * 64 * NSET + row]; });
         const int s = e == 0 ? es[0] : e == 1 ? es[1] : e == 2 ? es[2] : es[3];
         put(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp);
