@@ -747,17 +747,20 @@ bool loop_kernel_shape(const wind_model *m, int B, int T, int W, LoopDev *lp, si
 
 // ---- resident groups (wind_group_kernel, wind_group_f32_kernel)
 struct GroupInstance {
-  void (*kernel)(ModelDev, CallDev, GroupDev);
+  void (*kernel[3])(ModelDev, CallDev, GroupDev);   // kGroupMany, kGroupOne, kGroupLimited; null: no such call comes to this shape
   size_t smem;
   int dtype, H, ct, gw;
 };
 template <int KS, int CT, int GW>
 constexpr GroupInstance group_instance() {
-  return {wind_group_kernel<KS, CT, GW>, GroupCfg<KS, CT, GW>::smem, WIND_BF16, GroupCfg<KS, CT, GW>::H, CT, GW};
+  // two parts of W_out per workgroup: several slots (see group_shape)
+  if constexpr (CT == 1) return {{wind_group_kernel<KS, CT, GW, kGroupMany>, wind_group_kernel<KS, CT, GW, kGroupOne>, wind_group_kernel<KS, CT, GW, kGroupLimited>}, GroupCfg<KS, CT, GW>::smem, WIND_BF16, GroupCfg<KS, CT, GW>::H, CT, GW};
+  else return {{wind_group_kernel<KS, CT, GW, kGroupMany>, nullptr, nullptr}, GroupCfg<KS, CT, GW>::smem, WIND_BF16, GroupCfg<KS, CT, GW>::H, CT, GW};
 }
 template <int NK, int CT, int GW>
 constexpr GroupInstance group_f32_instance() {
-  return {wind_group_f32_kernel<NK, CT, GW>, GroupF32Cfg<NK, CT, GW>::smem, WIND_F32, GroupF32Cfg<NK, CT, GW>::H, CT, GW};
+  if constexpr (GW == 1) return {{nullptr, wind_group_f32_kernel<NK, CT, GW, kGroupOne>, wind_group_f32_kernel<NK, CT, GW, kGroupLimited>}, GroupF32Cfg<NK, CT, GW>::smem, WIND_F32, GroupF32Cfg<NK, CT, GW>::H, CT, GW};
+  else return {{wind_group_f32_kernel<NK, CT, GW, kGroupMany>, wind_group_f32_kernel<NK, CT, GW, kGroupOne>, nullptr}, GroupF32Cfg<NK, CT, GW>::smem, WIND_F32, GroupF32Cfg<NK, CT, GW>::H, CT, GW};
 }
 const GroupInstance kGroupInstances[] = {
     group_instance<1, 1, 32>(), group_instance<1, 2, 32>(), group_instance<2, 1, 32>(), group_instance<2, 2, 32>(), group_instance<3, 1, 32>(),
@@ -941,7 +944,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   unsigned long long turn = 0;
   if (gi) {
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
-    gd.limited = gd.max_iters < max_iters;
+    // calls that may stop short are asynchronous ones, with a group per utterance
+    const auto kernel = gi->kernel[gd.NG < B ? kGroupMany : gd.max_iters < max_iters ? kGroupLimited : kGroupOne];
+    if (!kernel || (gd.NG < B && gd.max_iters < max_iters)) return fail(WIND_ERR_UNSUPPORTED, "resident groups: no instance for this call");
     // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where another kernel can
     // decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
@@ -955,7 +960,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     }
     CallDev cr = c;
     cr.W = gd.reach;
-    gi->kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, cr, gd);
+    kernel<<<(unsigned)(gi->gw == 1 ? gd.NG : kGroups * gi->gw), 512, gi->smem, s>>>(m->dev, cr, gd);
     rc = check_launch("resident groups");
     if (rc) return rc;
     // An asynchronous call's results stay in its workspace until it is completed: it may be part of a graph that the caller launches
@@ -1370,7 +1375,8 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)enc_proj_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWideSmemBytes);
     static_assert(kFusedSteps == 5, "one resident loop instance per number of fused K steps: here and at the launch");
     for (const GroupInstance &i : kGroupInstances)
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
+      for (auto k : i.kernel)
+        if (e == hipSuccess && k) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     for (const BeamInstance &i : kBeamInstances)
       for (auto k : {i.search, i.scores, i.phases[0], i.phases[1], i.phases[2], i.phases[3]})
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);

@@ -78,7 +78,6 @@ struct GroupDev {
   int win;                              // the caller's window (the kernels' CallDev::W is the reach)
   unsigned win_inv;                     // 65536 / win + 1: x / win = x win_inv >> 16 for small x
   int max_iters;                        // windows (of the caller's size) an utterance may take
-  int limited;                          // 1: that is fewer than it can come to need
   unsigned spin_limit, start_limit;     // polls of a wait, and of the first one: until all workgroups of the group are on the chip
 };
 

@@ -34,8 +34,8 @@ struct GroupF32Cfg {
   static constexpr size_t oC = oRec + (size_t)SL * NR * 4;                 // float [SL][UPW]
   static constexpr size_t oW = oC + (size_t)SL * UPW * 4;                  // float [H] blank column of W_out
   static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1], [H], [H]
-  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], fail, near; float bp[PPW], bo[32 CT + 1]
-  static constexpr size_t oT = (oI + (64 + kNumStats + 2 + PPW + 32 * CT + 1) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
+  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], open windows [slots][2], fail, near; float bp[PPW], bo[32 CT + 1]
+  static constexpr size_t oT = (oI + (64 + kNumStats + 2 * kGroupSlots + 2 + PPW + 32 * CT + 1) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
   static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
 };
@@ -71,11 +71,12 @@ __device__ __forceinline__ float group_row_products(float h, const float *w) {
   return a;
 }
 
-template <int NK, int CT, int GW>
+template <int NK, int CT, int GW, int MODE>   // MODE: kGroupMany, ..
 __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev c, GroupDev gd) {
   using Cfg = GroupF32Cfg<NK, CT, GW>;
-  constexpr int H = Cfg::H, KW = Cfg::KW, NR = Cfg::NR, PPW = Cfg::PPW, QL = Cfg::QL, NSET = Cfg::NSET, SL = Cfg::SL;
-  constexpr bool SOLO = GW == 1;
+  constexpr int H = Cfg::H, KW = Cfg::KW, NR = Cfg::NR, PPW = Cfg::PPW, QL = Cfg::QL, NSET = Cfg::NSET;
+  constexpr bool SOLO = GW == 1, ONE = SOLO || MODE != kGroupMany, LIM = MODE == kGroupLimited;
+  constexpr int SL = ONE ? 1 : Cfg::SL;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int grp = SOLO ? (int)blockIdx.x : (int)blockIdx.x % kGroups, g = SOLO ? 0 : (int)blockIdx.x / kGroups;
   if (grp >= gd.NG) return;
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   float *hbuf = reinterpret_cast<float *>(smem + Cfg::oHb), *partl = reinterpret_cast<float *>(smem + Cfg::oPart);
   float *recs = reinterpret_cast<float *>(smem + Cfg::oRec), *cst = reinterpret_cast<float *>(smem + Cfg::oC);
   float *wbl = reinterpret_cast<float *>(smem + Cfg::oW);
-  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *counts = stat + 64, *fail = counts + kNumStats, *near_w = fail + 1;
+  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *counts = stat + 64, *fail = counts + kNumStats + 2 * kGroupSlots, *near_w = fail + 1;
   float *bpl = reinterpret_cast<float *>(near_w + 1), *bol = bpl + PPW;   // this workgroup's rows of b_pred, columns of b_out and blank's
 
   int lane = threadIdx.x & 63, tid = threadIdx.x, l15 = lane & 15, l4 = lane >> 4;
@@ -98,7 +99,8 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   unsigned long long *kbase = SOLO ? xs : gd.keys + (size_t)grp * 2 * kGroupRows * kstride;
   const int unit0 = g * Cfg::UPW, prow0 = g * PPW;
   const int n_order = *gd.n_order;
-  GroupLane sl = group_first_slots(c, gd, grp, lane, n_order);
+  GroupLane sl = group_first_slots<ONE>(c, gd, grp, lane, n_order);
+  GroupOpen open{0, 0};
 
   // ---- weights into registers
   float wo[2 * CT][NK], wv[NSET][KW];
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   for (int i = tid; i < H; i += 512) wbl[i] = m.w_blank[i];
   for (int i = tid; i < NS * NR; i += 512) recs[i] = m.start_rec[unit0 * 4 + i % NR];
   for (int i = tid; i < NS * Cfg::UPW; i += 512) cst[i] = m.start_c[unit0 + i % Cfg::UPW];
-  for (int i = tid; i < kNumStats; i += 512) counts[i] = 0;
+  for (int i = tid; i < kNumStats + 2 * kGroupSlots; i += 512) counts[i] = 0;
   for (int i = tid; i < PPW; i += 512) bpl[i] = m.b_pred[prow0 + i];
   for (int i = tid; i <= 32 * CT; i += 512) {
     const int part = (i >> 5) * GW + g, col = i < 32 * CT ? part * 32 + (i & 31) : V;
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     asm volatile("" : "+v"(lane), "+v"(tid));   // see group_loop
     l15 = lane & 15;
     l4 = lane >> 4;
-    const int nwin = group_window(c, gd, sl);   // lanes of empty slots: 0
+    const int nwin = group_window<LIM>(c, gd, sl, open);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
     const unsigned stamp = (unsigned)it + 1u, stamp16 = stamp & 0xFFFFu;
     unsigned long long *kp = SOLO ? kbase : kbase + (size_t)group_key_buffer(it) * kGroupRows * kstride;
@@ -308,10 +310,10 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     const unsigned long long m_nb = __ballot(lab != V);
     int tok;
     bool emits, fresh_slot;
-    group_outcome(c, gd, sl, grp, lane, n_order, nwin, V, m_nb, 0ull, lab, wave == 7 && g == 0, counts, tok, emits, fresh_slot);
+    group_outcome<LIM, ONE>(c, gd, sl, open, grp, lane, n_order, nwin, V, m_nb, 0ull, lab, wave == 7 && g == 0, counts, tok, emits, fresh_slot);
     const unsigned long long em = __ballot(emits), rf = __ballot(fresh_slot);
     if (em) {
-      const int n_em = __popcll(em);
+      const int n_em = ONE ? 1 : __popcll(em);
       int es[kGroupSlots] = {0, 0, 0, 0}, et[kGroupSlots] = {0, 0, 0, 0};
       {
         unsigned long long todo = em;

@@ -14,7 +14,7 @@ namespace wind {
 // (slots); when one is done the slot takes the next of the group's list.  Utterances are dealt by falling
 // length, back and forth over the slots.
 //
-// The weights the loop needs sit in registers, as matrix-core operands (all instances keep 100 to 150 scalars in lanes of vector
+// The weights the loop needs sit in registers, as matrix-core operands (all instances keep 70 to 131 scalars in lanes of vector
 // registers): per workgroup CT parts of 32
 // columns of W_out (waves 0-3, K split in four), the recurrent rows of UPW LSTM units and PPW rows of W_pred
 // (waves 4-7, K split in four).  LDS holds the projected frames of the windows: two windows' worth per
@@ -62,8 +62,8 @@ struct GroupCfg {
   static constexpr size_t oRec = oRecp + (size_t)4 * NR * 4 * 4;          // float [slots][NR]
   static constexpr size_t oC = oRec + (size_t)kGroupSlots * NR * 4;       // float [slots][UPW]
   static constexpr size_t oW = oC + (size_t)kGroupSlots * UPW * 4;        // float [H] blank column of W_out
-  static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], fail, flags; float bp[UPW]
-  static constexpr size_t oT = (oI + (64 + 64 + kNumStats + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
+  static constexpr size_t oI = oW + (size_t)H * 4;                        // int stat[64], stat2[64], cnt[kNumStats], open windows [slots][2], fail, flags; float bp[UPW]
+  static constexpr size_t oT = (oI + (64 + 64 + kNumStats + 2 * kGroupSlots + 2 + PPW) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
   static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
 };
@@ -173,11 +173,22 @@ __device__ __forceinline__ void group_touch(const void *src, unsigned lds) {
 // The part of the loop's state that every wave keeps for itself: lane a holds slot a.
 struct GroupLane {
   int b, t, len, sym, cnt;   // utterance, frame, length, labels on the frame, labels so far (len = t = 0: slot empty)
-  int wc;                    // windows of the caller's size so far (wc, ph: in the wave that writes, and in all of limited calls)
-  int ph;                    // blank frames of the open one that earlier iterations have seen (0: none is open)
   int rpos;                  // t modulo 2 W: the frame's row in its ring of projected frames
   int ld0, ld;               // frames loaded (or asked for) before the last decision, and now
   int nb, nlen, round;       // the slot's next utterance (-1: none)
+};
+// Calls with a group per utterance (up to 8 utterances) take instances of their own, without all that is there for several slots and for a
+// slot's next utterance: 640 units keep 105 scalars in lanes of vector registers instead of 136, and one utterance of 1000 frames
+// takes 749 instead of 837 us; fp32 models of 128 units and 128 labels keep no vector register in scratch memory (53, the weights
+// of W_out among them) and 500 frames take 807 instead of 1084 us.  Asynchronous calls that may stop short, whose windows of the caller's size
+// are counted to max_iters in every wave, have such instances too.
+enum { kGroupMany, kGroupOne, kGroupLimited };
+
+// What the caller's windows have come to in a slot.  In limited calls (LIM) every wave keeps it, since all have to stop at the same frame; else
+// it is in LDS, where only the wave that counts looks at it.
+struct GroupOpen {
+  int wc;   // windows of the caller's size so far
+  int ph;   // blank frames of the open one that earlier iterations have seen (0: none is open)
 };
 
 // The entry of order `round` of this lane's slot: utterances by falling length, dealt back and forth over the slots.
@@ -190,11 +201,14 @@ __device__ __forceinline__ void group_next(const CallDev &c, const GroupDev &gd,
     len = c.len[b];
   }
 }
+// ONE: a group per utterance, no slot has a next one
+template <bool ONE>
 __device__ __forceinline__ GroupLane group_first_slots(const CallDev &c, const GroupDev &gd, int grp, int lane, int n_order) {
   GroupLane sl;
   group_next(c, gd, grp, lane, n_order, 0, sl.b, sl.len);
-  group_next(c, gd, grp, lane, n_order, 1, sl.nb, sl.nlen);
-  sl.t = sl.sym = sl.cnt = sl.wc = sl.ph = sl.rpos = sl.ld0 = 0;
+  if constexpr (ONE) sl.nb = -1, sl.nlen = 0;
+  else group_next(c, gd, grp, lane, n_order, 1, sl.nb, sl.nlen);
+  sl.t = sl.sym = sl.cnt = sl.rpos = sl.ld0 = 0;
   sl.round = 1;
   if (sl.b < 0) sl.b = 0;
   sl.ld = min(sl.len, 2 * c.W);
@@ -203,9 +217,10 @@ __device__ __forceinline__ GroupLane group_first_slots(const CallDev &c, const G
 
 // Frames of the slot's window in this iteration: up to c.W, the reach (see group_shape), which may hold several windows of the caller's
 // size, gd.win, or end inside one; no more of those than the call may take.
-__device__ __forceinline__ int group_window(const CallDev &c, const GroupDev &gd, const GroupLane &sl) {
+template <bool LIM>
+__device__ __forceinline__ int group_window(const CallDev &c, const GroupDev &gd, const GroupLane &sl, const GroupOpen &open) {
   const int n = min(c.W, sl.len - sl.t);
-  return gd.limited ? min(n, gd.win * min(gd.max_iters - sl.wc, kGroupMaxW) - sl.ph) : n;
+  return LIM ? min(n, gd.win * min(gd.max_iters - open.wc, kGroupMaxW) - open.ph) : n;
 }
 
 // The frames that the slots of row tile rt have come to need (from ld0 to ld), into their rings of 2 W rows, one frame per wave
@@ -235,7 +250,8 @@ __device__ __forceinline__ void group_load_frames(const CallDev &c, const GroupD
 // What a decided iteration does to the slots, in every wave alike: m_nb = rows of the group whose label is not blank, lab = row
 // `lane`'s label, need = rows that were decided again in fp32.  `writer` (one wave of the group) writes the outputs and
 // counts.  Returns whether this lane's slot takes an LSTM step (for tok) and whether it took a new utterance.
-__device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &gd, GroupLane &sl, int grp, int lane, int n_order, int nwin, int V,
+template <bool LIM, bool ONE>
+__device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &gd, GroupLane &sl, GroupOpen &open, int grp, int lane, int n_order, int nwin, int V,
                                               unsigned long long m_nb, unsigned long long need, int lab, bool writer, int *counts, int &tok,
                                               bool &emits, bool &fresh_slot) {
   const int W = c.W, W2 = 2 * W, oshift = lane < gd.NS ? lane * W : 0;
@@ -256,25 +272,30 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
     sl.ld0 = sl.ld;
     sl.ld = max(sl.ld, min(sl.len, sl.t + W2));
     bool cut = false;
-    if (writer || gd.limited) {   // behind the state that everybody waits for: 50 ns of an iteration where every wave did this first
+    if (writer || LIM) {   // behind the state that everybody waits for: 50 ns of an iteration where every wave did this first
       // What that is in windows of the caller's size, which start where the last label or the last whole window left off: `full` blank ones,
       // and one that a label or the last frame closes, `rem` blank frames into it, or that stays open
-      const int seen = sl.ph + (first < 0 ? nwin : first), full = (int)(((unsigned)seen * gd.win_inv) >> 16), rem = seen - full * gd.win;
+      unsigned at0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)counts;
+      asm volatile("" : "+v"(at0));   // formed here: the compiler keeps addresses that do not change in registers over the loop
+      const auto kept = (__attribute__((address_space(3))) int *)(at0 + (kNumStats + 2 * lane) * 4);
+      if constexpr (!LIM) open = GroupOpen{kept[0], kept[1]};
+      const int seen = open.ph + (first < 0 ? nwin : first), full = (int)(((unsigned)seen * gd.win_inv) >> 16), rem = seen - full * gd.win;
       const bool closes = first >= 0 || (rem > 0 && t0 + nwin == sl.len);
       const int n_last = first < 0 ? rem : min(gd.win, sl.len - (t0 + first - rem));
-      const int looked = first < 0 ? W : min(W, (full + 1) * gd.win - sl.ph);   // rows of the frames up to the end of the window that decided
+      const int looked = first < 0 ? W : min(W, (full + 1) * gd.win - open.ph);   // rows of the frames up to the end of the window that decided
       const int rech = __popc((unsigned)(need >> oshift) & segm & ((1u << looked) - 1u));
-      sl.wc += full + closes;
-      sl.ph = closes ? 0 : rem;
-      cut = gd.limited && (wo.flag & 1) && sl.wc >= gd.max_iters;
+      open.wc += full + closes;
+      open.ph = closes ? 0 : rem;
+      if constexpr (LIM) cut = (wo.flag & 1) && open.wc >= gd.max_iters;
+      else {   // the slot's next utterance starts from zero
+        kept[0] = wo.flag & 1 ? open.wc : 0;
+        kept[1] = wo.flag & 1 ? open.ph : 0;
+      }
       if (writer) {
         // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
         // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
         const unsigned ev = wo.ev, forced = (ev >> 29) & 1u;
-        auto add = [&](int which, unsigned v) {
-          const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + which);
-          asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(v) : "memory");
-        };
+        auto add = [&](int which, unsigned v) { asm volatile("ds_add_u32 %0, %1" ::"v"(at0 + 4 * which), "v"(v) : "memory"); };
         const int blanks = full * gd.win;
         add(ST_WINDOWS, (unsigned)(full + closes));
         add(ST_ROWS, (unsigned)(blanks + (closes ? n_last : 0)));
@@ -285,20 +306,19 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
         add(ST_OVERFLOW, (ev >> 30) & 1u);
         add(kStatJump0 + gd.win, (unsigned)full);
         add(kStatJump0 + rem + (int)forced, closes ? 1u : 0u);
-        if (!(wo.flag & 1) || cut) {
-          const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) int *)(counts + ST_ITER);
-          asm volatile("ds_max_u32 %0, %1" ::"v"(at), "v"(sl.wc) : "memory");
-        }
-        if (cut) atomicAdd(&c.n_active[0], 1);
+        // no branch on the condition that decides below: the compiler would make two of that branch, with all of the state copied in each
+        asm volatile("ds_max_u32 %0, %1" ::"v"(at0 + 4 * ST_ITER), "v"((wo.flag & 1) && !cut ? 0 : open.wc) : "memory");
+        if (LIM && cut) atomicAdd(&c.n_active[0], 1);
       }
     }
     const bool done = !(wo.flag & 1) || cut;
     emits = (wo.flag & 2) && !done;
     if (done) {   // the slot's next utterance, or nothing
-      fresh_slot = sl.nb >= 0;
+      fresh_slot = !ONE && sl.nb >= 0;
       sl.b = fresh_slot ? sl.nb : 0;
       sl.len = fresh_slot ? sl.nlen : 0;
-      sl.t = sl.sym = sl.cnt = sl.wc = sl.ph = sl.rpos = sl.ld0 = 0;
+      sl.t = sl.sym = sl.cnt = sl.rpos = sl.ld0 = 0;
+      if constexpr (LIM) open = GroupOpen{0, 0};
       sl.ld = min(sl.len, W2);
       if (fresh_slot) {
         ++sl.round;
@@ -317,17 +337,19 @@ __device__ __forceinline__ void group_add_counters(const CallDev &c, const int *
   }
 }
 
-template <int KS, int CT, int GW, int ROLE>
+template <int KS, int CT, int GW, int MODE, int ROLE>
 __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, const GroupDev &gd, unsigned char *smem, int grp, int g) {
   using Cfg = GroupCfg<KS, CT, GW>;
   constexpr int H = Cfg::H, NR = Cfg::NR, QK = Cfg::QK, QL = Cfg::QL;
+  constexpr bool ONE = MODE != kGroupMany, LIM = MODE == kGroupLimited;
+  constexpr int SL = ONE ? 1 : kGroupSlots;
   float *ecache = reinterpret_cast<float *>(smem + Cfg::oE), *fred = reinterpret_cast<float *>(smem + Cfg::oFred);
   float *fbn = reinterpret_cast<float *>(smem + Cfg::oFbn), *pfull = reinterpret_cast<float *>(smem + Cfg::oP);
   bf16_t *hbuf = reinterpret_cast<bf16_t *>(smem + Cfg::oHb);
   float *predp = reinterpret_cast<float *>(smem + Cfg::oPred), *recp = reinterpret_cast<float *>(smem + Cfg::oRecp);
   float *recs = reinterpret_cast<float *>(smem + Cfg::oRec), *cst = reinterpret_cast<float *>(smem + Cfg::oC);
   float *wbl = reinterpret_cast<float *>(smem + Cfg::oW);
-  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *stat2 = stat + 64, *counts = stat2 + 64, *fail = counts + kNumStats, *near_w = fail + 1;
+  int *stat = reinterpret_cast<int *>(smem + Cfg::oI), *stat2 = stat + 64, *counts = stat2 + 64, *fail = counts + kNumStats + 2 * kGroupSlots, *near_w = fail + 1;
   float *bpl = reinterpret_cast<float *>(near_w + 1);   // this workgroup's rows of b_pred
 
   int lane = threadIdx.x & 63, tid1 = threadIdx.x & 255, l15 = lane & 15, l4 = lane >> 4;
@@ -341,7 +363,8 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
 
   // ---- the slots' first utterances
   const int n_order = *gd.n_order;
-  GroupLane sl = group_first_slots(c, gd, grp, lane, n_order);
+  GroupLane sl = group_first_slots<ONE>(c, gd, grp, lane, n_order);
+  GroupOpen open{0, 0};
 
   // ---- weights into registers
   bf16x8 wo[ROLE == 0 ? 2 * CT : 1][KS];                                   // W_out columns
@@ -379,7 +402,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
   } else {
     for (int i = tid1; i < NS * NR; i += 256) recs[i] = m.start_rec[unit0 * 4 + i % NR];
     for (int i = tid1; i < NS * Cfg::UPW; i += 256) cst[i] = m.start_c[unit0 + i % Cfg::UPW];
-    for (int i = tid1; i < kNumStats; i += 256) counts[i] = 0;
+    for (int i = tid1; i < kNumStats + 2 * kGroupSlots; i += 256) counts[i] = 0;
     if (tid1 < Cfg::PPW) bpl[tid1] = m.b_pred[prow0 + tid1];
     load_frames();
   }
@@ -436,7 +459,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     asm volatile("" : "+v"(lane), "+v"(tid1));
     l15 = lane & 15;
     l4 = lane >> 4;
-    const int nwin = group_window(c, gd, sl);   // lanes of empty slots: 0
+    const int nwin = group_window<LIM>(c, gd, sl, open);   // lanes of empty slots: 0
     if (!__any(nwin > 0)) break;
     const int tag = group_key_tag(it);
     const unsigned stamp = (unsigned)it + 1u;
@@ -618,15 +641,15 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     // ---- outcome of every slot's window; one wave of workgroup 0 writes the outputs
     int tok;
     bool emits, fresh_slot;
-    group_outcome(c, gd, sl, grp, lane, n_order, nwin, V, m_nb, need, lab, ROLE == 1 && wave == 7 && g == 0, counts, tok, emits, fresh_slot);
+    group_outcome<LIM, ONE>(c, gd, sl, open, grp, lane, n_order, nwin, V, m_nb, need, lab, ROLE == 1 && wave == 7 && g == 0, counts, tok, emits, fresh_slot);
     const unsigned long long em = __ballot(emits), rf = __ballot(fresh_slot);
     if (em) {
-      const int n_em = __popcll(em);
+      const int n_em = ONE ? 1 : __popcll(em);
       int es[kGroupSlots] = {0, 0, 0, 0}, et[kGroupSlots] = {0, 0, 0, 0};
       {
         unsigned long long todo = em;
 #pragma unroll
-        for (int e = 0; e < kGroupSlots; ++e)
+        for (int e = 0; e < SL; ++e)
           if (todo) {
             es[e] = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
             et[e] = __builtin_amdgcn_readlane(tok, es[e]);
@@ -651,17 +674,17 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       }
       if constexpr (ROLE == 1) {
         // ---- exchange 2: this wave's quarter of the new hidden vectors, as bf16 hi and lo rows
-        unsigned long long u[kGroupSlots][QL];
+        unsigned long long u[SL][QL];
         const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
 #pragma unroll
-          for (int e = 0; e < kGroupSlots; ++e)
+          for (int e = 0; e < SL; ++e)
             if (e < n_em) {
 #pragma unroll
               for (int q = 0; q < QL; ++q) u[e][q] = group_ld(hx + es[e] * H + w4 * QK + min(lane + 64 * q, QK - 1));
             }
           bool fresh = true;
 #pragma unroll
-          for (int e = 0; e < kGroupSlots; ++e)
+          for (int e = 0; e < SL; ++e)
             if (e < n_em) {
 #pragma unroll
               for (int q = 0; q < QL; ++q) fresh = fresh && (unsigned)(u[e][q] >> 32) == stamp;
@@ -670,7 +693,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         });
         if (!got && lane == 0) *fail = 1;
 #pragma unroll
-        for (int e = 0; e < kGroupSlots; ++e)
+        for (int e = 0; e < SL; ++e)
           if (e < n_em) {
 #pragma unroll
             for (int q = 0; q < QL; ++q)
@@ -714,21 +737,21 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         }
         pend = n_em;
 #pragma unroll
-        for (int e = 0; e < kGroupSlots; ++e) pend_slot[e] = es[e];
+        for (int e = 0; e < SL; ++e) pend_slot[e] = es[e];
       } else {
         group_barrier();   // B3
         // ---- exchange 3: this wave's quarter of the new projections
-        unsigned long long u[kGroupSlots][QL];
+        unsigned long long u[SL][QL];
         const bool got = group_poll(abort_word, gd.spin_limit, [&]() {
 #pragma unroll
-          for (int e = 0; e < kGroupSlots; ++e)
+          for (int e = 0; e < SL; ++e)
             if (e < n_em) {
 #pragma unroll
               for (int q = 0; q < QL; ++q) u[e][q] = group_ld(px + es[e] * H + w4 * QK + min(lane + 64 * q, QK - 1));
             }
           bool fresh = true;
 #pragma unroll
-          for (int e = 0; e < kGroupSlots; ++e)
+          for (int e = 0; e < SL; ++e)
             if (e < n_em) {
 #pragma unroll
               for (int q = 0; q < QL; ++q) fresh = fresh && (unsigned)(u[e][q] >> 32) == stamp;
@@ -737,7 +760,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         });
         if (!got && lane == 0) *fail = 1;
 #pragma unroll
-        for (int e = 0; e < kGroupSlots; ++e)
+        for (int e = 0; e < SL; ++e)
           if (e < n_em) {
 #pragma unroll
             for (int q = 0; q < QL; ++q)
@@ -767,14 +790,14 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
   }
 }
 
-template <int KS, int CT, int GW>
+template <int KS, int CT, int GW, int MODE>
 __global__ __launch_bounds__(512) void wind_group_kernel(ModelDev m, CallDev c, GroupDev gd) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;   // workgroups go to the XCDs in turn
   if (grp >= gd.NG) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) c.stats[kStatLoop] = (unsigned long long)wall_clock64();
-  if (threadIdx.x < 256) group_loop<KS, CT, GW, 0>(m, c, gd, smem_raw, grp, g);
-  else group_loop<KS, CT, GW, 1>(m, c, gd, smem_raw, grp, g);
+  if (threadIdx.x < 256) group_loop<KS, CT, GW, MODE, 0>(m, c, gd, smem_raw, grp, g);
+  else group_loop<KS, CT, GW, MODE, 1>(m, c, gd, smem_raw, grp, g);
 }
 
 }  // namespace wind

@@ -10,7 +10,7 @@ LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib", "llvm", "bi
 
 
 @pytest.fixture(scope="module")
-def assembly(tmp_path_factory):
+def code_object(tmp_path_factory):
     from paper_2505_13765_amd import build
 
     if build.stale():
@@ -19,7 +19,12 @@ def assembly(tmp_path_factory):
     lib = shutil.copy(build.LIB, where / "lib.so")
     subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", str(lib)], check=True, capture_output=True)
     (code,) = [f for f in os.listdir(where) if "gfx950" in f]
-    out = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", str(where / code)],
+    return str(where / code)
+
+
+@pytest.fixture(scope="module")
+def assembly(code_object):
+    out = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", code_object],
                          check=True, capture_output=True, text=True).stdout
     return out.splitlines()
 
@@ -74,3 +79,11 @@ def test_the_scan_finds_such_a_write():
     assert writes_before_lanes_are_back(planted) == ([("_Z1kv", "v_mov_b32_e32 v7, 1")], 1)
     planted[5], planted[6] = planted[6], planted[5]
     assert writes_before_lanes_are_back(planted)[0] == []
+
+
+def test_groups_of_one_utterance_keep_their_weights_in_registers(code_object):
+    """No vector register of the instances that calls of up to 8 utterances take lies in scratch memory (mode 1: the last template argument)."""
+    notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object], check=True, capture_output=True, text=True).stdout
+    kernels = re.findall(r"\.name:\s+(_Z\S+).*?\.vgpr_spill_count:\s+(\d+)", notes, flags=re.S)
+    spills = {n: int(k) for n, k in kernels if re.search(r"wind_group_(f32_)?kernelI\w*?Li1EEEv", n)}
+    assert len(spills) == 15 and not any(spills.values()), spills

@@ -376,3 +376,45 @@ def test_large_batches_count_windows_of_the_callers_size(V, B, W, bias, silent):
     print(f"{runs[0][3]} windows, late: {sum(runs[0][8][8:]) / runs[0][3]:.3f}", flush=True)
     assert runs[0] == runs[1] == runs[2]
     m.close()
+
+
+# asynchronous calls of fewer windows than they need, in groups whose reach holds several of the caller's: a group per utterance (bf16), a
+# workgroup per utterance (fp32 models that fit one CU)
+@pytest.mark.parametrize("dtype,H,V,B", [("bf16", 640, 300, 1), ("bf16", 128, 77, 2), ("f32", 64, 32, 3), ("f32", 128, 100, 2)])
+def test_limited_calls_stop_at_the_callers_windows(dtype, H, V, B):
+    """Labels, frames and counters of calls that stop short, and of those whose limit is what they need, of option lookahead = 1 against 0."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+    from paper_2505_13765_amd.binding import WindError, WIND_ERR_UNFINISHED
+
+    D = 64 if dtype == "bf16" else 68
+    cfg = wi.WindConfig("groups", 130 + H, B, 60, 90, D, 64, 1, H, H, V, dtype, (4,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=2.0, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    T = enc.shape[1]
+    cap = T * cfg.S
+    ws = torch.zeros(m.workspace_bytes(B, T, 16) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    for W in (1, 3, 5, 16):
+        m.set_option("lookahead", 0)
+        m.decode(d_enc, d_len, W, cfg.S)
+        need = m.stats().iterations
+        for limit in sorted({1, 2, 7, need // 2, need - 1, need, need + 3}):
+            runs = []
+            for look in (0, 1):
+                m.set_option("lookahead", look)
+                out = [torch.full((B, cap), -5, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.full((B,), -5, dtype=torch.int32, device="cuda")]
+                m.greedy_decode_async(d_enc, d_len, W, cfg.S, *out, ws, limit)
+                try:
+                    st = m.stats()
+                    runs.append((st.iterations, st.windows, st.rows, st.useful_rows, st.labels, st.forced_advances, list(st.jump_hist)))
+                except WindError as e:
+                    assert e.code == WIND_ERR_UNFINISHED
+                    runs.append("unfinished")
+                assert m.loop_info()[0] > 0
+                n = out[2].tolist()
+                runs[-1] = (runs[-1], n, [t[:max(k, 0)].tolist() for o in out[:2] for t, k in zip(o, n)])
+            assert runs[0] == runs[1], (W, limit)
+            assert (runs[1][0] == "unfinished") == (limit < need), (W, limit, need)
+    m.close()
