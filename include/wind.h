@@ -357,7 +357,7 @@ int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
  *             (default 1; bf16 models only; below it one wave per hidden unit does fp32 FMA)
  *   "loop_kernel"  1 (default): small decodes run the whole loop as one resident kernel; 0: always the graph of
  *             per-step kernels.  Two such kernels: groups of workgroups, one group per XCD with utterances of its
- *             own (up to 256 utterances, windows of at most 16 rows, up to 224 of more than 8; bf16, one LSTM layer, Hp = Hj a multiple of
+ *             own (up to 256 utterances, windows of at most 16 rows; bf16 (windows of more than 8 rows: up to 224), one LSTM layer, Hp = Hj a multiple of
  *             128 and at most 640, at most 1024 labels; fp32, one LSTM layer, Hp = Hj of
  *             64, 128, 256, 384, 512 or 640, at most 1024 labels; the options lstm_rec, atomic_lists, slot_rows, decide_two,
  *             joint_wide and pred_mfma_min_batch at their defaults where there are more than two utterances), and,

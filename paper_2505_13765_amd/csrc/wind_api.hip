@@ -231,10 +231,12 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
-// Utterances up to which windows of more than 8 rows take groups: each round of 32 utterances costs them the same, while the per-step
-// kernels' launches hardly grow and half as many of those are needed as for short windows.  640 units, 200 to 1500 frames, groups / per-step kernels:
-// W = 16 192 utterances 10.6 / 13.8 ms, 224 12.7 / 14.2, 256 13.2 / 14.6; W = 4 256 utterances 13.2 / 20.2 ms.  Models of 128 units with a label on
-// almost every frame lose earlier (W = 16: from about 176 utterances).
+// Utterances up to which windows of more than 8 rows of bf16 models take groups: each round of 32 utterances costs them the same, while the
+// per-step kernels' launches hardly grow, and half as many of those are needed as for short windows.  W = 16, groups / per-step kernels: 640 units, 200 to
+// 1500 frames, blanks 85 %: 176 utterances 8.8 / 13.6 ms, 224 12.0 / 14.1, 256 12.4 / 14.4; with a label on almost every frame (200 to 400
+// frames) 224 20.3 / 21.2, 256 23.1 / 21.8; 128 units, a label on almost every frame 224 21.9 / 23.7, 256 25.3 / 24.0, hardly any 176 0.55 / 0.60,
+// 224 0.67 / 0.62, 256 0.74 / 0.63.  Windows of up to 8 rows: 640 units, W = 4, 256 utterances 13.2 / 20.2.  fp32 models take groups
+// in any case: 256 units, 300 labels, W = 16, 240 utterances of 60 to 120 frames 11.0 / 40.1 ms.
 constexpr int kGroupMaxB16 = 224;
 constexpr unsigned kGroupStartPolls = 1u << 16;   // about 12 ms, what a batch of 32 takes with the per-step kernels
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
@@ -803,7 +805,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     gd->RG = m->dtype == WIND_F32 || gd->NS == 1 ? 1 : 2;   // row tiles: see wind_group_kernel.h; fp32: registers hold one part of W_out
     gd->SPT = (gd->NS + gd->RG - 1) / gd->RG;
     gd->reach = kGroupMaxW / gd->SPT;
-    if (W > 8 && B > kGroupMaxB16) return nullptr;
+    if (m->dtype == WIND_BF16 && W > 8 && B > kGroupMaxB16) return nullptr;
     ct = (nparts + gw / gd->RG - 1) / (gw / gd->RG);   // parts of W_out per workgroup: one, or two
   }
   gd->win = W;

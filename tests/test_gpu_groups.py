@@ -418,3 +418,24 @@ def test_limited_calls_stop_at_the_callers_windows(dtype, H, V, B):
             assert runs[0] == runs[1], (W, limit)
             assert (runs[1][0] == "unfinished") == (limit < need), (W, limit, need)
     m.close()
+
+
+def test_large_fp32_batches_decode_in_groups():
+    """All 256 utterances that groups take, at the widest window too (the per-step kernels take four times as long): the labels of the per-step kernels."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("groups", 77, 241, 1, 20, 68, 64, 1, 256, 256, 90, "f32", (16,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=3.0, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    for W in (9, 16):
+        here = m.decode(d_enc, d_len, W, cfg.S)
+        assert m.loop_info()[0] == 256
+        m.set_option("loop_kernel", 0)
+        steps = m.decode(d_enc, d_len, W, cfg.S)
+        assert m.loop_info()[0] == 0
+        m.set_option("loop_kernel", 1)
+        for a, b in zip(here, steps):
+            assert [x.tolist() for x in a] == [x.tolist() for x in b]
+    m.close()
