@@ -337,6 +337,22 @@ int wind_get_joint_launches(wind_model *m, int32_t *rows, float *us, int cap, in
 int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2);
 
 /*
+ * What ran, for tests and reports: counts since the model was loaded, but `iterations`.  HOST pointer; WIND_ERR_ARG for null pointers.
+ */
+typedef struct {
+  int64_t iterations;      /* loop iterations that the last decode on the per-step kernels ran; more than its wind_stats.iterations where windows were cut */
+  int64_t replays[6];      /* replays of the loop's graphs: whole windows; windows cut to 8 rows; whole windows of a call that has had cut ones; each
+                              with the joint kernel on 128-column tiles, then on 256-column tiles (option "joint_wide") */
+  int64_t beam_commands;   /* passes of beam searches that resident workgroups computed */
+  int64_t beam_launches;   /* launches of those workgroups */
+  int64_t beam_idle;       /* of those, launches that left because no command came */
+  int64_t beam_gave_up;    /* searches that went on without them */
+  int64_t scores_resident; /* scoring steps in one launch of workgroups that wait for each other */
+  int64_t scores_gave_up;  /* steps that had to be computed without waiting for each other */
+} wind_route_counts;
+int wind_get_route_counts(wind_model *m, wind_route_counts *out);
+
+/*
  * Tuning knobs, for benchmarks and tests.  key/value pairs:
  *   "graph"   1 (default): the decode loop is replayed from a captured HIP graph; 0: kernels are
  *             launched one by one (the with / without graph rows of Table 5)

@@ -18,7 +18,7 @@ EXPORTS = ("wind_load_weights", "wind_free", "wind_greedy_decode", "wind_sequent
            "wind_greedy_decode_async", "wind_get_stats", "wind_debug_joint_logits", "wind_set_option", "wind_last_error",
            "wind_get_kernel_times", "wind_get_joint_launches", "wind_get_call_times", "wind_beam_window_scores", "wind_beam_decode",
            "wind_workspace_bytes", "wind_debug_enc_proj", "wind_debug_joint_keys", "wind_beam_window_scores_static",
-           "wind_get_loop_info")
+           "wind_get_loop_info", "wind_get_route_counts")
 PREFIX_MODES = {"off": 0, "keep": 1, "remove": 2}
 KERNEL_NAMES = ("enc_proj", "build_z", "joint", "decide", "lstm", "pred_proj")
 
@@ -53,6 +53,13 @@ class WindBeamStats(C.Structure):
     _fields_ = [
         ("rounds", C.c_int64), ("hyps_scored", C.c_int64), ("decoder_steps", C.c_int64), ("completions", C.c_int64),
         ("completion_rows", C.c_int64), ("max_pending", C.c_int64), ("nodes", C.c_int64),
+    ]
+
+
+class WindRouteCounts(C.Structure):
+    _fields_ = [
+        ("iterations", C.c_int64), ("replays", C.c_int64 * 6), ("beam_commands", C.c_int64), ("beam_launches", C.c_int64),
+        ("beam_idle", C.c_int64), ("beam_gave_up", C.c_int64), ("scores_resident", C.c_int64), ("scores_gave_up", C.c_int64),
     ]
 
 
@@ -96,6 +103,7 @@ def load_library():
                                               C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_void_p]
         lib.wind_get_call_times.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_double)]
         lib.wind_get_loop_info.argtypes = [C.c_void_p, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        lib.wind_get_route_counts.argtypes = [C.c_void_p, C.POINTER(WindRouteCounts)]
         lib.wind_get_joint_launches.argtypes = [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_float), C.c_int,
                                                 C.POINTER(C.c_int)]
         lib.wind_beam_window_scores.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int,
@@ -230,6 +238,11 @@ class WindModel:
         g, one = C.c_int(0), C.c_int(0)
         _check(self._lib.wind_get_loop_info(self._h, C.byref(g), C.byref(one)))
         return int(g.value), bool(one.value)
+
+    def route_counts(self) -> WindRouteCounts:
+        r = WindRouteCounts()
+        _check(self._lib.wind_get_route_counts(self._h, C.byref(r)))
+        return r
 
     def joint_launches(self):
         """(rows, us) of every joint launch of the last decode made with option "profile" = 1."""

@@ -183,7 +183,8 @@ struct wind_model {
   int device = -1;
   int cu_count = 0;            // CUs of the device the model was loaded on (the resident loop kernel wants one per workgroup)
   int loop_info[2] = {0, 0};   // last decode call: workgroups of the resident loop kernel (0: not used), whether they shared one L2
-  long long prev_iters = 0;
+  long long prev_iters = 0, prev_ran = 0;   // of the previous call: iterations in windows of the caller's size, and as they ran (its windows may have been cut)
+  wind_route_counts route{};
   int prev_B = 0, prev_T = 0, prev_W = 0;
   wind_stats last_stats{};
   bool have_stats = false;
@@ -1053,7 +1054,6 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     return rc;
   }
   const int U = m->opt_unroll;
-  long long split_replays = 0;
   const bool use_graph = m->opt_graph && !m->opt_profile && !m->opt_host_sync;   // events cannot sit between graph nodes
   // Which joint kernel the iterations of a block of U run (either is right for any row count; the choice is
   // about speed): joint_wide_kernel while the call has more than wide_rows window rows per iteration.  The
@@ -1109,16 +1109,17 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     }
   } else {
     // Launch ahead by what the previous call of the same shape needed, then poll once per replay.
-    long long ahead = same_shape ? m->prev_iters / U : 1;
-    if (ahead < 1) ahead = 1;
+    const auto replays_of = [&](long long iterations) { return same_shape ? std::max(iterations / U, 1ll) : 1ll; };
+    long long ahead = replays_of(m->prev_iters);
     // Windows of half the rows where most labels lie in those: rows behind a window's first label are thrown away, and the joint kernel of a large
     // batch takes as long as its rows, while a window whose first kShortReach rows are blank takes a second iteration.  A call with rows enough for
-    // that is looked at after its first replay, with kCutLead replays queued so that the GPU has work meanwhile, and, once cut, every kCutReplays;
+    // that is looked at after its first replay, with kCutLead replays queued so that the GPU has work meanwhile (if the previous call of its shape needed
+    // more than those; else when it has come to them), and, once cut, every kCutReplays;
     // `late` is the share of its windows since the last look that had no label in time.  Results and counters are those of the caller's
     // window either way (decide_kernel<.., SPLIT>).  4096 labels, a label on every second
     // evaluation, W = 16, 100 to 1000 frames: 256 utterances 33.5 -> 30.1 ms, 128 26.5 -> 26.1, 80 25.1 -> 25.2; not cut (8192 labels, blanks 85 %): 128
     // utterances 31.7 -> 31.8, 70 13.0 -> 13.0.
-    const long long planned = ahead;
+    long long planned = ahead;
     bool cut = false, split = false;   // cut: windows of kShortReach rows now; split: so some time in this call
     unsigned long long seen_windows = 0, seen_late = 0;
     const auto look = [&]() {
@@ -1133,9 +1134,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     const long long max_launches = (max_iters + 2 * U) / U + 2;
     long long launches = 0;
     bool polled = false;
-    if (c.slot_win) {
+    if (c.slot_win && planned > kCutLead) {
       for (; launches < kCutLead; ++launches) {
-        HIP_TRY(hipGraphLaunch(m->graph_exec[(same_shape ? wide_by_history(launches) : wide_by_count(B)) ? 1 : 0], s));
+        const int g = wide_by_history(launches) ? 1 : 0;
+        HIP_TRY(hipGraphLaunch(m->graph_exec[g], s));
+        ++m->route.replays[g];
         if (launches > 0) continue;
         HIP_TRY(hipMemcpyAsync(m->h_flag, c.n_active, sizeof(int), hipMemcpyDeviceToHost, s));
         rc = enqueue_stats_copy(m, s);
@@ -1145,7 +1148,8 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       HIP_TRY(hipEventSynchronize(m->ev_call[2]));
       look();
       polled = split;
-      ahead = std::max(planned - launches, 1ll);
+      if (split) planned = replays_of(m->prev_ran);
+      ahead = std::max(planned - launches, 0ll);
       if (split) ahead = std::min(ahead, kCutReplays - launches);
     }
     for (;;) {
@@ -1158,6 +1162,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
             if (rc) return rc;
           }
           HIP_TRY(hipGraphLaunch(m->graph_exec[g], s));
+          ++m->route.replays[g];
         } else {
           for (int it = 0; it < U; ++it) {
             rc = enqueue_iteration(m, s, it & 1, false, wide);
@@ -1173,12 +1178,14 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
       if (rc) return rc;
       HIP_TRY(hipStreamSynchronize(s));
       prof_collect(m);
-      if (*m->h_flag == 0) {
-        if (split) split_replays = launches;
-        break;
+      if (*m->h_flag == 0) break;
+      if (c.slot_win && !split && launches == kCutLead) {   // the graphs of cut windows count from here
+        look();
+        if (split) planned = replays_of(m->prev_ran);
+      } else if (split && launches % kCutReplays == 0) {
+        look();
       }
       if (split) {
-        if (launches % kCutReplays == 0) look();
         if (launches < planned) ahead = std::min(planned - launches, kCutReplays - launches % kCutReplays);
       }
       if (launches > max_launches) return fail(WIND_ERR_HIP, "decode loop did not terminate");
@@ -1192,7 +1199,9 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     if (n) HIP_TRY(hipMemcpy(m->joint_rows.data(), c.iter_rows, n * sizeof(int), hipMemcpyDeviceToHost));
   }
   m->prev_B = B; m->prev_T = T; m->prev_W = W;
-  m->prev_iters = split_replays ? std::max((split_replays - 1) * U, 1ll) : m->last_stats.iterations;   // iterations launched: windows may have taken two
+  m->prev_iters = m->last_stats.iterations;
+  m->prev_ran = m->h_stats[kStatRan] ? kCutLead * U + (long long)m->h_stats[kStatRan] : m->prev_iters;
+  m->route.iterations = m->prev_ran;
   m->prev_wide_iters = m->last_wide_iters;
   if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
   return rc;
@@ -1565,6 +1574,12 @@ static int finish_async(wind_model *m) {
   }
   if (rc == WIND_ERR_OVERFLOW) return fail(rc, "an utterance produced more labels than cap");
   return rc;
+}
+
+int wind_get_route_counts(wind_model *m, wind_route_counts *out) {
+  if (!m || !out) return fail(WIND_ERR_ARG, "null argument");
+  *out = m->route;
+  return WIND_OK;
 }
 
 int wind_get_loop_info(wind_model *m, int *workgroups, int *one_l2) {

@@ -257,6 +257,7 @@ struct BeamSession {
     rc = check_launch("beam search on resident workgroups");
     if (rc) return rc;
     is_open = true;   // also if the event fails: the kernel is there
+    ++m->route.beam_launches;
     commands = 0;
     return resident_leave(gate, s, &turn);
   }
@@ -291,7 +292,7 @@ struct BeamSession {
       ++commands;
       bool left = false;
       for (unsigned spins = 1; !left; ++spins) {
-        if (arrived()) { *done = true; return WIND_OK; }
+        if (arrived()) { *done = true; ++m->route.beam_commands; return WIND_OK; }
         left = __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == br.session;
         if (!left && (spins & 0x3FFFu) == 0) {   // a kernel that failed never says that it has left
           const hipError_t e = hipStreamQuery(s);
@@ -302,11 +303,13 @@ struct BeamSession {
       }
       is_open = false;
       HIP_TRY(hipStreamSynchronize(s));
-      if (arrived()) { *done = true; return WIND_OK; }
+      if (arrived()) { *done = true; ++m->route.beam_commands; return WIND_OK; }
       if (__atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) != (br.session << 2 | kBeamExitIdle)) {
         usable = false;
+        ++m->route.beam_gave_up;
         return WIND_OK;
       }
+      ++m->route.beam_idle;
       // idle when the command came: the next launch takes it
     }
   }
@@ -383,6 +386,7 @@ int beam_scores_resident(wind_model *m, const float *enc_window, int n, const fl
     __builtin_ia32_pause();
   }
   resident_done(gate, turn);
+  ++(*done ? m->route.scores_resident : m->route.scores_gave_up);
   if (!*done) {   // some of its hypotheses may have been written: the count starts again
     HIP_TRY(hipMemsetAsync(&br.mem[0].word[1], 0, sizeof(unsigned), s));
     br.written = 0;

@@ -752,6 +752,9 @@ __global__ __launch_bounds__(1024) void decide_kernel(ModelDev m, CallDev c, int
         case 11:
           if constexpr (SPLIT) { which = kStatJump0 + c.win; add = whole; }
           break;
+        case 12:
+          if constexpr (SPLIT) { which = kStatRan; add = a == 0 ? 1ull : 0ull; }
+          break;
         default: break;
       }
       if (which >= 0 && add) atomicAdd(&c.stats[which], add);

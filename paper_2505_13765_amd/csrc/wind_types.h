@@ -12,7 +12,8 @@ constexpr int kMaxWindow = 64;
 constexpr int kTinyRows = 64;   // slots the resident loop kernel keeps in LDS (it runs far fewer)
 constexpr int kStatJump0 = 9;  // index of jump_hist[0] in the device counter array
 constexpr int kShortReach = 8;              // see decode()
-constexpr int kNumStats = kStatJump0 + kMaxWindow + 1;
+constexpr int kStatRan = kStatJump0 + kMaxWindow + 1;   // iterations with windows of another size than the caller's (decide_kernel<.., SPLIT>)
+constexpr int kNumStats = kStatRan + 1;
 // behind the counters, in the same array: device time stamps of the resident groups' calls (start of the call, start of the loop, end)
 constexpr int kStatStart = kNumStats, kStatLoop = kNumStats + 1, kStatEnd = kNumStats + 2, kStatWords = kNumStats + 3;
 enum { ST_ITER = 0, ST_WINDOWS, ST_ROWS, ST_USEFUL, ST_LABELS, ST_FORCED, ST_RECHECK, ST_OVERFLOW, ST_WIDE };   // ST_WIDE: iterations with more window rows than the gather kernel was told

@@ -373,8 +373,11 @@ def test_large_batches_count_windows_of_the_callers_size(V, B, W, bias, silent):
         st = m.stats()
         runs.append(([t.tolist() for t in toks], [f.tolist() for f in frs], st.iterations, st.windows, st.rows, st.useful_rows, st.labels,
                      st.forced_advances, list(st.jump_hist)))
-    print(f"{runs[0][3]} windows, late: {sum(runs[0][8][8:]) / runs[0][3]:.3f}", flush=True)
+    route = list(m.route_counts().replays)
+    print(f"{runs[0][3]} windows, late: {sum(runs[0][8][8:]) / runs[0][3]:.3f}, replays {route}", flush=True)
     assert runs[0] == runs[1] == runs[2]
+    assert (sum(route[2:4]) > 0) == (bias < 6.0)   # windows were cut where labels lie early
+    assert not silent or sum(route[4:]) > 0        # and not any more in the silence
     m.close()
 
 
@@ -438,4 +441,62 @@ def test_large_fp32_batches_decode_in_groups():
         m.set_option("loop_kernel", 1)
         for a, b in zip(here, steps):
             assert [x.tolist() for x in a] == [x.tolist() for x in b]
+    m.close()
+
+
+def test_launched_ahead_is_what_a_call_needs():
+    """Large batches whose windows may be cut: a call launches no more than one replay beyond its iterations, whatever the calls of its shape before
+    it came to: few iterations, windows that were cut, windows that were not."""
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("cut", 151, 80, 130, 400, 64, 64, 1, 128, 128, 4100, "bf16", (16,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=1.0, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    T = enc.shape[1]
+    d_enc = torch.from_numpy(enc).cuda()
+    silent = torch.zeros_like(d_enc)
+    long_, short = torch.from_numpy(lens).cuda(), torch.from_numpy(np.minimum(lens, 24).astype(np.int32)).cuda()
+    cap = T * cfg.S
+    out = [torch.zeros((cfg.B, cap), dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros((cfg.B,), dtype=torch.int32, device="cuda")]
+    had_cut, last = 0, None
+    for name, e, l in (("long", d_enc, long_), ("short", d_enc, short), ("short", d_enc, short), ("long", d_enc, long_), ("long", d_enc, long_), ("long", d_enc, long_),
+                       ("silent", silent, short), ("silent", silent, short), ("silent", silent, short)):
+        before = list(m.route_counts().replays)
+        m.greedy_decode(e, l, 16, cfg.S, *out)
+        after = m.route_counts()
+        ran = [b - a for a, b in zip(before, after.replays)]
+        print(name, m.stats().iterations, after.iterations, ran, flush=True)
+        had_cut += sum(ran[2:4])
+        if name == last:   # the call before it came to as many
+            assert sum(ran) <= after.iterations // 16 + 1, (name, ran)
+        last = name
+    assert had_cut > 0
+    m.close()
+
+
+# the other instances that cut windows run with: both joint kernels (8192 labels: 256-column tiles above 1024 rows), the
+# decision kernel for joint widths above 1024
+@pytest.mark.parametrize("Hp,Hj,V,B,bias,wide", [(128, 384, 8200, 150, 1.0, True), (128, 1152, 4100, 70, 1.0, False)])
+def test_cut_windows_in_every_kernel(Hp, Hj, V, B, bias, wide):
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    cfg = wi.WindConfig("cut", 171 + B, B, 150, 400, 64, 64, 1, Hp, Hj, V, "bf16", (4,), 3, 0.7)
+    m = WindModel.from_config(cfg, wi.make_weights(cfg, blank_bias=bias, pred_gain=4.0))
+    enc, lens = wi.make_batch(cfg)
+    enc[:, 150:] = 0.0
+    d_enc, d_len = torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda()
+    runs = []
+    for look in (0, 1, 1):
+        m.set_option("lookahead", look)
+        toks, frs = m.decode(d_enc, d_len, 16, cfg.S)
+        assert m.loop_info()[0] == 0
+        st = m.stats()
+        runs.append(([t.tolist() for t in toks], [f.tolist() for f in frs], st.iterations, st.windows, st.rows, st.useful_rows, st.labels,
+                     st.forced_advances, list(st.jump_hist)))
+    route = list(m.route_counts().replays)
+    print(f"{runs[0][3]} windows, late: {sum(runs[0][8][8:]) / runs[0][3]:.3f}, replays {route}", flush=True)
+    assert runs[0] == runs[1] == runs[2]
+    assert route[3 if wide else 2] > 0
     m.close()

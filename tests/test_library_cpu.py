@@ -60,6 +60,7 @@ def test_argument_errors_without_gpu(lib):
     assert lib.wind_get_joint_launches(None, None, None, 0, None) == binding.WIND_ERR_ARG
     assert lib.wind_get_call_times(None, None, None) == binding.WIND_ERR_ARG
     assert lib.wind_get_loop_info(None, None, None) == binding.WIND_ERR_ARG
+    assert lib.wind_get_route_counts(None, None) == binding.WIND_ERR_ARG
     assert lib.wind_free(None) == binding.WIND_OK
 
 
@@ -73,3 +74,5 @@ def test_binding_struct_layout_matches_header():
     order = re.findall(r"\b(D|E|Hp|L|Hj|V|dtype|emb|w_ih|w_hh|b_ih|b_hh|w_enc|b_enc|w_pred|b_pred|w_out|b_out)\b", body)
     assert order == [f[0] for f in binding._Weights._fields_]
     assert C.sizeof(binding.WindStats) == 8 * (7 + 65)
+    body = text[text.index("loop iterations that the last decode on the per-step") - 100: text.index("} wind_route_counts;")]
+    assert re.findall(r"int64_t (\w+)", body) == [f[0] for f in binding.WindRouteCounts._fields_]
