@@ -107,7 +107,9 @@ __device__ __forceinline__ bool beam_poll(unsigned *abort_word, unsigned session
 }
 __device__ __forceinline__ void beam_st(unsigned long long *p, unsigned lo, unsigned hi) { group_st(p, lo, hi, true); }
 
-// Eight floats as three bf16 vectors that add up to them exactly (24 bits)
+// Eight floats as three bf16 vectors that add up to them exactly (24 bits).  FINITE: none is infinite, as the LSTM's own vectors are not; a caller's
+// may be: its other two parts are then zero, not what is left of inf - inf, and the products are infinite or NaN as those of fp32 FMA
+template <bool FINITE>
 __device__ __forceinline__ void beam_split3(const float4 &a, const float4 &b, bf16x8 &hi, bf16x8 &mid, bf16x8 &lo) {
   const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
   u32x4 uh, um, ul;
@@ -115,7 +117,8 @@ __device__ __forceinline__ void beam_split3(const float4 &a, const float4 &b, bf
   for (int q = 0; q < 4; ++q) {
     const float x0 = x[2 * q], x1 = x[2 * q + 1];
     const unsigned h = pack_bf16x2(x0, x1);
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
+    const float h0 = __uint_as_float(h << 16), h1 = __uint_as_float(h & 0xFFFF0000u);
+    const float r0 = FINITE || fabsf(h0) != INFINITY ? x0 - h0 : 0.f, r1 = FINITE || fabsf(h1) != INFINITY ? x1 - h1 : 0.f;
     const unsigned d = pack_bf16x2(r0, r1);
     uh[q] = h;
     um[q] = d;
@@ -223,7 +226,7 @@ struct BeamRes {
   }
 
   // rows of products a x (16 weight rows): fp32 vectors as three bf16 vectors, the small parts in a chain of their own
-  template <int T>
+  template <int T, bool FINITE = true>
   __device__ __forceinline__ void products(const bf16x8 (&w)[T][KS], const float4 (&v)[KS][2], f32x4 (&acc)[T]) const {
     f32x4 small[T];
 #pragma unroll
@@ -231,7 +234,7 @@ struct BeamRes {
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
       bf16x8 hi, mid, lo;
-      beam_split3(v[i][0], v[i][1], hi, mid, lo);
+      beam_split3<FINITE>(v[i][0], v[i][1], hi, mid, lo);
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         small[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, w[t][i], small[t], 0, 0, 0);
@@ -764,7 +767,7 @@ struct BeamRes {
       *reinterpret_cast<float4 *>(&encp[((wave * Cfg::PT + t) * 16 + l15) * 20 + 4 * l4]) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
     if constexpr (HALF == 0) {
       f32x4 pacc[Cfg::PT];
-      products<Cfg::PT>(wp, v, pacc);
+      products<Cfg::PT, false>(wp, v, pacc);
       put_partial<Cfg::PT, Cfg::PT>(predp, 0, pacc);
     }
     if constexpr (PHASE < 0) meet();   // a barrier: the partial sums are in LDS

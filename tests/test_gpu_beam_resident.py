@@ -139,3 +139,38 @@ def test_one_scoring_step(torch_cuda, H, V, n, Bh, K, exact):  # noqa: F811
     for a, b in zip(unaligned, given_up):
         assert np.array_equal(a, b)
     m.close()
+
+
+@pytest.mark.parametrize("exact", [0, 1])
+@pytest.mark.parametrize("H,V", [(256, 100), (640, 1024)])
+def test_a_scoring_step_of_values_that_are_not_finite(torch_cuda, H, V, exact):  # noqa: F811
+    """Infinities and NaN in a frame or in a hypothesis: the pairs, and the places of scores that are not numbers, of the launches that take every
+    other shape."""
+    from paper_2505_13765_amd import WindModel
+
+    torch = torch_cuda
+    cfg, w = small(H, V, 16, 4, 4)
+    m = WindModel.from_config(cfg, w)
+    m.set_option("beam_exact", exact)
+    for what, value in (("frame", np.inf), ("frame", -np.inf), ("frame", np.nan), ("hypothesis", np.inf), ("hypothesis", -np.inf), ("hypothesis", np.nan),
+                        ("every frame", np.inf), ("every hypothesis", np.inf)):
+        g = torch.Generator(device="cpu").manual_seed(3)
+        e, d = torch.randn((8, cfg.D), generator=g), torch.tanh(torch.randn((10, H), generator=g))
+        if what.startswith("every"):
+            (e if "frame" in what else d)[:] = value
+        elif what == "frame":
+            e[3, 5] = value
+        else:
+            d[4, 7] = value
+        e, d = e.cuda(), d.cuda()
+        runs = []
+        for resident in (1, 0):
+            m.set_option("loop_kernel", resident)
+            runs.append(m.beam_window_scores(e, d, 4))
+        here, there = runs
+        assert np.array_equal(here[0], there[0]) and np.array_equal(here[1], there[1]), (what, value)
+        assert np.array_equal(np.isfinite(here[2]), np.isfinite(there[2])), (what, value)
+        ok = np.isfinite(there[2])
+        assert np.allclose(here[2][ok], there[2][ok], atol=2e-4 if exact else 4e-3, rtol=1e-5), (what, value)   # see test_one_scoring_step
+    assert m.route_counts().scores_resident == 8 and m.route_counts().scores_gave_up == 0
+    m.close()
