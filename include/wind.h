@@ -179,7 +179,7 @@ int wind_beam_window_scores(wind_model *m, const float *enc_window, int n, const
  * array of WIND_STATIC_SCRATCH_BYTES inside the library, one per GPU, held until the process ends.
  * Shapes whose scratch layout does not fit are rejected with WIND_ERR_ARG and a message that names
  * both sizes (the layout grows with Bh * n * (V + 1) * 4 bytes of logits; 16 hypotheses x 16 frames
- * of a 1024-label model need 1.9 MB).  Every call on a GPU uses that GPU's one array, whatever the
+ * of a 1024-label model need 1.9 MB; that is the layout of the kernels that take any shape, others need less).  Every call on a GPU uses that GPU's one array, whatever the
  * model or stream: calls that overlap in time on one GPU race; serialise them.
  * Arguments, outputs and tie order as wind_beam_window_scores.
  */

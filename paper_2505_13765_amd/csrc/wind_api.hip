@@ -121,6 +121,7 @@ struct BeamResident {
   } *host = nullptr, *dev = nullptr;            // pinned, and its device address
   unsigned session = 0, seq = 0;                // numbers of the last launch and of the last command
   unsigned written = 0;                         // hypotheses of all scoring steps so far
+  int rest_steps = 0, rest_searches = 0;        // scoring steps and searches to come that do without: the last one's workgroups could not meet
 };
 
 struct wind_model {
@@ -1489,9 +1490,8 @@ int wind_beam_window_scores(wind_model *m, const float *enc_window, int n, const
   int rc = beam_scores_check(m, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  bool done = false;
-  rc = beam_scores_resident(m, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s, &done);
-  if (rc || done) return rc;
+  if (beam_scores_shape(m, enc_window, n, dec_out, Bh, K) && !stream_capturing(s))   // a captured call has nobody to wait for it
+    return beam_scores_groups(m, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
   BeamWs ws;
   rc = beam_workspace(m, (size_t)n, (size_t)Bh, (size_t)Bh * n, &ws, s);
   if (rc) return rc;
@@ -1515,9 +1515,11 @@ int wind_beam_window_scores_static(wind_model *m, const float *enc_window, int n
   rc = static_scratch_address(&base);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  static_assert(sizeof(BeamGroupMem) <= WIND_STATIC_SCRATCH_BYTES, "one group at least");
-  if (beam_scores_shape(m, enc_window, n, dec_out, Bh, K))   // the sums of wind_beam_window_scores, which has the resident workgroups for these
-    return beam_scores_phases(m, reinterpret_cast<BeamGroupMem *>(base), WIND_STATIC_SCRATCH_BYTES, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
+  if (beam_scores_shape(m, enc_window, n, dec_out, Bh, K)) {   // the sums of wind_beam_window_scores, which has the resident workgroups for these
+    const BeamPhaseArea area = beam_phase_area(base, m->dev.Hj, m->dev.V, n, Bh, K);
+    if ((size_t)area.bytes * kGroups <= (size_t)WIND_STATIC_SCRATCH_BYTES)   // every such shape: 5.5 MB at most
+      return beam_scores_phases(m, area, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
+  }
   BeamWs ws;
   beam_carve(m, (size_t)n, (size_t)Bh, rows, base, &ws);
   // The buffer keeps the last call's contents.  The one place read before it is written: the rows
@@ -1681,6 +1683,7 @@ int wind_set_option(wind_model *m, const char *key, int64_t value) {
   if (!std::strcmp(key, "loop_spin_limit")) {
     if (value < 0 || value > (1ll << 30)) return fail(WIND_ERR_ARG, "loop_spin_limit must be in 0..2^30");
     m->opt_loop_spin_limit = value;
+    m->beam_res.rest_steps = m->beam_res.rest_searches = 0;
     return WIND_OK;
   }
   if (!std::strcmp(key, "enc_wide")) {

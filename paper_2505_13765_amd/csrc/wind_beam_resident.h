@@ -53,6 +53,21 @@ struct BeamGroupMem {
   unsigned long long lg[kBeamResRows * kBeamLgStride];
   unsigned long long row[kBeamResRows * kBeamRowWords];
 };
+// The scoring step as several launches: where a group's words lie, by the call's sizes.  A launch reads what the one before it wrote, so the
+// logits, most of it, need no numbers beside them.  8 groups of 8 hypotheses x 16 frames of 640 units and 1024 labels take 5.5 MB
+struct BeamPhaseArea {
+  unsigned char *base;
+  unsigned px, ex, row, bytes, lg_stride;   // byte offsets inside a group's part (logits: 0) and its size; floats of a row of logits
+};
+inline BeamPhaseArea beam_phase_area(void *base, int H, int V, int n, int Bh, int K) {
+  const unsigned hyps = (unsigned)(Bh + kGroups - 1) / kGroups, rows = hyps * (unsigned)n;
+  BeamPhaseArea a{(unsigned char *)base, 0, 0, 0, 0, ((unsigned)V + 32u) / 32u * 32u};
+  a.px = (rows * a.lg_stride * 4u + 255u) / 256u * 256u;
+  a.ex = a.px + hyps * (unsigned)H * 8u;
+  a.row = a.ex + (unsigned)n * (unsigned)H * 8u;
+  a.bytes = (a.row + rows * (2u + 2u * (unsigned)K) * 8u + 255u) / 256u * 256u;
+  return a;
+}
 struct BeamResDev {
   const unsigned long long *host_cmd;   // pinned: [kBeamCmdWords]
   unsigned long long *host_res;         // pinned: [kBeamResultWords]
@@ -68,7 +83,7 @@ struct BeamResDev {
   int n, Bh, K, split;
   int *out_labels, *out_jumps;
   float *out_scores;
-  int grp0, grp1;                       // as several launches: groups of this one, whose exchange words start at mem
+  BeamPhaseArea area;                   // as several launches
   unsigned written;                     // hypotheses written by all such launches (BeamGroupMem::word[1] of group 0) once this one is through
 };
 
@@ -79,6 +94,8 @@ struct BeamResCfg {
   static constexpr int QK = H / 4, QL = (QK + 63) / 64;     // a wave's quarter of K, and its words per lane
   static constexpr int EST = H + 4;                         // row stride in LDS (16 bytes of padding: banks)
   static constexpr int AST = 12;                            // partial sums of the prediction network: 8 rows, padded
+  // command, soft-max rows and merge: behind the rest, in launches of the scoring step ahead of it, some of which need no more
+  static constexpr size_t smem_rows = (4 * (kBeamCmdWords + 32 + 2 * 2 * 4 * kBeamResHyps + kBeamResFrames * kBeamRowWords) + 255) / 256 * 256;
   static constexpr size_t oE = 0;                                                   // float [16][EST] frames of the window
   static constexpr size_t oP = oE + (size_t)kBeamResFrames * EST * 4;               // float [16][EST] projections of the hypotheses
   static constexpr size_t oF = oP + (size_t)kBeamPrefixRows * EST * 4;                 // partial sums, one step at a time:
@@ -87,9 +104,9 @@ struct BeamResCfg {
                           oHst = oPredp + (size_t)4 * 16 * PT * AST * 4;            //   float [8][EST] new hidden vectors
   static constexpr size_t szNet = (size_t)4 * NR * AST * 4 + (size_t)4 * 16 * PT * AST * 4 + (size_t)kBeamResHyps * EST * 4;
   static constexpr size_t szEnc = (size_t)8 * 16 * PT * 20 * 4;                     //   one scoring step: float [8][16 PT][20]
-  static constexpr size_t oI = oF + (szLogits > szNet + szEnc ? szLogits : szNet + szEnc);
   static constexpr size_t oEncp = oF + szNet;
-  static constexpr size_t smem = oI + 4 * (kBeamCmdWords + 32 + 2 * 2 * 4 * kBeamResHyps + kBeamResFrames * kBeamRowWords);
+  static constexpr size_t oI = oF + (szLogits > szNet + szEnc ? szLogits : szNet + szEnc);
+  static constexpr size_t smem = oI + smem_rows;
   static_assert(smem <= 160 * 1024, "LDS");
 };
 
@@ -128,13 +145,15 @@ __device__ __forceinline__ void beam_split3(const float4 &a, const float4 &b, bf
 }
 
 // What both forms of the kernel do, per wave; HALF = wave / 4
-template <int KS, int HALF>
+// PHASES: the scoring step as several launches
+template <int KS, int HALF, bool PHASES = false>
 struct BeamRes {
   using Cfg = BeamResCfg<KS>;
   static constexpr int H = Cfg::H, QK = Cfg::QK, QL = Cfg::QL, EST = Cfg::EST, NR = Cfg::NR, UPW = Cfg::UPW;
   const ModelDev &m;
   const BeamResDev &r;
-  BeamGroupMem &x;
+  BeamGroupMem &x;               // not PHASES
+  unsigned char *const area;     // PHASES: this group's part
   int g, lane, l15, l4, wave, w4, tid;
   float *ecache, *pfull, *fred, *recp, *predp, *hst;
   int *cmd;                      // [kBeamCmdWords] the command; [0] first
@@ -147,15 +166,21 @@ struct BeamRes {
   bf16x8 wo[3][KS], wr[LH ? LH : 1][KS], wp[HALF == 0 ? Cfg::PT : 1][KS];
   float bias[3];
 
-  __device__ __forceinline__ BeamRes(const ModelDev &m_, const BeamResDev &r_, BeamGroupMem &x_, unsigned char *smem, int g_) : m(m_), r(r_), x(x_), g(g_) {
+  __device__ __forceinline__ unsigned long long *px() const { return PHASES ? reinterpret_cast<unsigned long long *>(area + r.area.px) : x.px; }
+  __device__ __forceinline__ unsigned long long *ex() const { return PHASES ? reinterpret_cast<unsigned long long *>(area + r.area.ex) : x.ex; }
+  __device__ __forceinline__ unsigned long long *row_words() const { return PHASES ? reinterpret_cast<unsigned long long *>(area + r.area.row) : x.row; }
+  __device__ __forceinline__ BeamRes(const ModelDev &m_, const BeamResDev &r_, int grp, unsigned char *smem, int g_)
+      : m(m_), r(r_), x(r_.mem[grp]), area(r_.area.base + (size_t)grp * r_.area.bytes), g(g_) {
     tid = threadIdx.x;
     lane = tid & 63; l15 = lane & 15; l4 = lane >> 4;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     w4 = wave & 3;
+    unsigned char *const small = smem + (PHASES ? 0 : Cfg::oI);
+    if (PHASES) smem += Cfg::smem_rows;
     ecache = reinterpret_cast<float *>(smem + Cfg::oE); pfull = reinterpret_cast<float *>(smem + Cfg::oP);
     fred = reinterpret_cast<float *>(smem + Cfg::oF); recp = reinterpret_cast<float *>(smem + Cfg::oRecp);
     predp = reinterpret_cast<float *>(smem + Cfg::oPredp); hst = reinterpret_cast<float *>(smem + Cfg::oHst);
-    cmd = reinterpret_cast<int *>(smem + Cfg::oI);
+    cmd = reinterpret_cast<int *>(small);
     s_max = reinterpret_cast<float *>(cmd + kBeamCmdWords); s_sum = s_max + 8; s_blank = s_sum + 8;
     flags = reinterpret_cast<int *>(s_blank + 2);
     s_wh = reinterpret_cast<unsigned *>(cmd + kBeamCmdWords + 32); s_wl = s_wh + 2 * 4 * kBeamResHyps;
@@ -196,6 +221,7 @@ struct BeamRes {
   // A wave that gave up goes on with whatever it holds, but nothing that follows from it is published under the command's number
   template <class Ask>
   __device__ __forceinline__ bool wait(const Ask &ask) const {
+    if constexpr (PHASES) { ask(); return true; }   // the launch before wrote them
     const bool got = beam_poll(abort_word(), r.session, r.spin_limit, ask);
     if (!got && lane == 0) flags[1] = 1;
     return got;
@@ -437,8 +463,11 @@ struct BeamRes {
         float v[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) v[w] = fred[(((w * 3 + t) * 4 + rt) * 4 + k) * 80 + lane];
-        if (row < rows && col <= m.V)
-          beam_st(&x.lg[row * kBeamLgStride + col], __float_as_uint((v[0] + v[1]) + (v[2] + v[3]) + (t == 0 ? bias[0] : t == 1 ? bias[1] : bias[2])), num);
+        const float logit = (v[0] + v[1]) + (v[2] + v[3]) + (t == 0 ? bias[0] : t == 1 ? bias[1] : bias[2]);
+        if (row < rows && col <= m.V) {
+          if constexpr (PHASES) reinterpret_cast<float *>(area)[(unsigned)row * r.area.lg_stride + (unsigned)col] = logit;
+          else beam_st(&x.lg[row * kBeamLgStride + col], __float_as_uint(logit), num);
+        }
       };
 #pragma unroll
       for (int q = 0; q < 4; ++q) finish(wave & 3, q, HALF);
@@ -464,7 +493,11 @@ struct BeamRes {
         wait([&]() {
           bool now = true;
 #pragma unroll
-          for (int i = 0; i < EPT; ++i) u[i] = group_ld(&x.lg[row * kBeamLgStride + min(v0 + 256 * i, V)]);
+          for (int i = 0; i < EPT; ++i) {
+            const int v = min(v0 + 256 * i, V);
+            if constexpr (PHASES) u[i] = __float_as_uint(reinterpret_cast<const float *>(area)[(unsigned)row * r.area.lg_stride + (unsigned)v]);
+            else u[i] = group_ld(&x.lg[row * kBeamLgStride + v]);
+          }
 #pragma unroll
           for (int i = 0; i < EPT; ++i) now = now && (unsigned)(u[i] >> 32) == seq;
           return now;
@@ -534,7 +567,7 @@ struct BeamRes {
             if (lane < 4 && myh == h && myl == l && h != 0u) ++head;
             if (lane == k) { res_h = h; res_l = l; }
           }
-          unsigned long long *out = x.row + row * (2 + 2 * K);
+          unsigned long long *out = row_words() + row * (2 + 2 * K);
           if (lane < K) {
             beam_st(out + 2 + 2 * lane, res_h != 0u ? __float_as_uint(beam_score_of(res_h)) : __float_as_uint(-INFINITY), seq);
             beam_st(out + 3 + 2 * lane, res_h != 0u ? ~res_l : ~0u, seq);
@@ -554,7 +587,7 @@ struct BeamRes {
   __device__ __forceinline__ void merge(int b, int n, int K, unsigned seq, const Put &put) {
     const int RW = 2 + 2 * K, total = n * RW, V1 = m.V + 1;
     constexpr int NQ = (kBeamResFrames * kBeamRowWords + 63) / 64;
-    const unsigned long long *src = x.row + (size_t)b * n * RW;
+    const unsigned long long *src = row_words() + (size_t)b * n * RW;
     unsigned long long u[NQ];
     const bool got = wait([&]() {
       bool now = true;
@@ -779,9 +812,9 @@ struct BeamRes {
         float v[8];
 #pragma unroll
         for (int w = 0; w < 8; ++w) v[w] = encp[(w * 16 * Cfg::PT + row) * 20 + e];
-        beam_st(&x.ex[e * H + u0 + row], __float_as_uint(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])) + m.b_enc[u0 + row]), seq);
+        beam_st(ex() + e * H + u0 + row, __float_as_uint(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])) + m.b_enc[u0 + row]), seq);
       } else {
-        beam_st(&x.px[(e - n) * H + u0 + row], __float_as_uint(sum4(predp, 16 * Cfg::PT, row, e - n) + m.b_pred[u0 + row]), seq);
+        beam_st(px() + (e - n) * H + u0 + row, __float_as_uint(sum4(predp, 16 * Cfg::PT, row, e - n) + m.b_pred[u0 + row]), seq);
       }
     }
     }
@@ -790,8 +823,8 @@ struct BeamRes {
     if (PHASE < 0 && 32 * g > m.V && g >= Bg * n) return;   // no column, no row
     if constexpr (PHASE < 0 || PHASE == 1) {
       if constexpr (PHASE == 1) load_w_out();
-      fetch_rows(x.ex, ecache, n, seq);
-      fetch_rows(x.px, pfull, Bg, seq);
+      fetch_rows(ex(), ecache, n, seq);
+      fetch_rows(px(), pfull, Bg, seq);
       group_barrier();
       logits(Bg * n, n, r.split, seq);
     }
@@ -819,8 +852,8 @@ __global__ __launch_bounds__(512) void beam_search_kernel(ModelDev m, BeamResDev
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   if (blockIdx.x % kGroups != 0) return;   // workgroups go to the XCDs in turn
   const int g = (int)blockIdx.x / kGroups;
-  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[0], smem_raw, g).search();
-  else BeamRes<KS, 1>(m, r, r.mem[0], smem_raw, g).search();
+  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, 0, smem_raw, g).search();
+  else BeamRes<KS, 1>(m, r, 0, smem_raw, g).search();
 }
 
 // One scoring step for up to 64 hypotheses and 16 frames, a group of workgroups per XCD, a single launch.  As five launches (two
@@ -831,16 +864,16 @@ __global__ __launch_bounds__(512) void beam_scores_kernel(ModelDev m, BeamResDev
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;
   if (grp >= r.Bh) return;
-  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp], smem_raw, g).template score<-1>(grp);
-  else BeamRes<KS, 1>(m, r, r.mem[grp], smem_raw, g).template score<-1>(grp);
+  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, grp, smem_raw, g).template score<-1>(grp);
+  else BeamRes<KS, 1>(m, r, grp, smem_raw, g).template score<-1>(grp);
 }
 template <int KS, int PHASE>
 __global__ __launch_bounds__(512) void beam_scores_phase_kernel(ModelDev m, BeamResDev r) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int grp = (int)blockIdx.x % kGroups, g = (int)blockIdx.x / kGroups;
-  if (grp >= r.Bh || grp < r.grp0 || grp >= r.grp1) return;
-  if (threadIdx.x < 256) BeamRes<KS, 0>(m, r, r.mem[grp - r.grp0], smem_raw, g).template score<PHASE>(grp);
-  else BeamRes<KS, 1>(m, r, r.mem[grp - r.grp0], smem_raw, g).template score<PHASE>(grp);
+  if (grp >= r.Bh) return;
+  if (threadIdx.x < 256) BeamRes<KS, 0, true>(m, r, grp, smem_raw, g).template score<PHASE>(grp);
+  else BeamRes<KS, 1, true>(m, r, grp, smem_raw, g).template score<PHASE>(grp);
 }
 
 }  // namespace wind

@@ -47,8 +47,7 @@ size_t beam_carve(const wind_model *m, size_t n, size_t Bh, size_t rows, char *b
 }
 
 // The model's own scoring workspace, allocated on first use and regrown on demand.
-int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws, hipStream_t s) {
-  const size_t off = beam_carve(m, n, Bh, rows, nullptr, nullptr);
+int beam_workspace_reserve(wind_model *m, size_t off, hipStream_t s) {
   if (off > m->beam_ws_bytes) {
     HIP_TRY(hipDeviceSynchronize());
     if (m->beam_ws) HIP_TRY(hipFree(m->beam_ws));
@@ -58,6 +57,11 @@ int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws, 
     m->beam_ws_bytes = off;
     HIP_TRY(hipMemsetAsync(m->beam_ws, 0, off, s));   // the MFMA pass reads whole row tiles; on the stream that the pass runs on
   }
+  return WIND_OK;
+}
+int beam_workspace(wind_model *m, size_t n, size_t Bh, size_t rows, BeamWs *ws, hipStream_t s) {
+  const int rc = beam_workspace_reserve(m, beam_carve(m, n, Bh, rows, nullptr, nullptr), s);
+  if (rc) return rc;
   beam_carve(m, n, Bh, rows, (char *)m->beam_ws, ws);
   return WIND_OK;
 }
@@ -188,13 +192,13 @@ struct BeamInstance {
   void (*search)(ModelDev, BeamResDev);
   void (*scores)(ModelDev, BeamResDev);
   void (*phases[4])(ModelDev, BeamResDev);
-  size_t smem;
+  size_t smem, smem_rows;
 };
 template <int KS>
 constexpr BeamInstance beam_instance() { return {beam_search_kernel<KS>,
                                                                    beam_scores_kernel<KS>,
                                                                    {beam_scores_phase_kernel<KS, 0>, beam_scores_phase_kernel<KS, 1>, beam_scores_phase_kernel<KS, 2>, beam_scores_phase_kernel<KS, 3>},
-                                                                   BeamResCfg<KS>::smem}; }
+                                                                   BeamResCfg<KS>::smem, BeamResCfg<KS>::smem_rows}; }
 const BeamInstance kBeamInstances[] = {beam_instance<1>(), beam_instance<2>(), beam_instance<3>(), beam_instance<4>(), beam_instance<5>()};   // by width / 128
 // Models that resident workgroups hold: bf16, one LSTM layer as wide as the joiner and of up to 640 units, up to 1024 labels, as the
 // resident groups of the decoder; and the options that ask for those
@@ -220,6 +224,7 @@ int beam_resident_reserve(wind_model *m, hipStream_t s) {
 }
 
 constexpr unsigned kBeamSessionCommands = 256;    // commands of one launch: whatever else waits for the stream gets its turn
+constexpr int kBeamRestSearches = 8;              // searches on launches after one whose workgroups could not meet
 constexpr double kBeamIdleMs = 1.0;               // without a command for this long the workgroups leave (a callback may take any time)
 
 // The resident workgroups as one search uses them.  They stay from open() to close(), or until they have been idle, have
@@ -306,6 +311,7 @@ struct BeamSession {
       if (arrived()) { *done = true; ++m->route.beam_commands; return WIND_OK; }
       if (__atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) != (br.session << 2 | kBeamExitIdle)) {
         usable = false;
+        br.rest_searches = kBeamRestSearches;   // the wait for the workgroups took up to 12 ms: the next searches do without
         ++m->route.beam_gave_up;
         return WIND_OK;
       }
@@ -320,77 +326,91 @@ bool beam_scores_shape(const wind_model *m, const float *enc_window, int n, cons
   return Bh <= kGroups * kBeamResHyps && n <= kBeamResFrames && K <= kBeamResHyps && beam_resident_model(m) && ((uintptr_t)enc_window | (uintptr_t)dec_out) % 16 == 0;
 }
 
-// The same sums in launches that wait for nobody (see BeamRes::score), with as many groups at a time as `mem` has room for
-int beam_scores_phases(wind_model *m, BeamGroupMem *mem, size_t bytes, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
+// The same sums in launches that wait for nobody (see BeamRes::score), in `area`.  Static entry point, n = 16, K = 8, 640 units, 1024 labels, called
+// alone: 1 / 8 / 16 / 64 hypotheses 41 / 41 / 42 / 53 us; as two projections, logits, rows and merge 53 / 48 / 52 / 73
+int beam_scores_phases(wind_model *m, const BeamPhaseArea &area, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
                        int32_t *out_jumps, float *out_scores, hipStream_t s) {
   BeamResDev r{};
-  r.mem = mem;
+  r.mem = reinterpret_cast<BeamGroupMem *>(area.base);   // not looked at
+  r.area = area;
   r.session = r.first = 1;
-  r.spin_limit = kGroupStartPolls;
   r.enc = enc_window; r.dec = dec_out;
   r.n = n; r.Bh = Bh; r.K = K; r.split = m->opt_beam_exact ? 1 : 0;
   r.out_labels = out_labels; r.out_jumps = out_jumps; r.out_scores = out_scores;
   const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
-  const int step = (int)std::min<size_t>(bytes / sizeof(BeamGroupMem), kGroups);
-  for (r.grp0 = 0; r.grp0 < std::min(Bh, kGroups); r.grp0 = r.grp1) {
-    r.grp1 = r.grp0 + step;
-    for (auto phase : k.phases) phase<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
-  }
+  const int hyps = (Bh + kGroups - 1) / kGroups;
+  const int wgs[4] = {kBeamResWgs, kBeamResWgs, std::min(kBeamResWgs, hyps * n), hyps};   // workgroups that have a part in a phase
+  for (int p = 0; p < 4; ++p) k.phases[p]<<<kGroups * wgs[p], 512, p < 2 ? k.smem : k.smem_rows, s>>>(m->dev, r);
   return check_launch("beam scoring step");
 }
 
-// One scoring step as a single launch.  `done`: the results are in the caller's buffers; else (the workgroups could not meet) nothing of it
-// runs any more and the caller takes the launches.
-int beam_scores_resident(wind_model *m, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
-                         int32_t *out_jumps, float *out_scores, hipStream_t s, bool *done) {
-  *done = false;
-  // a captured call has nobody to wait for it
-  if (!beam_scores_shape(m, enc_window, n, dec_out, Bh, K) || stream_capturing(s)) return WIND_OK;
-  int rc = beam_resident_reserve(m, s);
-  if (rc) return rc;
+// Workgroups of a scoring step wait this long (about 1.5 ms) for all of their group to be on the chip: beside a stream of large matrix products a step
+// takes 0.95 ms that way and 3.5 as several launches, which each wait for CUs as well.  Where something keeps CUs for longer, every step would
+// lose that: after a failure the next kBeamRest steps take the launches at once.
+constexpr unsigned kBeamStepStartPolls = 1u << 13;
+constexpr int kBeamRest = 256;
+
+// One scoring step of a shape that beam_scores_shape takes, as a single launch, or, if its workgroups cannot meet, as several.  Either way the same
+// sums, to the bit; returns with the results in the caller's buffers.
+int beam_scores_groups(wind_model *m, const float *enc_window, int n, const float *dec_out, int Bh, int K, int32_t *out_labels,
+                       int32_t *out_jumps, float *out_scores, hipStream_t s) {
   BeamResident &br = m->beam_res;
-  BeamResDev r{};
-  r.host_exit = &br.dev->exit;
-  r.mem = br.mem;
-  r.session = ++br.session;
-  r.first = ++br.seq;
-  r.spin_limit = (unsigned)m->opt_loop_spin_limit;
-  r.start_limit = std::min(r.spin_limit, kGroupStartPolls);
-  r.enc = enc_window; r.dec = dec_out;
-  r.n = n; r.Bh = Bh; r.K = K; r.split = m->opt_beam_exact ? 1 : 0;
-  r.out_labels = out_labels; r.out_jumps = out_jumps; r.out_scores = out_scores;
-  r.written = br.written += (unsigned)Bh;
-  ResidentGate &gate = g_resident[m->device];
-  unsigned long long turn = 0;
-  {
-    std::lock_guard<std::mutex> lock(gate.mutex);
-    rc = resident_enter(gate, s);
+  if (br.rest_steps > 0) {
+    --br.rest_steps;
+  } else {
+    int rc = beam_resident_reserve(m, s);
     if (rc) return rc;
-    const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
-    k.scores<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
-    rc = check_launch("beam scoring step");
-    if (rc) return rc;
-    rc = resident_leave(gate, s, &turn);
-    if (rc) return rc;
-  }
-  const auto arrived = [&]() { return __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == r.session; };
-  for (unsigned spins = 1; !(*done = arrived()); ++spins) {
-    if ((spins & 0x3FFu) == 0) {
-      const hipError_t e = hipStreamQuery(s);
-      if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("beam scoring step: ") + hipGetErrorString(e));
-      if (e == hipSuccess) {
-        *done = arrived();
-        break;
-      }
+    BeamResDev r{};
+    r.host_exit = &br.dev->exit;
+    r.mem = br.mem;
+    r.session = ++br.session;
+    r.first = ++br.seq;
+    r.spin_limit = (unsigned)m->opt_loop_spin_limit;
+    r.start_limit = std::min(r.spin_limit, kBeamStepStartPolls);
+    r.enc = enc_window; r.dec = dec_out;
+    r.n = n; r.Bh = Bh; r.K = K; r.split = m->opt_beam_exact ? 1 : 0;
+    r.out_labels = out_labels; r.out_jumps = out_jumps; r.out_scores = out_scores;
+    r.written = br.written += (unsigned)Bh;
+    ResidentGate &gate = g_resident[m->device];
+    unsigned long long turn = 0;
+    {
+      std::lock_guard<std::mutex> lock(gate.mutex);
+      rc = resident_enter(gate, s);
+      if (rc) return rc;
+      const BeamInstance &k = kBeamInstances[m->dev.Hj / 128 - 1];
+      k.scores<<<kGroups * kBeamResWgs, 512, k.smem, s>>>(m->dev, r);
+      rc = check_launch("beam scoring step");
+      if (rc) return rc;
+      rc = resident_leave(gate, s, &turn);
+      if (rc) return rc;
     }
-    __builtin_ia32_pause();
-  }
-  resident_done(gate, turn);
-  ++(*done ? m->route.scores_resident : m->route.scores_gave_up);
-  if (!*done) {   // some of its hypotheses may have been written: the count starts again
-    HIP_TRY(hipMemsetAsync(&br.mem[0].word[1], 0, sizeof(unsigned), s));
+    bool done = false;
+    const auto arrived = [&]() { return __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == r.session; };
+    for (unsigned spins = 1; !(done = arrived()); ++spins) {
+      if ((spins & 0x3FFu) == 0) {
+        const hipError_t e = hipStreamQuery(s);
+        if (e != hipSuccess && e != hipErrorNotReady) return fail(WIND_ERR_HIP, std::string("beam scoring step: ") + hipGetErrorString(e));
+        if (e == hipSuccess) {
+          done = arrived();
+          break;
+        }
+      }
+      __builtin_ia32_pause();
+    }
+    resident_done(gate, turn);
+    ++(done ? m->route.scores_resident : m->route.scores_gave_up);
+    if (done) return WIND_OK;
+    br.rest_steps = kBeamRest;
+    HIP_TRY(hipMemsetAsync(&br.mem[0].word[1], 0, sizeof(unsigned), s));   // some of its hypotheses may have been written: the count starts again
     br.written = 0;
   }
+  BeamPhaseArea area = beam_phase_area(nullptr, m->dev.Hj, m->dev.V, n, Bh, K);
+  int rc = beam_workspace_reserve(m, (size_t)area.bytes * std::min(Bh, kGroups), s);
+  if (rc) return rc;
+  area.base = (unsigned char *)m->beam_ws;
+  rc = beam_scores_phases(m, area, enc_window, n, dec_out, Bh, K, out_labels, out_jumps, out_scores, s);
+  if (rc) return rc;
+  HIP_TRY(hipStreamSynchronize(s));
   return WIND_OK;
 }
 
@@ -491,12 +511,13 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
   if (rc) return rc;
   st.decoder_steps = 1;
   BeamSession session(m, s);
+  BeamResident &br = m->beam_res;
   if (K <= kBeamResHyps && window <= kBeamResFrames && beam_resident_model(m)) {
     rc = beam_resident_reserve(m, s);
     if (rc) return rc;
-    session.usable = true;
+    if (br.rest_searches > 0) --br.rest_searches;
+    else session.usable = true;
   }
-  BeamResident &br = m->beam_res;
   auto put = [](unsigned (&words)[kBeamCmdWords], int kind, int fresh, int Bh, int n, int t, int K, int split) {
     words[kBeamAtHead] = (unsigned)(kind | fresh << 8 | Bh << 16 | n << 24);
     words[kBeamAtFrame] = (unsigned)t;
