@@ -225,7 +225,12 @@ int beam_resident_reserve(wind_model *m, hipStream_t s) {
 
 constexpr unsigned kBeamSessionCommands = 256;    // commands of one launch: whatever else waits for the stream gets its turn
 constexpr int kBeamRestSearches = 8;              // searches on launches after one whose workgroups could not meet
-constexpr double kBeamIdleMs = 1.0;               // without a command for this long the workgroups leave (a callback may take any time)
+constexpr double kBeamIdleMs = 1.0;               // without a command for this long the workgroups leave
+// .. of a search with a callback, which may take any time and may wait for the GPU, workgroups included: about a pass with launches.  Once they have
+// left for that reason kBeamSlowCallbacks times in a row they are sent away ahead of the search's callbacks.  A callback that synchronises with the device, 280 passes: 16.2 ms
+// on launches, 292 with a wait of 1 ms each, now 12
+constexpr double kBeamCallbackIdleMs = 0.04;
+constexpr int kBeamSlowCallbacks = 3;
 
 // The resident workgroups as one search uses them.  They stay from open() to close(), or until they have been idle, have
 // had their number of commands, or another call waits for its turn; the next command launches them again.
@@ -233,6 +238,8 @@ struct BeamSession {
   wind_model *m;
   hipStream_t s;
   bool usable = false, is_open = false;   // usable: shape and options allow it, and nothing has gone wrong so far
+  bool callback = false;
+  int idle_callbacks = 0;   // callbacks in a row in which the workgroups went idle; from kBeamSlowCallbacks on for the rest of the search
   unsigned long long turn = 0;
   unsigned commands = 0;
 
@@ -253,7 +260,7 @@ struct BeamSession {
     r.first = br.seq;
     r.spin_limit = (unsigned)m->opt_loop_spin_limit;
     r.start_limit = std::min(r.spin_limit, kGroupStartPolls);
-    r.idle_ticks = (unsigned long long)(kBeamIdleMs * m->clock_khz);
+    r.idle_ticks = (unsigned long long)((callback ? kBeamCallbackIdleMs : kBeamIdleMs) * m->clock_khz);
     std::lock_guard<std::mutex> lock(gate.mutex);
     int rc = resident_enter(gate, s);
     if (rc) return rc;
@@ -286,6 +293,7 @@ struct BeamSession {
     BeamResident &br = m->beam_res;
     *done = false;
     if (is_open && (commands >= kBeamSessionCommands || g_resident[m->device].turn.load(std::memory_order_relaxed) != turn)) close();
+    bool stayed = is_open;
     for (;;) {
       ++br.seq;   // a number of its own for every try: under the last one idle workgroups have been told to leave
       for (int i = 0; i < nres; ++i) __atomic_store_n(&br.host->res[i], 0ull, __ATOMIC_RELAXED);
@@ -297,7 +305,12 @@ struct BeamSession {
       ++commands;
       bool left = false;
       for (unsigned spins = 1; !left; ++spins) {
-        if (arrived()) { *done = true; ++m->route.beam_commands; return WIND_OK; }
+        if (arrived()) {
+          *done = true;
+          ++m->route.beam_commands;
+          if (stayed && idle_callbacks < kBeamSlowCallbacks) idle_callbacks = 0;
+          return WIND_OK;
+        }
         left = __atomic_load_n(&br.host->exit, __ATOMIC_ACQUIRE) >> 2 == br.session;
         if (!left && (spins & 0x3FFFu) == 0) {   // a kernel that failed never says that it has left
           const hipError_t e = hipStreamQuery(s);
@@ -316,6 +329,8 @@ struct BeamSession {
         return WIND_OK;
       }
       ++m->route.beam_idle;
+      stayed = false;
+      if (callback) ++idle_callbacks;
       // idle when the command came: the next launch takes it
     }
   }
@@ -517,6 +532,7 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     if (rc) return rc;
     if (br.rest_searches > 0) --br.rest_searches;
     else session.usable = true;
+    session.callback = on_round != nullptr;
   }
   auto put = [](unsigned (&words)[kBeamCmdWords], int kind, int fresh, int Bh, int n, int t, int K, int split) {
     words[kBeamAtHead] = (unsigned)(kind | fresh << 8 | Bh << 16 | n << 24);
@@ -775,6 +791,7 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     st.hyps_scored += Bh;
 
     if (on_round) {
+      if (session.idle_callbacks >= kBeamSlowCallbacks) session.close();
       cb_len.clear(); cb_tok.clear(); cb_fr.clear(); cb_sym.clear(); cb_score.clear();
       for (const BeamHyp &h : hyps) {
         const std::vector<int> tk = tokens_of(h.node);

@@ -210,3 +210,32 @@ def test_steps_and_searches_after_a_failed_meeting(torch_cuda):  # noqa: F811
     m.beam_window_scores(e, d, 4)
     assert m.route_counts().scores_resident == 2
     m.close()
+
+
+def test_callbacks_that_wait_for_the_gpu(torch_cuda):  # noqa: F811
+    """A callback that synchronises with the device waits for the workgroups too, until they leave: the first few times, and no longer than a pass
+    with launches takes."""
+    from paper_2505_13765_amd import WindModel
+
+    torch = torch_cuda
+    cfg, w = small(640, 1024, 60, 4, 3)
+    m = WindModel.from_config(cfg, w)
+    e = torch.from_numpy(wi.make_batch(cfg)[0][0]).cuda()
+    want = m.beam_decode(e, 16, 4, 3)
+    waits = []
+
+    class Waiting(list):
+        def append(self, x):
+            t = time.perf_counter()
+            torch.cuda.synchronize()
+            waits.append(time.perf_counter() - t)
+            super().append(x)
+
+    before = m.route_counts()
+    got = m.beam_decode(e, 16, 4, 3, trace=Waiting())
+    after = m.route_counts()
+    assert got[0].tolist() == want[0].tolist() and got[2] == want[2] and len(waits) == got[3].rounds > 40
+    print(f"{len(waits)} callbacks, wait {1e6 * np.median(waits):.0f} us, {after.beam_idle - before.beam_idle} idle")
+    assert after.beam_idle - before.beam_idle <= 4 and after.beam_gave_up == 0
+    assert np.median(waits) < 200e-6   # 1 ms of an idle launch each before; a synchronisation alone takes 10 us
+    m.close()
