@@ -384,8 +384,9 @@ int wind_get_route_counts(wind_model *m, wind_route_counts *out);
  *   "lookahead"  1 (default): an iteration of the resident groups looks at as many frames of an utterance as their row tiles
  *             have rows for (16, or 8 with more than two utterances per XCD), also beyond the end of the caller's window: labels
  *             and frames do not depend on how the frames are cut into windows, and the counters stay those of the
- *             caller's.  Large synchronous batches of the per-step kernels (64 utterances, windows of 16 and more) may look at
- *             8 rows of a window at a time where most labels lie in those.  0: always the caller's window (what a window of that size costs; the standard loop frame by frame)
+ *             caller's.  Bf16 batches of more than 16 utterances look at 8 frames at a time with either value.  Large synchronous batches of the per-step kernels (64 utterances, windows of 16 and more) may look at
+ *             8 rows of a window at a time where most labels lie in those.  0: no further than the caller's window (what a window of that size costs, but for windows of more than 8 frames in bf16 groups of more
+ *             than 16 utterances, see above; the standard loop frame by frame)
  *   "loop_fused"  1 (default): with at most 16 window rows and a joint hidden size that is a multiple of 128,
  *             at most 640, that kernel builds the window rows directly as matrix-core operands; 0: it
  *             stages them in LDS (the form for every other shape)

@@ -934,8 +934,8 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   // Behind an asynchronous call no host decodes it again if the groups cannot meet: it takes them only where no two workgroups have to
   // (one per utterance), or where the other choice is a kernel whose workgroups have to meet as well.
   if (async && gi && gi->gw != 1 && !use_loop) gi = nullptr;
-  // Calls whose windows may be cut (see the loop below); res_state has no use there (lists_atomic) and the room.  An asynchronous call's caller
-  // counts iterations
+  // Calls whose windows may be cut (see the loop below).  What is open in an utterance's window lies in res_state, which has no
+  // use here (lists_atomic) and the room for two lists from 64 utterances on (slot_stride == B).  An asynchronous call's caller counts iterations
   if (!gi && !use_loop && !async && c.lists_atomic && m->opt_lookahead && m->opt_graph && !m->opt_profile && !m->opt_host_sync && W >= 2 * kShortReach &&
       T >= 8 * m->opt_unroll && B == c.slot_stride && (long long)B * W > cut_rows(m))
     c.slot_win = reinterpret_cast<int2 *>(c.res_state);

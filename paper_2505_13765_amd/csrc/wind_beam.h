@@ -354,16 +354,14 @@ __device__ __forceinline__ unsigned beam_order_bits(float s) {
 __device__ __forceinline__ float beam_score_of(unsigned hi) {
   return __uint_as_float((hi & 0x80000000u) ? (hi & 0x7FFFFFFFu) : ~hi);
 }
-// Largest (hi, lo) pair of each group of WIDTH lanes (64: the wave, 16: a row of lanes, 4: a quad), in every lane of the group.
+// Largest (hi, lo) pair of each group of WIDTH lanes (64: the wave, 16: a row of lanes), in every lane of the group.
 // The largest hi by DPP permutations (one instruction a step, no trip through the LDS crossbar), then the lo of the lane that has
 // it; only where several do (equal scores, or nothing left) are their lo words compared as well.  As one 64-bit comparison per
 // step a round took three times the instructions.
 template <int WIDTH>
 __device__ __forceinline__ unsigned lanes_max_u32(unsigned v) {
-  if (WIDTH > 4) {
-    v = max(v, (unsigned)dpp_i32<kDppRowMirror>((int)v));
-    v = max(v, (unsigned)dpp_i32<kDppRowHalfMirror>((int)v));
-  }
+  v = max(v, (unsigned)dpp_i32<kDppRowMirror>((int)v));
+  v = max(v, (unsigned)dpp_i32<kDppRowHalfMirror>((int)v));
   v = max(v, (unsigned)dpp_i32<kDppQuadXor2>((int)v));
   v = max(v, (unsigned)dpp_i32<kDppQuadXor1>((int)v));
   if (WIDTH == 64)

@@ -1,5 +1,5 @@
 // Beam search on resident workgroups: the passes of a search without a launch and without a wait for the stream, and one scoring
-// step as a single launch.
+// step as a single launch, or as four that wait for nobody.
 #pragma once
 #include "wind_beam.h"
 #include "wind_group_kernel.h"
@@ -13,7 +13,7 @@ namespace wind {
 // weights in registers as matrix-core operands, and exchange through that XCD's L2 as the resident groups of the decoder do: every
 // 8-byte word carries the number of the command it belongs to, a reader asks until all it needs are of its own.
 // 640 units, 1024 labels, K = 4, windows of 16: a command takes 14.7 us as the host sees it: network step 3.8 (two exchanges),
-// projections 1.3, logits 2.4, soft-max rows 2.1, merge 2.2, the bus and the pass-on 2.9; a search of 250 frames 51.1 -> 24.1 ms.
+// projections 1.3, logits 2.4, soft-max rows 2.1, merge 2.2, the bus and the pass-on 2.9; a search of 250 frames 51.1 -> 24.1 ms (18.7 to 20 with the host's part as it is now).
 //
 // Commands come from the host, one per pass, through pinned memory, results go back the same way, both as such words: a pass is one
 // trip over the bus each way (about 2 us), four exchanges in the L2 and the steps between them.
@@ -23,6 +23,10 @@ namespace wind {
 // workgroup is done with that one: no word is overwritten before its readers have it.  Every other wait is bounded by spin_limit
 // (the first one, for all workgroups to be on the chip, by start_limit); a wave that gives up sets the abort word, all leave, and
 // the host runs the rest of the search with launches.
+//
+// The state slots (h, c, p) carry no numbers and are read through each CU's own vector cache: a slot is written once in a launch, by all workgroups,
+// and no line of it is read before that (the host hands out slots that rise and never come back, and every index that is clamped, for
+// lanes or sequences beyond the last, is clamped to one that the command names).  Whoever uses a slot again has to read it past that cache.
 //
 // Workgroup g: columns 32 g .. 32 g + 31 of W_out (the blank of 1024-label models: workgroup 31 as well), 4 KS LSTM units, 4 KS rows
 // of W_pred.  K is split in four over the waves of a half; the halves (waves 0-3 and 4-7) share the row tiles of the logits and the recurrent

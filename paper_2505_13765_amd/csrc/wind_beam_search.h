@@ -1,8 +1,8 @@
 // Host side of WIND beam search (section "A Novel Beam-search Algorithm for WIND", Algorithm 3):
 // the map from frames to hypotheses, recombination, the prefix step, pruning and the expansion
 // loop run on the host; every model evaluation (encoder projection, prediction-network steps for
-// new label sequences, joiner rows, soft-max, P' of Eq. 1 and the K best pairs) runs in kernels of
-// wind_beam.h.  Included by wind_api.hip after wind_model and its helpers.
+// new label sequences, joiner rows, soft-max, P' of Eq. 1 and the K best pairs) runs on the GPU: on the
+// resident workgroups of wind_beam_resident.h where model and search fit them, else in the kernels of wind_beam.h.  Included by wind_api.hip after wind_model and its helpers.
 //
 // Label sequences are nodes of a trie (parent, label), so that "same sequence" is "same node" and
 // "A is a prefix of B" is "A is an ancestor of B".  A node gets a state slot (LSTM h and c of every
@@ -740,7 +740,7 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
       BeamNode &nd = nodes[hyps[b].node];
       fresh_of[b] = 0;
       if (nd.slot < 0) {
-        nd.slot = next_slot++;
+        nd.slot = next_slot++;   // never used again in this search: see the resident workgroups' reads
         parent[fresh] = nodes[nd.parent].slot; child[fresh] = nd.slot; tok[fresh] = nd.token;
         fresh_of[b] = ++fresh;
       }

@@ -42,7 +42,9 @@ namespace wind {
 // are cut into RG = 2 row groups, each covering all columns with GW / 2 workgroups.  640 units, 1024 labels, lengths 200 .. 1500: 13 utterances
 // (two slots), one tile of 2 x 8 rows 1.51 ms, two of 16 1.39; 20 (three slots), 3 x 5 rows 1.83, two tiles of 2 x 8 1.68, three
 // of 16 1.73; 32 (four), 4 x 4 2.90, two tiles of 2 x 8 2.47, four of 16 2.63.  As many frames as the caller's
-// window, before: one utterance of 1000 frames 2.94 / 1.26 / 0.98 / 0.84 ms at W = 1 / 4 / 8 / 16, now 0.84 at each.
+// window, before: one utterance of 1000 frames 2.94 / 1.26 / 0.98 / 0.84 ms at W = 1 / 4 / 8 / 16, now 0.84 at each (0.75 with kGroupOne).
+// With three and four slots two tiles cost something where hardly any frame has a label and windows are long: 32 utterances at W = 16, four
+// tiles of 16 rows / two of 2 x 8: 15 labels in 100 frames 2.61 / 2.45 ms, 6 1.82 / 1.75, 2 0.85 / 0.93, none 0.53 / 0.71.
 template <int KS, int CT, int GW>
 struct GroupCfg {
   static constexpr int H = 128 * KS;                      // = Hp = Hj
