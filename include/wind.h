@@ -397,7 +397,8 @@ int wind_get_route_counts(wind_model *m, wind_route_counts *out);
  *   "loop_spin_limit"  polls a workgroup of a resident kernel waits for the others before it gives up
  *             (default 2^21, about half a second); the decode then returns WIND_ERR_HIP.  Groups that are not all on the chip
  *             within 2^16 polls, about 12 ms, leave the call to the kernels that take it without them (an asynchronous
- *             call: the whole limit, and the error).  Tests set it
+ *             call: the whole limit, and the error; a beam scoring step: 2^13 polls, and the next 256 steps, as the next 8 searches after a
+ *             search's 2^16, do without).  Tests set it
  *             to 0 to exercise that path: every workgroup still leaves the kernel normally
  *   "atomic_lists"  1 (default): in the graph of per-step kernels of bf16 models, every workgroup of the
  *             decision kernel claims its utterance's place in the next iteration's list of active
