@@ -242,13 +242,16 @@ void set_tau(wind_model *m) {
 constexpr int kGroupMaxB16 = 224;
 constexpr unsigned kGroupStartPolls = 1u << 16;   // about 12 ms, what a batch of 32 takes with the per-step kernels
 constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long);   // flags and counters as group_collect_kernel writes them
+constexpr int kGroupMaxV = 1024;   // labels of models that wind_group_kernel takes
+// Quads of a window, at most, in wind_group_vocab_kernel: the rings of projected frames fill LDS (two windows of 8 rows each for 32 slots)
+constexpr int vocab_qmax(int slots) { return slots > 16 ? 2 : 4; }
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {
   size_t total, Mpad, st;
   bool big_enc;
   int slot_stride, nparts, nparts_tiny;
   size_t o_e, o_encb, o_len, o_nact, o_eidx, o_eltok, o_slot, o_slotc, o_rst, o_raux, o_nemit, o_ticket, o_h, o_c, o_hn, o_hb,
-      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder, o_gout;
+      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder, o_gout, o_vx, o_v0;
 };
 
 WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
@@ -292,12 +295,15 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_lbar = take((size_t)(1 + 256) * kLoopFlagStride * 4); w.o_lh = take((size_t)kLoopMaxB * d.Hp * 4);
   w.o_lp = take((size_t)kLoopMaxB * d.Hj * 4);
   w.o_lparts = take((size_t)2 * kLoopRows * w.nparts_tiny * 8);
-  const bool grouped = d.start_p != nullptr;   // models that decode in resident groups
-  w.o_gbar = take(grouped ? (size_t)kGroups * kGroupBarInts * 4 : 0);
+  const bool resident = d.start_p != nullptr, vocab = resident && d.V > kGroupMaxV, grouped = resident && !vocab;   // models that decode in resident groups
+  w.o_gbar = take(resident ? (size_t)kGroups * kGroupBarInts * 4 : 0);
   w.o_gx = take(grouped ? (size_t)2 * kGroups * kGroupSlots * d.Hp * 8 : 0);
   w.o_gkeys = take(grouped ? (size_t)kGroups * 2 * kGroupRows * (w.nparts_tiny + 1) * 8 : 0);
-  w.o_gorder = take(grouped ? (size_t)(kGroupMaxB + 1) * 4 : 0);
-  w.o_gout = take(grouped ? kGroupOutBytes : 0);   // an asynchronous call's flags and counters
+  w.o_gorder = take(resident ? (size_t)(kGroupMaxB + 1) * 4 : 0);
+  w.o_gout = take(resident ? kGroupOutBytes : 0);   // an asynchronous call's flags and counters
+  const int vslots = std::min(kVocabSlots, (B + kGroups - 1) / kGroups);
+  const VocabLayout v = vocab ? vocab_layout(d.Hj, w.nparts_tiny, vslots, vocab_qmax(vslots)) : VocabLayout{};
+  w.o_vx = take(v.ones * kGroups * 8); w.o_v0 = take(v.zeros * kGroups * 8);
   w.total = off;
   return w;
 }
@@ -381,6 +387,8 @@ void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B) {
   m->group.keys = (unsigned long long *)(base + w.o_gkeys);
   m->group.order = (int *)(base + w.o_gorder);
   m->group.n_order = m->group.order + kGroupMaxB;
+  m->group.vx = (unsigned long long *)(base + w.o_vx);
+  m->group.v0 = (unsigned long long *)(base + w.o_v0);
   m->group_out = (int *)(base + w.o_gout);
 }
 
@@ -771,11 +779,24 @@ const GroupInstance kGroupInstances[] = {
     group_instance<3, 2, 32>(), group_instance<4, 1, 32>(), group_instance<4, 2, 32>(), group_instance<5, 1, 32>(), group_instance<5, 2, 32>(),
     group_f32_instance<2, 1, 1>(), group_f32_instance<2, 4, 1>(), group_f32_instance<4, 1, 1>(), group_f32_instance<4, 4, 1>(), group_f32_instance<2, 1, 32>(), group_f32_instance<4, 1, 32>(),
     group_f32_instance<8, 1, 32>(), group_f32_instance<12, 1, 32>(), group_f32_instance<16, 1, 32>(), group_f32_instance<20, 1, 32>()};
+template <int KS>
+constexpr GroupInstance vocab_instance() {
+  return {{wind_group_vocab_kernel<KS>, wind_group_vocab_kernel<KS>, nullptr}, VocabCfg<KS>::smem, WIND_BF16, VocabCfg<KS>::H, 4, 32};
+}
+const GroupInstance kVocabInstances[] = {vocab_instance<1>(), vocab_instance<2>(), vocab_instance<3>(), vocab_instance<4>(), vocab_instance<5>()};
+// Four parts of 32 labels per workgroup, one per wave that multiplies, fill its registers.  More labels take the per-step kernels.  With any
+// number of utterances, width, window and share of labels groups were ahead in that range (wind_group_vocab_kernel.h).
+constexpr int kVocabMaxV = 4096;
 
 // Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts), a width
 // that some instance has.
 bool group_model(int dtype, const ModelDev &d) {
-  if (d.L != 1 || d.Hp != d.Hj || d.V > 1024 || (unsigned long long)(d.V + 1) * 4 * d.Hp >= (1ull << 31)) return false;
+  if (d.L != 1 || d.Hp != d.Hj || (unsigned long long)(d.V + 1) * 4 * d.Hp >= (1ull << 31)) return false;
+  if (d.V > kGroupMaxV) {   // bf16, 1025 to 4096 labels: wind_group_vocab_kernel
+    for (const GroupInstance &i : kVocabInstances)
+      if (dtype == WIND_BF16 && d.V <= kVocabMaxV && i.H == d.Hj) return true;
+    return false;
+  }
   for (const GroupInstance &i : kGroupInstances)
     if (i.dtype == dtype && i.H == d.Hj) return true;
   return false;
@@ -791,6 +812,24 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
   if (B > kLoopMaxB && (!m->opt_lstm_rec || !m->opt_atomic_lists || !m->opt_slot_rows || !m->opt_decide_two || m->opt_joint_wide != 1 ||
                         m->opt_pred_mfma_min_batch > B)) return nullptr;
   const int nparts = (d.V + kTinyCols - 1) / kTinyCols;
+  gd->qmax = 0;
+  if (d.V > kGroupMaxV) {
+    gd->NG = gd->NX = std::min(kGroups, B);
+    gd->NS = (B + gd->NG - 1) / gd->NG;
+    gd->RG = gd->SPT = 1;
+    gd->qmax = vocab_qmax(gd->NS);
+    gd->qmin = gd->NS <= 2 ? 4 : gd->NS <= 4 ? 2 : 1;   // as many rows as one chunk of products has room for
+    gd->ring = gd->NS > 16 ? 16 : 32;
+    gd->reach = m->opt_lookahead ? kGroupMaxW : std::min(kGroupMaxW, W);
+    gd->win = W;
+    gd->win_inv = 65536u / (unsigned)W + 1u;
+    const VocabLayout v = vocab_layout(d.Hj, nparts, gd->NS, gd->qmax);
+    gd->n_ones = v.ones * gd->NG;
+    gd->n_zeros = v.zeros * gd->NG;
+    for (const GroupInstance &i : kVocabInstances)
+      if (m->dtype == WIND_BF16 && i.H == d.Hj) return &i;
+    return nullptr;
+  }
   int gw = 32, ct;   // workgroups of a group: the CUs of an XCD
   if (m->dtype == WIND_F32 && d.Hj <= 128 && nparts <= 4) {
     // a model that fits one CU: a workgroup per utterance
@@ -933,7 +972,7 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   const GroupInstance *gi = group_shape(m, B, T, W, &gd);
   // Behind an asynchronous call no host decodes it again if the groups cannot meet: it takes them only where no two workgroups have to
   // (one per utterance), or where the other choice is a kernel whose workgroups have to meet as well.
-  if (async && gi && gi->gw != 1 && !use_loop) gi = nullptr;
+  if (async && gi && (gi->gw != 1 && !use_loop || gd.qmax > 0)) gi = nullptr;
   // Calls whose windows may be cut (see the loop below).  What is open in an utterance's window lies in res_state, which has no
   // use here (lists_atomic) and the room for two lists from 64 utterances on (slot_stride == B).  An asynchronous call's caller counts iterations
   if (!gi && !use_loop && !async && c.lists_atomic && m->opt_lookahead && m->opt_graph && !m->opt_profile && !m->opt_host_sync && W >= 2 * kShortReach &&
@@ -1389,6 +1428,8 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     for (const GroupInstance &i : kGroupInstances)
       for (auto k : i.kernel)
         if (e == hipSuccess && k) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
+    for (const GroupInstance &i : kVocabInstances)
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)i.kernel[0], hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);
     for (const BeamInstance &i : kBeamInstances)
       for (auto k : {i.search, i.scores, i.phases[0], i.phases[1], i.phases[2], i.phases[3]})
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)i.smem);

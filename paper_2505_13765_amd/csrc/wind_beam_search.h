@@ -204,7 +204,7 @@ const BeamInstance kBeamInstances[] = {beam_instance<1>(), beam_instance<2>(), b
 // resident groups of the decoder; and the options that ask for those
 bool beam_resident_model(const wind_model *m) {
   const ModelDev &d = m->dev;
-  return m->dtype == WIND_BF16 && d.start_p && d.Hj <= 640 && m->cu_count >= kGroups * 32 && m->device >= 0 && m->device < kMaxDevices && m->opt_loop_kernel &&
+  return m->dtype == WIND_BF16 && d.start_p && d.V <= kGroupMaxV && d.Hj <= 640 && m->cu_count >= kGroups * 32 && m->device >= 0 && m->device < kMaxDevices && m->opt_loop_kernel &&
          m->opt_loop_fused && m->opt_loop_one_xcd && !m->opt_profile && m->opt_graph && !m->opt_host_sync && !m->opt_debug_stamps;
 }
 int beam_resident_reserve(wind_model *m, hipStream_t s) {

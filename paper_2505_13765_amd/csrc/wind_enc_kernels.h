@@ -79,6 +79,10 @@ struct GroupDev {
   unsigned win_inv;                     // 65536 / win + 1: x / win = x win_inv >> 16 for small x
   int max_iters;                        // windows (of the caller's size) an utterance may take
   unsigned spin_limit, start_limit;     // polls of a wait, and of the first one: until all workgroups of the group are on the chip
+  // wind_group_vocab_kernel: words that start as all ones and as zeros (vocab_layout, per group; in all), frames of a slot's ring, quads of a window
+  unsigned long long *vx, *v0;
+  size_t n_ones, n_zeros;
+  int ring, qmin, qmax;
 };
 
 // Everything the resident groups expect to find: clamped lengths, the utterances by falling length, zeroed counters and
@@ -86,8 +90,13 @@ struct GroupDev {
 // call's first launch (a launch of its own costs 5 us at the front of every call).  lens: LDS for kGroupMaxB ints.
 __device__ __forceinline__ void group_init(const ModelDev &m, const CallDev &c, const GroupDev &gd, int block, int nblocks, int *lens) {
   const int tid = threadIdx.x;
-  const size_t nbar = (size_t)gd.NX * kGroupBarInts, nx = (size_t)gd.NX * kGroupSlots * m.Hp;
-  const size_t nk = (size_t)gd.NX * 2 * kGroupRows * (c.nparts_tiny + 1);
+  const bool vocab = gd.qmax > 0;
+  const size_t nbar = (size_t)gd.NX * kGroupBarInts, nx = vocab ? 0 : (size_t)gd.NX * kGroupSlots * m.Hp;
+  const size_t nk = vocab ? 0 : (size_t)gd.NX * 2 * kGroupRows * (c.nparts_tiny + 1);
+  if (vocab) {
+    for (size_t i = (size_t)block * 256 + tid; i < gd.n_ones; i += (size_t)nblocks * 256) gd.vx[i] = ~0ull;
+    for (size_t i = (size_t)block * 256 + tid; i < gd.n_zeros; i += (size_t)nblocks * 256) gd.v0[i] = 0ull;
+  }
   for (size_t i = (size_t)block * 256 + tid; i < nbar + 2 * nx + nk; i += (size_t)nblocks * 256) {
     if (i < nbar) gd.bar[i] = 0u;
     else if (i < nbar + nx) gd.h_x[i - nbar] = 0ull;

@@ -24,7 +24,7 @@
 // wave-per-unit kernels (the start-token step of the resident loop kernel), generic FMA (fp32
 // models).  fp32 models replace build_z + joint by joint_exact (fp32 FMA, argmax taken directly).
 // Small batches of a one-layer model run the whole loop as one resident kernel: a group of workgroups per
-// XCD, each with utterances of its own (wind_group_kernel), or, for one or two utterances of the shapes
+// XCD, each with utterances of its own (wind_group_kernel, wind_group_vocab_kernel), or, for one or two utterances of the shapes
 // that one does not take, workgroups over the whole chip (wind_loop_kernel).
 #pragma once
 #include "wind_types.h"
@@ -35,3 +35,4 @@
 #include "wind_loop_kernel.h"
 #include "wind_group_kernel.h"
 #include "wind_group_f32_kernel.h"
+#include "wind_group_vocab_kernel.h"

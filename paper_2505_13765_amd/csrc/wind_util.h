@@ -75,6 +75,12 @@ __device__ __forceinline__ int row16_max_i32(int v) {
   v = max(v, dpp_i32<kDppQuadXor2>(v));
   return max(v, dpp_i32<kDppQuadXor1>(v));
 }
+__device__ __forceinline__ float row16_sum_f32(float v) {
+  v += dpp_f32<kDppRowMirror>(v);
+  v += dpp_f32<kDppRowHalfMirror>(v);
+  v += dpp_f32<kDppQuadXor2>(v);
+  return v + dpp_f32<kDppQuadXor1>(v);
+}
 __device__ __forceinline__ int row16_sum_i32(int v) {
   v += dpp_i32<kDppRowMirror>(v);
   v += dpp_i32<kDppRowHalfMirror>(v);

@@ -1,0 +1,140 @@
+"""The resident groups that decode batches of one-layer models with 1025 to 4096 labels, against the oracle and, counter for counter, against the
+graph of per-step kernels: one to 32 slots per group, every width the kernel is built for, windows of one to four quads of rows, column parts that are
+empty and ragged, empty utterances, frames that are not finite, groups that cannot meet."""
+import numpy as np
+import pytest
+
+import oracle
+import wind_inputs as wi
+from parity import compare_batch
+
+pytestmark = pytest.mark.gpu
+
+
+def model(H, V, B, lo, hi, bias, seed=0):
+    import torch
+    from paper_2505_13765_amd import WindModel
+
+    assert torch.cuda.is_available(), "this test needs the MI355X"
+
+    cfg = wi.WindConfig("vocab", 200 + B + seed, B, lo, hi, 64, 64, 1, H, H, V, "bf16", (4,), 3, 0.7)
+    w = wi.make_weights(cfg, blank_bias=bias, pred_gain=4.0)
+    enc, lens = wi.make_batch(cfg)
+    return cfg, w, enc, lens, WindModel.from_config(cfg, w)
+
+
+def decode(m, cfg, enc, lens, W):
+    import torch
+
+    toks, frs = m.decode(torch.from_numpy(enc).cuda(), torch.from_numpy(lens).cuda(), W, cfg.S)
+    st = m.stats()
+    assert st.rechecks <= st.rows
+    return [t.tolist() for t in toks], [f.tolist() for f in frs], (st.iterations, st.windows, st.rows, st.useful_rows, st.labels, st.forced_advances,
+                                                                   list(st.jump_hist))
+
+
+# H, V, B, W: 1, 2, 3, 6, 16, 17 and 32 slots per group; one to four column parts per workgroup, the last of them empty in most workgroups, or ragged
+SHAPES = [(128, 1025, 1, 16), (640, 4096, 2, 1), (640, 4096, 11, 16), (512, 1500, 24, 5), (384, 2049, 41, 16), (256, 3001, 128, 9), (640, 4000, 130, 16),
+          (128, 4096, 256, 8), (256, 1100, 255, 16)]
+
+
+@pytest.mark.parametrize("H,V,B,W", SHAPES)
+def test_groups_of_larger_vocabularies(H, V, B, W):
+    cfg, w, enc, lens, m = model(H, V, B, 1, 60, 2.0)
+    lens[0], lens[B // 2] = 0 if B > 2 else lens[0], 1 if B > 4 else lens[B // 2]
+    for b in range(B):
+        enc[b, lens[b]:] = np.nan
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, W))
+        assert m.loop_info()[0] == (32 * min(B, 8) if loop else 0)
+    print(f"H={H} V={V} B={B} W={W}: {runs[0][2][:6]}", flush=True)
+    excluded = compare_batch(oracle.Oracle.from_config(cfg, w), enc, lens, cfg.S, [np.array(t, np.int32) for t in runs[0][0]], [np.array(f, np.int32) for f in runs[0][1]])
+    assert excluded <= 1 + B // 16
+    assert runs[0][2][4] == sum(map(len, runs[0][0])) > 0
+    if excluded == 0:   # a near-tie may fall either way on either route
+        assert runs[0] == runs[1]
+    m.close()
+
+
+@pytest.mark.parametrize("bias", [1.0, 7.0])
+@pytest.mark.parametrize("H,V,B,Ws", [(128, 4096, 1, (1, 3, 16)), (256, 1025, 20, (2, 5, 16)), (128, 2500, 60, (1, 7, 12)), (384, 1300, 140, (3, 16))])
+def test_counters_are_those_of_the_callers_windows(H, V, B, Ws, bias):
+    """Labels, frames and counters with a label on almost every frame and on hardly any: of windows of quads that grow and fall back (lookahead = 1), of
+    none beyond the caller's window (0), and of the per-step kernels."""
+    cfg, w, enc, lens, m = model(H, V, B, 40, 95, bias)
+    if B > 4:
+        lens[B // 2] = 1
+    for W in Ws:
+        runs = []
+        for loop, look in ((1, 1), (1, 0), (0, 0)):
+            m.set_option("loop_kernel", loop)
+            m.set_option("lookahead", look)
+            runs.append(decode(m, cfg, enc, lens, W))
+            assert (m.loop_info()[0] > 0) == bool(loop)
+        assert runs[0] == runs[1] == runs[2], W
+        hist = runs[0][2][6]
+        assert sum(hist) == runs[0][2][1] and sum(k * n for k, n in enumerate(hist)) == int(lens.sum())
+    m.close()
+
+
+@pytest.mark.parametrize("H,V,B,W", [(640, 4096, 3, 8), (128, 1100, 40, 16)])
+def test_frames_that_are_not_finite(H, V, B, W):
+    """NaN frames are decided by the biases, infinite ones are blank; see the groups of smaller vocabularies."""
+    cfg, w, enc, lens, m = model(H, V, B, 30, 75, 2.0)
+    bad = []
+    for b in range(B):
+        enc[b, 4] = np.nan
+        bad.append({5, 6, 7, 20, int(lens[b]) - 1})
+        for t in bad[b]:
+            enc[b, t, t % 64] = np.inf if t % 2 else -np.inf
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, W))
+    assert runs[0] == runs[1]
+    assert not any(bad[b] & set(f) for b, f in enumerate(runs[0][1])) and all(0 <= x < V for t in runs[0][0] for x in t)
+    m.close()
+
+
+@pytest.mark.parametrize("H,V,B,W", [(128, 1500, 3, 8), (640, 2100, 20, 16)])
+def test_near_ties(H, V, B, W):
+    """Every label's logit the same but for the biases: rows of many near-ties, parts whose second key is inside the band too, the winner the third."""
+    cfg, w, enc, lens, m = model(H, V, B, 10, 25, 0.0)
+    m.close()
+    from paper_2505_13765_amd import WindModel
+
+    for k in ("w_enc", "w_pred", "b_pred", "w_out"):
+        w[k][:] = 0.0
+    w["b_enc"][:] = 1.0
+    w["w_out"][0, 0] = 4.0
+    w["b_out"][:] = -50.0
+    w["b_out"][[1030, 1040, 1050]] = 1.0, 1.0 - 1e-3, 1.0 + 2e-3   # one part of 32 labels
+    w["b_out"][7] = 1.0 + 1e-3
+    m = WindModel.from_config(cfg, w)
+    toks, _, st = decode(m, cfg, enc, lens, W)
+    assert m.loop_info()[0] > 0
+    assert all(x == 1050 for t in toks for x in t) and st[4] == 3 * int(lens.sum())
+    m.close()
+
+
+def test_groups_that_cannot_meet_leave_the_call_to_the_per_step_kernels():
+    """See the groups of smaller vocabularies: a limit of no polls, set from the host; also asynchronous calls, which take the per-step kernels."""
+    cfg, w, enc, lens, m = model(256, 1300, 20, 1, 60, 2.0)
+    m.set_option("loop_kernel", 0)
+    want = decode(m, cfg, enc, lens, 8)
+    m.set_option("loop_kernel", 1)
+    for limit, resident in ((0, False), (1 << 21, True)):
+        m.set_option("loop_spin_limit", limit)
+        got = decode(m, cfg, enc, lens, 8)
+        assert (m.loop_info()[0] > 0) == resident
+        assert got == want
+    m.close()
+
+
+def test_calls_without_a_frame():
+    cfg, w, enc, lens, m = model(128, 1100, 20, 5, 9, 2.0)
+    toks, frs, st = decode(m, cfg, enc, np.zeros_like(lens), 8)
+    assert m.loop_info()[0] == 256 and st[1] == 0 and not any(map(len, toks))
+    m.close()
