@@ -193,7 +193,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
 #pragma unroll
       for (int t = 0; t < 2 * CT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
       const int gq = div_w(l15), ga = gq < NS ? gq : 0, gj = gq < NS ? l15 - ga * W : 0;
-      int rr = __shfl(sl.rpos, ga, kWave) + gj;
+      int rr = (ONE ? __builtin_amdgcn_readfirstlane(sl.rpos) : __shfl(sl.rpos, ga, kWave)) + gj;
       if (rr >= W2) rr -= W2;
       const float *er = ecache + (ga * W2 + rr) * Cfg::EST + wave * KW + l4 * NK;
       const float *pr = pfull + ga * H + wave * KW + l4 * NK, *br = wbl + wave * KW + l4 * NK;
@@ -227,8 +227,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         for (int t = 0; t < 2 * CT; ++t) acc[t] += NB == 2 ? blk[0][t] + blk[NB - 1][t] : blk[0][t];
         __builtin_amdgcn_sched_barrier(0);   // a block's LDS operands at a time: registers
       }
-      dot += __shfl_xor(dot, 16, kWave);
-      dot += __shfl_xor(dot, 32, kWave);
+      dot = quarter_sum(dot);
 #pragma unroll
       for (int t = 0; t < 2 * CT; ++t)
 #pragma unroll
@@ -271,7 +270,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     if constexpr (SOLO) group_barrier();
     if (4 * wave < R) {
       const int row = 4 * wave + l4, a = div_w(row);
-      const bool valid = row - a * W < __shfl(nwin, a, kWave);
+      const bool valid = row - a * W < (ONE ? __builtin_amdgcn_readfirstlane(nwin) : __shfl(nwin, a, kWave));
       unsigned long long kA = 0ull, kB = 0ull, kC = 0ull;
       const bool got = wait([&]() {
         if (!valid) return true;

@@ -260,7 +260,8 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
   const unsigned segm = (1u << W) - 1u;
   const unsigned seg = lane < gd.NS ? (unsigned)(m_nb >> oshift) & segm : 0u;
   const int first = seg ? __ffs((int)seg) - 1 : -1;
-  tok = __shfl(lab, oshift + max(first, 0), kWave);
+  if constexpr (ONE) tok = __builtin_amdgcn_readlane(lab, max(__builtin_amdgcn_readfirstlane(first), 0));   // only lane 0 has a slot
+  else tok = __shfl(lab, oshift + max(first, 0), kWave);
   tok = min(max(tok, 0), V);
   emits = false;
   fresh_slot = false;
@@ -481,7 +482,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
       for (int t = 0; t < 2 * CT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
       const int gq = div_w(l15), gl = gq < SPT ? gq : 0, gj = gq < SPT ? l15 - gl * W : 0;   // row l15 of the tile: slot, row of its window
       const int ga = min(rt * SPT + gl, NS - 1), gloc = max(ga - rt * SPT, 0);
-      int rr = __shfl(sl.rpos, ga, kWave) + gj;
+      int rr = (ONE ? __builtin_amdgcn_readfirstlane(sl.rpos) : __shfl(sl.rpos, ga, kWave)) + gj;
       if (rr >= W2) rr -= W2;
       const float *er = ecache + (gloc * W2 + rr) * Cfg::EST + w4 * QK + l4 * 8;
       const float *pr = pfull + ga * H + w4 * QK + l4 * 8;
@@ -514,8 +515,8 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
         for (int t = 0; t < 2 * CT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, zu), wo[t][i], acc[t], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);   // keeps the reads at one step ahead: registers
       }
-      dot += __shfl_xor(dot, 16, kWave); nrm += __shfl_xor(nrm, 16, kWave);
-      dot += __shfl_xor(dot, 32, kWave); nrm += __shfl_xor(nrm, 32, kWave);
+      dot = quarter_sum(dot);
+      nrm = quarter_sum(nrm);
       // register r of lane l: row 4 l4 + r, column l15 of tile t; 80 floats per r: the readers below hit different banks
 #pragma unroll
       for (int t = 0; t < 2 * CT; ++t)
@@ -571,7 +572,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     // ---- exchange 1: four rows per wave, 16 lanes per row, lane s with the keys of parts s and s + 16
     if (4 * wave < R) {
       const int row = 4 * wave + l4, a = div_w(row);
-      const bool valid = row - a * W < __shfl(nwin, a, kWave);
+      const bool valid = row - a * W < (ONE ? __builtin_amdgcn_readfirstlane(nwin) : __shfl(nwin, a, kWave));
       float2 kA = make_float2(kKeyNone, kKeyNone), kB = kA, kC = make_float2(0.f, 0.f);
       auto pair = [](unsigned long long u) { return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32))); };
       const unsigned long long *kr = kp + (size_t)row * kstride;

@@ -484,7 +484,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
         const int hi4 = 4 * (lane >> 5);
 #pragma unroll
         for (int r = 0; r < 16; ++r) push_top2(k1, k2, make_key(acc[r], 8 * (r >> 2) + (r & 3) + hi4));
-        merge_top2(k1, k2, __shfl_xor(k1, 32, kWave), __shfl_xor(k2, 32, kWave));
+        merge_top2(k1, k2, xor32_f32(k1), xor32_f32(k2));
         const int qi = (ch - 1) * 8 + ((lane & 31) >> 2);
         if (lane < 32 && qi < nquads) {
           const int q = qtab[qi], quad = (q & 31) * qmax + ((q >> 5) & 3);

@@ -88,6 +88,19 @@ __device__ __forceinline__ int row16_sum_i32(int v) {
   return v + dpp_i32<kDppQuadXor1>(v);
 }
 
+// x of the lane 32 further round, and sums over lanes 16 and 32 apart: gfx950 swaps rows of lanes between two registers, where a shuffle goes
+// through the LDS crossbar (two of them in a row: 0.1 us)
+__device__ __forceinline__ float xor32_f32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float quarter_sum(float v) {   // over the four lanes 16 apart
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f32<kDppRowMirror>(v);
   v += dpp_f32<kDppRowHalfMirror>(v);
