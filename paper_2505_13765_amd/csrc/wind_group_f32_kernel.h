@@ -270,7 +270,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     if constexpr (SOLO) group_barrier();
     if (4 * wave < R) {
       const int row = 4 * wave + l4, a = div_w(row);
-      const bool valid = row - a * W < (ONE ? __builtin_amdgcn_readfirstlane(nwin) : __shfl(nwin, a, kWave));
+      const bool valid = ONE ? row < __builtin_amdgcn_readfirstlane(nwin) : row - a * W < __shfl(nwin, a, kWave);   // one slot: no row past its window
       unsigned long long kA = 0ull, kB = 0ull, kC = 0ull;
       const bool got = wait([&]() {
         if (!valid) return true;

@@ -572,7 +572,7 @@ __device__ __forceinline__ void group_loop(const ModelDev &m, const CallDev &c, 
     // ---- exchange 1: four rows per wave, 16 lanes per row, lane s with the keys of parts s and s + 16
     if (4 * wave < R) {
       const int row = 4 * wave + l4, a = div_w(row);
-      const bool valid = row - a * W < (ONE ? __builtin_amdgcn_readfirstlane(nwin) : __shfl(nwin, a, kWave));
+      const bool valid = ONE ? row < __builtin_amdgcn_readfirstlane(nwin) : row - a * W < __shfl(nwin, a, kWave);   // one slot: no row past its window
       float2 kA = make_float2(kKeyNone, kKeyNone), kB = kA, kC = make_float2(0.f, 0.f);
       auto pair = [](unsigned long long u) { return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32))); };
       const unsigned long long *kr = kp + (size_t)row * kstride;
