@@ -373,7 +373,7 @@ int wind_get_route_counts(wind_model *m, wind_route_counts *out);
  *             (default 1; bf16 models only; below it one wave per hidden unit does fp32 FMA)
  *   "loop_kernel"  1 (default): small decodes run the whole loop as one resident kernel; 0: always the graph of
  *             per-step kernels.  Two such kernels: groups of workgroups, one group per XCD with utterances of its
- *             own (up to 256 utterances, windows of at most 16 rows; bf16 (windows of more than 8 rows: up to 224), one LSTM layer, Hp = Hj a multiple of
+ *             own (up to 256 utterances, windows of at most 16 rows; bf16 (windows of more than 8 rows of models of less than 993 labels: up to 224), one LSTM layer, Hp = Hj a multiple of
  *             128 and at most 640, at most 1024 labels, or (with windows of any of these sizes up to 256 utterances) 1025 to 4096; fp32, one LSTM layer, Hp = Hj of
  *             64, 128, 256, 384, 512 or 640, at most 1024 labels; the options lstm_rec, atomic_lists, slot_rows, decide_two,
  *             joint_wide and pred_mfma_min_batch at their defaults where there are more than two utterances), and,
@@ -384,7 +384,7 @@ int wind_get_route_counts(wind_model *m, wind_route_counts *out);
  *   "lookahead"  1 (default): an iteration of the resident groups looks at as many frames of an utterance as their row tiles
  *             have rows for (16, or 8 with more than two utterances per XCD), also beyond the end of the caller's window: labels
  *             and frames do not depend on how the frames are cut into windows, and the counters stay those of the
- *             caller's.  Bf16 batches of more than 16 utterances look at 8 frames at a time with either value; models of more than 1024 labels look at 4
+ *             caller's.  Bf16 batches of more than 16 utterances look at 8 frames at a time with either value; models of more than 1024 labels, and batches of more than 64 utterances of more than 992, look at 4
  *             to 16 frames (more than 128 utterances: 8), more behind a stretch without a label than behind one, with 0 at no more than the window's.  Large synchronous batches of the per-step kernels (64 utterances, windows of 16 and more) may look at
  *             8 rows of a window at a time where most labels lie in those.  0: no further than the caller's window (what a window of that size costs, but for windows of more than 8 frames in bf16 groups of more
  *             than 16 utterances, see above; the standard loop frame by frame)

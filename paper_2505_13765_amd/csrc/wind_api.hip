@@ -233,7 +233,7 @@ void set_tau(wind_model *m) {
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
 }
 
-// Utterances up to which windows of more than 8 rows of bf16 models take groups: each round of 32 utterances costs them the same, while the
+// Utterances up to which windows of more than 8 rows of bf16 models of less than 993 labels (see vocab_model) take groups: each round of 32 utterances costs them the same, while the
 // per-step kernels' launches hardly grow, and half as many of those are needed as for short windows.  W = 16, groups / per-step kernels: 640 units, 200 to
 // 1500 frames, blanks 85 %: 176 utterances 8.8 / 13.6 ms, 224 12.0 / 14.1, 256 12.4 / 14.4; with a label on almost every frame (200 to 400
 // frames) 224 20.3 / 21.2, 256 23.1 / 21.8; 128 units, a label on almost every frame 224 21.9 / 23.7, 256 25.3 / 24.0, hardly any 176 0.55 / 0.60,
@@ -245,6 +245,15 @@ constexpr size_t kGroupOutBytes = 64 + kStatWords * sizeof(unsigned long long); 
 constexpr int kGroupMaxV = 1024;   // labels of models that wind_group_kernel takes
 // Quads of a window, at most, in wind_group_vocab_kernel: the rings of projected frames fill LDS (two windows of 8 rows each for 32 slots)
 constexpr int vocab_qmax(int slots) { return slots > 16 ? 2 : 4; }
+// Whether a call's groups are those of wind_group_vocab_kernel, which needs a part of 32 labels for every workgroup.  Up to 1024 labels it takes the batches
+// that come to more than two rounds of four utterances per group: a round costs the other groups the same each, while all of these are
+// decoded at once.  640 units, 1024 labels, 200 to 1500 frames, W = 8 / 16, rounds / all at once: 33 utterances 2.68 / 3.25 ms, 48 3.01 / 3.38, 64 4.03 / 4.21, 128
+// 7.15 / 4.95, 256 (W = 16: per-step kernels) 14.9 / 7.2; with hardly any label 64 1.11 / 1.07, 128 1.96 / 1.53, 256 3.27 / 2.98; a label on almost every frame (200 to 400
+// frames) 64 44.4 / 30.3, 256 138 / 50
+constexpr int kVocabMinB = 2 * kGroups * kGroupSlots + 1;
+bool vocab_model(const wind_model *m, int B) {
+  return m->dtype == WIND_BF16 && (m->dev.V > kGroupMaxV || (m->dev.V > kGroupMaxV - kTinyCols && B >= kVocabMinB));
+}
 // Where everything of a decode call lives inside the one workspace slab.
 struct WsLayout {
   size_t total, Mpad, st;
@@ -295,7 +304,8 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_lbar = take((size_t)(1 + 256) * kLoopFlagStride * 4); w.o_lh = take((size_t)kLoopMaxB * d.Hp * 4);
   w.o_lp = take((size_t)kLoopMaxB * d.Hj * 4);
   w.o_lparts = take((size_t)2 * kLoopRows * w.nparts_tiny * 8);
-  const bool resident = d.start_p != nullptr, vocab = resident && d.V > kGroupMaxV, grouped = resident && !vocab;   // models that decode in resident groups
+  // models that decode in resident groups, of one kind or (see group_shape) of either
+  const bool resident = d.start_p != nullptr, vocab = resident && vocab_model(m, B), grouped = resident && d.V <= kGroupMaxV;
   w.o_gbar = take(resident ? (size_t)kGroups * kGroupBarInts * 4 : 0);
   w.o_gx = take(grouped ? (size_t)2 * kGroups * kGroupSlots * d.Hp * 8 : 0);
   w.o_gkeys = take(grouped ? (size_t)kGroups * 2 * kGroupRows * (w.nparts_tiny + 1) * 8 : 0);
@@ -813,7 +823,7 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
                         m->opt_pred_mfma_min_batch > B)) return nullptr;
   const int nparts = (d.V + kTinyCols - 1) / kTinyCols;
   gd->qmax = 0;
-  if (d.V > kGroupMaxV) {
+  if (vocab_model(m, B)) {
     gd->NG = gd->NX = std::min(kGroups, B);
     gd->NS = (B + gd->NG - 1) / gd->NG;
     gd->RG = gd->SPT = 1;

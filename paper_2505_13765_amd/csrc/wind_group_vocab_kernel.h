@@ -8,7 +8,7 @@
 namespace wind {
 
 // ---------------------------------------------------------------------------------------------
-// Like wind_group_kernel, for up to 4096 labels and up to 32 utterances per group at a time, each in a slot of its own from the first to
+// Like wind_group_kernel, for 993 to 4096 labels and up to 32 utterances per group at a time, each in a slot of its own from the first to
 // the last frame.  There every workgroup forms every window row and takes every slot's decision, which with 32 slots and 128 key
 // parts would be all that it did; here the work is cut so that none is done twice:
 //   z     workgroup g holds PPW columns of W_pred and of the joint hidden vector: it adds its columns of the window's projected frames (LDS) and
