@@ -1389,11 +1389,14 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     }
     chk(upload(m, wb, &tmp)); d.w_blank = (const float *)tmp;
     double wmax = 0.0;
+    float largest = 0.f;
     for (int v = 0; v < w->V; ++v) {
       double s2 = 0.0;
-      for (int k = 0; k < w->Hj; ++k) { double x = w->w_out[(size_t)v * w->Hj + k]; s2 += x * x; }
+      for (int k = 0; k < w->Hj; ++k) { double x = w->w_out[(size_t)v * w->Hj + k]; s2 += x * x; largest = std::max(largest, std::fabs(w->w_out[(size_t)v * w->Hj + k])); }
       wmax = s2 > wmax ? s2 : wmax;
     }
+    d.w16_scale = 1.f;
+    if (largest > 0.f && std::isfinite(largest)) d.w16_scale = std::ldexp(1.f, std::min(std::max(14 - std::ilogb(largest), -100), 100));
     m->wnorm_max = std::sqrt(wmax);
     set_tau(m);
   }

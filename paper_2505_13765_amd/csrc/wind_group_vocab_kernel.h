@@ -13,7 +13,7 @@ namespace wind {
 // parts would be all that it did; here the work is cut so that none is done twice:
 //   z     workgroup g holds PPW columns of W_pred and of the joint hidden vector: it adds its columns of the window's projected frames (LDS) and
 //         of the slots' projections (its own sums), applies the ReLU and rounds: its columns of every window row, and its part of the
-//         row's blank logit and squared norm                                                        -> exchange z (bf16), bn (fp32)
+//         row's blank logit and squared norm                                                        -> exchange z (fp16), bn (fp32)
 //   keys  it fetches all window rows, in chunks of 32, through registers (waves 4-7) into LDS, and multiplies them (waves 0-3, each a part
 //         of 32 columns over the whole of K, weights in registers, the transposed product: a lane holds 16 logits of one row)
 //                                                                                                   -> exchange keys
@@ -28,7 +28,8 @@ namespace wind {
 // 0.5 / 0.6 / 1.9, hidden vectors and projection 1.3 / 1.5 / 2.5.
 // Whole decodes of up to 1000 frames, W = 16, per-step kernels (four launches, 22 to 30 us per iteration) / groups: a label on every second evaluation,
 // 8 utterances 18.1 / 5.9 ms, 45 22.1 / 6.7, 128 26.8 / 9.1, 256 30.6 / 11.6; hardly any label 8 utterances 1.14 / 0.45, 64 1.45 / 0.71, 128 1.84 / 1.00, 256 2.61 / 2.01.
-// Tried: the deciding wave brings its label's row of input sums into the L2 ahead of the step: what the asking took it (0.6 us) was more than
+// Tried: waves 4-7 form every other 256 items of the window rows (32 slots: 0.3 us less there, 0.5 more until the first chunk, whose fetching waits for
+// the recurrent sums behind that); the deciding wave brings its label's row of input sums into the L2 ahead of the step: what the asking took it (0.6 us) was more than
 // the step gained; a wave per quad for windows of one quad too (18 words per lane instead of 5): 0.8 us slower.
 //
 // Rows of a window: quads of 4, `qmin` to `qmax` per slot: a window without a label doubles its slot's next one, a label takes it back, so
@@ -47,6 +48,22 @@ namespace wind {
 // Waits are bounded as in wind_group_kernel.
 constexpr int kVocabSlots = 32;
 constexpr int kTie = 0x3FFF;   // instead of a label: a near-tie
+// The screening products are fp16: as fast as bf16 and with eight times less rounding of the hidden row, so that near-ties, each of which holds all
+// slots up for 2 us, are eight times rarer (one iteration in eight with 16 slots instead of two in three).  The rows are scaled by 64 and the weights by a
+// power of two that makes the largest about 2^14 (ModelDev::w16_scale), which keeps what fp16 cannot hold in full far below the rounding of the rest; a row
+// whose norm says that a unit might not fit, is decided in fp32 over all labels.  Rows decided again, 256 utterances of 640 units and 4096 labels: 9283
+// with bf16, now 1311; 11.4 -> 11.0 ms, 45 utterances 6.61 -> 6.42, 8 5.94 -> 5.87.
+constexpr float kZ16Scale = 64.f, kZ16Max = 1000.f;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
+__device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
+  const f32x2_t v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));
+}
+// How far below the best a label may be to be looked at in fp32: see decide_row; the rounding of fp16, and what its smallest numbers lose
+__device__ __forceinline__ float vocab_band(const ModelDev &m, float znorm, float top) {
+  return m.tau_scale * fmaf(0.125f, znorm, 0.04f) + 6.2e-5f * fabsf(top);
+}
 
 template <int KS>
 struct VocabCfg {
@@ -128,9 +145,11 @@ __device__ __forceinline__ int vocab_recheck(const ModelDev &m, const float *er,
     for (int c0 = 0; c0 < nc; c0 += 4) {
       int col[4];
       uint32_t x[4][KS];
+      float o[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         col[k] = __builtin_amdgcn_readlane(mycol, min(c0 + k, nc - 1));
+        o[k] = m.b_out[col[k]];
 #pragma unroll
         for (int i = 0; i < KS; ++i) x[k][i] = *reinterpret_cast<const uint32_t *>(w + (size_t)col[k] * (128 * KS) + 2 * lane + 128 * i);
       }
@@ -147,7 +166,7 @@ __device__ __forceinline__ int vocab_recheck(const ModelDev &m, const float *er,
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float v = wave_sum(a[k]) + m.b_out[col[k]];
+        const float v = wave_sum(a[k]) + o[k];
         if (v > bestv || (v == bestv && col[k] < besti)) { bestv = v; besti = col[k]; }
       }
     }
@@ -200,14 +219,20 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
   const int unit0 = g * UPW, col0 = g * PPW;
 
   // ---- weights into registers
-  bf16x8 wo[ROLE == 0 ? 8 * KS : 1];                                         // 32 columns of W_out over the whole of K
+  f16x8 wo[ROLE == 0 ? 8 * KS : 1];                                          // 32 columns of W_out over the whole of K, scaled
   bf16x8 wr[ROLE == 1 ? Cfg::LT : 1][KS], wp[ROLE == 1 ? Cfg::PT : 1][KS];   // a quarter of K of the recurrent rows and of the projection rows
   const int part = 32 * w4 + g;                                              // ROLE 0
   if constexpr (ROLE == 0) {
     const int col = min(part * 32 + (lane & 31), m.Vpad - 1);
     const bf16_t *src = reinterpret_cast<const bf16_t *>(m.w_out) + (size_t)col * H + (lane >> 5) * 8;
 #pragma unroll
-    for (int i = 0; i < 8 * KS; ++i) wo[i] = *reinterpret_cast<const bf16x8 *>(src + i * 16);
+    for (int i = 0; i < 8 * KS; ++i) {
+      const u32x4 b = *reinterpret_cast<const u32x4 *>(src + i * 16);
+      u32x4 h;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h[q] = pack_f16x2(__uint_as_float(b[q] << 16) * m.w16_scale, __uint_as_float(b[q] & 0xFFFF0000u) * m.w16_scale);
+      wo[i] = __builtin_bit_cast(f16x8, h);
+    }
   } else {
 #pragma unroll
     for (int t = 0; t < Cfg::LT; ++t) {
@@ -352,6 +377,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
       }
   };
 
+  const float unscale = 1.f / (kZ16Scale * m.w16_scale);   // a power of two
   bool bad = false;   // a wait of this wave has given up: told to the workgroup ahead of the decisions' barrier
   for (int it = 0;; ++it) {
     // opaque: see wind_group_kernel
@@ -388,8 +414,8 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
         }
         const float dot = fmaf(y[3], w[3], fmaf(y[2], w[2], fmaf(y[1], w[1], y[0] * w[0])));
         const int quad = s * qmax + qq;
-        group_st(ones + (size_t)(quad * H + (g * NC + i) * 4 + r), (pack_bf16x2(y[0], y[1]) & 0x7FFF7FFFu) | tagz,
-                 (pack_bf16x2(y[2], y[3]) & 0x7FFF7FFFu) | tagz, near);
+        group_st(ones + (size_t)(quad * H + (g * NC + i) * 4 + r), (pack_f16x2(y[0] * kZ16Scale, y[1] * kZ16Scale) & 0x7FFF7FFFu) | tagz,
+                 (pack_f16x2(y[2] * kZ16Scale, y[3] * kZ16Scale) & 0x7FFF7FFFu) | tagz, near);
         group_st(bx + (size_t)(quad * H + (g * NC + i) * 4 + r), __float_as_uint(dot), (__float_as_uint(nrm) & ~1u) | tag, near);
         if (fresh && qq == 0) {
           const float mine = r == 0 ? p[0] : r == 1 ? p[1] : r == 2 ? p[2] : p[3];
@@ -459,16 +485,12 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
         const bf16_t *zs = zbuf + ((ch - 1) & 1) * (Cfg::kZBuf / 2) + (lane & 31) * ZST + (lane >> 5) * 8;
         f32x16 acc;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const f32x4 b4 = *reinterpret_cast<const f32x4 *>(bias + 32 * w4 + 8 * r + 4 * (lane >> 5));
-#pragma unroll
-          for (int k = 0; k < 4; ++k) acc[4 * r + k] = b4[k];
-        }
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
         // the rows' operands are read three steps of two ahead
-        bf16x8 zf[4][2];
+        f16x8 zf[4][2];
         auto read_rows = [&](int s) {
 #pragma unroll
-          for (int i = 0; i < 2; ++i) zf[s & 3][i] = *reinterpret_cast<const bf16x8 *>(zs + (2 * s + i) * 16);
+          for (int i = 0; i < 2; ++i) zf[s & 3][i] = *reinterpret_cast<const f16x8 *>(zs + (2 * s + i) * 16);
         };
 #pragma unroll
         for (int s = 0; s < 3; ++s) read_rows(s);
@@ -476,14 +498,18 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
         for (int s = 0; s < 4 * KS; ++s) {
           if (s + 3 < 4 * KS) read_rows(s + 3);
 #pragma unroll
-          for (int i = 0; i < 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wo[2 * s + i], zf[s & 3][i], acc, 0, 0, 0);
+          for (int i = 0; i < 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wo[2 * s + i], zf[s & 3][i], acc, 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);   // keeps the reads there: registers
         }
         // accumulator r: column 8 (r / 4) + 4 (lane / 32) + r % 4 of the part; row lane % 32
         float k1 = kKeyNone, k2 = kKeyNone;
         const int hi4 = 4 * (lane >> 5);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) push_top2(k1, k2, make_key(acc[r], 8 * (r >> 2) + (r & 3) + hi4));
+        for (int r = 0; r < 4; ++r) {
+          const f32x4 b4 = *reinterpret_cast<const f32x4 *>(bias + 32 * w4 + 8 * r + hi4);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) push_top2(k1, k2, make_key(fmaf(acc[4 * r + k], unscale, b4[k]), 8 * r + k + hi4));
+        }
         merge_top2(k1, k2, xor32_f32(k1), xor32_f32(k2));
         const int qi = (ch - 1) * 8 + ((lane & 31) >> 2);
         if (lane < 32 && qi < nquads) {
@@ -548,12 +574,13 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           for (int k = 0; k < kBn; ++k) { dot += first(v[k]); nrm += second(v[k]); }
           const float vblank = wave_sum(dot) + m.b_out[V], znorm = sqrtf(wave_sum(nrm));
           const float kbest = wave_max_f32(fmaxf(kA.x, kB.x)), vbest = key_val(kbest), top = fmaxf(vbest, vblank);
-          const float thresh = top - (m.tau_scale * znorm + 6.2e-5f * fabsf(top));
+          float thresh = top - vocab_band(m, znorm, top);
           int label = V;
-          if (w4 < n && !(vbest < thresh)) {
+          const bool large = znorm > kZ16Max && znorm < INFINITY;
+          if (w4 < n && (large || !(vbest < thresh))) {
             const int cnt = __popcll(__ballot(key_val(kA.x) >= thresh)) + __popcll(__ballot(key_val(kA.y) >= thresh)) +
                             __popcll(__ballot(key_val(kB.x) >= thresh)) + __popcll(__ballot(key_val(kB.y) >= thresh));
-            if (cnt == 1 && vblank < thresh) {
+            if (!large && cnt == 1 && vblank < thresh) {
               int col = 0;
               if (kA.x == kbest) col = lane * 32 + key_col(kbest);
               if (kB.x == kbest) col = (lane + 64) * 32 + key_col(kbest);
@@ -565,6 +592,11 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           if (lane == 0) { rech[w4] = 0; stat[w4] = mark | label; }
           int st;
           if (label == kTie && settled(w4, st) < 0) {
+            if (large) {   // every part whole
+              thresh = -INFINITY;
+              if (lane < nparts) kA.y = INFINITY;
+              if (lane + 64 < nparts) kB.y = INFINITY;
+            }
             label = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + w4) * H, pfull, vblank, thresh, kA, kB);
             if (lane == 0) { rech[w4] = 1; stat[w4] = mark | label; }
           }
@@ -592,7 +624,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           for (int k = 0; k < 8; ++k) kbest = fmaxf(kbest, l15 + 16 * k < nparts ? first(u[k]) : kKeyNone);
           kbest = row16_max_f32(kbest);
           const float vblank = row16_sum_f32(dot) + m.b_out[V], znorm = sqrtf(row16_sum_f32(nrm)), vbest = key_val(kbest), top = fmaxf(vbest, vblank);
-          const float thresh = top - (m.tau_scale * znorm + 6.2e-5f * fabsf(top));
+          const float thresh = top - vocab_band(m, znorm, top);
           int cnt = 0, col = 0;   // with NaN logits no key is a label's
 #pragma unroll
           for (int k = 0; k < 8; ++k)
@@ -604,7 +636,8 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           col = row16_max_i32(col);
           const int j = 4 * w4 + l4;
           int label = V;
-          if (j < n && !(vbest < thresh)) label = cnt == 1 && vblank < thresh ? min(col, V) : kTie;
+          const bool large = znorm > kZ16Max && znorm < INFINITY;
+          if (j < n && (large || !(vbest < thresh))) label = !large && cnt == 1 && vblank < thresh ? min(col, V) : kTie;
           if (l15 == 0) { rech[j] = 0; stat[j] = mark | label; }
           // near-ties ahead of the first certain label, in the order of their rows
           for (unsigned long long todo = __ballot(l15 == 0 && label != V); todo; todo &= todo - 1) {
@@ -616,7 +649,13 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
             const unsigned long long *kt = kr + (src >> 4);
             if (lane < nparts) { const unsigned long long x = group_ld(kt + 4 * lane); kA.x = first(x); kA.y = key_with_tag(second(x), 0); }
             if (lane + 64 < nparts) { const unsigned long long x = group_ld(kt + 4 * (lane + 64)); kB.x = first(x); kB.y = key_with_tag(second(x), 0); }
-            const int l = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + row) * H, pfull, readlane_f32(vblank, src), readlane_f32(thresh, src), kA, kB);
+            float th = readlane_f32(thresh, src);
+            if (__builtin_amdgcn_readlane(large, src)) {   // every part whole
+              th = -INFINITY;
+              if (lane < nparts) kA.y = INFINITY;
+              if (lane + 64 < nparts) kB.y = INFINITY;
+            }
+            const int l = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + row) * H, pfull, readlane_f32(vblank, src), th, kA, kB);
             if (lane == 0) { rech[row] = 1; stat[row] = mark | l; }
             if (l != V) break;
           }

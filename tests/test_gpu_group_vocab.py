@@ -119,6 +119,21 @@ def test_near_ties(H, V, B, W):
     m.close()
 
 
+@pytest.mark.parametrize("H,V,B,W", [(128, 1100, 3, 16), (640, 1030, 40, 4)])
+def test_hidden_rows_beyond_fp16(H, V, B, W):
+    """The screening products are fp16 (rows times 64): frames whose hidden units are too large for that are decided over all labels in fp32."""
+    cfg, w, enc, lens, m = model(H, V, B, 8, 20, 2.0)
+    enc[:, 3] *= 4096.0
+    enc[:, 6] *= 65536.0
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, W))
+    assert runs[0] == runs[1] and sum(map(len, runs[0][0])) > 0
+    assert any(3 in f or 6 in f for f in runs[0][1])
+    m.close()
+
+
 def test_groups_that_cannot_meet_leave_the_call_to_the_per_step_kernels():
     """See the groups of smaller vocabularies: a limit of no polls, set from the host; also asynchronous calls, which take the per-step kernels."""
     cfg, w, enc, lens, m = model(256, 1300, 20, 1, 60, 2.0)
