@@ -13,7 +13,8 @@ namespace wind {
 //     vector is read from LDS as a broadcast, nothing is summed over lanes).  One row tile per group: slots x W <= 16.
 //     640 units do not quite fit (19 vector registers in scratch memory), nor 128 units with 128 labels on one CU (21);
 //   - small models (GW = 1: a whole model fits one CU's registers) run one workgroup per utterance, which
-//     tells itself through LDS, behind workgroup barriers.
+//     tells itself through LDS, behind workgroup barriers: hidden vectors and projections where their readers want them, and with one
+//     part of labels the rows are decided where their logits are added up.
 // Bound by the chain of steps like the bf16 groups; of 640 units the products of a 16-row tile take 1.2 us (fp32 rate).
 constexpr int kGroupNoLabel = 0xFFFF;   // in a word's column field; above every column
 template <int NK, int CT, int GW>
@@ -33,8 +34,8 @@ struct GroupF32Cfg {
   static constexpr size_t oRec = oPart + (size_t)8 * SL * 64 * NSET * 4;   // float [SL][NR]
   static constexpr size_t oC = oRec + (size_t)SL * NR * 4;                 // float [SL][UPW]
   static constexpr size_t oW = oC + (size_t)SL * UPW * 4;                  // float [H] blank column of W_out
-  static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1], [H], [H]
-  static constexpr size_t oI = oX + (GW == 1 ? (size_t)(16 * (CT + 1) + 2 * H) * 8 : 0);   // int stat[64], cnt[kNumStats], open windows [slots][2], fail, near; float bp[PPW], bo[32 CT + 1]
+  static constexpr size_t oX = (oW + (size_t)H * 4 + 15) / 16 * 16;        // GW = 1: exchange words [16][CT + 1]
+  static constexpr size_t oI = oX + (GW == 1 ? (size_t)16 * (CT + 1) * 8 : 0);   // int stat[64], cnt[kNumStats], open windows [slots][2], fail, near; float bp[PPW], bo[32 CT + 1]
   static constexpr size_t oT = (oI + (64 + kNumStats + 2 * kGroupSlots + 2 + PPW + 32 * CT + 1) * 4 + 255) / 256 * 256;   // 256 bytes that group_touch writes to
   static constexpr size_t smem = oT + 256;
   static_assert(smem <= 160 * 1024, "LDS");
@@ -77,6 +78,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   constexpr int H = Cfg::H, KW = Cfg::KW, NR = Cfg::NR, PPW = Cfg::PPW, QL = Cfg::QL, NSET = Cfg::NSET;
   constexpr bool SOLO = GW == 1, ONE = SOLO || MODE != kGroupMany, LIM = MODE == kGroupLimited;
   constexpr int SL = ONE ? 1 : Cfg::SL;
+  constexpr bool kDirect = SOLO && CT == 1;   // one part of columns, and it is here
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int grp = SOLO ? (int)blockIdx.x : (int)blockIdx.x % kGroups, g = SOLO ? 0 : (int)blockIdx.x / kGroups;
   if (grp >= gd.NG) return;
@@ -94,8 +96,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
   const int W = c.W, V = m.V, NS = gd.NS, W2 = 2 * W, R = NS * W, nparts = c.nparts_tiny, kstride = nparts + 1;
   unsigned *abort_word = SOLO ? nullptr : gd.bar + grp * kGroupBarInts;
   unsigned long long *xs = reinterpret_cast<unsigned long long *>(smem + Cfg::oX);
-  unsigned long long *hx = SOLO ? xs + 16 * (CT + 1) : gd.h_x + (size_t)grp * kGroupSlots * H;
-  unsigned long long *px = SOLO ? hx + H : gd.p_x + (size_t)grp * kGroupSlots * H;
+  unsigned long long *hx = gd.h_x + (size_t)grp * kGroupSlots * H, *px = gd.p_x + (size_t)grp * kGroupSlots * H;   // not SOLO
   unsigned long long *kbase = SOLO ? xs : gd.keys + (size_t)grp * 2 * kGroupRows * kstride;
   const int unit0 = g * Cfg::UPW, prow0 = g * PPW;
   const int n_order = *gd.n_order;
@@ -251,9 +252,16 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
       const int at = part * 32 + l15 + (v[0] == b ? 0 : 16);   // ties: the lower column
       const int col = kGroupNoLabel - row16_max_i32(b == bm ? kGroupNoLabel - at : 0);
       const int row = 4 * q4 + l4;
-      if (part < nparts && l15 == 0 && row < R) put(kp + row * kstride + part, __float_as_uint(bm), (unsigned)(col & 0xFFFF) | (stamp16 << 16));
+      if constexpr (kDirect) {   // all labels are in this part: the row is decided here
+        const float blank = group_sum8([&](int w) { return fbn[w * 16 + row]; }) + bol[32 * CT];
+        // blank has the highest id: it wins only if strictly larger, and where no label has a logit
+        const int label = row >= __builtin_amdgcn_readfirstlane(nwin) || col >= V || !(bm >= kKeyNone) || blank > bm ? V : col;
+        if (l15 == 0) stat[row] = label;
+        if (label < V && l15 < min((NR * 4 + 127) / 128 + 1, 16))   // see group_loop
+          group_touch(m.emb_gates + (unsigned)label * (4u * H) + (unsigned)min(l15 * 32, NR - 1), touch_lds);
+      } else if (part < nparts && l15 == 0 && row < R) put(kp + row * kstride + part, __float_as_uint(bm), (unsigned)(col & 0xFFFF) | (stamp16 << 16));
     }
-    if (wave == 4 && g == 0 && lane < R) {   // R <= 16
+    if (!kDirect && wave == 4 && g == 0 && lane < R) {   // R <= 16
       const float d2 = group_sum8([&](int w) { return fbn[w * 16 + lane]; }) + bol[32 * CT];
       put(kp + lane * kstride + nparts, __float_as_uint(d2), stamp16 << 16);
     }
@@ -267,8 +275,8 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
     pend = 0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last iteration's frames have landed
     // ---- exchange 1: four rows per wave, 16 lanes per row
-    if constexpr (SOLO) group_barrier();
-    if (4 * wave < R) {
+    if constexpr (SOLO && !kDirect) group_barrier();
+    if (!kDirect && 4 * wave < R) {
       const int row = 4 * wave + l4, a = div_w(row);
       const bool valid = ONE ? row < __builtin_amdgcn_readfirstlane(nwin) : row - a * W < __shfl(nwin, a, kWave);   // one slot: no row past its window
       unsigned long long kA = 0ull, kB = 0ull, kC = 0ull;
@@ -339,7 +347,8 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
           const int u = li >> 2;
           const float cn = fg * cst[s * Cfg::UPW + u] + ig * gg;
           cst[s * Cfg::UPW + u] = cn;
-          put(hx + s * H + unit0 + u, __float_as_uint(og * tanhf(cn)), stamp);
+          if constexpr (SOLO) hbuf[u] = og * tanhf(cn);
+          else put(hx + s * H + unit0 + u, __float_as_uint(og * tanhf(cn)), stamp);
         }
       }
       // ---- exchange 2 / 3: this wave's part of the emitting slots' vectors, into its part of `to`
@@ -388,7 +397,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         partl[(wave * SL + e) * 64 * NSET + t * 64 + lane] = a;
       };
       if constexpr (SOLO) group_barrier();
-      fetch(hx, hbuf, false);
+      else fetch(hx, hbuf, false);
       for (int e = 0; e < n_em; ++e) {
         take_vector(e);
 #pragma unroll
@@ -399,7 +408,8 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
         const int e = tid / PPW, row = tid - e * PPW;
         const float v = group_sum8([&](int w) { return partl[(w * SL + e) * 64 * NSET + row]; });
         const int s = e == 0 ? es[0] : e == 1 ? es[1] : e == 2 ? es[2] : es[3];
-        put(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp);
+        if constexpr (SOLO) pfull[row] = v + bpl[row];
+        else put(px + s * H + prow0 + row, __float_as_uint(v + bpl[row]), stamp);
       }
       // ---- while the projections travel: the recurrent sums of the next step (added behind the next barrier)
       for (int e = 0; e < n_em; ++e) {
@@ -411,7 +421,7 @@ __global__ __launch_bounds__(512) void wind_group_f32_kernel(ModelDev m, CallDev
 #pragma unroll
       for (int e = 0; e < SL; ++e) pend_slot[e] = es[e];
       if constexpr (SOLO) group_barrier();
-      fetch(px, pfull, true);
+      else fetch(px, pfull, true);
     }
     load_frames();
     if (rf) {   // slots that took a new utterance: the state after the start token, their first frames
