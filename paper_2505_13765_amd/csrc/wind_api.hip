@@ -828,7 +828,6 @@ const GroupInstance *group_shape(const wind_model *m, int B, int T, int W, Group
     gd->NS = (B + gd->NG - 1) / gd->NG;
     gd->RG = gd->SPT = 1;
     gd->qmax = vocab_qmax(gd->NS);
-    gd->qmin = gd->NS <= 2 ? 4 : gd->NS <= 4 ? 2 : 1;   // as many rows as one chunk of products has room for
     gd->ring = gd->NS > 16 ? 16 : 32;
     gd->reach = m->opt_lookahead ? kGroupMaxW : std::min(kGroupMaxW, W);
     gd->win = W;

@@ -82,7 +82,7 @@ struct GroupDev {
   // wind_group_vocab_kernel: words that start as all ones and as zeros (vocab_layout, per group; in all), frames of a slot's ring, quads of a window
   unsigned long long *vx, *v0;
   size_t n_ones, n_zeros;
-  int ring, qmin, qmax;
+  int ring, qmax;
 };
 
 // Everything the resident groups expect to find: clamped lengths, the utterances by falling length, zeroed counters and

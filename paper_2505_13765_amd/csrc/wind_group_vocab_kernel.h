@@ -18,22 +18,23 @@ namespace wind {
 //         of 32 columns over the whole of K, weights in registers, the transposed product: a lane holds 16 logits of one row)
 //                                                                                                   -> exchange keys
 //   step  workgroup s decides slot s (its keys, near-ties in fp32)                                  -> exchange dec
-//   h     everybody takes the LSTM step of its units for all slots with a label                     -> exchange h (fp32)
+//   h     everybody takes the LSTM step of its units for all slots with a label                     -> exchange h (bf16, high and low part)
 //         and forms the projection columns of the new hidden vectors (waves 4-7, K split in four; the recurrent sums of the next
 //         step likewise, beside the decisions)
 // What bounds it: the chain of four exchanges through the group's L2 (0.6 to 1 us each) and the label's row of input gate
 // sums from memory; with many slots the products and the rows' way through LDS (a chunk of 32 rows 1.05 us: 0.6 of products, whose rows come from LDS at
-// the 128 bytes per clock that it gives).  640 units, 4096 labels, us per iteration, 1 / 6 / 32 slots: z 0.7 / 0.7 / 1.4, first chunk in LDS
-// 0.8 / 0.9 / 0.3, products 1.2 / 1.2 / 4.3, decision 2.8 (16 rows) / 1.7 / 2.2, its word and the slots' states 0.5 / 1.3 / 2.4 (somebody's near-tie), LSTM step
-// 0.5 / 0.6 / 1.9, hidden vectors and projection 1.3 / 1.5 / 2.5.
+// the 128 bytes per clock that it gives).  640 units, 4096 labels, us per iteration, 6 / 32 slots: z 0.8 / 1.5, first chunk in LDS
+// 0.8 / 0.3, products 1.2 / 4.4, decision 1.6 / 2.2, its word and the slots' states 1.0 / 1.6, LSTM step 1.1 / 1.9, hidden vectors and projection 1.5 / 2.5.
 // Whole decodes of up to 1000 frames, W = 16, per-step kernels (four launches, 22 to 30 us per iteration) / groups: a label on every second evaluation,
-// 8 utterances 18.1 / 5.9 ms, 45 22.1 / 6.7, 128 26.8 / 9.1, 256 30.6 / 11.6; hardly any label 8 utterances 1.14 / 0.45, 64 1.45 / 0.71, 128 1.84 / 1.00, 256 2.61 / 2.01.
+// 8 utterances 18.1 / 5.4 ms, 45 21.9 / 6.5, 128 26.8 / 8.8, 256 29.8 / 11.0; hardly any label 8 utterances 1.42 / 0.53, 64 2.1 / 0.89, 128 2.4 / 1.19, 256 3.2 / 2.0.
 // Tried: waves 4-7 form every other 256 items of the window rows (32 slots: 0.3 us less there, 0.5 more until the first chunk, whose fetching waits for
 // the recurrent sums behind that); the deciding wave brings its label's row of input sums into the L2 ahead of the step: what the asking took it (0.6 us) was more than
 // the step gained; a wave per quad for windows of one quad too (18 words per lane instead of 5): 0.8 us slower.
 //
-// Rows of a window: quads of 4, `qmin` to `qmax` per slot: a window without a label doubles its slot's next one, a label takes it back, so
-// that rows behind labels are not computed and stretches of blanks go by in long steps.  A quad of z holds, per 4 columns, its 4 rows' words of 8
+// Rows of a window: quads of 4, one to `qmax` per slot: a window without a label doubles its slot's next one, a label takes it back, so
+// that rows behind labels are not computed and stretches of blanks go by in long steps.  With few slots longer windows to begin with (16 rows for up to
+// two, 8 for up to four, all in one chunk of products) take fewer iterations and a slower decision: 8 utterances, a label on every second evaluation 5.86 / 5.26 ms,
+// 24 5.56 / 5.21; hardly any label 0.50 / 0.52.  A quad of z holds, per 4 columns, its 4 rows' words of 8
 // bytes: what a workgroup writes and what a wave fetches are whole segments.
 //
 // No barrier between workgroups and no flag words: every word tells whether it is the one that is waited for.  z has a free sign bit
@@ -270,9 +271,9 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
     if (lane < NS && rank < n_order) {
       s.b = gd.order[rank];
       s.len = c.len[s.b];
-      s.nwin = min(min(gd.reach, 4 * gd.qmin), s.len);
+      s.nwin = min(min(gd.reach, 4), s.len);
     }
-    s.quads = gd.qmin;
+    s.quads = 1;
     if (lane < 32) slots[lane] = s;
     const unsigned long long act = __ballot(s.nwin > 0);
     if (lane == 0) { head[0] = (int)(unsigned)act; head[1] = 0; }
@@ -683,7 +684,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
         const WindowOutcome wo = window_outcome(c, make_int4(s.b, s.t, s.len, s.sym), s.cnt, s.nwin, first, tok, V, 0, false);
         const int nqe = (s.nwin + 3) >> 2;
         s.t = wo.slot.y; s.sym = wo.slot.w; s.cnt = wo.cnt;
-        s.quads = (first < 0 ? min(2 * (s.quads & 255), qmax) : gd.qmin) | ((s.quads >> 8) ^ ((1 << nqe) - 1)) << 8;
+        s.quads = (first < 0 ? min(2 * (s.quads & 255), qmax) : 1) | ((s.quads >> 8) ^ ((1 << nqe) - 1)) << 8;
         emits = (wo.flag & 2) != 0;
         if (emits) ++s.steps;
         if (!(wo.flag & 1)) s.t = s.len = 0;
