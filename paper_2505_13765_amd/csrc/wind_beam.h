@@ -509,45 +509,102 @@ __global__ __launch_bounds__(256) void beam_score_kernel(const float *logits, in
 // largest label logits with their labels (ties: lower label first).  Adding the row's constant
 // (blank prefix sum minus log-sum-exp) keeps their order, so these are the only entries of the row
 // that can be among the hypothesis' K best.
-template <int EPT>
-__global__ __launch_bounds__(256) void beam_row_kernel(const float *logits, int V, int K, float *lse_out,
-                                                       float *blank_lp, float *cand_logit, int *cand_label) {
-  __shared__ float s_f[4];
+//
+// The K largest: every wave takes the ceil(K / NW)-th largest of its lanes' own maxima.  At least K labels are not below the least of
+// these NW values, so the others drop out with one comparison each; some 20 to 60 of 8192 remain, are listed in LDS, and
+// each counts how many of the list come before it: its place.  Rows with more than kBeamList that remain (many equal logits, or
+// a wave without K / NW labels) take K rounds of "largest remaining entry of the wave" over registers, which for every row took
+// most of the kernel's time: 8193 columns, 16 / 128 / 512 rows (K = 4 / 8 / 16) 23.5 / 23.5 / 52 us, now 9.4 / 9.4 / 17; 1025 columns,
+// 256 / 512 rows (K = 12 / 16) 12.3 / 17.0, now 6.8 / 8.3.  Rows of more than 2048 columns are spread over eight waves instead of four.
+constexpr int kBeamList = 256;
+template <int EPT, int NW>
+__global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float *logits, int V, int K, float *lse_out,
+                                                           float *blank_lp, float *cand_logit, int *cand_label) {
+  constexpr int NT = 64 * NW;
+  __shared__ float s_f[NW];
+  __shared__ unsigned s_thr[NW];
+  __shared__ int s_n;
+  __shared__ __attribute__((aligned(16))) uint2 s_list[kBeamList];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V1 = V + 1;
   const float *row = logits + (size_t)blockIdx.x * V1;
   float x[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) x[i] = tid + 256 * i < V1 ? row[tid + 256 * i] : -INFINITY;
+  for (int i = 0; i < EPT; ++i) x[i] = tid + NT * i < V1 ? row[tid + NT * i] : -INFINITY;
+  if (tid == 0) s_n = 0;
   float mx = x[0];
 #pragma unroll
   for (int i = 1; i < EPT; ++i) mx = fmaxf(mx, x[i]);
   mx = wave_max_f32(mx);
-  if (lane == 0) s_f[wave] = mx;
+  unsigned hi[EPT], top = 0u;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    hi[i] = tid + NT * i < V ? beam_order_bits(x[i]) : 0u;   // blank and padding never compete
+    top = max(top, hi[i]);
+  }
+  unsigned thr = 0u;
+  for (int r = 0; r < K; r += NW) {   // equal maxima go together: the bound is lower then, and still one
+    thr = lanes_max_u32<64>(top);
+    if (top == thr) top = 0u;
+  }
+  if (lane == 0) { s_f[wave] = mx; s_thr[wave] = thr; }
   __syncthreads();
-  mx = fmaxf(fmaxf(s_f[0], s_f[1]), fmaxf(s_f[2], s_f[3]));
-  __syncthreads();
+  mx = s_f[0];
+  thr = s_thr[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) { mx = fmaxf(mx, s_f[w]); thr = min(thr, s_thr[w]); }
+  thr = max(thr, 1u);   // 0: no entry
+#pragma unroll
+  for (int i = 0; i < EPT; ++i)
+    if (hi[i] >= thr) {
+      const int at = atomicAdd(&s_n, 1);
+      if (at < kBeamList) s_list[at] = make_uint2(hi[i], ~(unsigned)(tid + NT * i));
+    }
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < EPT; ++i) sum += expf(x[i] - mx);
   sum = wave_sum(sum);
+  __syncthreads();   // the waves' maxima are read, the list is complete
   if (lane == 0) s_f[wave] = sum;
+  const int n = s_n;
+  if (n <= kBeamList) {
+    if (tid < K && tid >= n) {   // fewer than K labels
+      cand_logit[(size_t)blockIdx.x * K + tid] = -INFINITY;
+      cand_label[(size_t)blockIdx.x * K + tid] = -1;
+    }
+    if (tid < n) {
+      const uint2 me = s_list[tid];
+      int place = 0;
+      for (int j = 0; j < n; ++j) {
+        const uint2 o = s_list[j];
+        place += o.x > me.x || (o.x == me.x && o.y > me.y) ? 1 : 0;
+      }
+      if (place < K) {
+        cand_logit[(size_t)blockIdx.x * K + place] = beam_score_of(me.x);
+        cand_label[(size_t)blockIdx.x * K + place] = (int)~me.y;
+      }
+    }
+  }
   __syncthreads();
-  const float lse = mx + logf((s_f[0] + s_f[1]) + (s_f[2] + s_f[3]));
   if (tid == 0) {
+    float all = s_f[0];
+    if (NW == 4) all = (s_f[0] + s_f[1]) + (s_f[2] + s_f[3]);
+    else {
+#pragma unroll
+      for (int w = 1; w < NW; ++w) all += s_f[w];
+    }
+    const float lse = mx + logf(all);
     lse_out[blockIdx.x] = lse;
     blank_lp[blockIdx.x] = row[V] - lse;
   }
-  // The row's K largest label logits.  Level 1: every wave takes K rounds of "largest remaining entry of
-  // my 64 lanes" (no workgroup barrier); level 2: wave 0 merges the four sorted lists.
-  __shared__ unsigned s_wh[4][kBeamMaxK], s_wl[4][kBeamMaxK];
-  unsigned hi[EPT];
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) hi[i] = tid + 256 * i < V ? beam_order_bits(x[i]) : 0u;   // blank and padding never compete
+  if (n <= kBeamList) return;
+  // Level 1: every wave takes K rounds of "largest remaining entry of my 64 lanes" (no workgroup barrier); level 2: wave 0 merges the
+  // NW sorted lists.
+  __shared__ unsigned s_wh[NW][kBeamMaxK], s_wl[NW][kBeamMaxK];
   for (int r = 0; r < K; ++r) {
     unsigned bh = 0u, bl = 0u;
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const unsigned l = ~(unsigned)(tid + 256 * i);
+      const unsigned l = ~(unsigned)(tid + NT * i);
       const bool better = hi[i] > bh || (hi[i] == bh && hi[i] != 0u && l > bl);
       bh = better ? hi[i] : bh;
       bl = better ? l : bl;
@@ -555,22 +612,22 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float *logits, int 
     unsigned wh = bh, wl = bl;
     wave_max_pair(wh, wl);
     const int v = (int)~wl;
-    if (wh != 0u && (v & 255) == tid) {   // the winner's owner retires it
+    if (wh != 0u && (v & (NT - 1)) == tid) {   // the winner's owner retires it
 #pragma unroll
       for (int i = 0; i < EPT; ++i)
-        if (i == (v >> 8)) hi[i] = 0u;
+        if (i == v / NT) hi[i] = 0u;
     }
     if (lane == 0) { s_wh[wave][r] = wh; s_wl[wave][r] = wl; }
   }
   __syncthreads();
   if (wave == 0) {
-    int h2 = 0;   // lanes 0..3: head of wave `lane`'s list
+    int h2 = 0;   // lanes 0..NW-1: head of wave `lane`'s list
     unsigned res_h = 0u, res_l = 0u;   // lane r keeps the r-th winner; stored after the rounds
     for (int r = 0; r < K; ++r) {
-      unsigned h = (lane < 4 && h2 < K) ? s_wh[lane][h2] : 0u, l = (lane < 4 && h2 < K) ? s_wl[lane][h2] : 0u;
+      unsigned h = (lane < NW && h2 < K) ? s_wh[lane][h2] : 0u, l = (lane < NW && h2 < K) ? s_wl[lane][h2] : 0u;
       const unsigned myh = h, myl = l;
       wave_max_pair(h, l);
-      if (lane < 4 && myh == h && myl == l && h != 0u) ++h2;
+      if (lane < NW && myh == h && myl == l && h != 0u) ++h2;
       if (lane == r) { res_h = h; res_l = l; }
     }
     if (lane < K) {

@@ -99,8 +99,8 @@ void beam_enqueue_topk(wind_model *m, const BeamWs &ws, int n, int Bh, int K, in
   const size_t rows = (size_t)Bh * n, V1 = (size_t)d.V + 1;
   if (V1 <= 256 * 36) {
     // one workgroup per row, then one wave per hypothesis
-    if (V1 <= 256 * 8) beam_row_kernel<8><<<(unsigned)rows, 256, 0, s>>>(ws.logits, d.V, K, ws.lse, ws.blp, ws.cl, ws.cv);
-    else beam_row_kernel<36><<<(unsigned)rows, 256, 0, s>>>(ws.logits, d.V, K, ws.lse, ws.blp, ws.cl, ws.cv);
+    if (V1 <= 256 * 8) beam_row_kernel<8, 4><<<(unsigned)rows, 256, 0, s>>>(ws.logits, d.V, K, ws.lse, ws.blp, ws.cl, ws.cv);
+    else beam_row_kernel<18, 8><<<(unsigned)rows, 512, 0, s>>>(ws.logits, d.V, K, ws.lse, ws.blp, ws.cl, ws.cv);
     beam_merge_kernel<<<(unsigned)Bh, 64, 0, s>>>(ws.lse, ws.blp, ws.cl, ws.cv, n, d.V, K, out_labels, out_jumps, out_scores);
   } else if (K <= 8) {
     beam_score_kernel<8><<<(unsigned)Bh, 256, 0, s>>>(ws.logits, n, d.V, K, out_labels, out_jumps, out_scores);

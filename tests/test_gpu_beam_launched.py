@@ -1,0 +1,41 @@
+"""The launched kernels of wind_beam_window_scores (models and calls that the resident workgroups do not take): the choice of
+a row's K largest labels, exactly, on logits that tie."""
+import numpy as np
+import pytest
+
+import wind_inputs as wi
+
+pytestmark = pytest.mark.gpu
+
+
+def config(V, Hj=64, dtype="f32", D=64):
+    return wi.WindConfig("launched", 11, 2, 70, 80, D, 64, 1, 64, Hj, V, dtype, (4,), 3, 0.5)
+
+
+# 2047 / 2048: the last row of the four-wave instance and the first of the eight-wave one; 9215: the longest row; fewer labels than K
+@pytest.mark.parametrize("V", [5, 63, 300, 2047, 2048, 9215])
+@pytest.mark.parametrize("K", [1, 7, 32])
+def test_row_choice_on_ties(V, K):
+    """Logits are the output bias (no weights): `top` labels share the largest value, up to all of them, more than the list of a row
+    holds; the order of equal scores is earlier frame, then lower label."""
+    import torch
+
+    from paper_2505_13765_amd import WindModel
+
+    cfg = config(V)
+    w = wi.make_weights(cfg)
+    w["w_out"] = np.zeros_like(w["w_out"])
+    rng = np.random.default_rng(V * 100 + K)
+    for top in sorted({1, min(V, 3), min(V, 40), min(V, 600), V}):
+        b = (-1.0 - rng.integers(0, 3, V + 1) * 0.5).astype(np.float32)
+        b[rng.choice(V, top, replace=False)] = 2.0
+        b[V] = -30.0                                                     # blank: the second frame is out of reach
+        w["b_out"] = b
+        m = WindModel.from_config(cfg, w)
+        win, g = torch.randn((2, cfg.D), device="cuda"), torch.randn((3, cfg.Hp), device="cuda")
+        lab, jmp, _ = m.beam_window_scores(win, g, K)
+        m.close()
+        order = np.lexsort((np.arange(V), -b[:V]))[:K]
+        n = len(order)
+        for h in range(3):
+            assert lab[h, :n].tolist() == order.tolist() and (jmp[h, :n] == 0).all(), (top, h)
