@@ -1471,6 +1471,9 @@ int wind_load_weights(const wind_weights *w, void *stream, wind_model **out) try
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void *)pred_proj_dma_kernel<PredCfg>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, PredCfg::SMEM_BYTES);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void *)beam_logits_dma_kernel<PredCfg>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, PredCfg::SMEM_BYTES);
     if (e != hipSuccess) rc = fail(WIND_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
   }
   if (rc != WIND_OK) {

@@ -191,6 +191,45 @@ __global__ __launch_bounds__(512) void beam_logits_tiny_kernel(ModelDev m, const
   }
 }
 
+// More rows (bf16 models): 64 x 64 blocks of logits on the ring of LDS stages, hidden rows from beam_hidden_kernel (`z_lo`: the split's
+// second vector; whole row tiles have to be readable).  Bound by the latency of its ring's K loop, 16 tiles of 64 for 1024 units; the 32 x 32 blocks above
+// read 256 KB of fp32 rows each, 53 us for 256 rows and 8193 columns, where this one and the hidden rows take 20.
+// grid = (ceil((V+1) / BN) rounded up to eight, ceil(rows / BM)).
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::NT) void beam_logits_dma_kernel(ModelDev m, const bf16_t *z, const bf16_t *z_lo, int rows, float *logits) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
+  const int n0 = blockIdx.x * Cfg::BN, row0 = blockIdx.y * Cfg::BM, Hj = m.Hj, V1 = m.V + 1;
+  if (n0 >= V1) return;
+  const bf16_t *w = reinterpret_cast<const bf16_t *>(m.w_out) + (size_t)n0 * Hj;
+  float bias[Cfg::NI];
+#pragma unroll
+  for (int ni = 0; ni < Cfg::NI; ++ni) bias[ni] = m.b_out[min(n0 + wn * Cfg::WN + ni * 32 + (lane & 31), m.V)];
+  f32x16 acc[Cfg::MI][Cfg::NI];
+#pragma unroll
+  for (int mi = 0; mi < Cfg::MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < Cfg::NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+  for (int half = 0; half < (z_lo ? 2 : 1); ++half) {
+    if (half) __syncthreads();   // the first pass may still be reading its last stage
+    gemm_mainloop_dma<Cfg>((half ? z_lo : z) + (size_t)row0 * Hj, w, Hj, smem_raw, acc);
+  }
+#pragma unroll
+  for (int ni = 0; ni < Cfg::NI; ++ni) {
+    const int col = n0 + wn * Cfg::WN + ni * 32 + (lane & 31);
+    if (col >= V1) continue;
+#pragma unroll
+    for (int mi = 0; mi < Cfg::MI; ++mi)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = row0 + wm * Cfg::WM + acc_row(mi, r, lane);
+        if (row < rows) logits[(size_t)row * V1 + col] = acc[mi][ni][r] + bias[ni];
+      }
+  }
+}
+
 // out[r] = log softmax(logits[r, :])[tok[r]]: one workgroup per row.
 __global__ __launch_bounds__(256) void beam_token_logp_kernel(const float *logits, int V1, BeamIndex tok, float *out) {
   __shared__ float s_f[4];

@@ -73,7 +73,13 @@ void beam_enqueue_logits(wind_model *m, const BeamWs &ws, const float *e_win, in
                          int Bh, hipStream_t s) {
   const ModelDev &d = m->dev;
   const size_t rows = (size_t)Bh * n, rows_pad = round_up(rows, JointCfg::BM), V1 = (size_t)d.V + 1;
-  if (m->dtype == WIND_BF16 && d.Hj <= kBeamTinyMaxHj && rows <= (size_t)kBeamTinyMaxRows) {
+  const size_t tiny_tiles = ((V1 + 31) / 32) * ((rows + 31) / 32), row_tiles = (rows + PredCfg::BM - 1) / PredCfg::BM,
+               col_tiles = (V1 + PredCfg::BN - 1) / PredCfg::BN;
+  // 32 x 32 blocks, which form their hidden rows themselves, while they fit the chip one per CU: every column tile forms all rows again.  Whole scoring step, us,
+  // 32 x 32 / 64 x 64 blocks: 8192 labels, 1024 units (264 blocks per 32 rows), 16 rows 65 / 62, 64 71 / 64, 128 84 / 67, 256 109 / 76; 1024 labels, 640 units
+  // (33), 32 rows 48 / 52, 64 49 / 52, 256 54.5 / 53.7.  64 x 64 blocks up to eight per CU, 128 x 128 above: 1024 labels, 512 rows 57 / 67, 1024 rows 62 / 70;
+  // 8192 labels, 512 rows 90 / 91, 1024 113 / 115, 4096 265 / 232.
+  if (m->dtype == WIND_BF16 && d.Hj <= kBeamTinyMaxHj && rows <= (size_t)kBeamTinyMaxRows && tiny_tiles <= (size_t)m->cu_count) {
     const int split = m->opt_beam_exact ? 1 : 0;
     const size_t smem = beam_tiny_smem(d.Hj, split);
     const dim3 grid((unsigned)round_up((V1 + 31) / 32, 8), (unsigned)((rows + 31) / 32));
@@ -85,8 +91,13 @@ void beam_enqueue_logits(wind_model *m, const BeamWs &ws, const float *e_win, in
   } else if (m->dtype == WIND_BF16) {
     bf16_t *z_lo = m->opt_beam_exact ? ws.z_lo : nullptr;
     beam_hidden_kernel<<<(unsigned)rows, 256, 0, s>>>(e_win, p, pi, ws.z, z_lo, n, d.Hj);
-    dim3 grid((unsigned)(rows_pad / JointCfg::BM), (unsigned)((V1 + JointCfg::BN - 1) / JointCfg::BN));
-    joint_mfma_store_kernel<JointCfg><<<grid, JointCfg::NT, JointCfg::SMEM_BYTES, s>>>(d, ws.z, z_lo, (int)rows, ws.logits);
+    if (row_tiles * col_tiles <= 8 * (size_t)m->cu_count) {
+      const dim3 grid((unsigned)round_up(col_tiles, 8), (unsigned)row_tiles);
+      beam_logits_dma_kernel<PredCfg><<<grid, PredCfg::NT, PredCfg::SMEM_BYTES, s>>>(d, ws.z, z_lo, (int)rows, ws.logits);
+    } else {
+      dim3 grid((unsigned)(rows_pad / JointCfg::BM), (unsigned)((V1 + JointCfg::BN - 1) / JointCfg::BN));
+      joint_mfma_store_kernel<JointCfg><<<grid, JointCfg::NT, JointCfg::SMEM_BYTES, s>>>(d, ws.z, z_lo, (int)rows, ws.logits);
+    }
   } else {
     beam_logits_kernel<float><<<(unsigned)rows, 256, (size_t)d.Hj * 4, s>>>(d, e_win, p, pi, n, ws.logits);
   }

@@ -1,9 +1,12 @@
 """The launched kernels of wind_beam_window_scores (models and calls that the resident workgroups do not take): the choice of
-a row's K largest labels, exactly, on logits that tie."""
+a row's K largest labels, exactly, on logits that tie, and the logits' two block sizes against the fp64 oracle."""
 import numpy as np
 import pytest
 
+import oracle
 import wind_inputs as wi
+from oracle import beam_scores as bs
+from test_gpu_beam_scores import check_against_oracle, hypotheses
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +42,26 @@ def test_row_choice_on_ties(V, K):
         n = len(order)
         for h in range(3):
             assert lab[h, :n].tolist() == order.tolist() and (jmp[h, :n] == 0).all(), (top, h)
+
+
+# rows around the edges of 64-row blocks; 8200 labels: 257 blocks of 32 x 32 per row tile, past one per CU; 1088 units: none of those;
+# 300 rows of 64 units at 1500 labels: many rows, few columns
+@pytest.mark.parametrize("exact", [0, 1])
+@pytest.mark.parametrize("V,Hj,n,Bh", [(8200, 64, 1, 1), (8200, 320, 16, 4), (8200, 192, 13, 5), (1500, 64, 20, 15), (1100, 1088, 7, 3), (8100, 64, 3, 2)])
+def test_logit_blocks(V, Hj, n, Bh, exact):
+    import torch
+
+    from paper_2505_13765_amd import WindModel
+
+    cfg = config(V, Hj, "bf16", 128)
+    w = wi.make_weights(cfg)
+    o = oracle.Oracle.from_config(cfg, w)
+    m = WindModel.from_config(cfg, w)
+    m.set_option("beam_exact", exact)
+    enc, _ = wi.make_batch(cfg)
+    g = hypotheses(o, cfg, np.random.default_rng(3), Bh, 4)
+    win = np.ascontiguousarray(enc[0, 5:5 + n])
+    _, _, _, full = bs.beam_window(o, win, g, 9)
+    lab, jmp, sc = m.beam_window_scores(torch.from_numpy(win).cuda(), torch.from_numpy(g.astype(np.float32)).cuda(), 9)
+    check_against_oracle(cfg, full, 9, lab, jmp, sc, 1e-3 if exact else 2e-2)   # split: about 16 mantissa bits of the hidden vector
+    m.close()
