@@ -1533,9 +1533,7 @@ static int beam_scores_check(const wind_model *m, const float *enc_window, int n
 // the scoring step's kernels, on a workspace that is already laid out
 static int beam_scores_enqueue(wind_model *m, const BeamWs &ws, const float *enc_window, int n, const float *dec_out,
                                int Bh, int K, int32_t *out_labels, int32_t *out_jumps, float *out_scores, hipStream_t s) {
-  const ModelDev &d = m->dev;
-  beam_enqueue_linear(m, d.w_enc, d.b_enc, enc_window, ws.e, n, d.Hj, d.D, true, s);
-  beam_enqueue_linear(m, d.w_pred, d.b_pred, dec_out, ws.p, Bh, d.Hj, d.Hp, false, s);
+  beam_enqueue_projections(m, enc_window, ws.e, n, dec_out, ws.p, Bh, s);
   beam_enqueue_logits(m, ws, ws.e, n, ws.p, beam_identity(), Bh, s);
   beam_enqueue_topk(m, ws, n, Bh, K, out_labels, out_jumps, out_scores, s);
   return check_launch("beam window scores");

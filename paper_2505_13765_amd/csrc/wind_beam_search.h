@@ -122,17 +122,15 @@ void beam_enqueue_topk(wind_model *m, const BeamWs &ws, int n, int Bh, int K, in
   }
 }
 
-// out[r, :] = w x[r] + bias for fp32 rows x, weights in the model's storage type.
-void beam_enqueue_linear(wind_model *m, const void *w, const float *bias, const float *x, float *out, int rows, int n_out,
-                         int K, bool round_x, hipStream_t s) {
+// out[r, :] = w x[r] + bias for fp32 rows x, weights in the model's storage type: the encoder projection of `n` frames to `e` and, with
+// rows, the prediction network's projection of `rows` hidden vectors to `p`, in one launch.
+void beam_enqueue_projections(wind_model *m, const float *frames, float *e, int n, const float *hidden, float *p, int rows, hipStream_t s) {
   constexpr int kR = 8;   // rows that share one pass over a weight row
-  const dim3 grid((unsigned)((n_out + 3) / 4), (unsigned)((rows + kR - 1) / kR));
-  if (m->dtype == WIND_BF16 && round_x)
-    beam_linear_kernel<bf16_t, true, kR><<<grid, 256, 0, s>>>((const bf16_t *)w, bias, x, out, rows, n_out, K);
-  else if (m->dtype == WIND_BF16)
-    beam_linear_kernel<bf16_t, false, kR><<<grid, 256, 0, s>>>((const bf16_t *)w, bias, x, out, rows, n_out, K);
-  else
-    beam_linear_kernel<float, false, kR><<<grid, 256, 0, s>>>((const float *)w, bias, x, out, rows, n_out, K);
+  const ModelDev &d = m->dev;
+  const int jb = (d.Hj + 3) / 4, blocks_e = jb * ((n + kR - 1) / kR), blocks_p = jb * ((rows + kR - 1) / kR);
+  const BeamLinear le{d.w_enc, d.b_enc, frames, e, n, d.Hj, d.D, m->dtype == WIND_BF16}, lp{d.w_pred, d.b_pred, hidden, p, rows, d.Hj, d.Hp, 0};
+  if (m->dtype == WIND_BF16) beam_linear_kernel<bf16_t, kR><<<(unsigned)(blocks_e + blocks_p), 256, 0, s>>>(le, lp, blocks_e);
+  else beam_linear_kernel<float, kR><<<(unsigned)(blocks_e + blocks_p), 256, 0, s>>>(le, lp, blocks_e);
 }
 
 // ---- state pool and staging ---------------------------------------------------------------------
@@ -518,7 +516,7 @@ int beam_decode(wind_model *m, const float *enc_out, int T, int window, int K, i
     HIP_TRY(hipMalloc((void **)&bp.e_all, (size_t)T * d.Hj * 4));
     bp.e_bytes = (size_t)T * d.Hj * 4;
   }
-  beam_enqueue_linear(m, d.w_enc, d.b_enc, enc_out, bp.e_all, T, d.Hj, d.D, true, s);
+  beam_enqueue_projections(m, enc_out, bp.e_all, T, nullptr, nullptr, 0, s);
 
   // trie of label sequences; slot 0 holds the zero state, the empty sequence is one step from it on the start id
   std::vector<BeamNode> nodes;

@@ -65,3 +65,32 @@ def test_logit_blocks(V, Hj, n, Bh, exact):
     lab, jmp, sc = m.beam_window_scores(torch.from_numpy(win).cuda(), torch.from_numpy(g.astype(np.float32)).cuda(), 9)
     check_against_oracle(cfg, full, 9, lab, jmp, sc, 1e-3 if exact else 2e-2)   # split: about 16 mantissa bits of the hidden vector
     m.close()
+
+
+# 60: rows that eight values do not divide; shift: inputs at an address that is no multiple of 16 bytes; 9 frames, 17 hypotheses: one
+# more than a group of eight rows each
+@pytest.mark.parametrize("dtype,D,shift", [("f32", 60, 0), ("f32", 64, 1), ("bf16", 64, 0), ("bf16", 64, 3)])
+def test_projections(dtype, D, shift):
+    import torch
+
+    from paper_2505_13765_amd import WindModel
+
+    cfg = config(1200, 64, dtype, D)
+    w = wi.make_weights(cfg)
+    o = oracle.Oracle.from_config(cfg, w)
+    m = WindModel.from_config(cfg, w)
+    enc, _ = wi.make_batch(cfg)
+    g = hypotheses(o, cfg, np.random.default_rng(3), 17, 4).astype(np.float32)
+    win = np.ascontiguousarray(enc[0, 5:14])
+
+    def place(x):
+        buf = torch.zeros(x.size + shift, device="cuda")
+        buf[shift:] = torch.from_numpy(x).cuda().flatten()
+        t = buf[shift:].view(*x.shape)
+        assert t.data_ptr() % 16 == 4 * shift
+        return t
+
+    _, _, _, full = bs.beam_window(o, win, g.astype(np.float64), 9)
+    lab, jmp, sc = m.beam_window_scores(place(win), place(g), 9)
+    check_against_oracle(cfg, full, 9, lab, jmp, sc, 1e-4 if dtype == "f32" else 2e-2)
+    m.close()
