@@ -15,4 +15,8 @@ constexpr bool group_keys_suffice(int nparts, int column_groups, int row_groups)
 // Either way no two workgroups are more than two iterations apart, as the tag needs.
 constexpr int group_keys_need(int it) { return it - 1; }
 
+// The slots with a label (wind_group_vocab_kernel.h), as one wave of a workgroup lists them for the steps behind iteration `it - 1`: the others read the
+// list until the end of iteration `it`, and that wave writes the next one as soon as it has the decisions, with no barrier in between.
+constexpr int vocab_emit_list(int it) { return it & 1; }
+
 }  // namespace wind

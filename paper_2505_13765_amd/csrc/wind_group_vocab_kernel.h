@@ -85,8 +85,8 @@ struct VocabCfg {
   static constexpr size_t oWb = oB + 512;                                      // float [PPW] blank column, [PPW] projection biases
   static constexpr size_t oS = oWb + (size_t)2 * PPW * 4;                      // VocabSlot [2][32], of this iteration and of the next
   static constexpr size_t oQ = oS + 2 * kVocabSlots * 32;                      // int [64] quads of the iteration
-  static constexpr size_t oI = oQ + 64 * 4;                                    // int info[32], emap[32], stat[16], rech[16], head[4], counts[kNumStats + 2], fail, near
-  static constexpr size_t smem = oI + (size_t)(32 + 32 + 16 + 16 + 4 + kNumStats + 2 + 2) * 4;
+  static constexpr size_t oI = oQ + 64 * 4;                                    // int info[32], emap[2][32], stat[16], rech[16], head[4], counts[kNumStats + 2], fail, near
+  static constexpr size_t smem = oI + (size_t)(32 + 64 + 16 + 16 + 4 + kNumStats + 2 + 2) * 4;
   static_assert((size_t)4 * kVocabSlots * NR * 4 <= kZBuf, "partial sums in a row buffer");
   static_assert(smem <= 160 * 1024, "LDS");
 };
@@ -205,9 +205,9 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
   float *pfull = reinterpret_cast<float *>(smem + Cfg::oPf), *bias = reinterpret_cast<float *>(smem + Cfg::oB);
   float *wbl = reinterpret_cast<float *>(smem + Cfg::oWb), *bpl = wbl + PPW;
   VocabSlot *slots = reinterpret_cast<VocabSlot *>(smem + Cfg::oS);
-  int *qtab = reinterpret_cast<int *>(smem + Cfg::oQ), *info = reinterpret_cast<int *>(smem + Cfg::oI), *emap = info + 32;
-  volatile int *stat = emap + 32;
-  int *rech = emap + 48, *head = rech + 16, *counts = head + 4, *fail = counts + kNumStats + 2, *near_w = fail + 1;
+  int *qtab = reinterpret_cast<int *>(smem + Cfg::oQ), *info = reinterpret_cast<int *>(smem + Cfg::oI), *emaps = info + 32;
+  volatile int *stat = emaps + 64;
+  int *rech = emaps + 80, *head = rech + 16, *counts = head + 4, *fail = counts + kNumStats + 2, *near_w = fail + 1;
 
   int lane = threadIdx.x & 63, tid = threadIdx.x, tid1 = tid & 255, l15 = lane & 15, l4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w4 = wave & 3;
@@ -330,10 +330,10 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
   if (*fail) return;
   const __amdgpu_buffer_rsrc_t zr = vocab_rsrc(ones, lay.keys * 8), hr = vocab_rsrc(hx, (size_t)2 * NS * H * 4);
 
-  // The hidden vectors of 16 slots with a label as operand rows: lane (row l15, K group l4) its 8 units per step of 32 of this wave's
+  // The hidden vectors of 16 slots with a label (of the list emap) as operand rows: lane (row l15, K group l4) its 8 units per step of 32 of this wave's
   // quarter of K, as bf16 hi and lo
   bf16x8 hi[ROLE == 1 ? KS : 1], lo[ROLE == 1 ? KS : 1];
-  auto hidden_rows = [&](int tile, int n_em) -> bool {
+  auto hidden_rows = [&](const int *emap, int tile, int n_em) -> bool {
     const int en = emap[min(16 * tile + l15, n_em - 1)];
     const unsigned tag = (unsigned)((en >> 9) & 1) << 14;
     const int base = ((((en >> 8) & 1) * NS + (en & 255)) * H + w4 * QK + l4 * 8) * 4;
@@ -388,6 +388,8 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
     const unsigned act = (unsigned)__builtin_amdgcn_readfirstlane(head[0]), em = (unsigned)__builtin_amdgcn_readfirstlane(head[1]);
     const int nquads = __builtin_amdgcn_readfirstlane(head[2]), n_em = __popc(em), nch = (nquads + 7) >> 3;
     VocabSlot *now = slots + (it & 1) * kVocabSlots, *next = slots + ((it & 1) ^ 1) * kVocabSlots;
+    const int *emap = emaps + 32 * vocab_emit_list(it);
+    int *emap_next = emaps + 32 * vocab_emit_list(it + 1);
     const unsigned stamp = (unsigned)it + 1u;
     if (!act) break;
     if constexpr (ROLE == 0) {
@@ -524,7 +526,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
       // ---- the recurrent sums that the last labels left behind
       for (int tile = (n_em - 1) >> 4; n_em > 0 && tile >= 0; --tile) {
         if (16 * tile + 16 < n_em) {   // not the tile whose sums are at hand
-          bad |= !hidden_rows(tile, n_em);
+          bad |= !hidden_rows(emap, tile, n_em);
           recurrent_sums();
         }
 #pragma unroll
@@ -694,7 +696,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
       if (lane < 32) {
         next[lane] = s;
         info[lane] = (emits ? 1 << 15 | tok : 0) | ((em >> lane) & 1 ? __popc(em & below) : 63) << 16 | ((s.steps - 1) & 3) << 24;
-        if (emits) emap[__popc(em1 & below)] = lane | ((s.steps - 1) & 3) << 8;
+        if (emits) emap_next[__popc(em1 & below)] = lane | ((s.steps - 1) & 3) << 8;
         if (lane == g) { head[3] = (int)(unsigned)u; }
       }
       if (lane == 0) { head[0] = (int)act1; head[1] = (int)em1; }
@@ -744,7 +746,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
       // ---- the projection columns of the new hidden vectors: partial sums over this wave's quarter of K
       const int n_new = __popc((unsigned)__builtin_amdgcn_readfirstlane(head[1]));
       for (int tile = 0; 16 * tile < n_new; ++tile) {
-        bad |= !hidden_rows(tile, n_new);
+        bad |= !hidden_rows(emap_next, tile, n_new);
 #pragma unroll
         for (int t = 0; t < Cfg::PT; ++t) {
           f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};

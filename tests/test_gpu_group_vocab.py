@@ -58,6 +58,19 @@ def test_groups_of_larger_vocabularies(H, V, B, W):
     m.close()
 
 
+def test_labels_in_both_tiles_of_slots():
+    """32 slots per group that all take a label on most iterations: hidden vectors of two tiles of 16 slots, whose list of emitting slots one wave
+    writes for the next iteration while the others may still be at this one's recurrent sums."""
+    cfg, w, enc, lens, m = model(640, 1040, 256, 60, 60, 0.0)
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, 16))
+        assert (m.loop_info()[0] > 0) == bool(loop)
+    assert runs[0] == runs[1] and runs[0][2][4] > 2 * int(lens.sum())
+    m.close()
+
+
 @pytest.mark.parametrize("bias", [1.0, 7.0])
 @pytest.mark.parametrize("H,V,B,Ws", [(128, 4096, 1, (1, 3, 16)), (256, 1025, 20, (2, 5, 16)), (128, 2500, 60, (1, 7, 12)), (384, 1300, 140, (3, 16)), (128, 1000, 66, (2, 16))])
 def test_counters_are_those_of_the_callers_windows(H, V, B, Ws, bias):

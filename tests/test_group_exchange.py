@@ -35,3 +35,19 @@ def test_the_model_shows_what_the_rule_is_for(model):
     for nparts, rg, empty_from, held in ((3, 1, 0, 20), (32, 2, 40, 31), (32, 4, 0, 24)):
         assert model(32, nparts, rg, empty_from, 1000, held, 0, 0, 1) in ("stuck", "wrong")
         assert model(32, nparts, rg, empty_from, 1000, held, 0, 0, 0) == "stuck"
+
+
+def test_no_wave_mistakes_the_next_list_of_emitting_slots_for_its_own(tmp_path):
+    """Two lists, by the iteration; with one, a wave that is held back reads what the first wave has written for the next iteration."""
+    exe = str(tmp_path / "model")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, os.path.join(HERE, "emit_list_model.cpp"), "-o", exe], check=True)
+
+    def run(held, seed, rule):
+        return subprocess.run([exe, str(held), str(seed), str(rule)], check=True, capture_output=True, text=True, timeout=60).stdout.strip()
+
+    for held in range(4):
+        assert run(held, 0, 1) == "done", held
+    for seed in range(8):
+        assert run(-1, seed, 1) == "done", seed
+    assert run(0, 0, 0) == "done"
+    assert [run(held, 0, 0) for held in (1, 2, 3)] == ["wrong"] * 3
