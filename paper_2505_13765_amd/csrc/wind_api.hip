@@ -995,10 +995,11 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
   std::unique_lock<std::mutex> gate_lock(gate.mutex, std::defer_lock);
   unsigned long long turn = 0;
   if (gi) {
+    // calls that may stop short are asynchronous ones, with a group per utterance; the others end by themselves, with any number of symbols per frame
     gd.max_iters = (int)std::min<long long>(async ? std::min(async_iters, max_iters) : max_iters, 1 << 30);
-    // calls that may stop short are asynchronous ones, with a group per utterance
-    const auto kernel = gi->kernel[gd.NG < B ? kGroupMany : gd.max_iters < max_iters ? kGroupLimited : kGroupOne];
-    if (!kernel || (gd.NG < B && gd.max_iters < max_iters)) return fail(WIND_ERR_UNSUPPORTED, "resident groups: no instance for this call");
+    const bool limited = async && gd.max_iters < max_iters;
+    const auto kernel = gi->kernel[gd.NG < B ? kGroupMany : limited ? kGroupLimited : kGroupOne];
+    if (!kernel || (gd.NG < B && limited)) return fail(WIND_ERR_UNSUPPORTED, "resident groups: no instance for this call");
     // Once a group is on the chip its waits end.  Until then something else may hold CUs for any time: where another kernel can
     // decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;

@@ -295,7 +295,7 @@ __device__ __forceinline__ void group_outcome(const CallDev &c, const GroupDev &
         kept[1] = wo.flag & 1 ? open.ph : 0;
       }
       if (writer) {
-        // The call's counters (fewer than 2^31 each: B T (S + 1) is an int).  LDS additions that nobody waits for, written as assembly: the
+        // The call's counters (32 bits each).  LDS additions that nobody waits for, written as assembly: the
         // compiler turns an atomicAdd of several lanes into a loop over them, half a microsecond for all of these.
         const unsigned ev = wo.ev, forced = (ev >> 29) & 1u;
         auto add = [&](int which, unsigned v) { asm volatile("ds_add_u32 %0, %1" ::"v"(at0 + 4 * which), "v"(v) : "memory"); };

@@ -500,3 +500,36 @@ def test_cut_windows_in_every_kernel(Hp, Hj, V, B, bias, wide):
     assert runs[0] == runs[1] == runs[2]
     assert route[3 if wide else 2] > 0
     m.close()
+
+
+# one utterance per group, several, several rounds; fp32 with and without a workgroup per utterance; larger vocabularies (1100 and, from 65 utterances, 1000 labels)
+@pytest.mark.parametrize("dtype,H,V,B,W", [("bf16", 128, 300, 1, 8), ("bf16", 128, 300, 20, 4), ("bf16", 256, 300, 100, 8), ("f32", 64, 30, 2, 4), ("f32", 128, 300, 5, 8),
+                                           ("bf16", 128, 1100, 2, 16), ("bf16", 128, 1100, 140, 8), ("bf16", 128, 1000, 256, 16)])
+def test_no_limit_on_symbols_per_frame(dtype, H, V, B, W):
+    """max_symbols_per_step = INT_MAX as "no limit".  The model's one label comes on a frame that asks for it, and raises blank behind it for good."""
+    import torch
+
+    from paper_2505_13765_amd import WindModel
+
+    T = 40
+    cfg = wi.WindConfig("no_limit", 9, B, T, T, 64, 64, 1, H, H, V, dtype, (4,), 1, 0.7)
+    w = {k: np.zeros_like(v) for k, v in wi.make_weights(cfg).items()}
+    w["emb"][:V, 0] = 1.0
+    w["b_ih0"][:H], w["b_ih0"][H:2 * H], w["b_ih0"][3 * H:] = 8.0, -8.0, 8.0   # gates i, f, g, o: the cell is what the last label makes it
+    w["w_ih0"][2 * H, 0] = 8.0
+    w["w_pred"][1, 0], w["w_out"][V, 1] = 16.0, 1.0     # a label: hidden unit 1, blank
+    w["w_enc"][0, 0], w["w_out"][5, 0] = 1.0, 1.0       # a frame: hidden unit 0, label 5
+    w["b_out"][:V], w["b_out"][5], w["b_out"][V] = -5.0, 0.0, 2.0
+    enc = np.zeros((B, T, 64), np.float32)
+    want = [[7 * b % T] if b % 3 == 0 else [] for b in range(B)]
+    for b in range(B):
+        enc[b, want[b], 0] = 6.0
+    m = WindModel.from_config(cfg, w)
+    out_t, out_f = torch.zeros((B, T), dtype=torch.int32, device="cuda"), torch.zeros((B, T), dtype=torch.int32, device="cuda")
+    n = torch.zeros(B, dtype=torch.int32, device="cuda")
+    lens = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    m.greedy_decode(torch.from_numpy(enc).cuda(), lens, W, 2 ** 31 - 1, out_t, out_f, n)
+    assert m.loop_info()[0] > 0
+    n = n.tolist()
+    assert [out_f[b, :n[b]].tolist() for b in range(B)] == want and all(out_t[b, :n[b]].tolist() == [5] * len(want[b]) for b in range(B))
+    m.close()
