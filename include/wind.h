@@ -369,7 +369,8 @@ int wind_get_route_counts(wind_model *m, wind_route_counts *out);
  *             not aligned with z (random or trained dense rows).  For rows aligned with z the error can
  *             reach 2^-8 |w| |z| (kappa ~ 7.4 sqrt(Hj)); raise kappa for such models: the band only
  *             costs fp32 re-evaluations, never correctness.  Where more than 1024 labels (or batches of more than 64 utterances of more than 992) decode in
- *             resident groups the hidden vector is fp16, with an eighth of that rounding and of that band
+ *             resident groups the hidden vector is fp16, with an eighth of that rounding and of that band; a
+ *             call that comes upon one longer than 64000, which fp16 might not hold, is decoded by the per-step kernels from its start
  *   "pred_mfma_min_batch"  smallest B for which the prediction network runs on MFMA tiles
  *             (default 1; bf16 models only; below it one wave per hidden unit does fp32 FMA)
  *   "loop_kernel"  1 (default): small decodes run the whole loop as one resident kernel; 0: always the graph of

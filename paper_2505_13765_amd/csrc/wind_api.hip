@@ -231,6 +231,9 @@ void set_tau(wind_model *m) {
   // about 2.1e-3 * |w| * |z| / sqrt(Hj) for weights that are not aligned with z.  kappa such
   // deviations make the band.
   m->dev.tau_scale = (float)(m->kappa * 2.1e-3 * m->wnorm_max / std::sqrt((double)m->dev.Hj));
+  // fp16 operands (wind_group_vocab_kernel): a unit below 2^-14 is rounded to a multiple of 2^-24, so by at most 2^-25, which moves a logit by at most |w|
+  // sqrt(Hj) 2^-25, whatever the signs, and the difference of two by twice that
+  m->dev.tau16_floor = (float)(m->wnorm_max * std::sqrt((double)m->dev.Hj) * std::ldexp(1.0, -24));
 }
 
 // Utterances up to which windows of more than 8 rows of bf16 models of less than 993 labels (see vocab_model) take groups: each round of 32 utterances costs them the same, while the

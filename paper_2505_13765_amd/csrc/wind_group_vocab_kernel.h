@@ -50,20 +50,25 @@ namespace wind {
 constexpr int kVocabSlots = 32;
 constexpr int kTie = 0x3FFF;   // instead of a label: a near-tie
 // The screening products are fp16: as fast as bf16 and with eight times less rounding of the hidden row, so that near-ties, each of which holds all
-// slots up for 2 us, are eight times rarer (one iteration in eight with 16 slots instead of two in three).  The rows are scaled by 64 and the weights by a
-// power of two that makes the largest about 2^14 (ModelDev::w16_scale), which keeps what fp16 cannot hold in full far below the rounding of the rest; a row
-// whose norm says that a unit might not fit, is decided in fp32 over all labels.  Rows decided again, 256 utterances of 640 units and 4096 labels: 9283
-// with bf16, now 1311; 11.4 -> 11.0 ms, 45 utterances 6.61 -> 6.42, 8 5.94 -> 5.87.
-constexpr float kZ16Scale = 64.f, kZ16Max = 1000.f;
+// slots up for 2 us, are eight times rarer (one iteration in eight with 16 slots instead of two in three).  The weights are scaled by a power of two that
+// makes the largest about 2^14 (ModelDev::w16_scale), which keeps what fp16 cannot hold of them in full far below the rounding of the rest; the rows are not:
+// fp16 holds units of up to 65504, and the products take its smallest numbers as they are.  Rows longer than kZ16Max, where a unit might not fit, leave the call to the
+// per-step kernels at once (as groups that cannot meet do): 640 units, 4096 labels, every row such, 8 / 128 utterances of up to 100 frames 3.09 / 4.19 ms, with those kernels
+// from the start 2.95 / 4.04, where rows that fit take 0.97 / 1.43.  (Decided over all labels in fp32 by one wave, at lengths above 1000: 191 / 527 ms.)
+// Rows decided again, 256 utterances of 640 units and 4096 labels: 9283 with bf16, now 1311; 11.4 -> 11.0 ms, 45 utterances 6.61 -> 6.42, 8 5.94 -> 5.87.
+constexpr float kZ16Max = 64000.f;
+// A row's squared norm is exchanged in parts of four units.  Their sums stay below kNormInfinite where all units are finite, also where squares overflow, and
+// with an infinite unit they do not (a word's lowest bit is its tag: no infinity).
+constexpr float kNormPart = 1e35f, kNormInfinite = 1e38f;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
 __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
   const f32x2_t v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));
 }
-// How far below the best a label may be to be looked at in fp32: see decide_row; the rounding of fp16, and what its smallest numbers lose
+// How far below the best a label may be to be looked at in fp32: see decide_row; an eighth of bf16's rounding, and what fp16's smallest numbers lose
 __device__ __forceinline__ float vocab_band(const ModelDev &m, float znorm, float top) {
-  return m.tau_scale * fmaf(0.125f, znorm, 0.04f) + 6.2e-5f * fabsf(top);
+  return fmaf(m.tau_scale * 0.125f, znorm, m.tau16_floor) + 6.2e-5f * fabsf(top);
 }
 
 template <int KS>
@@ -71,9 +76,9 @@ struct VocabCfg {
   static constexpr int GW = 32, H = 128 * KS, UPW = H / GW, NR = 4 * UPW, PPW = H / GW;
   static constexpr int LT = NR / 16, PT = (PPW + 15) / 16;
   static constexpr int QK = H / 4;
-  static constexpr int ZST = H + 8;                                            // bf16 per row in LDS (16 bytes of padding: banks)
+  static constexpr int ZST = H + 8;                                            // fp16 per row in LDS (16 bytes of padding: banks)
   static constexpr int NC = PPW / 4;                                           // groups of 4 columns
-  static constexpr size_t oZ = 0;                                              // bf16 [2][32][ZST]; between them the partial sums of the recurrent rows, float [4][32][NR]
+  static constexpr size_t oZ = 0;                                              // fp16 [2][32][ZST]; between them the partial sums of the recurrent rows, float [4][32][NR]
   static constexpr size_t kZBuf = (size_t)32 * ZST * 2;
   static constexpr size_t oE = oZ + 2 * kZBuf;                                 // float4 [NC][512]: slot x ring
   static constexpr size_t oPred = oE + (size_t)NC * 512 * 16;                  // float [4][32][PPW]
@@ -378,7 +383,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
       }
   };
 
-  const float unscale = 1.f / (kZ16Scale * m.w16_scale);   // a power of two
+  const float unscale = 1.f / m.w16_scale;   // a power of two
   bool bad = false;   // a wait of this wave has given up: told to the workgroup ahead of the decisions' barrier
   for (int it = 0;; ++it) {
     // opaque: see wind_group_kernel
@@ -415,10 +420,11 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           y[k] = valid ? fmaxf(e[k] + v, 0.f) : 0.f;
           nrm = fmaf(y[k], y[k], nrm);
         }
+        nrm = fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])) == INFINITY ? 3.f * kNormInfinite : fminf(nrm, kNormPart);
         const float dot = fmaf(y[3], w[3], fmaf(y[2], w[2], fmaf(y[1], w[1], y[0] * w[0])));
         const int quad = s * qmax + qq;
-        group_st(ones + (size_t)(quad * H + (g * NC + i) * 4 + r), (pack_f16x2(y[0] * kZ16Scale, y[1] * kZ16Scale) & 0x7FFF7FFFu) | tagz,
-                 (pack_f16x2(y[2] * kZ16Scale, y[3] * kZ16Scale) & 0x7FFF7FFFu) | tagz, near);
+        group_st(ones + (size_t)(quad * H + (g * NC + i) * 4 + r), (pack_f16x2(y[0], y[1]) & 0x7FFF7FFFu) | tagz,
+                 (pack_f16x2(y[2], y[3]) & 0x7FFF7FFFu) | tagz, near);
         group_st(bx + (size_t)(quad * H + (g * NC + i) * 4 + r), __float_as_uint(dot), (__float_as_uint(nrm) & ~1u) | tag, near);
         if (fresh && qq == 0) {
           const float mine = r == 0 ? p[0] : r == 1 ? p[1] : r == 2 ? p[2] : p[3];
@@ -553,6 +559,11 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           });
           return at;
         };
+        // A row that fp16 cannot hold: the groups give the call up, and this wave's rows are blank so that nobody here waits for them
+        auto leave = [&]() {
+          bad = true;
+          if (lane == 0) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
         if (nq == 1) {
           // one quad: row w4, lane with the keys of parts lane and lane + 64
           const unsigned long long *kr = kx + (size_t)g * qmax * nparts * 4 + w4, *br = bx + (size_t)g * qmax * H + w4;
@@ -575,15 +586,16 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           float dot = 0.f, nrm = 0.f;
 #pragma unroll
           for (int k = 0; k < kBn; ++k) { dot += first(v[k]); nrm += second(v[k]); }
-          const float vblank = wave_sum(dot) + m.b_out[V], znorm = sqrtf(wave_sum(nrm));
+          const float vblank = wave_sum(dot) + m.b_out[V], norm2 = wave_sum(nrm);
           const float kbest = wave_max_f32(fmaxf(kA.x, kB.x)), vbest = key_val(kbest), top = fmaxf(vbest, vblank);
-          float thresh = top - vocab_band(m, znorm, top);
-          int label = V;
-          const bool large = znorm > kZ16Max && znorm < INFINITY;
-          if (w4 < n && (large || !(vbest < thresh))) {
+          const float thresh = top - vocab_band(m, sqrtf(norm2), top);
+          int label = V;   // also of a row with an infinite unit
+          if (w4 < n && norm2 > kZ16Max * kZ16Max && norm2 < kNormInfinite) {
+            leave();
+          } else if (w4 < n && norm2 < kNormInfinite && !(vbest < thresh)) {
             const int cnt = __popcll(__ballot(key_val(kA.x) >= thresh)) + __popcll(__ballot(key_val(kA.y) >= thresh)) +
                             __popcll(__ballot(key_val(kB.x) >= thresh)) + __popcll(__ballot(key_val(kB.y) >= thresh));
-            if (!large && cnt == 1 && vblank < thresh) {
+            if (cnt == 1 && vblank < thresh) {
               int col = 0;
               if (kA.x == kbest) col = lane * 32 + key_col(kbest);
               if (kB.x == kbest) col = (lane + 64) * 32 + key_col(kbest);
@@ -595,11 +607,6 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           if (lane == 0) { rech[w4] = 0; stat[w4] = mark | label; }
           int st;
           if (label == kTie && settled(w4, st) < 0) {
-            if (large) {   // every part whole
-              thresh = -INFINITY;
-              if (lane < nparts) kA.y = INFINITY;
-              if (lane + 64 < nparts) kB.y = INFINITY;
-            }
             label = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + w4) * H, pfull, vblank, thresh, kA, kB);
             if (lane == 0) { rech[w4] = 1; stat[w4] = mark | label; }
           }
@@ -626,8 +633,8 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
 #pragma unroll
           for (int k = 0; k < 8; ++k) kbest = fmaxf(kbest, l15 + 16 * k < nparts ? first(u[k]) : kKeyNone);
           kbest = row16_max_f32(kbest);
-          const float vblank = row16_sum_f32(dot) + m.b_out[V], znorm = sqrtf(row16_sum_f32(nrm)), vbest = key_val(kbest), top = fmaxf(vbest, vblank);
-          const float thresh = top - vocab_band(m, znorm, top);
+          const float vblank = row16_sum_f32(dot) + m.b_out[V], norm2 = row16_sum_f32(nrm), vbest = key_val(kbest), top = fmaxf(vbest, vblank);
+          const float thresh = top - vocab_band(m, sqrtf(norm2), top);
           int cnt = 0, col = 0;   // with NaN logits no key is a label's
 #pragma unroll
           for (int k = 0; k < 8; ++k)
@@ -639,8 +646,11 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
           col = row16_max_i32(col);
           const int j = 4 * w4 + l4;
           int label = V;
-          const bool large = znorm > kZ16Max && znorm < INFINITY;
-          if (j < n && (large || !(vbest < thresh))) label = !large && cnt == 1 && vblank < thresh ? min(col, V) : kTie;
+          if (j < n && norm2 < kNormInfinite && !(vbest < thresh)) label = cnt == 1 && vblank < thresh ? min(col, V) : kTie;
+          if (__any(j < n && norm2 > kZ16Max * kZ16Max && norm2 < kNormInfinite)) {
+            leave();
+            label = V;
+          }
           if (l15 == 0) { rech[j] = 0; stat[j] = mark | label; }
           // near-ties ahead of the first certain label, in the order of their rows
           for (unsigned long long todo = __ballot(l15 == 0 && label != V); todo; todo &= todo - 1) {
@@ -652,13 +662,7 @@ __device__ __forceinline__ void vocab_loop(const ModelDev &m, const CallDev &c, 
             const unsigned long long *kt = kr + (src >> 4);
             if (lane < nparts) { const unsigned long long x = group_ld(kt + 4 * lane); kA.x = first(x); kA.y = key_with_tag(second(x), 0); }
             if (lane + 64 < nparts) { const unsigned long long x = group_ld(kt + 4 * (lane + 64)); kB.x = first(x); kB.y = key_with_tag(second(x), 0); }
-            float th = readlane_f32(thresh, src);
-            if (__builtin_amdgcn_readlane(large, src)) {   // every part whole
-              th = -INFINITY;
-              if (lane < nparts) kA.y = INFINITY;
-              if (lane + 64 < nparts) kB.y = INFINITY;
-            }
-            const int l = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + row) * H, pfull, readlane_f32(vblank, src), th, kA, kB);
+            const int l = vocab_recheck<KS>(m, c.e + ((size_t)b * c.T + t + row) * H, pfull, readlane_f32(vblank, src), readlane_f32(thresh, src), kA, kB);
             if (lane == 0) { rech[row] = 1; stat[row] = mark | l; }
             if (l != V) break;
           }

@@ -44,6 +44,7 @@ struct ModelDev {
   const float *start_c, *start_p, *start_rec;   // one-layer models that decode in resident groups: the state after the start token (cell state
                                 //   [Hp], projection [Hj], recurrent gate sums [4Hp]), the same for every utterance; else null
   float w16_scale;              // power of two: W_out times this as fp16 operands (wind_group_vocab_kernel)
+  float tau16_floor;            // what fp16's smallest numbers add to the near-tie band there
   float tau_scale;              // near-tie band = tau_scale * |z|_2 (+ key truncation)
 };
 

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import wind_inputs as wi
-from parity import compare_batch
+from parity import compare_batch, compare_utterance
 
 pytestmark = pytest.mark.gpu
 
@@ -132,9 +132,72 @@ def test_near_ties(H, V, B, W):
     m.close()
 
 
+def test_hidden_rows_of_other_sizes_are_screened():
+    """Hidden vectors of a length of some 30, 8000 and 0.1, with output rows that make the same logits of them: near-ties are as rare."""
+    cfg, w, enc, lens, m = model(256, 1300, 20, 40, 60, 2.0)
+    m.close()
+    from paper_2505_13765_amd import WindModel
+
+    runs, again = [], []
+    for scale, loop in ((1.0, 0), (1.0, 1), (2.0 ** 8, 1), (2.0 ** -8, 1)):
+        ws = dict(w, w_out=w["w_out"] / np.float32(scale))
+        for k in ("w_enc", "b_enc", "w_pred", "b_pred"):
+            ws[k] = w[k] * np.float32(scale)
+        m = WindModel.from_config(cfg, ws)
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, 8))
+        again.append(m.stats().rechecks)
+        assert (m.loop_info()[0] > 0) == bool(loop)
+        m.close()
+    print(f"decided again {again} of {runs[0][2][2]}", flush=True)
+    assert runs[0] == runs[1] == runs[2] == runs[3]
+    assert 0 < again[1] and max(again[2:]) <= 1.25 * again[1] + 8
+
+
+@pytest.mark.parametrize("gain", [2.0 ** 17, 2.0 ** 67])
+@pytest.mark.parametrize("H,V,B,W", [(128, 1100, 3, 16), (640, 1030, 40, 4)])
+def test_calls_with_hidden_rows_beyond_fp16_take_the_per_step_kernels(H, V, B, W, gain):
+    """Units above 65504, and units whose squares are past fp32 (they are finite, unlike those of infinite frames, which are blank)."""
+    cfg, w, enc, lens, m = model(H, V, B, 8, 20, 2.0)
+    enc[B - 1, 3] *= np.float32(gain)
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, W))
+        assert m.loop_info()[0] == 0
+    assert runs[0] == runs[1] and 3 in runs[0][1][B - 1]
+    o = oracle.Oracle.from_config(cfg, w)
+    for b in (0, B - 1):
+        compare_utterance(o, enc[b, :lens[b]], cfg.S, np.array(runs[0][0][b], np.int32), np.array(runs[0][1][b], np.int32))
+    m.set_option("loop_kernel", 1)
+    enc[B - 1, 3] = 0.0
+    decode(m, cfg, enc, lens, W)
+    assert m.loop_info()[0] > 0   # that call and no other
+    m.close()
+
+
+@pytest.mark.parametrize("V", [1025, 1130])
+def test_large_weights_of_blank(V):
+    """The output row of blank shares a part of 32 columns with labels.  Its weights are not among those that fp16 operands are scaled for."""
+    cfg, w, enc, lens, m = model(256, V, 12, 20, 40, 2.0)
+    m.close()
+    from paper_2505_13765_amd import WindModel
+
+    w["w_out"][V, 3] = 512.0
+    w["b_out"][V] -= 256.0
+    m = WindModel.from_config(cfg, w)
+    runs = []
+    for loop in (1, 0):
+        m.set_option("loop_kernel", loop)
+        runs.append(decode(m, cfg, enc, lens, 8))
+        assert (m.loop_info()[0] > 0) == bool(loop)
+    assert runs[0] == runs[1] and 0 < runs[0][2][4] < cfg.S * int(lens.sum())
+    m.close()
+
+
 @pytest.mark.parametrize("H,V,B,W", [(128, 1100, 3, 16), (640, 1030, 40, 4)])
 def test_hidden_rows_beyond_fp16(H, V, B, W):
-    """The screening products are fp16 (rows times 64): frames whose hidden units are too large for that are decided over all labels in fp32."""
+    """The screening products are fp16: frames whose hidden units are near the end of what that holds, and beyond it."""
     cfg, w, enc, lens, m = model(H, V, B, 8, 20, 2.0)
     enc[:, 3] *= 4096.0
     enc[:, 6] *= 65536.0
