@@ -242,7 +242,8 @@ int wind_beam_decode(wind_model *m, const float *enc_out, int T, int window, int
  * Device memory, in bytes, of the workspace that a decode call of this shape needs (encoder
  * projections of every frame, window rows, keys, prediction-network state, ...).  The model owns
  * one workspace, allocated on the first call and regrown when a later call needs more; this query
- * lets a caller budget HBM before the call.  HOST pointer.  No GPU work.
+ * lets a caller budget HBM before the call.  Synchronous calls that decode in the resident groups of larger vocabularies (993 to
+ * 4096 labels) keep up to 10 MB beside it, once per model.  HOST pointer.  No GPU work.
  */
 int wind_workspace_bytes(const wind_model *m, int B, int T, int W, size_t *bytes);
 

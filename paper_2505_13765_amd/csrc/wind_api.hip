@@ -170,6 +170,7 @@ struct wind_model {
   bool fma_pred_step = false;   // this call's prediction-network steps keep their state in fp32 (the resident loop kernel reads it)
   LoopDev loop{};
   GroupDev group{};
+  unsigned long long *vocab_mem = nullptr;   // see vocab_exchange
   int *group_out = nullptr;    // kGroupOutBytes in the workspace
   int *dbg_len = nullptr, *dbg_out = nullptr;   // lengths and outputs of the debug entry points (inside the workspace)
   void *beam_ws = nullptr;   // workspace of the beam scoring step
@@ -263,7 +264,7 @@ struct WsLayout {
   bool big_enc;
   int slot_stride, nparts, nparts_tiny;
   size_t o_e, o_encb, o_len, o_nact, o_eidx, o_eltok, o_slot, o_slotc, o_rst, o_raux, o_nemit, o_ticket, o_h, o_c, o_hn, o_hb,
-      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder, o_gout, o_vx, o_v0;
+      o_hz, o_rec, o_p, o_z, o_bl, o_zn, o_parts, o_rl, o_stats, o_dbg, o_iter, o_dbglen, o_dbgout, o_lbar, o_lh, o_lp, o_lparts, o_gbar, o_gx, o_gkeys, o_gorder, o_gout;
 };
 
 WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
@@ -307,16 +308,12 @@ WsLayout workspace_layout(const wind_model *m, int B, int T, int W) {
   w.o_lbar = take((size_t)(1 + 256) * kLoopFlagStride * 4); w.o_lh = take((size_t)kLoopMaxB * d.Hp * 4);
   w.o_lp = take((size_t)kLoopMaxB * d.Hj * 4);
   w.o_lparts = take((size_t)2 * kLoopRows * w.nparts_tiny * 8);
-  // models that decode in resident groups, of one kind or (see group_shape) of either
-  const bool resident = d.start_p != nullptr, vocab = resident && vocab_model(m, B), grouped = resident && d.V <= kGroupMaxV;
-  w.o_gbar = take(resident ? (size_t)kGroups * kGroupBarInts * 4 : 0);
+  const bool grouped = d.start_p != nullptr && d.V <= kGroupMaxV;   // models that decode in resident groups; those of larger vocabularies: see vocab_exchange
+  w.o_gbar = take(grouped ? (size_t)kGroups * kGroupBarInts * 4 : 0);
   w.o_gx = take(grouped ? (size_t)2 * kGroups * kGroupSlots * d.Hp * 8 : 0);
   w.o_gkeys = take(grouped ? (size_t)kGroups * 2 * kGroupRows * (w.nparts_tiny + 1) * 8 : 0);
-  w.o_gorder = take(resident ? (size_t)(kGroupMaxB + 1) * 4 : 0);
-  w.o_gout = take(resident ? kGroupOutBytes : 0);   // an asynchronous call's flags and counters
-  const int vslots = std::min(kVocabSlots, (B + kGroups - 1) / kGroups);
-  const VocabLayout v = vocab ? vocab_layout(d.Hj, w.nparts_tiny, vslots, vocab_qmax(vslots)) : VocabLayout{};
-  w.o_vx = take(v.ones * kGroups * 8); w.o_v0 = take(v.zeros * kGroups * 8);
+  w.o_gorder = take(grouped ? (size_t)(kGroupMaxB + 1) * 4 : 0);
+  w.o_gout = take(grouped ? kGroupOutBytes : 0);   // an asynchronous call's flags and counters
   w.total = off;
   return w;
 }
@@ -339,6 +336,22 @@ int ensure_workspace(wind_model *m, int B, int T, int W, hipStream_t s) {
     HIP_TRY(hipMemsetAsync(m->ws, 0, w.total, s));
   }
   carve_workspace(m, w, (char *)m->ws, B);
+  return WIND_OK;
+}
+
+// What the groups of wind_group_vocab_kernel exchange in: the model's own, apart from the workspace, because asynchronous calls have no use for it, and as
+// large as any call needs (10 MB for 640 units and 4096 labels) from the first one on, because the need does not grow with the batch (windows of up to four quads for
+// up to 16 slots, of two for more).
+int vocab_exchange(wind_model *m, GroupDev *gd) {
+  static_assert(kVocabSlots * vocab_qmax(kVocabSlots) >= kVocabSlots / 2 * vocab_qmax(kVocabSlots / 2), "the most slots need the most words");
+  const VocabLayout v = vocab_layout(m->dev.Hj, (m->dev.V + kTinyCols - 1) / kTinyCols, kVocabSlots, vocab_qmax(kVocabSlots));
+  const size_t words = (v.ones + v.zeros) * kGroups;
+  if (!m->vocab_mem) HIP_TRY(hipMalloc((void **)&m->vocab_mem, words * 8 + (kGroups * kGroupBarInts + kGroupMaxB + 1) * 4));
+  gd->vx = m->vocab_mem;
+  gd->v0 = m->vocab_mem + v.ones * kGroups;
+  gd->bar = (unsigned *)(m->vocab_mem + words);
+  gd->order = (int *)(gd->bar + kGroups * kGroupBarInts);
+  gd->n_order = gd->order + kGroupMaxB;
   return WIND_OK;
 }
 
@@ -400,8 +413,6 @@ void carve_workspace(wind_model *m, const WsLayout &w, char *base, int B) {
   m->group.keys = (unsigned long long *)(base + w.o_gkeys);
   m->group.order = (int *)(base + w.o_gorder);
   m->group.n_order = m->group.order + kGroupMaxB;
-  m->group.vx = (unsigned long long *)(base + w.o_vx);
-  m->group.v0 = (unsigned long long *)(base + w.o_v0);
   m->group_out = (int *)(base + w.o_gout);
 }
 
@@ -1007,6 +1018,10 @@ int decode(wind_model *m, const float *enc, const int32_t *lengths, int B, int T
     // decode the call, it waits for no more than about the time that takes.
     gd.spin_limit = (unsigned)m->opt_loop_spin_limit;
     gd.start_limit = async ? gd.spin_limit : std::min(gd.spin_limit, kGroupStartPolls);
+    if (gd.qmax > 0) {
+      rc = vocab_exchange(m, &gd);
+      if (rc) return rc;
+    }
     enqueue_enc_proj(m, s, &gd);
     const bool meets = gi->gw != 1;   // one workgroup per utterance: waits for nobody
     if (meets) {
@@ -1502,6 +1517,7 @@ int wind_free(wind_model *m) {
   if (m->cap_stream) (void)hipStreamDestroy(m->cap_stream);
   for (void *p : m->allocs) (void)hipFree(p);
   if (m->ws) (void)hipFree(m->ws);
+  if (m->vocab_mem) (void)hipFree(m->vocab_mem);
   if (m->beam_ws) (void)hipFree(m->beam_ws);
   beam_pool_free(m);
   if (m->beam_res.mem) (void)hipFree(m->beam_res.mem);

@@ -195,6 +195,16 @@ def test_large_weights_of_blank(V):
     m.close()
 
 
+@pytest.mark.parametrize("H,V", [(640, 4096), (128, 1000)])
+def test_workspaces_grow_with_the_batch(H, V):
+    """A workspace for the largest batch takes every smaller one; what only synchronous calls need is not part of a caller's."""
+    cfg, w, enc, lens, m = model(H, V, 2, 8, 8, 0.0)
+    for T, W in ((10, 1), (200, 16)):
+        sizes = [m.workspace_bytes(B, T, W) for B in range(1, 300)]
+        assert sizes == sorted(sizes)
+    m.close()
+
+
 @pytest.mark.parametrize("H,V,B,W", [(128, 1100, 3, 16), (640, 1030, 40, 4)])
 def test_hidden_rows_beyond_fp16(H, V, B, W):
     """The screening products are fp16: frames whose hidden units are near the end of what that holds, and beyond it."""
