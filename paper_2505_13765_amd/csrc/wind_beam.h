@@ -39,26 +39,20 @@ struct BeamIndex {
 // weight row is read once per group.  round_x rounds x to bf16 first (what the encoder projection
 // of a bf16 model does with its input).  Two such products in one launch: the first `blocks_a` workgroups take a, the others c.
 // Bound by the trips of its loads: eight weights and eight values per lane at once where the rows are aligned for it.
-// 16 frames of 1024 units and 16 vectors of 640, both onto 1024: two launches of scalar loads 17.4 us, one of these 10.6.
+// 16 frames of 1024 units and 16 vectors of 640, both onto 1024: two launches of scalar loads 17.4 us, one of these 9.6.
 struct BeamLinear {
   const void *w;
   const float *bias, *x;
   float *out;
   int rows, n_out, K, round_x;
 };
-template <class WT, int R>
-__global__ __launch_bounds__(256) void beam_linear_kernel(BeamLinear a, BeamLinear c, int blocks_a) {
-  const bool second = (int)blockIdx.x >= blocks_a;
-  const BeamLinear q = second ? c : a;
-  const int block = (int)blockIdx.x - (second ? blocks_a : 0), jb = (q.n_out + 3) / 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = block % jb * 4 + wave, r0 = block / jb * R, K = q.K;
-  if (j >= q.n_out) return;
-  const WT *w = reinterpret_cast<const WT *>(q.w) + (size_t)j * K;
-  const float bias = q.bias[j];
-  float acc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = 0.f;
+// The lane's part of R rows' sums.  ROUND is a template argument: with many rows bound by instructions, the rounding of every value for each output among them, and a
+// choice per value is one more.  Rows of 1024 onto 640, scalar loads / these with the choice inside / now: 16 rows 9.1 / 8.4 / 8.1 us, 64 11.6 / 10.9 /
+// 10.6, 250 31.4 / 36.1 / 28.9, 1500 166 / 199 / 150.  (Four values at 4 lane and four 256 on, so that a load's lanes lie side by side: 13 / 14.5 / 39 / 199.)
+template <bool ROUND, class WT, int R>
+__device__ __forceinline__ void beam_linear_rows(const BeamLinear &q, const WT *w, int r0, float (&acc)[R]) {
+  const int lane = threadIdx.x & 63, K = q.K;
+  auto value = [](float v) { return ROUND ? bf16_bits_to_f32(f32_to_bf16_bits(v)) : v; };
   if ((K & 7) == 0 && (((uintptr_t)q.w | (uintptr_t)q.x) & 15) == 0) {   // x may be a caller's, at any multiple of 4 bytes
     for (int k = lane * 8; k < K; k += 512) {
       float wv[8];
@@ -67,25 +61,34 @@ __global__ __launch_bounds__(256) void beam_linear_kernel(BeamLinear a, BeamLine
       for (int r = 0; r < R; ++r) {
         const float *xr = q.x + (size_t)min(r0 + r, q.rows - 1) * K + k;
         const float4 x0 = *reinterpret_cast<const float4 *>(xr), x1 = *reinterpret_cast<const float4 *>(xr + 4);
-        float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+        const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if (q.round_x) xv[i] = bf16_bits_to_f32(f32_to_bf16_bits(xv[i]));
-          acc[r] = fmaf(wv[i], xv[i], acc[r]);
-        }
+        for (int i = 0; i < 8; ++i) acc[r] = fmaf(wv[i], value(xv[i]), acc[r]);
       }
     }
   } else {
     for (int k = lane; k < K; k += 64) {
       const float wv = ldw(w, k);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float xv = q.x[(size_t)min(r0 + r, q.rows - 1) * K + k];
-        if (q.round_x) xv = bf16_bits_to_f32(f32_to_bf16_bits(xv));
-        acc[r] = fmaf(wv, xv, acc[r]);
-      }
+      for (int r = 0; r < R; ++r) acc[r] = fmaf(wv, value(q.x[(size_t)min(r0 + r, q.rows - 1) * K + k]), acc[r]);
     }
   }
+}
+template <class WT, int R>
+__global__ __launch_bounds__(256) void beam_linear_kernel(BeamLinear a, BeamLinear c, int blocks_a) {
+  const bool second = (int)blockIdx.x >= blocks_a;
+  const BeamLinear q = second ? c : a;
+  const int block = (int)blockIdx.x - (second ? blocks_a : 0), jb = (q.n_out + 3) / 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = block % jb * 4 + wave, r0 = block / jb * R;
+  if (j >= q.n_out) return;
+  const WT *w = reinterpret_cast<const WT *>(q.w) + (size_t)j * q.K;
+  const float bias = q.bias[j];
+  float acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0.f;
+  if (q.round_x) beam_linear_rows<true>(q, w, r0, acc);
+  else beam_linear_rows<false>(q, w, r0, acc);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const float tot = wave_sum(acc[r]);

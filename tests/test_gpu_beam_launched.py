@@ -68,8 +68,8 @@ def test_logit_blocks(V, Hj, n, Bh, exact):
 
 
 # 60: rows that eight values do not divide; shift: inputs at an address that is no multiple of 16 bytes; 9 frames, 17 hypotheses: one
-# more than a group of eight rows each
-@pytest.mark.parametrize("dtype,D,shift", [("f32", 60, 0), ("f32", 64, 1), ("bf16", 64, 0), ("bf16", 64, 3)])
+# more than a group of eight rows each; 1032, 1088: two steps of 512 values and a rest
+@pytest.mark.parametrize("dtype,D,shift", [("f32", 60, 0), ("f32", 64, 1), ("bf16", 64, 0), ("bf16", 64, 3), ("f32", 1032, 0), ("bf16", 1088, 0)])
 def test_projections(dtype, D, shift):
     import torch
 
