@@ -195,6 +195,24 @@ def test_large_weights_of_blank(V):
     m.close()
 
 
+def test_more_iterations_than_a_row_word_counts():
+    """A row's word in LDS holds 17 bits of the iteration's number.  131070 windows of one quad, then blank ones, the second of which has rows that no
+    iteration has had before."""
+    T, n = 131100, 131070
+    cfg = wi.WindConfig("vocab_long", 5, 1, T, T, 64, 64, 1, 128, 128, 1030, "bf16", (4,), 1, 0.7)
+    w = {k: np.zeros_like(v) for k, v in wi.make_weights(cfg).items()}
+    w["w_enc"][0, 0], w["w_out"][5, 0], w["b_out"][cfg.V] = 1.0, 1.0, 2.0
+    enc = np.zeros((1, T, 64), np.float32)
+    enc[0, :n, 0] = 6.0
+    from paper_2505_13765_amd import WindModel
+
+    m = WindModel.from_config(cfg, w)
+    toks, frs, _ = decode(m, cfg, enc, np.array([T], np.int32), 16)
+    assert m.loop_info()[0] > 0
+    assert toks[0] == [5] * n and frs[0] == list(range(n))
+    m.close()
+
+
 @pytest.mark.parametrize("H,V", [(640, 4096), (128, 1000)])
 def test_workspaces_grow_with_the_batch(H, V):
     """A workspace for the largest batch takes every smaller one; what only synchronous calls need is not part of a caller's."""
