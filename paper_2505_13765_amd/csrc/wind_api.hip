@@ -812,8 +812,8 @@ const GroupInstance kVocabInstances[] = {vocab_instance<1>(), vocab_instance<2>(
 // number of utterances, width, window and share of labels groups were ahead in that range (wind_group_vocab_kernel.h).
 constexpr int kVocabMaxV = 4096;
 
-// Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts), a width
-// that some instance has.
+// Models that can decode in resident groups: one LSTM layer as wide as the joiner, at most 1024 labels (32 parts; bf16 models of
+// some widths: 4096), a width that some instance has.
 bool group_model(int dtype, const ModelDev &d) {
   if (d.L != 1 || d.Hp != d.Hj || (unsigned long long)(d.V + 1) * 4 * d.Hp >= (1ull << 31)) return false;
   if (d.V > kGroupMaxV) {   // bf16, 1025 to 4096 labels: wind_group_vocab_kernel

@@ -47,6 +47,9 @@ namespace wind {
 //   h                      of a step: everybody reads it for the projection and, up to the next decision, for the recurrent sums; it is
 //                          overwritten two steps of the slot later
 // Waits are bounded as in wind_group_kernel.
+//
+// Registers: the weights of 640 units fill them: nine vector registers (40 bytes per lane) lie in scratch memory there, none with fewer units, and 78 to 143
+// scalars in lanes of vector registers.
 constexpr int kVocabSlots = 32;
 constexpr int kTie = 0x3FFF;   // instead of a label: a near-tie
 // The screening products are fp16: as fast as bf16 and with eight times less rounding of the hidden row, so that near-ties, each of which holds all

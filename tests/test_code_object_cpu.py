@@ -81,9 +81,20 @@ def test_the_scan_finds_such_a_write():
     assert writes_before_lanes_are_back(planted)[0] == []
 
 
-def test_groups_of_one_utterance_keep_their_weights_in_registers(code_object):
-    """No vector register of the instances that calls of up to 8 utterances take lies in scratch memory (mode 1: the last template argument)."""
+def vector_spills(code_object, pattern):
     notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object], check=True, capture_output=True, text=True).stdout
     kernels = re.findall(r"\.name:\s+(_Z\S+).*?\.vgpr_spill_count:\s+(\d+)", notes, flags=re.S)
-    spills = {n: int(k) for n, k in kernels if re.search(r"wind_group_(f32_)?kernelI\w*?Li1EEEv", n)}
+    return {n: int(k) for n, k in kernels if re.search(pattern, n)}
+
+
+def test_groups_of_one_utterance_keep_their_weights_in_registers(code_object):
+    """No vector register of the instances that calls of up to 8 utterances take lies in scratch memory (mode 1: the last template argument)."""
+    spills = vector_spills(code_object, r"wind_group_(f32_)?kernelI\w*?Li1EEEv")
     assert len(spills) == 15 and not any(spills.values()), spills
+
+
+def test_groups_of_larger_vocabularies_keep_their_weights_in_registers(code_object):
+    """128 to 512 units: no vector register in scratch memory.  640 units: nine, which the kernel's description states."""
+    spills = vector_spills(code_object, r"wind_group_vocab_kernelI")
+    assert len(spills) == 5
+    assert {int(re.search(r"kernelILi(\d)E", n).group(1)): k for n, k in spills.items() if k} in ({}, {5: 9}), spills

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import wind_inputs as wi
-from parity import compare_batch, compare_utterance
+from parity import compare_utterance
 
 pytestmark = pytest.mark.gpu
 
@@ -50,11 +50,15 @@ def test_groups_of_larger_vocabularies(H, V, B, W):
         runs.append(decode(m, cfg, enc, lens, W))
         assert m.loop_info()[0] == (32 * min(B, 8) if loop else 0)
     print(f"H={H} V={V} B={B} W={W}: {runs[0][2][:6]}", flush=True)
-    excluded = compare_batch(oracle.Oracle.from_config(cfg, w), enc, lens, cfg.S, [np.array(t, np.int32) for t in runs[0][0]], [np.array(f, np.int32) for f in runs[0][1]])
-    assert excluded <= 1 + B // 16
+    o = oracle.Oracle.from_config(cfg, w)
+    refs = o.greedy_batch(enc, lens, cfg.S, want_log=True)
+    excluded = [compare_utterance(o, enc[b, :lens[b]], cfg.S, np.array(runs[0][0][b], np.int32), np.array(runs[0][1][b], np.int32),
+                                  oracle_result=tuple(r[b] for r in refs)) for b in range(B)]
+    assert sum(excluded) <= 1 + B // 16
     assert runs[0][2][4] == sum(map(len, runs[0][0])) > 0
-    if excluded == 0:   # a near-tie may fall either way on either route
-        assert runs[0] == runs[1]
+    for b in range(B):   # a near-tie may fall either way on either route
+        assert excluded[b] or (runs[0][0][b], runs[0][1][b]) == (runs[1][0][b], runs[1][1][b]), b
+    assert sum(excluded) or runs[0][2] == runs[1][2]
     m.close()
 
 
@@ -112,8 +116,8 @@ def test_frames_that_are_not_finite(H, V, B, W):
 
 
 @pytest.mark.parametrize("H,V,B,W", [(128, 1500, 3, 8), (640, 2100, 20, 16)])
-def test_near_ties(H, V, B, W):
-    """Every label's logit the same but for the biases: rows of many near-ties, parts whose second key is inside the band too, the winner the third."""
+def test_labels_by_their_biases(H, V, B, W):
+    """Every label's logit the same but for the biases, which are a thousandth apart."""
     cfg, w, enc, lens, m = model(H, V, B, 10, 25, 0.0)
     m.close()
     from paper_2505_13765_amd import WindModel
@@ -129,6 +133,59 @@ def test_near_ties(H, V, B, W):
     toks, _, st = decode(m, cfg, enc, lens, W)
     assert m.loop_info()[0] > 0
     assert all(x == 1050 for t in toks for x in t) and st[4] == 3 * int(lens.sum())
+    m.close()
+
+
+# frame of the crafted evaluation: in a window of one quad (frames 0 to 3), of two (4 to 11), of four (12 to 27); 130 utterances: windows of up to two quads
+@pytest.mark.parametrize("V,col0,B,at", [(1100, 64, 2, 2), (4000, 2080, 3, 9), (1500, 1472, 2, 20), (1200, 1152, 130, 6)])
+def test_third_label_of_a_part_inside_the_band(V, col0, B, at):
+    """Two keys are kept of a part of 32 labels.  Here the label that wins in fp32 comes third in its part once the hidden row is rounded to fp16, and
+    3e-3 clear of the next in the oracle (so no near-tie exclusion applies): the part is decided again whole.  One part's weight rows are made large, so
+    that the rounding moves their logits by several 1e-3, and the output biases set so that on frame `at` of utterance 0 every logit is known.  The frames
+    before it are the same but for a hidden unit of their own that makes them blank."""
+    H = 256
+    cfg = wi.WindConfig("vocab_third", 301, B, 30, 30, 64, 64, 1, H, H, V, "bf16", (4,), 1, 0.7)
+    w = wi.make_weights(cfg, blank_bias=0.0, pred_gain=4.0)
+    enc, lens = wi.make_batch(cfg)
+    w["w_enc"][0], w["w_enc"][:, 0], w["b_enc"][0], w["w_pred"][0], w["b_pred"][0], w["w_out"][:, 0] = 0.0, 0.0, 0.0, 0.0, 0.0, 0.0
+    w["w_enc"][0, 0], w["w_out"][V, 0] = 1.0, 64.0         # input 0 -> hidden unit 0 -> blank
+    enc[0, :at] = enc[0, at]
+    enc[0, :, 0] = 0.0
+    enc[0, :at, 0] = 16.0
+    part, found, scale = slice(col0, col0 + 32), None, 1.0
+    while found is None and scale <= 1024.0:
+        scale *= 2.0
+        w2 = {k: v.copy() for k, v in w.items()}
+        w2["w_out"][part] *= np.float32(scale)              # a power of two: the rows stay bf16 values
+        o = oracle.Oracle.from_config(cfg, w2)
+        g0 = o.decoder_from_scratch([])
+        z = np.maximum(o.encoder_projection(enc[0, at]) + w2["w_pred"].astype(np.float64) @ g0 + w2["b_pred"], 0.0)
+        zh = z.astype(np.float16).astype(np.float64)
+        wz = w2["w_out"].astype(np.float64) @ z
+        noise = w2["w_out"].astype(np.float64)[part] @ (zh - z)
+        order = np.argsort(noise)
+        if noise[order[-2]] - noise[order[0]] > 1.2e-2:
+            found = (col0 + int(order[0]), [col0 + int(order[-1 - k]) for k in range(2)])
+    assert found is not None, "no scale gave the rounding noise the construction needs"
+    win, others = found
+    b_out = (4.0 - wz).astype(np.float32)
+    b_out[win] = np.float32(5.0 - wz[win])
+    for k, col in enumerate(others):
+        b_out[col] = np.float32(5.0 - 3e-3 * (k + 1) - wz[col])
+    w2["b_out"] = b_out
+    o = oracle.Oracle.from_config(cfg, w2)
+    ref = np.sort(o.joiner(enc[0, at], g0))
+    assert int(np.argmax(o.joiner(enc[0, at], g0))) == win and ref[-1] - ref[-2] > 2e-3
+    screen = w2["w_out"].astype(np.float64) @ zh + b_out
+    assert all(screen[col] > screen[win] + 2e-3 for col in others), "the winner must rank third in its part"
+    from paper_2505_13765_amd import WindModel
+
+    m = WindModel.from_config(cfg, w2)
+    toks, frs, _ = decode(m, cfg, enc, lens, 16)
+    assert m.loop_info()[0] > 0 and m.stats().rechecks > 0
+    assert (toks[0][0], frs[0][0]) == (win, at)
+    o_tok, o_frs, log = o.greedy(enc[0], cfg.S)
+    compare_utterance(o, enc[0], cfg.S, np.array(toks[0], np.int32), np.array(frs[0], np.int32), oracle_result=(o_tok, o_frs, log))
     m.close()
 
 
@@ -183,7 +240,7 @@ def test_large_weights_of_blank(V):
     m.close()
     from paper_2505_13765_amd import WindModel
 
-    w["w_out"][V, 3] = 512.0
+    w["w_out"][V, 3] = 512.0   # past fp16 by the labels' scale
     w["b_out"][V] -= 256.0
     m = WindModel.from_config(cfg, w)
     runs = []
