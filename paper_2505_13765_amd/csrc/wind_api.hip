@@ -253,7 +253,8 @@ constexpr int vocab_qmax(int slots) { return slots > 16 ? 2 : 4; }
 // that come to more than two rounds of four utterances per group: a round costs the other groups the same each, while all of these are
 // decoded at once.  640 units, 1024 labels, 200 to 1500 frames, W = 8 / 16, rounds / all at once: 33 utterances 2.68 / 3.25 ms, 48 3.01 / 3.38, 64 4.03 / 4.21, 128
 // 7.15 / 4.95, 256 (W = 16: per-step kernels) 14.9 / 7.2; with hardly any label 64 1.11 / 1.07, 128 1.96 / 1.53, 256 3.27 / 2.98; a label on almost every frame (200 to 400
-// frames) 64 44.4 / 30.3, 256 138 / 50
+// frames) 64 44.4 / 30.3, 256 138 / 50.  128, 256 and 640 units, 993 labels, 65 to 256 utterances of up to 20 and up to 200 frames, any share of labels: ahead, up to 4 times, but for
+// the shortest calls (65 utterances of up to 20 frames without a label 55 / 60 us).
 constexpr int kVocabMinB = 2 * kGroups * kGroupSlots + 1;
 bool vocab_model(const wind_model *m, int B) {
   return m->dtype == WIND_BF16 && (m->dev.V > kGroupMaxV || (m->dev.V > kGroupMaxV - kTinyCols && B >= kVocabMinB));

@@ -583,11 +583,13 @@ __global__ __launch_bounds__(256) void beam_score_kernel(const float *logits, in
 // that can be among the hypothesis' K best.
 //
 // The K largest: every wave takes the ceil(K / NW)-th largest of its lanes' own maxima.  At least K labels are not below the least of
-// these NW values, so the others drop out with one comparison each; some 20 to 60 of 8192 remain, are listed in LDS, and
-// each counts how many of the list come before it: its place.  Rows with more than kBeamList that remain (many equal logits, or
+// these NW values (with K < NW: than the K-th largest of them), so the others drop out with one comparison each; some 20 to 60 of 8192 remain, are
+// listed in LDS, and each counts how many of the list come before it: its place.  Rows with more than kBeamList that remain (many equal logits, or
 // a wave without K / NW labels) take K rounds of "largest remaining entry of the wave" over registers, which for every row took
 // most of the kernel's time: 8193 columns, 16 / 128 / 512 rows (K = 4 / 8 / 16) 23.5 / 23.5 / 52 us, now 9.4 / 9.4 / 17; 1025 columns,
-// 256 / 512 rows (K = 12 / 16) 12.3 / 17.0, now 6.8 / 8.3.  Rows of more than 2048 columns are spread over eight waves instead of four.
+// 256 / 512 rows (K = 12 / 16) 12.3 / 17.0, now 6.8 / 8.3.  With few labels asked for those rounds were short, and the least of the waves' values lets more
+// through than they cost (4097 columns, 2048 rows, rounds / least / K-th largest: K = 1 21.0 / 26.7 / 18.1 us, 2 27.6 / 26.5 / 18.3, 4 40.4 / 25.6 / 19.0; 1501 columns, 256 rows: K = 1
+// 4.1 / 6.1 / 3.9, 2 4.7 / 5.8 / 4.3).  Rows of more than 2048 columns are spread over eight waves instead of four.
 constexpr int kBeamList = 256;
 template <int EPT, int NW>
 __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float *logits, int V, int K, float *lse_out,
@@ -624,6 +626,16 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float *logits, 
   thr = s_thr[0];
 #pragma unroll
   for (int w = 1; w < NW; ++w) { mx = fmaxf(mx, s_f[w]); thr = min(thr, s_thr[w]); }
+  if (K < NW) {
+    const unsigned mine = lane < NW ? s_thr[lane] : 0u;
+    int place = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const unsigned o = s_thr[w];
+      place += o > mine || (o == mine && w < lane) ? 1 : 0;
+    }
+    thr = (unsigned)__builtin_amdgcn_readlane((int)mine, __ffsll((long long)__ballot(lane < NW && place == K - 1)) - 1);
+  }
   thr = max(thr, 1u);   // 0: no entry
 #pragma unroll
   for (int i = 0; i < EPT; ++i)

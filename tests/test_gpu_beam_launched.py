@@ -15,9 +15,10 @@ def config(V, Hj=64, dtype="f32", D=64):
     return wi.WindConfig("launched", 11, 2, 70, 80, D, 64, 1, 64, Hj, V, dtype, (4,), 3, 0.5)
 
 
-# 2047 / 2048: the last row of the four-wave instance and the first of the eight-wave one; 9215: the longest row; fewer labels than K
+# 2047 / 2048: the last row of the four-wave instance and the first of the eight-wave one; 9215: the longest row; fewer labels than K; K below the number
+# of waves (1 and 3 of four and eight, 7 of eight) and above
 @pytest.mark.parametrize("V", [5, 63, 300, 2047, 2048, 9215])
-@pytest.mark.parametrize("K", [1, 7, 32])
+@pytest.mark.parametrize("K", [1, 3, 7, 32])
 def test_row_choice_on_ties(V, K):
     """Logits are the output bias (no weights): `top` labels share the largest value, up to all of them, more than the list of a row
     holds; the order of equal scores is earlier frame, then lower label."""
